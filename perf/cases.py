@@ -56,7 +56,7 @@ def draw(rng):
     op, arch, b_hi, k_hi = rng.choice([
         ("round", "tiny", 64, 4), ("round", "state", 64, 8), ("round", "state_bf16", 256, 16), ("round", "image", 256, 8),
         ("round", "fleet", 1024, 16), ("round", "other", 64, 8), ("observe", "image", 256, 8), ("observe", "fleet", 1024, 16),
-        ("observe", "state", 64, 8), ("predict", "state", 4, 8), ("plain", "state_bf16", 64, 16), ("plain", "image", 8, 8),
+        ("observe", "state", 64, 8), ("predict", "state", 4, 8), ("plain", "state_bf16", 64, 16),
         ("accept", "state", 65536, 16), ("accept", "image", 16384, 16), ("distill", "state", 16384, 16)])
     case = {"op": op, "arch": arch, "B": _log_int(rng, 1, b_hi), "K": rng.randint(2, k_hi)}
     if op in ("round", "observe"):
