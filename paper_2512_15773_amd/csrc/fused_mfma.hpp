@@ -280,7 +280,7 @@ struct FusedCfg {
   static_assert((HEADS % HP) == 0 && (HP * 3 * DH) % (16 * NW) == 0 && (CM == 0 || (HPX * DH) % (16 * NW) == 0) &&
                 (HEADS % HPX) == 0, "shape");
   static_assert(CH % (16 * NW) == 0 && (4 * D) % CH == 0, "shape");
-  static_assert(CM == 0 || (SX % 16 == 0 && SX >= 16 && ES == 2), "cross-attention: bf16 only, tokens a multiple of 16");
+  static_assert(CM == 0 || (SX % 16 == 0 && SX >= 16 && ES == 2 && D % 256 == 0), "cross-attention: bf16 only, tokens a multiple of 16, k_cond_kv tiles");
 };
 
 // Configuration of the persistent drafter: a rollout has few workgroups in flight (one per environment tile), so no
@@ -1185,39 +1185,6 @@ __global__ __launch_bounds__(256) void k_mod_gemm(const void* __restrict__ modw,
     }
     asm volatile("" : "+v"(lane));
   }
-}
-
-// Cross-attention operands in MFMA fragment order (see FusedNet::kc / vct), from fp32 [B*S, d] projections.
-__global__ void k_pack_kc(const float* __restrict__ Kp, __bf16* __restrict__ out, int B, int S, int d, int heads, int L,
-                          int layer) {
-  const int DH = d / heads, SF = S / 16, KS = DH / 32;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long long)B * heads * SF * KS * 64) return;
-  const int lane = (int)(i % 64);
-  long long r = i / 64;
-  const int ks = (int)(r % KS); r /= KS;
-  const int sf = (int)(r % SF); r /= SF;
-  const int head = (int)(r % heads);
-  const int env = (int)(r / heads);
-  const float* src = Kp + ((long long)env * S + sf * 16 + (lane & 15)) * d + head * DH + ks * 32 + (lane >> 4) * 8;
-  __bf16* dst = out + ((((((long long)env * L + layer) * heads + head) * SF + sf) * KS + ks) * 64 + lane) * 8;
-  for (int j = 0; j < 8; ++j) dst[j] = (__bf16)src[j];
-}
-
-__global__ void k_pack_vct(const float* __restrict__ Vp, __bf16* __restrict__ out, int B, int S, int d, int heads, int L,
-                           int layer) {
-  const int DH = d / heads, SF = S / 16, CF = DH / 16;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long long)B * heads * CF * SF * 64) return;
-  const int lane = (int)(i % 64);
-  long long r = i / 64;
-  const int sf = (int)(r % SF); r /= SF;
-  const int cf = (int)(r % CF); r /= CF;
-  const int head = (int)(r % heads);
-  const int env = (int)(r / heads);
-  const float* src = Vp + ((long long)env * S + sf * 16 + (lane >> 4) * 4) * d + head * DH + cf * 16 + (lane & 15);
-  __bf16* dst = out + ((((((long long)env * L + layer) * heads + head) * CF + cf) * SF + sf) * 64 + lane) * 4;
-  for (int j = 0; j < 4; ++j) dst[j] = (__bf16)src[(long long)j * d];
 }
 
 }  // namespace tsdp

@@ -13,6 +13,7 @@
 #include "../../include/tsdp.h"
 #include "kernels_f32.hpp"
 #include "fused_mfma.hpp"
+#include "cond_kernels.hpp"
 #include "round_kernels.hpp"
 
 using namespace tsdp;
@@ -51,6 +52,8 @@ struct Net {
   int draft_rpt_small = 0, draft_rpt_big = 0;
   uint16_t* kc_pk = nullptr;    // fragment-ordered bf16 keys / transposed values of every (env, layer, head)
   uint16_t* vct_pk = nullptr;
+  uint8_t* kv_w = nullptr;      // key / value projections of all layers as MFMA fragments (fused bf16 cross-attention)
+  float* kv_b = nullptr;        // their biases, [L][k|v][d]
 };
 
 }  // namespace
@@ -74,6 +77,7 @@ struct tsdp_ctx {
   Net net[2];
   bool cond_set = false;
   int cond_B = 0;
+  uint8_t* cond_planes = nullptr;   // bf16 planes of the observation tokens (k_split_cond), shared by both networks
   int32_t* status = nullptr;
   int32_t* live = nullptr;      // environments still running (chain driver)
   int32_t* K_sel = nullptr;     // [B_max] per-round picks from the stage tables (staged chain driver)
@@ -383,8 +387,25 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   f.modw = P(mod_off); f.modb = n.modb; f.temb = n.temb; f.cemb = cf.cond_mode == 0 ? n.cemb : nullptr;
   if (cf.cond_mode == 1) {
     const size_t S = cf.cond_tokens, cnt = (size_t)cf.B_max * L * S * d;
-    if ((rc = dev_alloc(c, &n.kc_pk, cnt))) return rc;
-    if ((rc = dev_alloc(c, &n.vct_pk, cnt))) return rc;
+    if (!n.kc_pk && (rc = dev_alloc(c, &n.kc_pk, cnt))) return rc;
+    if (!n.vct_pk && (rc = dev_alloc(c, &n.vct_pk, cnt))) return rc;
+    // key / value projections, per layer the key rows then the value rows (k_cond_kv)
+    std::vector<uint8_t> kv;
+    std::vector<float> kvb;
+    for (int l = 0; l < L; ++l) {
+      const LayerOff& o = n.lay[l];
+      pack_frags(kv, f32, &w[o.ck_w], cf.cond_dim, d, ident);
+      pack_frags(kv, f32, &w[o.cv_w], cf.cond_dim, d, ident);
+      kvb.insert(kvb.end(), &w[o.ck_b], &w[o.ck_b] + d);
+      kvb.insert(kvb.end(), &w[o.cv_b], &w[o.cv_b] + d);
+    }
+    if (!n.kv_w && (rc = dev_alloc(c, &n.kv_w, kv.size()))) return rc;
+    if (!n.kv_b && (rc = dev_alloc(c, &n.kv_b, kvb.size()))) return rc;
+    HIPCHK(c, hipMemcpy(n.kv_w, kv.data(), kv.size(), hipMemcpyHostToDevice));
+    HIPCHK(c, hipMemcpy(n.kv_b, kvb.data(), kvb.size() * sizeof(float), hipMemcpyHostToDevice));
+    if (!c->cond_planes && (rc = dev_alloc(c, &c->cond_planes, (size_t)cf.B_max * S * ((cf.cond_dim + 31) / 32) * 32 * 6)))
+      return rc;
+    HIPCHK(c, hipFuncSetAttribute(reinterpret_cast<const void*>(k_cond_kv), hipFuncAttributeMaxDynamicSharedMemorySize, COND_LDS));
     f.kc = reinterpret_cast<const bf16x8*>(n.kc_pk);
     f.vct = reinterpret_cast<const bf16x4*>(n.vct_pk);
   }
@@ -688,10 +709,6 @@ int tsdp_load_weights(tsdp_ctx* c, int which, const float* h_blob, size_t nbytes
     if ((rc = dev_alloc(c, &n.modb, modb.size()))) return rc;
     if (cf.cond_mode == 0) {
       if ((rc = dev_alloc(c, &n.cemb, (size_t)cf.B_max * d))) return rc;
-    } else {
-      const size_t cnt = (size_t)L * cf.B_max * cf.cond_tokens * d;
-      if ((rc = dev_alloc(c, &n.kc, cnt))) return rc;
-      if ((rc = dev_alloc(c, &n.vc, cnt))) return rc;
     }
   }
   HIPCHK(c, hipDeviceSynchronize());
@@ -708,6 +725,11 @@ int tsdp_load_weights(tsdp_ctx* c, int which, const float* h_blob, size_t nbytes
     if (find_fused(cf.dtype, n.d, cf.H, n.heads, cf.cond_mode, cf.cond_tokens, n.m / n.d, n.L, fk) &&
         (rc = build_fused(c, n, w, modw, fk)))
       return rc;
+  }
+  if (!n.fused && cf.cond_mode == 1 && !n.kc) {        // fp32 keys / values of the operator kernels
+    const size_t cnt = (size_t)L * cf.B_max * cf.cond_tokens * d;
+    if ((rc = dev_alloc(c, &n.kc, cnt))) return rc;
+    if ((rc = dev_alloc(c, &n.vc, cnt))) return rc;
   }
   if (n.fused && n.fused_mod && cf.cond_mode == 1) {
     // With token conditioning no conditioning vector enters the FiLM projections: they depend on the timestep
@@ -735,26 +757,31 @@ int tsdp_set_cond(tsdp_ctx* c, const float* d_cond, int B, void* stream) {
   if (!c->net[0].loaded || !c->net[1].loaded) return fail(c, TSDP_E_STATE, "weights of both networks must be loaded");
   hipStream_t s = (hipStream_t)stream;
   const tsdp_config& cf = c->cfg;
+  CondIO io{};
   for (int which = 0; which < 2; ++which) {
     Net& n = c->net[which];
     const float* w = n.blob;
     if (cf.cond_mode == 0) {
       linear<0>(s, d_cond, w + n.c_w, w + n.c_b, n.cemb, B, 1, n.d, cf.cond_dim, nullptr);
+    } else if (n.fused) {                             // bf16 (fused cross-attention is): one launch for both networks, below
+      io.net[which] = {reinterpret_cast<const bf16x8*>(n.kv_w), n.kv_b, reinterpret_cast<__bf16*>(n.kc_pk),
+                       reinterpret_cast<__bf16*>(n.vct_pk), n.L, n.d, n.heads, n.L * 2 * n.d / (COND_FF * 16)};
     } else {
       const int S = cf.cond_tokens;
       const size_t per_layer = (size_t)cf.B_max * S * n.d;
       for (int l = 0; l < n.L; ++l) {
         linear<0>(s, d_cond, w + n.lay[l].ck_w, w + n.lay[l].ck_b, n.kc + l * per_layer, B * S, 1, n.d, cf.cond_dim, nullptr);
         linear<0>(s, d_cond, w + n.lay[l].cv_w, w + n.lay[l].cv_b, n.vc + l * per_layer, B * S, 1, n.d, cf.cond_dim, nullptr);
-        if (n.fused) {
-          const long long cnt = (long long)B * S * n.d / 8;
-          hipLaunchKernelGGL(k_pack_kc, grid1(cnt, 256), dim3(256), 0, s, (const float*)(n.kc + l * per_layer),
-                             reinterpret_cast<__bf16*>(n.kc_pk), B, S, n.d, n.heads, n.L, l);
-          hipLaunchKernelGGL(k_pack_vct, grid1(2 * cnt, 256), dim3(256), 0, s, (const float*)(n.vc + l * per_layer),
-                             reinterpret_cast<__bf16*>(n.vct_pk), B, S, n.d, n.heads, n.L, l);
-        }
       }
     }
+  }
+  if (const int tiles = io.net[0].tiles + io.net[1].tiles) {
+    const int M = B * cf.cond_tokens;
+    io.planes = reinterpret_cast<const bf16x8*>(c->cond_planes);
+    io.MF = M / 16; io.KS = (cf.cond_dim + 31) / 32; io.SF = cf.cond_tokens / 16;
+    hipLaunchKernelGGL(k_split_cond, grid1((long long)io.MF * io.KS * 64, 256), dim3(256), 0, s, d_cond, M, cf.cond_dim, io.KS,
+                       reinterpret_cast<bf16x8*>(c->cond_planes));
+    hipLaunchKernelGGL(k_cond_kv, dim3(tiles * ((io.MF + COND_TF - 1) / COND_TF)), dim3(512), COND_LDS, s, io);
   }
   HIPCHK(c, hipGetLastError());
   c->cond_set = true;

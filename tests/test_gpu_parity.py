@@ -137,6 +137,15 @@ def test_c4_cross_attention_stages():
     _stage_parity(wl, 2, t0, K, s, paths=("bf16-mfma-fused", "bf16-mfma-fused"))
 
 
+@pytest.mark.parametrize("B, cond_dim, S", [(1, 768, 64), (3, 36, 64), (5, 768, 64)])
+def test_cross_attention_operands_at_tile_edges(B, cond_dim, S):
+    # the key / value product takes 128 tokens (two environments) at a time and 32 observation features per k-step: odd
+    # batches end in half a tile, 36 features in a k-step of 4
+    wl = ti.small_variant(ti.C4, B=B, cond_dim=cond_dim, cond_tokens=S, base=ti.NetShape(1, 512, 8), draft=ti.NetShape(1, 256, 8))
+    t0 = np.full(B, 50); K = np.full(B, 2); s = np.ones(B)
+    _stage_parity(wl, B, t0, K, s, paths=("bf16-mfma-fused", "bf16-mfma-fused"))
+
+
 def _round_parity(wl, B, t0, K, s, env, head_scale=1.0):
     """tsdp_round against the oracle's round.  The same inputs also go through the three stages with diagnostics,
     which gives the GPU's own log alpha of every row: the fused round must equal the stages bit for bit, accept
