@@ -401,19 +401,25 @@ __global__ void k_fill_i32(int32_t* p, int n, int32_t v) {
 }
 
 // Distillation-loss forward: per row the squared distance of the two noise predictions and of the two posterior
-// means in units of sigma_t, reduced in fp64.  One row per group of 16 lanes; every workgroup writes one partial
-// pair, a second single-workgroup kernel adds the partials in a fixed order (deterministic result).
+// means in units of sigma_t, reduced in fp64.  One row per group of 16 lanes; at most DISTILL_WGS workgroups walk the
+// rows and each writes one triple (sum of both terms, number of rows with t > 0), a second single-workgroup kernel adds
+// the triples in a fixed order (deterministic result).  Bound by its read stream; the workgroup limit keeps eight
+// workgroups on every CU and the second kernel's share small (262 144 rows of 160: with a pair per 16 rows and the
+// timesteps counted by the second kernel that one took 267 us behind 56 us of reading).
+constexpr int DISTILL_WGS = 2048;
+
 template <bool CLIP>
 __global__ __launch_bounds__(256) void k_distill_partial(int R, int D, const int32_t* __restrict__ row_t,
                                                          const float* __restrict__ states, const float* __restrict__ eps_p,
                                                          const float* __restrict__ eps_q, SchedTables tb, float clip_val,
                                                          double* __restrict__ partial) {
   __shared__ double sp[16], sn[16];
-  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 4, gl = threadIdx.x & 15;
-  const int r = blockIdx.x * 16 + grp;
+  __shared__ int sc[16];
+  const int grp = threadIdx.x >> 4, gl = threadIdx.x & 15;
   const int nb = D >> 2;
   double pred = 0.0, nrm = 0.0;
-  if (r < R) {
+  int noisy = 0;
+  for (int r = blockIdx.x * 16 + grp; r < R; r += gridDim.x * 16) {
     const int t = row_t[r];
     const double sa = tb.sqrt_abar[t], s1 = tb.sqrt_1m[t], c0 = tb.c0[t], ce = tb.ce[t], sig = tb.sigma[t], cv = clip_val;
     const float4* ep = reinterpret_cast<const float4*>(eps_p + (long long)r * D);
@@ -421,10 +427,10 @@ __global__ __launch_bounds__(256) void k_distill_partial(int R, int D, const int
     const float4* st = reinterpret_cast<const float4*>(states + (long long)r * D);
     double dd = 0.0, dm = 0.0;
     for (int i = gl; i < nb; i += 16) {
-      const float4 p = ep[i], q = eq[i];
+      const float4 p = load_once(ep + i), q = load_once(eq + i);
       const float pp[4] = {p.x, p.y, p.z, p.w}, qq[4] = {q.x, q.y, q.z, q.w};
       float yy[4] = {0, 0, 0, 0};
-      if (CLIP) { const float4 y = st[i]; yy[0] = y.x; yy[1] = y.y; yy[2] = y.z; yy[3] = y.w; }
+      if (CLIP) { const float4 y = load_once(st + i); yy[0] = y.x; yy[1] = y.y; yy[2] = y.z; yy[3] = y.w; }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const double de = (double)pp[j] - (double)qq[j];
@@ -438,32 +444,29 @@ __global__ __launch_bounds__(256) void k_distill_partial(int R, int D, const int
       }
     }
     dd = group16_sum(dd); dm = group16_sum(dm);
-    pred = dd;
+    pred += dd;
     if (t > 0) {
       const double kap = CLIP ? 1.0 / sig : (ce - (c0 * s1) / sa) / sig;
-      nrm = kap * kap * (CLIP ? dm : dd);
+      nrm += kap * kap * (CLIP ? dm : dd);
+      ++noisy;
     }
   }
-  (void)lane;
-  if (gl == 0) { sp[grp] = pred; sn[grp] = nrm; }
+  if (gl == 0) { sp[grp] = pred; sn[grp] = nrm; sc[grp] = noisy; }
   __syncthreads();
   if (threadIdx.x == 0) {
     double a = 0.0, b = 0.0;
-    for (int i = 0; i < 16; ++i) { a += sp[i]; b += sn[i]; }
-    partial[2 * blockIdx.x] = a; partial[2 * blockIdx.x + 1] = b;
+    int n = 0;
+    for (int i = 0; i < 16; ++i) { a += sp[i]; b += sn[i]; n += sc[i]; }
+    partial[3 * blockIdx.x] = a; partial[3 * blockIdx.x + 1] = b; partial[3 * blockIdx.x + 2] = (double)n;
   }
 }
 
-__global__ __launch_bounds__(256) void k_distill_final(int nparts, int R, const int32_t* __restrict__ row_t,
-                                                       const double* __restrict__ partial, float lam1, float lam2,
-                                                       double* __restrict__ loss) {
-  __shared__ double sa[256], sb[256];
-  __shared__ int sc[256];
-  double a = 0.0, b = 0.0;
-  int noisy = 0;
-  for (int i = threadIdx.x; i < nparts; i += 256) { a += partial[2 * i]; b += partial[2 * i + 1]; }
-  for (int i = threadIdx.x; i < R; i += 256) noisy += row_t[i] > 0;
-  sa[threadIdx.x] = a; sb[threadIdx.x] = b; sc[threadIdx.x] = noisy;
+__global__ __launch_bounds__(256) void k_distill_final(int nparts, int R, const double* __restrict__ partial, float lam1,
+                                                       float lam2, double* __restrict__ loss) {
+  __shared__ double sa[256], sb[256], sc[256];
+  double a = 0.0, b = 0.0, n = 0.0;
+  for (int i = threadIdx.x; i < nparts; i += 256) { a += partial[3 * i]; b += partial[3 * i + 1]; n += partial[3 * i + 2]; }
+  sa[threadIdx.x] = a; sb[threadIdx.x] = b; sc[threadIdx.x] = n;
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) {
     if ((int)threadIdx.x < o) { sa[threadIdx.x] += sa[threadIdx.x + o]; sb[threadIdx.x] += sb[threadIdx.x + o]; sc[threadIdx.x] += sc[threadIdx.x + o]; }

@@ -58,13 +58,13 @@ struct Net {
 
 }  // namespace
 
-// Scratch of tsdp_distill_loss_noalloc: the per-workgroup partial sums of the loss (one pair of doubles per 16
-// rows) live in a file-scope device array instead of context memory, so that entry point allocates nothing.  Every
-// GPU holds its own copy; host code uses the address hipGetSymbolAddress returns for the current device, looked up
-// once per device in tsdp_create, never the symbol itself.
+// Scratch of tsdp_distill_loss_noalloc: the per-workgroup partial sums of the loss (three doubles each) live in a
+// file-scope device array instead of context memory, so that entry point allocates nothing.  Every GPU holds its own
+// copy; host code uses the address hipGetSymbolAddress returns for the current device, looked up once per device in
+// tsdp_create, never the symbol itself.
 constexpr int NOALLOC_MAX_ROWS = 65536;
 constexpr int NOALLOC_MAX_DEVICES = 64;
-static __device__ __align__(256) double scratch[2 * (NOALLOC_MAX_ROWS / 16) + 2];
+static __device__ __align__(256) double scratch[3 * DISTILL_WGS];
 static double* g_scratch_ptr[NOALLOC_MAX_DEVICES];   // device address of `scratch` on each device, null until looked up
 
 struct tsdp_ctx {
@@ -1085,7 +1085,7 @@ int tsdp_prepare(tsdp_ctx* c) {
   int rc;
   if ((rc = ensure_workspace(c))) return rc;
   if ((rc = ensure_chain_buffers(c))) return rc;
-  if (!c->loss_partial && (rc = dev_alloc(c, &c->loss_partial, 2 * ((rows_max(c->cfg) + 15) / 16) + 2))) return rc;
+  if (!c->loss_partial && (rc = dev_alloc(c, &c->loss_partial, 3 * DISTILL_WGS))) return rc;
   // the launch attributes of the fused kernels (dynamic LDS size): a launch over zero rows sets them and enqueues nothing
   FusedIO io{};
   DraftIO dio{};
@@ -1104,10 +1104,10 @@ int tsdp_prepare(tsdp_ctx* c) {
   return TSDP_OK;
 }
 
-// partial: room for 2 * ceil(R / 16) doubles; every entry that is read is written first by the same call
+// partial: room for 3 * DISTILL_WGS doubles; every entry that is read is written first by the same call
 static int distill_launch(tsdp_ctx* c, int R, const int32_t* d_row_t, const float* d_states, const float* d_eps_p,
                           const float* d_eps_q, float lambda1, float lambda2, double* partial, double* d_loss, hipStream_t s) {
-  const int parts = (R + 15) / 16;
+  const int parts = std::min((R + 15) / 16, DISTILL_WGS);
   if (parts > 0) {
     if (c->cfg.clip_x0)
       hipLaunchKernelGGL(k_distill_partial<true>, dim3(parts), dim3(256), 0, s, R, c->D, d_row_t, d_states, d_eps_p, d_eps_q,
@@ -1116,8 +1116,7 @@ static int distill_launch(tsdp_ctx* c, int R, const int32_t* d_row_t, const floa
       hipLaunchKernelGGL(k_distill_partial<false>, dim3(parts), dim3(256), 0, s, R, c->D, d_row_t, d_states, d_eps_p, d_eps_q,
                          c->tb, c->cfg.clip_val, partial);
   }
-  hipLaunchKernelGGL(k_distill_final, dim3(1), dim3(256), 0, s, parts, R, d_row_t, (const double*)partial, lambda1,
-                     lambda2, d_loss);
+  hipLaunchKernelGGL(k_distill_final, dim3(1), dim3(256), 0, s, parts, R, (const double*)partial, lambda1, lambda2, d_loss);
   HIPCHK(c, hipGetLastError());
   return TSDP_OK;
 }
@@ -1129,7 +1128,7 @@ int tsdp_distill_loss(tsdp_ctx* c, int R, const int32_t* d_row_t, const float* d
   if (!d_loss || (R > 0 && (!d_row_t || !d_states || !d_eps_p || !d_eps_q)))
     return fail(c, TSDP_E_INVAL, "null pointer passed to tsdp_distill_loss");
   if (!c->loss_partial) {
-    int rc = dev_alloc(c, &c->loss_partial, 2 * ((rows_max(c->cfg) + 15) / 16) + 2);
+    int rc = dev_alloc(c, &c->loss_partial, 3 * DISTILL_WGS);
     if (rc) return rc;
   }
   return distill_launch(c, R, d_row_t, d_states, d_eps_p, d_eps_q, lambda1, lambda2, c->loss_partial, d_loss,
