@@ -42,6 +42,7 @@ struct FusedNet {
   FusedLayer layer[FUSED_MAX_LAYERS];
   int L;
   const float* tok_w; const float* tok_b; const float* pos;   // fp32 [D,A], [D], [H,D]
+  const float* tok_wt;         // [A,D] (k_few_*)
   const void* head;            // [ceil(A/16)][D/32][64] fragments of head_w, rows padded to a multiple of 16
   const float* head_b;         // [A]
   const void* modw;            // [L*4D/16][D/32][64] FiLM projections of all layers (drafter kernel)
@@ -132,6 +133,49 @@ __device__ __forceinline__ bf16x4 to_bf16x4(f32x4 v) {
   return r;
 }
 
+// Lane sums / maxima across the four rows of 16 lanes: x combined with the lane 16 (32) away, by lane swaps.
+__device__ __forceinline__ float2 swap_row16(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+  return make_float2(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+}
+__device__ __forceinline__ float2 swap_half32(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+  return make_float2(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+}
+__device__ __forceinline__ float add_row16(float x) { const float2 r = swap_row16(x); return r.x + r.y; }
+__device__ __forceinline__ float add_half32(float x) { const float2 r = swap_half32(x); return r.x + r.y; }
+__device__ __forceinline__ float max_row16(float x) { const float2 r = swap_row16(x); return fmaxf(r.x, r.y); }
+__device__ __forceinline__ float max_half32(float x) { const float2 r = swap_half32(x); return fmaxf(r.x, r.y); }
+
+// Workgroup barrier that orders LDS accesses only.  __syncthreads also waits for every outstanding global load (loads
+// and stores share one counter), which would drain the weights that are requested ahead of a phase.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// softmax over the keys (rows of s, NK key fragments) for the 16 queries of one fragment
+template <class TT, int NK>
+__device__ __forceinline__ void softmax_keys(f32x4 (&s)[NK], typename TT::vec4 (&p)[NK], int DH) {
+  const float scale = rsqrtf((float)DH);
+  float mx = -INFINITY;
+#pragma unroll
+  for (int kf = 0; kf < NK; ++kf)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { s[kf][i] *= scale; mx = fmaxf(mx, s[kf][i]); }
+  mx = fmaxf(mx, __shfl_xor(mx, 16)); mx = fmaxf(mx, __shfl_xor(mx, 32));
+  float sum = 0.0f;
+#pragma unroll
+  for (int kf = 0; kf < NK; ++kf)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { s[kf][i] = __expf(s[kf][i] - mx); sum += s[kf][i]; }
+  sum += __shfl_xor(sum, 16); sum += __shfl_xor(sum, 32);
+  const float inv = __builtin_amdgcn_rcpf(sum);       // one approximate reciprocal (1 ulp) instead of an IEEE division
+#pragma unroll
+  for (int kf = 0; kf < NK; ++kf) p[kf] = TT::cvt(s[kf] * inv);
+}
+
 // Measured choices of the kernels below (each was timed against its alternative on the full-size workloads).
 constexpr int INFLIGHT_CLK = 384;   // cycles of matrix work between the request of a weight fragment and its use
 constexpr int PF_MAX = 4;           // upper limit of the weight ring's depth in k-steps
@@ -144,13 +188,14 @@ constexpr int PF_MAX = 4;           // upper limit of the weight ring's depth in
 // that about INFLIGHT_CLK cycles of MFMA work separate a request from its use (one L2 round trip)
 // without flooding the small vector L1.  issue() requests k-step 0 only and may be called a whole phase
 // early (before an epilogue, a barrier or the attention of the previous phase); run() does the rest.
-template <class TT, int MB, int NB, int NKS, int BD = 2>
+// PFX > 0 sets the ring depth directly.
+template <class TT, int MB, int NB, int NKS, int BD = 2, int PFX = 0>
 struct FragGemm {
   typedef typename TT::frag frag;
   typedef typename TT::elem elem;
   static constexpr int STEP_CLK = MB * NB * 16;
   static constexpr int PFW = (INFLIGHT_CLK + STEP_CLK - 1) / STEP_CLK;
-  static constexpr int PF0 = PFW < 1 ? 1 : (PFW > PF_MAX ? PF_MAX : PFW);
+  static constexpr int PF0 = PFX > 0 ? PFX : (PFW < 1 ? 1 : (PFW > PF_MAX ? PF_MAX : PFW));
   static constexpr int PF = PF0 > NKS ? NKS : PF0;
   frag a[PF + 1][MB];
   const frag* wl;
@@ -494,27 +539,6 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
     __syncthreads();
   };
 
-  // softmax over the keys (rows of s, NK key fragments) for the 16 queries of one fragment
-  auto softmax_col = [&](auto& s, auto& p, auto KF) {
-    constexpr int NK = decltype(KF)::value;
-    const float scale = rsqrtf((float)DH);
-    float mx = -INFINITY;
-#pragma unroll
-    for (int kf = 0; kf < NK; ++kf)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { s[kf][i] *= scale; mx = fmaxf(mx, s[kf][i]); }
-    mx = fmaxf(mx, __shfl_xor(mx, 16)); mx = fmaxf(mx, __shfl_xor(mx, 32));
-    float sum = 0.0f;
-#pragma unroll
-    for (int kf = 0; kf < NK; ++kf)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { s[kf][i] = __expf(s[kf][i] - mx); sum += s[kf][i]; }
-    sum += __shfl_xor(sum, 16); sum += __shfl_xor(sum, 32);
-    const float inv = __builtin_amdgcn_rcpf(sum);     // one approximate reciprocal (1 ulp) instead of an IEEE division
-#pragma unroll
-    for (int kf = 0; kf < NK; ++kf) p[kf] = TT::cvt(s[kf] * inv);
-  };
-
   // softmax(q k^T) v for query fragment qf of (row, head) held in LDS; the result overwrites those q rows
   auto self_attention = [&](int r, int hh, int qf) {
     elem* qp = qbuf + (r * H + qf * 16) * QTS + hh * DH;
@@ -532,7 +556,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
       }
     }
     vec4 p[NKF];
-    softmax_col(s, p, std::integral_constant<int, NKF>{});
+    softmax_keys<TT, NKF>(s, p, DH);
     const elem* vp = vtb + (size_t)(hh * RPT + r) * DH * VS;
 #pragma unroll
     for (int cf = 0; cf < DH / 16; ++cf) {
@@ -585,7 +609,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
         for (int kf = 0; kf < SF; ++kf) s[kf] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[ks][kf], qb, s[kf], 0, 0, 0);
       }
       vec4 pv[SF];
-      softmax_col(s, pv, std::integral_constant<int, SF>{});
+      softmax_keys<TT, SF>(s, pv, DH);
 #pragma unroll
       for (int kf = 0; kf < SF; ++kf) p[kf] = __builtin_bit_cast(bf16x4, pv[kf]);
     }

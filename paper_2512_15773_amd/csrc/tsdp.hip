@@ -14,11 +14,20 @@
 #include "kernels_f32.hpp"
 #include "fused_mfma.hpp"
 #include "cond_kernels.hpp"
+#include "few_rows.hpp"
 #include "round_kernels.hpp"
 
 using namespace tsdp;
 
 namespace {
+
+struct FewRun {                 // one forward pass of k_few_*
+  const float* x; const int32_t* row_t; const int32_t* row_env; const int32_t* d_R;
+  int R_cap, safe_rows, A, T;
+  const float* mod;             // [R][L*4D], or the network's table over timesteps
+  float* eps_out;
+  float* h[2]; float* part[2]; size_t pstride;
+};
 
 struct LayerOff {
   size_t mod_w, mod_b, qkv_w, qkv_b, o_w, o_b, cq_w, cq_b, ck_w, ck_b, cv_w, cv_b, co_w, co_b, up_w, up_b, dn_w, dn_b;
@@ -50,6 +59,13 @@ struct Net {
   hipError_t (*fused_draft_small)(const FusedNet&, const DraftIO&, int A, hipStream_t) = nullptr;   // few environments per workgroup
   hipError_t (*fused_draft_big)(const FusedNet&, const DraftIO&, int A, hipStream_t) = nullptr;     // many environments per workgroup
   int draft_rpt_small = 0, draft_rpt_big = 0;
+  bool few = false;             // the forward pass of this context's rows is spread over the chip (k_few_*)
+  bool few_roll = false;        // so is the drafter's rollout
+  void (*few_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr;
+  void (*few_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;
+  void (*few_film)(const FusedNet&, const int32_t*, int, const int32_t*, int, int, const int32_t*, int, float*, hipStream_t) = nullptr;
+  int few_slices = 0;           // partial sums per row
+  float* tok_wt = nullptr;      // [A, d] token embedding, transposed
   uint16_t* kc_pk = nullptr;    // fragment-ordered bf16 keys / transposed values of every (env, layer, head)
   uint16_t* vct_pk = nullptr;
   uint8_t* kv_w = nullptr;      // key / value projections of all layers as MFMA fragments (fused bf16 cross-attention)
@@ -89,6 +105,8 @@ struct tsdp_ctx {
   // network workspace (lazy)
   bool ws_ready = false;
   float *h = nullptr, *a = nullptr, *qkv = nullptr, *ao = nullptr, *u = nullptr, *sg = nullptr, *mod = nullptr;
+  // k_few_*: residual, partial sums, latents between two transitions, FiLM vectors of all transitions of a rollout
+  float *few_h[2] = {nullptr, nullptr}, *few_part[2] = {nullptr, nullptr}, *few_y[2] = {nullptr, nullptr}, *few_mod = nullptr;
   float* eps_tmp = nullptr;     // [B_max, D] drafter output of the current step
   int32_t *row_t_chk = nullptr, *row_env_chk = nullptr;   // [rows] range-checked copy of a caller's row table (tsdp_verify)
   int32_t* Bconst = nullptr;    // device ints holding B for row-count reads of dense (per-env) launches
@@ -236,7 +254,133 @@ void launch_mod(const FusedNet& n, const int32_t* t_arr, int t_sub, const int32_
                      R_cap, mod);
 }
 
+// The launches of one spread forward pass: every kernel reads the residual and the partial sums its predecessor left
+// and writes the other pair of buffers.
+template <class C>
+struct FewPass {
+  typedef typename C::TT TT;
+  static constexpr int D = C::D;
+  const FusedNet& n;
+  const FewRun& r;
+  hipStream_t s;
+  FewIO io{};
+  DraftIO dr{};
+  int at = 0;
+  const int la = few_lds_attn<TT>(D, C::H, C::DH), lm = few_lds_mlp<TT>(D, C::H, C::CH);
+
+  FewPass(const FusedNet& n_, const FewRun& r_, hipStream_t s_) : n(n_), r(r_), s(s_) {
+    io.by_row = r.R_cap >= (std::getenv("TSDP_BYROW") ? atoi(std::getenv("TSDP_BYROW")) : 8);
+    io.R_cap = r.R_cap; io.safe_rows = r.safe_rows; io.word = r.d_R; io.pstride = r.pstride;
+    io.by_t = n.modtab != nullptr; io.mod_stride = n.L * 4 * D; io.row_t = r.row_t; io.T = r.T; io.row_env = r.row_env;
+    io.x = r.x; io.tok_wt = n.tok_wt; io.tok_b = n.tok_b; io.pos = n.pos; io.A = r.A;
+    io.head = n.head; io.head_b = n.head_b; io.eps_out = r.eps_out; io.kc = n.kc; io.vct = n.vct; io.L = n.L; io.rms = n.rms;
+  }
+  static constexpr int FIRST = C::WIDE ? 0 : C::NPM;   // residual that the previous MLP block left
+  // buffers of the next launch: partial sums and residual change places; wide rows keep their residual where it is
+  // (`move` where a launch starts a new one while its other workgroups may still read the old)
+  void flip(bool move = false) {
+    if (C::WIDE) {
+      io.h_in = r.h[at];
+      if (move) at ^= 1;
+      io.h_out = r.h[at];
+    } else {
+      io.h_in = r.h[at]; io.part_in = r.part[at];
+      at ^= 1;
+      io.h_out = r.h[at]; io.part_out = r.part[at];
+    }
+  }
+  int rows() const { return io.by_row ? (r.R_cap + 7) / 8 * 8 : r.R_cap; }
+  // h += product of the activations the previous launch left, K of them per token
+  template <int K>
+  void out(const void* w, const float* bias) {
+    if constexpr (C::WIDE) {
+      flip();
+      io.part_in = r.part[0]; io.w2 = w; io.bias_in = bias;
+      hipLaunchKernelGGL((k_few_out<C, K>), dim3(rows() * (D / 64)), dim3(C::TH), C::NW * C::H * 64 * 4, s, io);
+    } else {
+      io.bias_in = bias;
+    }
+  }
+  void start(bool ends_step) {
+    const dim3 th(C::TH), ga(rows() * C::HEADS);
+    if (ends_step) hipLaunchKernelGGL((k_few_attn<C, FIRST, true>), ga, th, la + FEW_STEP_LDS, s, io, dr);
+    else hipLaunchKernelGGL((k_few_attn<C, FEW_EMBED>), ga, th, la + FEW_STEP_LDS, s, io, FewNone{});
+  }
+  // all layers; mod = FiLM vectors of row 0; ends_step: the first launch ends the rollout's previous transition
+  void layers(const float* mod, bool ends_step) {
+    const dim3 th(C::TH), ga(rows() * C::HEADS), gm(rows() * C::NCH);
+    if (C::WIDE) io.part_out = r.part[0];
+    for (int l = 0; l < n.L; ++l) {
+      const FusedLayer& w = n.layer[l];
+      flip(l == 0);
+      io.mod = mod + (size_t)l * 4 * D; io.w1 = w.qkv; io.b1 = w.qkv_b; io.w2 = w.o; io.layer = l;
+      if (l == 0) start(ends_step);
+      else hipLaunchKernelGGL((k_few_attn<C, FIRST>), ga, th, la, s, io, FewNone{});
+      out<D>(w.o, w.o_b);
+      if constexpr (C::SX > 0) {
+        flip();
+        io.w1 = w.cq; io.b1 = w.cq_b; io.w2 = w.co;
+        hipLaunchKernelGGL((k_few_cross<C, C::NPA>), ga, th, la, s, io);
+        out<D>(w.co, w.co_b);
+      }
+      flip();
+      io.mod += 2 * D; io.w1 = w.up; io.b1 = w.up_b; io.w2 = w.dn;
+      hipLaunchKernelGGL((k_few_mlp<C, C::NPA>), gm, th, lm, s, io);
+      out<4 * D>(w.dn, w.dn_b);
+    }
+  }
+  void head() {
+    flip();
+    hipLaunchKernelGGL((k_few_head<C, FIRST>), dim3(r.R_cap), dim3(C::TH), lm, s, io);
+  }
+};
+
+template <class C>
+void few_forward(const FusedNet& n, const FewRun& r, hipStream_t s) {
+  FewPass<C> p(n, r, s);
+  p.layers(r.mod, false);
+  p.head();
+}
+
+// The drafter's rollout: 2 L launches per transition (3 L with cross-attention) and one that ends the last.  r.mod holds
+// the FiLM vectors of every transition, [env][k_max] rows (unless they come from the table).
+template <class C>
+void few_draft(const FusedNet& n, const FewRun& r, const DraftIO& dr, int k_max, float* const* y, hipStream_t s) {
+  FewPass<C> p(n, r, s);
+  const int stride = n.L * 4 * C::D;
+  p.dr = dr;
+  p.io.word = dr.K_eff;
+  p.io.roll = 1;
+  p.io.x = dr.y;
+  if (!p.io.by_t) p.io.mod_stride = k_max * stride;
+  for (int k = 1; k <= k_max + 1; ++k) {
+    p.io.step = k;
+    p.io.t_sub = k - 1;
+    p.io.y_in = k == 2 ? dr.y : y[(k - 1) & 1];
+    p.io.y_out = y[k & 1];
+    if (k <= k_max) {
+      p.layers(p.io.by_t ? r.mod : r.mod + (size_t)(k - 1) * stride, k > 1);
+    } else {
+      p.flip(true);
+      p.start(true);
+    }
+  }
+}
+
+template <class TT, int D>
+void launch_few_film(const FusedNet& n, const int32_t* t_arr, int t_sub, const int32_t* env_arr, int k_max, int T,
+                     const int32_t* d_R, int R_cap, float* mod, hipStream_t s) {
+  const int Nm = n.L * 4 * D;
+  hipLaunchKernelGGL((k_few_film<TT, D>), dim3((Nm / 16 + 3) / 4, (R_cap + 15) / 16), dim3(256),
+                     16 * (D + TT::PAD) * (int)sizeof(typename TT::elem), s, n.modw, n.modb, n.temb, n.cemb, t_arr, t_sub, env_arr,
+                     k_max, T, D, Nm, d_R, R_cap, mod);
+}
+
 struct FusedKernels {
+  void (*few_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr;
+  void (*few_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;
+  void (*few_film)(const FusedNet&, const int32_t*, int, const int32_t*, int, int, const int32_t*, int, float*, hipStream_t) = nullptr;
+  int few_slices = 0;
   // variant for batches of at most one tile per CU: one 8-wave workgroup per CU instead of two 4-wave ones
   hipError_t (*verify_few)(const FusedNet&, const FusedIO&, int, int, hipStream_t) = nullptr;
   int rpt_verify = 0;
@@ -257,6 +401,7 @@ constexpr int F256_CH = 256;
 constexpr int FEW_TILES = 288;   // up to this many tiles the 8-wave verify variant (one workgroup per CU) is used
 constexpr int V512_HPX = 8;      // heads per cross-attention phase of the d = 512 verify kernel
 constexpr int V512_CH = 256;     // hidden-chunk width of the d = 512 verify kernel
+constexpr size_t FEW_TOKENS = 2176, FEW_LAYER_BYTES = 700000;   // build_fused
 // shapes with compiled fused kernels
 bool find_fused(int dtype, int D, int H, int heads, int cm, int S, int mlp_ratio, int L, FusedKernels& k) {
   if (mlp_ratio != 4 || L > FUSED_MAX_LAYERS) return false;
@@ -264,6 +409,9 @@ bool find_fused(int dtype, int D, int H, int heads, int cm, int S, int mlp_ratio
   if (dtype == DT_ && D == D_ && H == H_ && heads == HD_ && cm == CM_ && (CM_ == 0 || S == SX_)) {             \
     k.verify = launch_verify<FusedCfg<TT_, D_, NTV, H_, HD_, CM_, CHV, SX_, HPV, NWV, HPXV>>;                  \
     k.rpt_verify = NTV / H_;                                                                                   \
+    typedef FewCfg<TT_, D_, H_, HD_, SX_> F_;                                                                   \
+    k.few_forward = few_forward<F_>; k.few_draft = few_draft<F_>; k.few_slices = std::max(F_::NCH, F_::HEADS);   \
+    k.few_film = launch_few_film<TT_, D_>;                                                                       \
     k.mod = DT_ == 1 ? launch_mod<D_> : nullptr;                                                               \
     k.draft_small = launch_draft<FusedCfg<TT_, D_, NTS, H_, HD_, CM_, CHS, SX_, HPS, NWS>>; k.rpt_small = NTS / H_; \
     k.draft_big = launch_draft<FusedCfg<TT_, D_, NTB, H_, HD_, CM_, CHB, SX_, HPB, NWD>>;   k.rpt_big = NTB / H_;   \
@@ -292,6 +440,9 @@ bool find_fused(int dtype, int D, int H, int heads, int cm, int S, int mlp_ratio
 #undef TSDP_SHAPE
   return false;
 }
+
+// rows of the ragged batch a context must hold: K_max per environment, one more with the bonus row
+inline size_t rows_max(const tsdp_config& cf) { return (size_t)cf.B_max * (cf.K_max + (cf.bonus_row ? 1 : 0)); }
 
 size_t layout_net(const tsdp_config& cf, int which, Net& n) {
   n.L = which == 0 ? cf.base_layers : cf.draft_layers;
@@ -329,7 +480,7 @@ size_t layout_net(const tsdp_config& cf, int which, Net& n) {
 // group) and fills n.fnet.  `w` is the host copy of the bf16-rounded canonical blob.
 int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vector<float>& modw_cat, const FusedKernels& fk) {
   const tsdp_config& cf = c->cfg;
-  const int d = n.d, m = n.m, L = n.L, DH = d / n.heads, HP = DH >= 64 ? 1 : 64 / DH;
+  const int d = n.d, m = n.m, L = n.L, DH = d / n.heads;
   const bool f32 = cf.dtype == 0;
   std::vector<uint8_t> pk;
   std::vector<float> qb((size_t)L * 3 * d);
@@ -338,10 +489,9 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   auto ident = [](int r) { return r; };
   for (int l = 0; l < L; ++l) {
     const LayerOff& o = n.lay[l];
-    // logical row lr of the q|k|v matrix: groups of HP heads, inside a group per head [q(DH) k(DH) v(DH)]
+    // logical row lr of the q|k|v matrix: per head [q(DH) k(DH) v(DH)]
     auto qkv_row = [&](int lr) {
-      const int g = lr / (HP * 3 * DH), r = lr % (HP * 3 * DH);
-      const int head = g * HP + r / (3 * DH), cls = (r / DH) % 3, cdim = r % DH;
+      const int head = lr / (3 * DH), cls = (lr / DH) % 3, cdim = lr % DH;
       return cls * d + head * DH + cdim;
     };
     off[l].qkv = pk.size(); pack_frags(pk, f32, &w[o.qkv_w], d, 3 * d, qkv_row);
@@ -380,6 +530,12 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
       fl.cq_b = n.blob + o.cq_b; fl.co_b = n.blob + o.co_b;
     }
   }
+  std::vector<float> tokt((size_t)cf.A * d);
+  for (int i = 0; i < d; ++i)
+    for (int a = 0; a < cf.A; ++a) tokt[(size_t)a * d + i] = w[n.tok_w + (size_t)i * cf.A + a];
+  if (!n.tok_wt && (rc = dev_alloc(c, &n.tok_wt, tokt.size()))) return rc;
+  HIPCHK(c, hipMemcpy(n.tok_wt, tokt.data(), tokt.size() * sizeof(float), hipMemcpyHostToDevice));
+  f.tok_wt = n.tok_wt;
   f.tok_w = n.blob + n.tok_w; f.tok_b = n.blob + n.tok_b; f.pos = n.blob + n.pos;
   f.head = P(head_off); f.head_b = n.blob + n.head_b;
   f.modtab = nullptr;
@@ -416,6 +572,20 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   n.fused_mod = fk.mod;
   n.fused_draft_small = fk.draft_small; n.fused_draft_big = fk.draft_big;
   n.draft_rpt_small = fk.rpt_small; n.draft_rpt_big = fk.rpt_big;
+  n.few_forward = fk.few_forward; n.few_draft = fk.few_draft; n.few_film = fk.few_film; n.few_slices = fk.few_slices;
+  // Few rows: the spread kernels.  One workgroup per tile takes the same time from 1 to 256 tiles, the spread launches
+  // grow with the rows; they meet at about 2200 tokens (verify, us, tile / spread, 64 and 128 and 192 rows of 16 tokens:
+  // bf16 d = 256 213 / 125, 172, 239; bf16 d = 384 340 / 188, 335, 516; fp32 d = 256 462 / 257, 443, 700; 64 and 128 rows
+  // of 32 tokens, d = 512: 1117 / 818, 1382).  A layer of less than 700 KB passes through one compute unit faster than
+  // through two launches (fp32 d = 64, 393 KB in all: 21 us against 25).  The capacity of the context decides, not the call: an
+  // environment's result must not depend on the batch it is computed in.
+  const size_t layer_bytes = (size_t)(cf.cond_mode == 1 ? 14 : 12) * d * d * (f32 ? 4 : 2);
+  n.few = rows_max(cf) * cf.H <= FEW_TOKENS && layer_bytes >= FEW_LAYER_BYTES;
+  // The rollout: fp32 layers are bound by one unit's matrix rate (d = 128: 39 us per transition, spread 27), bf16 drafters
+  // of this size are not (d = 192: spread 2 us per transition slower).  A drafter of the base network's own shape takes
+  // the base network's kernels, so that equal weights give equal predictions.
+  const bool twin = cf.base_d == cf.draft_d && cf.base_layers == cf.draft_layers && cf.base_heads == cf.draft_heads;
+  n.few_roll = n.few && (twin || f32);
   n.path = f32 ? "f32-mfma-fused" : "bf16-mfma-fused";
   return TSDP_OK;
 }
@@ -469,11 +639,20 @@ void forward_f32(tsdp_ctx* c, Net& n, const float* x_rows, int R_cap, const int3
   linear<0>(s, c->a, w + n.head_w, w + n.head_b, eps_out, R_cap, H, A, d, d_R);
 }
 
+FewRun few_run(tsdp_ctx* c, const Net& n, int R_cap, int safe_rows, const int32_t* t_arr, const int32_t* env_arr, const float* mod) {
+  FewRun r{};
+  r.row_t = t_arr; r.row_env = env_arr; r.R_cap = R_cap; r.safe_rows = std::min(safe_rows, R_cap);
+  r.A = c->cfg.A; r.T = c->cfg.T; r.mod = n.fnet.modtab ? n.fnet.modtab : mod;
+  for (int i = 0; i < 2; ++i) { r.h[i] = c->few_h[i]; r.part[i] = c->few_part[i]; }
+  r.pstride = (size_t)R_cap * c->cfg.H * n.d;
+  return r;
+}
+
 // eps[R,H,A] = network(x_rows; t, cond): fused bf16 MFMA kernel where the shape has one, fp32 operators otherwise.
 // mod_ready: the FiLM vectors of these rows are already in c->mod (computed on the auxiliary stream; the caller has
 // made `s` wait for them)
 int forward(tsdp_ctx* c, Net& n, const float* x_rows, int R_cap, const int32_t* d_R, const int32_t* t_arr,
-            int t_sub, const int32_t* env_arr, float* eps_out, hipStream_t s, bool mod_ready = false) {
+            int t_sub, const int32_t* env_arr, float* eps_out, hipStream_t s, bool mod_ready = false, int safe_rows = 0) {
   if (!n.fused) {
     forward_f32(c, n, x_rows, R_cap, d_R, t_arr, t_sub, env_arr, eps_out, s);
     return TSDP_OK;
@@ -486,14 +665,20 @@ int forward(tsdp_ctx* c, Net& n, const float* x_rows, int R_cap, const int32_t* 
     if (base) tick(c, 3, 0, s);
     n.fused_mod(n.fnet, t_arr, t_sub, env_arr, cf.T, d_R, R_cap, c->mod, s);
     if (base) tick(c, 3, 1, s);
-  } else {                                            // fp32 networks: exact fp32 FiLM vectors from the operator kernels
-    hipLaunchKernelGGL(k_gvec, grid1((long long)R_cap * n.d, 256), dim3(256), 0, s, t_arr, t_sub, env_arr, n.temb,
-                       cf.cond_mode == 0 ? n.cemb : nullptr, c->sg, n.d, cf.T, d_R, R_cap);
-    linear<0>(s, c->sg, n.modw, n.modb, c->mod, R_cap, 1, n.L * 4 * n.d, n.d, d_R);
+  } else {                                            // fp32 networks: fp32 products
+    n.few_film(n.fnet, t_arr, t_sub, env_arr, 0, cf.T, d_R, R_cap, c->mod, s);
+  }
+  const int stage = (&n == &c->net[0]) ? 1 : -1;          // only the base network's forward is the verify stage
+  if (n.few && stage == 1) {
+    FewRun r = few_run(c, n, R_cap, safe_rows, t_arr, env_arr, c->mod);
+    r.x = x_rows; r.d_R = d_R; r.eps_out = eps_out;
+    tick(c, 1, 0, s);
+    n.few_forward(n.fnet, r, s);
+    tick(c, 1, 1, s);
+    return TSDP_OK;
   }
   FusedIO io;
   io.x_rows = x_rows; io.mod = c->mod; io.row_t = t_arr; io.t_sub = t_sub; io.T = cf.T; io.row_env = env_arr; io.d_R = d_R; io.R_cap = R_cap; io.eps_out = eps_out;
-  const int stage = (&n == &c->net[0]) ? 1 : -1;          // only the base network's forward is the verify stage
   if (stage == 1) tick(c, 1, 0, s);
   const bool few = n.fused_verify_few && (R_cap + n.verify_rpt - 1) / n.verify_rpt <= FEW_TILES;
   HIPCHK(c, (few ? n.fused_verify_few : n.fused_verify)(n.fnet, io, cf.A, R_cap, s));
@@ -511,10 +696,31 @@ size_t fused_draft_lds(const Net& n, const tsdp_config& cf, int rpt) {
   return act + scr + 2 * 8 * NT * 4 + 2 * NT * cf.A * 4 + (size_t)rpt * n.L * 4 * D * 4 + 16 * (D + PAD) * ES;  // upper bound
 }
 
-// rows of the ragged batch a context must hold: K_max per environment, one more with the bonus row
-inline size_t rows_max(const tsdp_config& cf) { return (size_t)cf.B_max * (cf.K_max + (cf.bonus_row ? 1 : 0)); }
+int ensure_few(tsdp_ctx* c) {
+  const tsdp_config& cf = c->cfg;
+  size_t h = 0, part = 0;
+  int rc;
+  for (const Net& n : c->net) {
+    if (!n.few) continue;
+    h = std::max(h, rows_max(cf) * cf.H * n.d);
+    part = std::max(part, rows_max(cf) * cf.H * n.d * n.few_slices);
+  }
+  if (h && !c->few_h[0]) {
+    for (int i = 0; i < 2; ++i) {
+      if ((rc = dev_alloc(c, &c->few_h[i], h))) return rc;
+      if ((rc = dev_alloc(c, &c->few_part[i], part))) return rc;
+      if ((rc = dev_alloc(c, &c->few_y[i], (size_t)cf.B_max * c->D))) return rc;
+    }
+  }
+  const Net& dn = c->net[1];
+  if (dn.few_roll && cf.cond_mode == 0 && !c->few_mod &&
+      (rc = dev_alloc(c, &c->few_mod, (size_t)cf.B_max * cf.K_max * dn.L * 4 * dn.d)))
+    return rc;
+  return TSDP_OK;
+}
 
 int ensure_workspace(tsdp_ctx* c) {
+  if (int rc = ensure_few(c)) return rc;
   if (c->ws_ready) return TSDP_OK;
   const tsdp_config& cf = c->cfg;
   const size_t Rw = rows_max(cf), Mw = Rw * cf.H;
@@ -818,11 +1024,11 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
                      d_row_env, d_y_last, d_states, d_eps_p, d_xi, gated ? (const int32_t*)c->n_draft : nullptr);
   Net& dn = c->net[1];
   if (dn.fused) {
-    // persistent drafter kernel: pick the tile (environments per workgroup) that fills the chip best
+    // persistent drafter kernel (or the spread launches): pick the tile (environments per workgroup) that fills the chip best
     const bool big = (B + dn.draft_rpt_big - 1) / dn.draft_rpt_big >= 192;
     const int rpt = big ? dn.draft_rpt_big : dn.draft_rpt_small;
     const size_t lds = fused_draft_lds(dn, cf, rpt);
-    if (lds <= 160 * 1024) {
+    if (dn.few_roll || lds <= 160 * 1024) {
       Net& bn = c->net[0];
       if (base_mod_rows > 0 && bn.fused && bn.fused_mod && !bn.fnet.modtab) {
         // fork: the fused rollout keeps its FiLM vectors in LDS, so the shared buffer is free for the base network's
@@ -840,7 +1046,13 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
       io.y = d_y_last; io.states = d_states; io.eps_p = d_eps_p; io.xi = d_xi;
       io.gate = c->n_draft + 1;
       tick(c, 0, 0, s);
-      HIPCHK(c, (big ? dn.fused_draft_big : dn.fused_draft_small)(dn.fnet, io, cf.A, s));
+      if (dn.few_roll) {
+        if (!dn.fnet.modtab) dn.few_film(dn.fnet, d_t0, 0, nullptr, cf.K_max, cf.T, nullptr, B * cf.K_max, c->few_mod, s);
+        const FewRun r = few_run(c, dn, B, B, d_t0, nullptr, c->few_mod);
+        dn.few_draft(dn.fnet, r, io, cf.K_max, c->few_y, s);
+      } else {
+        HIPCHK(c, (big ? dn.fused_draft_big : dn.fused_draft_small)(dn.fnet, io, cf.A, s));
+      }
       tick(c, 0, 1, s);
       bonus_rows();
       HIPCHK(c, hipGetLastError());
@@ -887,7 +1099,7 @@ static int verify_impl(tsdp_ctx* c, int B, int R_cap, const int32_t* d_row_ptr, 
     d_row_env = c->row_env_chk;
   }
   if (mod_ready) HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));   // join: the FiLM vectors computed beside the rollout
-  if ((rc = forward(c, c->net[0], d_states, R_cap, d_row_ptr + B, d_row_t, 0, d_row_env, d_eps_q, s, mod_ready))) return rc;
+  if ((rc = forward(c, c->net[0], d_states, R_cap, d_row_ptr + B, d_row_t, 0, d_row_env, d_eps_q, s, mod_ready, B))) return rc;
   HIPCHK(c, hipGetLastError());
   return TSDP_OK;
 }

@@ -146,6 +146,38 @@ def test_cross_attention_operands_at_tile_edges(B, cond_dim, S):
     _stage_parity(wl, B, t0, K, s, paths=("bf16-mfma-fused", "bf16-mfma-fused"))
 
 
+@pytest.mark.parametrize("base, B, K_max", [
+    (ti.replace(ti.C2, base=ti.NetShape(2, 256, 4)), 1, 1),       # one row
+    (ti.replace(ti.C2, base=ti.NetShape(2, 256, 4)), 9, 1),       # rows not a multiple of the eight XCDs
+    (ti.replace(ti.C2, base=ti.NetShape(1, 256, 4)), 17, 8),      # the largest capacity of the spread kernels (2176 tokens)
+    (ti.replace(ti.C2, base=ti.NetShape(1, 256, 4)), 18, 8),      # and the smallest beyond it
+    (ti.replace(ti.C5, ragged=False, base=ti.NetShape(2, 384, 6)), 3, 5),
+    (ti.replace(ti.C4, base=ti.NetShape(2, 512, 8)), 3, 3),       # wide rows with cross-attention
+])
+def test_forward_of_few_rows_at_its_edges(base, B, K_max):
+    wl = ti.small_variant(base, B=B, K_max=K_max)
+    rng = np.random.default_rng(B)
+    t0 = rng.integers(0, wl.T, B); K = rng.integers(1, K_max + 1, B); s = rng.uniform(1.0, 1.5, B)
+    t0[-1] = min(1, wl.T - 1); K[0] = K_max; t0[0] = wl.T - 1
+    _stage_parity(wl, B, t0, K, s, clip=1.5 if B == 9 else None, norm=B == 3, bonus=B == 17 and K_max == 1)
+
+
+@pytest.mark.parametrize("wl", [ti.small_variant(ti.C3, base=ti.NetShape(2, 256, 4), draft=ti.NetShape(2, 256, 4), K_max=3),
+                                ti.small_variant(ti.C4, base=ti.NetShape(1, 512, 8), draft=ti.NetShape(1, 512, 8), K_max=3)])
+def test_few_rows_of_equal_networks_give_equal_predictions(wl):
+    # a drafter with the base network's weights: its rollout and the verify forward of the same states agree bit for bit
+    import torch
+    B = 3
+    wb = ti.make_weights(wl, "base", b_std=0.02)
+    ctx = gpu_side(wl, wb, wb, ti.make_cond(wl, B), B_max=B)
+    rows = ctx.alloc_rows(B)
+    K = to_dev(np.array([3, 1, 2], np.int32))
+    ctx.tsdp_draft(to_dev(ti.make_latents(wl, B)), to_dev(np.array([90, 40, 9], np.int32)), K, to_dev(np.ones(B, np.float32)), None, rows)
+    ctx.tsdp_verify(B, rows)
+    assert torch.equal(rows["eps_p"][:6], rows["eps_q"][:6])
+    ctx.close()
+
+
 def _round_parity(wl, B, t0, K, s, env, head_scale=1.0):
     """tsdp_round against the oracle's round.  The same inputs also go through the three stages with diagnostics,
     which gives the GPU's own log alpha of every row: the fused round must equal the stages bit for bit, accept
