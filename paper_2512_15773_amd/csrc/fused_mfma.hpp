@@ -164,13 +164,13 @@ __device__ __forceinline__ void softmax_keys(f32x4 (&s)[NK], typename TT::vec4 (
   for (int kf = 0; kf < NK; ++kf)
 #pragma unroll
     for (int i = 0; i < 4; ++i) { s[kf][i] *= scale; mx = fmaxf(mx, s[kf][i]); }
-  mx = fmaxf(mx, __shfl_xor(mx, 16)); mx = fmaxf(mx, __shfl_xor(mx, 32));
+  mx = max_half32(max_row16(mx));
   float sum = 0.0f;
 #pragma unroll
   for (int kf = 0; kf < NK; ++kf)
 #pragma unroll
     for (int i = 0; i < 4; ++i) { s[kf][i] = __expf(s[kf][i] - mx); sum += s[kf][i]; }
-  sum += __shfl_xor(sum, 16); sum += __shfl_xor(sum, 32);
+  sum = add_half32(add_row16(sum));
   const float inv = __builtin_amdgcn_rcpf(sum);       // one approximate reciprocal (1 ulp) instead of an IEEE division
 #pragma unroll
   for (int kf = 0; kf < NK; ++kf) p[kf] = TT::cvt(s[kf] * inv);
@@ -408,7 +408,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
       }
     }
   }
-  __syncthreads();
+  lds_barrier();
 
   // writes LN(h) (1 + g) + b as bf16 into act; which = 0 (attention) / 2 (MLP) selects the FiLM pair, -1 = none.
   // Statistics: per-wave partial results (fp32) exchanged through LDS, one barrier.
@@ -463,7 +463,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
         for (int mb = 0; mb < MBH; ++mb)
 #pragma unroll
           for (int i = 0; i < 4; ++i) s += h[mb][nb][i];
-        s += __shfl_xor(s, 16); s += __shfl_xor(s, 32);
+        s = add_half32(add_row16(s));
         const float mw = __fmul_rn(s, 1.0f / NWF);
 #pragma unroll
         for (int mb = 0; mb < MBH; ++mb)
@@ -474,12 +474,12 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
         for (int mb = 0; mb < MBH; ++mb)
 #pragma unroll
           for (int i = 0; i < 4; ++i) { s += h[mb][nb][i]; q = fmaf(h[mb][nb][i], h[mb][nb][i], q); }
-        s += __shfl_xor(s, 16); s += __shfl_xor(s, 32);
+        s = add_half32(add_row16(s));
       }
-      q += __shfl_xor(q, 16); q += __shfl_xor(q, 32);
+      q = add_half32(add_row16(q));
       if (lane < 16) { red1[wave * NT + nb * 16 + lane] = s; red2[wave * NT + nb * 16 + lane] = q; }
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       const int t = nb * 16 + l16;
@@ -536,7 +536,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
       }
       if (!LNPF && !LNST) __builtin_amdgcn_sched_barrier(0);   // keep the FiLM loads of one fragment row in flight, not all
     }
-    __syncthreads();
+    lds_barrier();
   };
 
   // softmax(q k^T) v for query fragment qf of (row, head) held in LDS; the result overwrites those q rows
@@ -678,7 +678,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
         if (!XPF) gq.issue(W.qkv, KD, g * (HP * 3 * DH / 16) + wave, 0, lane, NW);
         gq.run(act, AS, acc, lane);
         if (XPF) go.issue(W.o, KD, wave * MBH, g * HP * KH, lane);      // needed only after the attention
-        if (g > 0) __syncthreads();                     // previous group's O-projection has read qbuf
+        if (g > 0) lds_barrier();                     // previous group's O-projection has read qbuf
 #pragma unroll
         for (int mb = 0; mb < MBQ; ++mb) {
           const int lr = (mb * NW + wave) * 16;         // first logical row of this fragment inside the group (rows are
@@ -700,10 +700,10 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
           }
         }
       }
-      __syncthreads();
+      lds_barrier();
       for (int task = wave; task < RPT * HP * NKF; task += NW)
           self_attention((task / NKF) % RPT, task / (NKF * RPT), task % NKF);
-      __syncthreads();
+      lds_barrier();
       if (XPF && g + 1 < NG) gq.issue(W.qkv, KD, (g + 1) * (HP * 3 * DH / 16) + wave, 0, lane, NW);
       if (!XPF) go.issue(W.o, KD, wave * MBH, g * HP * KH, lane);
       go.run(qbuf, QTS, h, lane);                        // one product over the heads of the group
@@ -752,7 +752,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
           if (!XPF) gc.issue(W.cq, KD, g * (HPX * DH / 16) + wave * MBC, 0, lane);
           gc.run(act, AS, acc, lane);
           if (XPF) go.issue(W.co, KD, wave * MBH, g * HPX * KH, lane);
-          if (g > 0) __syncthreads();
+          if (g > 0) lds_barrier();
 #pragma unroll
           for (int mb = 0; mb < MBC; ++mb) {
             const int c0 = (wave * MBC + mb) * 16 + lg * 4;      // column = head-of-phase * DH + feature
@@ -768,7 +768,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
           cross_load_k(task_row(task_of(0)), layer, g * HPX + task_head(task_of(0)), ka);
           cross_load_v(task_row(task_of(0)), layer, g * HPX + task_head(task_of(0)), va);
         }
-        __syncthreads();
+        lds_barrier();
 #pragma unroll
         for (int i = 0; i < TPW; ++i) {
           const int task = task_of(i), nxt = task_of(i + 1);
@@ -787,7 +787,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
             __builtin_amdgcn_sched_barrier(0);
           }
         }
-        __syncthreads();
+        lds_barrier();
         if (XPF && g + 1 < NGX) gc.issue(W.cq, KD, (g + 1) * (HPX * DH / 16) + wave * MBC, 0, lane);
         if (!XPF) go.issue(W.co, KD, wave * MBH, g * HPX * KH, lane);
         go.run(qbuf, QXS, h, lane);
@@ -853,7 +853,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
 #pragma unroll
           for (int idx = HALF; idx < PARTS; ++idx) gelu_part(c, cur, idx);
         }
-        __syncthreads();
+        lds_barrier();
         if (!PRIME) gd.issue(W.dn, KM, wave * MBH, c * (KC), lane);
         if constexpr (NEXT) {
           const int c2 = c + 2 < NC ? c + 2 : NC - 1;
@@ -911,7 +911,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
         if (XPF) gd.issue(W.dn, KM, wave * MBH, c * (KC), lane);
         // single buffer: the previous chunk's down-projection has read ubuf; double buffer: the buffer written
         // now was last read two chunks ago, and every wave has passed a barrier since
-        if (c > 0 && !C::UDB) __syncthreads();
+        if (c > 0 && !C::UDB) lds_barrier();
         elem* ub = ubuf + (C::UDB ? (c & 1) * NT * US : 0);
 #pragma unroll
         for (int mb = 0; mb < MBU; ++mb) {
@@ -925,7 +925,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
           }
         }
       }
-      __syncthreads();
+      lds_barrier();
       if (XPF) {
         if (c + 1 < NC) gu.issue(W.up, KD, (c + 1) * (CH / 16) + wave * MBU, 0, lane);
         else if (layer + 1 < net.L) gq.issue(net.layer[layer + 1].qkv, KD, wave, 0, lane, NW);
@@ -994,7 +994,7 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void k_fused_forward(Fuse
       mrow[threadIdx.x] = io.mod + (size_t)r * mod_stride;
     }
   }
-  __syncthreads();
+  lds_barrier();
   fused_body<C>(net, lds, xt, A, mrow, envs, io.eps_out + tok0 * A, ntok_live);
 }
 
@@ -1028,7 +1028,7 @@ __global__ __launch_bounds__(C::THREADS) void k_fused_draft(FusedNet net, DraftI
   const int env0 = blockIdx.x * RPT;
   if (io.gate && *io.gate == 0) return;
   if (threadIdx.x == 0) s_kmax = 0;
-  __syncthreads();
+  lds_barrier();
   if (threadIdx.x < RPT) {
     const int b = env0 + threadIdx.x;
     const bool live = b < io.B;
@@ -1051,7 +1051,7 @@ __global__ __launch_bounds__(C::THREADS) void k_fused_draft(FusedNet net, DraftI
     const int b = env0 + i / DE;
     yt[i] = b < io.B ? io.y[(size_t)env0 * DE + i] : 0.0f;
   }
-  __syncthreads();
+  lds_barrier();
   const int kmax = s_kmax;
   for (int k = 1; k <= kmax; ++k) {
     if (net.modtab) {                                   // FiLM vectors of timestep t_k straight from the table
@@ -1073,7 +1073,7 @@ __global__ __launch_bounds__(C::THREADS) void k_fused_draft(FusedNet net, DraftI
       if (net.cemb) g += net.cemb[(size_t)envs[r] * D + c];
       sgbuf[j * SGS + c] = (elem)silu_fast(g);
     }
-    __syncthreads();
+    lds_barrier();
     {
       constexpr int MBM = 2;
       const int fpw = net.L * 4 * D / (16 * C::NW);     // mod fragments per wave
@@ -1096,9 +1096,9 @@ __global__ __launch_bounds__(C::THREADS) void k_fused_draft(FusedNet net, DraftI
     }
     }
     }
-    __syncthreads();
+    lds_barrier();
     fused_body<DraftCfg<C>>(net, lds, yt, A, mrow, envs, et, NT, dbias);
-    __syncthreads();
+    lds_barrier();
     // DDPM step of transition k for the environments that still draft
     const int nblk = DE >> 2;
     for (int i = threadIdx.x; i < RPT * nblk; i += TH) {
@@ -1127,7 +1127,7 @@ __global__ __launch_bounds__(C::THREADS) void k_fused_draft(FusedNet net, DraftI
       if (io.xi) *reinterpret_cast<f32x4*>(io.xi + row * DE + 4 * blk) = z;
       *reinterpret_cast<f32x4*>(yp) = o;
     }
-    __syncthreads();
+    lds_barrier();
   }
   for (int i = threadIdx.x; i < NT * A; i += TH) {
     const int b = env0 + i / DE;
