@@ -23,6 +23,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "fused_mfma.hpp"
+#include "kernels_f32.hpp"
 
 namespace tsdp {
 
@@ -40,12 +41,14 @@ struct FewCfg {
   static_assert(D % 32 == 0 && H % 16 == 0 && CH % TT_::KSTEP == 0 && CH % 16 == 0 && DH % TT_::KSTEP == 0, "shape");
 };
 
-// Run-time sizes (fp32): any D, head width and hidden width that are multiples of 16; H = 16 NB.
+// Run-time sizes (fp32, with the exact functions of the operator kernels): any D, head width and hidden width that are
+// multiples of 16; H = 16 NB.
 template <int NB_>
 struct FewDyn {
   typedef TF32 TT;
   static constexpr bool DYN = true, WIDE = false;
-  static constexpr int D = 0, H = NB_ * 16, HEADS = 0, SX = 0, NCH = 0, DH = 0, CH = 0, NB = NB_, JV = 4, NW = 4, TH = 256, NPA = 1, NPM = 1;
+  static constexpr int D = 0, H = NB_ * 16, HEADS = 0, SX = 0, NCH = 0, DH = 0, CH = 0, NB = NB_, JV = 4, NW = 4, TH = 256;
+  static constexpr int NPA = 1, NPM = 1;           // (the number is in FewIO)
 };
 
 struct FewIO {
@@ -308,7 +311,7 @@ __device__ __forceinline__ void few_norm(const FewIO& io, const FewFilm<C>& fm, 
   for (int p = 0; p < W::NPASS; ++p) rstd[p] = lane_sum<W::LPT>(rstd[p]);
 #pragma unroll
   for (int p = 0; p < W::NPASS; ++p) {
-    const float rs = rsqrtf(rstd[p] * rD + 1e-5f);
+    const float rs = C::DYN ? 1.0f / sqrtf(rstd[p] * rD + 1e-5f) : rsqrtf(rstd[p] * rD + 1e-5f);
     const int tk = W::tok(p, wave, lane);
 #pragma unroll
     for (int j = 0; j < JV; ++j) {
@@ -584,7 +587,7 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_attn(FewIO io, std::conditiona
         TT::mma(*reinterpret_cast<const frag*>(k + (kf * 16 + l16) * QS + ks * KSTEP + lg * VW), qb, s[kf]);
     }
     vec4 p[NB];
-    softmax_keys<TT, NB>(s, p, DH);
+    softmax_keys<TT, NB, C::DYN>(s, p, DH);
 #pragma unroll
     for (int cf = 0; cf < DH / 16; ++cf) {
       f32x4 o = f32x4{0, 0, 0, 0};
@@ -708,7 +711,7 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_mlp(FewIO io) {
     for (int nb = 0; nb < NB; ++nb) {
       f32x4 r = acc[nb] + b;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) r[i] = gelu_fast(r[i]);
+      for (int i = 0; i < 4; ++i) r[i] = C::DYN ? gelu_tanh_f(r[i]) : gelu_fast(r[i]);
       if constexpr (C::WIDE) few_store_act<C>(io, row, nb * 16 + l16, M, slice * CH + f * 16 + lg * 4, TT::cvt(r));
       else *reinterpret_cast<typename TT::vec4*>(u + (nb * 16 + l16) * US + f * 16 + lg * 4) = TT::cvt(r);
     }

@@ -40,7 +40,7 @@ constexpr int FUSED_MAX_LAYERS = 16;
 
 struct FusedNet {
   FusedLayer layer[FUSED_MAX_LAYERS];
-  int L;
+  int L, D, heads, M;
   const float* tok_w; const float* tok_b; const float* pos;   // fp32 [D,A], [D], [H,D]
   const float* tok_wt;         // [A,D] (k_few_*)
   const void* head;            // [ceil(A/16)][D/32][64] fragments of head_w, rows padded to a multiple of 16
@@ -156,9 +156,9 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // softmax over the keys (rows of s, NK key fragments) for the 16 queries of one fragment
-template <class TT, int NK>
+template <class TT, int NK, bool EXACT = false>
 __device__ __forceinline__ void softmax_keys(f32x4 (&s)[NK], typename TT::vec4 (&p)[NK], int DH) {
-  const float scale = rsqrtf((float)DH);
+  const float scale = EXACT ? 1.0f / sqrtf((float)DH) : rsqrtf((float)DH);
   float mx = -INFINITY;
 #pragma unroll
   for (int kf = 0; kf < NK; ++kf)
@@ -169,9 +169,9 @@ __device__ __forceinline__ void softmax_keys(f32x4 (&s)[NK], typename TT::vec4 (
 #pragma unroll
   for (int kf = 0; kf < NK; ++kf)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { s[kf][i] = __expf(s[kf][i] - mx); sum += s[kf][i]; }
+    for (int i = 0; i < 4; ++i) { s[kf][i] = EXACT ? expf(s[kf][i] - mx) : __expf(s[kf][i] - mx); sum += s[kf][i]; }
   sum = add_half32(add_row16(sum));
-  const float inv = __builtin_amdgcn_rcpf(sum);       // one approximate reciprocal (1 ulp) instead of an IEEE division
+  const float inv = EXACT ? 1.0f / sum : __builtin_amdgcn_rcpf(sum);   // one approximate reciprocal (1 ulp), no IEEE division
 #pragma unroll
   for (int kf = 0; kf < NK; ++kf) p[kf] = TT::cvt(s[kf] * inv);
 }

@@ -256,17 +256,24 @@ void launch_mod(const FusedNet& n, const int32_t* t_arr, int t_sub, const int32_
 
 // The launches of one spread forward pass: every kernel reads the residual and the partial sums its predecessor left
 // and writes the other pair of buffers.
+// slices of a run-time hidden width: eight where fragments of 16 allow it
+inline int few_slices_dyn(int M) {
+  int n = 8;
+  while (M % (16 * n)) n /= 2;
+  return n;
+}
+
 template <class C>
 struct FewPass {
   typedef typename C::TT TT;
-  static constexpr int D = C::D;
   const FusedNet& n;
   const FewRun& r;
   hipStream_t s;
   FewIO io{};
   DraftIO dr{};
   int at = 0;
-  const int la = few_lds_attn<TT>(D, C::H, C::DH), lm = few_lds_mlp<TT>(D, C::H, C::CH);
+  const int D = C::DYN ? n.D : C::D, heads = C::DYN ? n.heads : C::HEADS, nch = C::DYN ? few_slices_dyn(n.M) : C::NCH;
+  const int la = few_lds_attn<TT>(D, C::H, D / heads), lm = few_lds_mlp<TT>(D, C::H, n.M / nch);
 
   FewPass(const FusedNet& n_, const FewRun& r_, hipStream_t s_) : n(n_), r(r_), s(s_) {
     io.by_row = r.R_cap >= (std::getenv("TSDP_BYROW") ? atoi(std::getenv("TSDP_BYROW")) : 8);
@@ -274,6 +281,7 @@ struct FewPass {
     io.by_t = n.modtab != nullptr; io.mod_stride = n.L * 4 * D; io.row_t = r.row_t; io.T = r.T; io.row_env = r.row_env;
     io.x = r.x; io.tok_wt = n.tok_wt; io.tok_b = n.tok_b; io.pos = n.pos; io.A = r.A;
     io.head = n.head; io.head_b = n.head_b; io.eps_out = r.eps_out; io.kc = n.kc; io.vct = n.vct; io.L = n.L; io.rms = n.rms;
+    io.D = D; io.DH = D / heads; io.heads = heads; io.M = n.M; io.CH = n.M / nch;
   }
   static constexpr int FIRST = C::WIDE ? 0 : C::NPM;   // residual that the previous MLP block left
   // buffers of the next launch: partial sums and residual change places; wide rows keep their residual where it is
@@ -296,41 +304,42 @@ struct FewPass {
     if constexpr (C::WIDE) {
       flip();
       io.part_in = r.part[0]; io.w2 = w; io.bias_in = bias;
-      hipLaunchKernelGGL((k_few_out<C, K>), dim3(rows() * (D / 64)), dim3(C::TH), C::NW * C::H * 64 * 4, s, io);
+      hipLaunchKernelGGL((k_few_out<C, K>), dim3(rows() * (C::D / 64)), dim3(C::TH), C::NW * C::H * 64 * 4, s, io);
     } else {
       io.bias_in = bias;
     }
   }
   void start(bool ends_step) {
-    const dim3 th(C::TH), ga(rows() * C::HEADS);
+    const dim3 th(C::TH), ga(rows() * heads);
     if (ends_step) hipLaunchKernelGGL((k_few_attn<C, FIRST, true>), ga, th, la + FEW_STEP_LDS, s, io, dr);
     else hipLaunchKernelGGL((k_few_attn<C, FEW_EMBED>), ga, th, la + FEW_STEP_LDS, s, io, FewNone{});
   }
   // all layers; mod = FiLM vectors of row 0; ends_step: the first launch ends the rollout's previous transition
   void layers(const float* mod, bool ends_step) {
-    const dim3 th(C::TH), ga(rows() * C::HEADS), gm(rows() * C::NCH);
+    const dim3 th(C::TH), ga(rows() * heads), gm(rows() * nch);
     if (C::WIDE) io.part_out = r.part[0];
     for (int l = 0; l < n.L; ++l) {
       const FusedLayer& w = n.layer[l];
       flip(l == 0);
-      io.mod = mod + (size_t)l * 4 * D; io.w1 = w.qkv; io.b1 = w.qkv_b; io.w2 = w.o; io.layer = l;
+      io.mod = mod + (size_t)l * 4 * D; io.w1 = w.qkv; io.b1 = w.qkv_b; io.w2 = w.o; io.layer = l; io.n_part = nch;
       if (l == 0) start(ends_step);
       else hipLaunchKernelGGL((k_few_attn<C, FIRST>), ga, th, la, s, io, FewNone{});
-      out<D>(w.o, w.o_b);
+      out<C::D>(w.o, w.o_b);
       if constexpr (C::SX > 0) {
         flip();
         io.w1 = w.cq; io.b1 = w.cq_b; io.w2 = w.co;
         hipLaunchKernelGGL((k_few_cross<C, C::NPA>), ga, th, la, s, io);
-        out<D>(w.co, w.co_b);
+        out<C::D>(w.co, w.co_b);
       }
       flip();
-      io.mod += 2 * D; io.w1 = w.up; io.b1 = w.up_b; io.w2 = w.dn;
+      io.mod += 2 * D; io.w1 = w.up; io.b1 = w.up_b; io.w2 = w.dn; io.n_part = heads;
       hipLaunchKernelGGL((k_few_mlp<C, C::NPA>), gm, th, lm, s, io);
-      out<4 * D>(w.dn, w.dn_b);
+      out<4 * C::D>(w.dn, w.dn_b);
     }
   }
   void head() {
     flip();
+    io.n_part = nch;
     hipLaunchKernelGGL((k_few_head<C, FIRST>), dim3(r.R_cap), dim3(C::TH), lm, s, io);
   }
 };
@@ -347,7 +356,7 @@ void few_forward(const FusedNet& n, const FewRun& r, hipStream_t s) {
 template <class C>
 void few_draft(const FusedNet& n, const FewRun& r, const DraftIO& dr, int k_max, float* const* y, hipStream_t s) {
   FewPass<C> p(n, r, s);
-  const int stride = n.L * 4 * C::D;
+  const int stride = n.L * 4 * p.D;
   p.dr = dr;
   p.io.word = dr.K_eff;
   p.io.roll = 1;
@@ -362,6 +371,7 @@ void few_draft(const FusedNet& n, const FewRun& r, const DraftIO& dr, int k_max,
       p.layers(p.io.by_t ? r.mod : r.mod + (size_t)(k - 1) * stride, k > 1);
     } else {
       p.flip(true);
+      p.io.n_part = p.nch;
       p.start(true);
     }
   }
@@ -370,10 +380,10 @@ void few_draft(const FusedNet& n, const FewRun& r, const DraftIO& dr, int k_max,
 template <class TT, int D>
 void launch_few_film(const FusedNet& n, const int32_t* t_arr, int t_sub, const int32_t* env_arr, int k_max, int T,
                      const int32_t* d_R, int R_cap, float* mod, hipStream_t s) {
-  const int Nm = n.L * 4 * D;
+  const int d = D ? D : n.D, Nm = n.L * 4 * d;
   hipLaunchKernelGGL((k_few_film<TT, D>), dim3((Nm / 16 + 3) / 4, (R_cap + 15) / 16), dim3(256),
-                     16 * (D + TT::PAD) * (int)sizeof(typename TT::elem), s, n.modw, n.modb, n.temb, n.cemb, t_arr, t_sub, env_arr,
-                     k_max, T, D, Nm, d_R, R_cap, mod);
+                     16 * (d + TT::PAD) * (int)sizeof(typename TT::elem), s, n.modw, n.modb, n.temb, n.cemb, t_arr, t_sub, env_arr,
+                     k_max, T, d, Nm, d_R, R_cap, mod);
 }
 
 struct FusedKernels {
@@ -401,7 +411,7 @@ constexpr int F256_CH = 256;
 constexpr int FEW_TILES = 288;   // up to this many tiles the 8-wave verify variant (one workgroup per CU) is used
 constexpr int V512_HPX = 8;      // heads per cross-attention phase of the d = 512 verify kernel
 constexpr int V512_CH = 256;     // hidden-chunk width of the d = 512 verify kernel
-constexpr size_t FEW_TOKENS = 2176, FEW_LAYER_BYTES = 700000;   // build_fused
+constexpr size_t FEW_TOKENS = 2176, FEW_TOKENS_DYN = 32768, FEW_LAYER_BYTES = 700000;   // build_fused
 // shapes with compiled fused kernels
 bool find_fused(int dtype, int D, int H, int heads, int cm, int S, int mlp_ratio, int L, FusedKernels& k) {
   if (mlp_ratio != 4 || L > FUSED_MAX_LAYERS) return false;
@@ -439,6 +449,27 @@ bool find_fused(int dtype, int D, int H, int heads, int cm, int S, int mlp_ratio
   TSDP_SHAPE(TF32, 0, 32, 16, 2, 0, 0, 16, 32, 2, 2, 2, 16, 128, 2, 2, 16, 128, 2, 2)
 #undef TSDP_SHAPE
   return false;
+}
+
+// Shapes without a compiled kernel: up to FEW_TOKENS_DYN tokens the spread kernels (d = 96 / 48, rounds of 64, 512, 2048 rows:
+// 235, 408, 1108 us; one launch per operator 816, 934, 1359; equal at 8192 rows) with run-time sizes (vector conditioning, sizes in fragments of
+// 16, a row's operands in the LDS; 48 and 64 tokens would spill the residual).
+template <class C>
+hipError_t few_dyn_kernels(FusedKernels& k) {
+  k.few_forward = few_forward<C>; k.few_draft = few_draft<C>; k.few_film = launch_few_film<TF32, 0>;
+  for (const void* f : {(const void*)k_few_attn<C, FEW_EMBED>, (const void*)k_few_attn<C, 1>, (const void*)k_few_attn<C, 1, true>,
+                        (const void*)k_few_mlp<C, 1>, (const void*)k_few_head<C, 1>, (const void*)k_few_film<TF32, 0>})
+    if (hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)) return e;
+  return hipSuccess;
+}
+
+hipError_t find_few_dyn(const tsdp_config& cf, const Net& n, FusedKernels& k) {
+  const int dh = n.d / n.heads, ch = n.m % 16 ? 0 : n.m / few_slices_dyn(n.m);
+  if (cf.cond_mode != 0 || (cf.H != 16 && cf.H != 32) || n.d % 16 || dh % 16 || n.m % 16 || n.L > FUSED_MAX_LAYERS ||
+      few_lds_attn<TF32>(n.d, cf.H, dh) + FEW_STEP_LDS > 160 * 1024 || few_lds_mlp<TF32>(n.d, cf.H, ch) > 160 * 1024)
+    return hipSuccess;
+  k.few_slices = std::max(n.heads, few_slices_dyn(n.m));
+  return cf.H == 16 ? few_dyn_kernels<FewDyn<1>>(k) : few_dyn_kernels<FewDyn<2>>(k);
 }
 
 // rows of the ragged batch a context must hold: K_max per environment, one more with the bonus row
@@ -481,7 +512,7 @@ size_t layout_net(const tsdp_config& cf, int which, Net& n) {
 int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vector<float>& modw_cat, const FusedKernels& fk) {
   const tsdp_config& cf = c->cfg;
   const int d = n.d, m = n.m, L = n.L, DH = d / n.heads;
-  const bool f32 = cf.dtype == 0;
+  const bool dyn = !fk.verify, f32 = dyn || cf.dtype == 0;   // run-time sizes: fp32 operands, as in the operator kernels
   std::vector<uint8_t> pk;
   std::vector<float> qb((size_t)L * 3 * d);
   struct Off { size_t qkv, o, up, dn, cq, co; };
@@ -517,7 +548,7 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   HIPCHK(c, hipMemcpy(dqb, qb.data(), qb.size() * sizeof(float), hipMemcpyHostToDevice));
   FusedNet& f = n.fnet;
   std::memset(&f, 0, sizeof(f));
-  f.L = L;
+  f.L = L; f.D = d; f.heads = n.heads; f.M = m;
   auto P = [&](size_t o) { return reinterpret_cast<const void*>(dpk + o); };
   for (int l = 0; l < L; ++l) {
     const LayerOff& o = n.lay[l];
@@ -565,7 +596,7 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
     f.kc = reinterpret_cast<const bf16x8*>(n.kc_pk);
     f.vct = reinterpret_cast<const bf16x4*>(n.vct_pk);
   }
-  n.fused = true;
+  n.fused = !dyn;
   n.fused_verify = fk.verify;
   n.fused_verify_few = fk.verify_few;
   n.verify_rpt = fk.rpt_verify;
@@ -580,13 +611,13 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   // through two launches (fp32 d = 64, 393 KB in all: 21 us against 25).  The capacity of the context decides, not the call: an
   // environment's result must not depend on the batch it is computed in.
   const size_t layer_bytes = (size_t)(cf.cond_mode == 1 ? 14 : 12) * d * d * (f32 ? 4 : 2);
-  n.few = rows_max(cf) * cf.H <= FEW_TOKENS && layer_bytes >= FEW_LAYER_BYTES;
+  n.few = dyn ? rows_max(cf) * cf.H <= FEW_TOKENS_DYN : rows_max(cf) * cf.H <= FEW_TOKENS && layer_bytes >= FEW_LAYER_BYTES;
   // The rollout: fp32 layers are bound by one unit's matrix rate (d = 128: 39 us per transition, spread 27), bf16 drafters
   // of this size are not (d = 192: spread 2 us per transition slower).  A drafter of the base network's own shape takes
   // the base network's kernels, so that equal weights give equal predictions.
   const bool twin = cf.base_d == cf.draft_d && cf.base_layers == cf.draft_layers && cf.base_heads == cf.draft_heads;
   n.few_roll = n.few && (twin || f32);
-  n.path = f32 ? "f32-mfma-fused" : "bf16-mfma-fused";
+  if (!dyn) n.path = f32 ? "f32-mfma-fused" : "bf16-mfma-fused";
   return TSDP_OK;
 }
 
@@ -653,7 +684,7 @@ FewRun few_run(tsdp_ctx* c, const Net& n, int R_cap, int safe_rows, const int32_
 // made `s` wait for them)
 int forward(tsdp_ctx* c, Net& n, const float* x_rows, int R_cap, const int32_t* d_R, const int32_t* t_arr,
             int t_sub, const int32_t* env_arr, float* eps_out, hipStream_t s, bool mod_ready = false, int safe_rows = 0) {
-  if (!n.fused) {
+  if (!n.fused && !n.few) {
     forward_f32(c, n, x_rows, R_cap, d_R, t_arr, t_sub, env_arr, eps_out, s);
     return TSDP_OK;
   }
@@ -669,7 +700,7 @@ int forward(tsdp_ctx* c, Net& n, const float* x_rows, int R_cap, const int32_t* 
     n.few_film(n.fnet, t_arr, t_sub, env_arr, 0, cf.T, d_R, R_cap, c->mod, s);
   }
   const int stage = (&n == &c->net[0]) ? 1 : -1;          // only the base network's forward is the verify stage
-  if (n.few && stage == 1) {
+  if (n.few && (stage == 1 || !n.fused)) {
     FewRun r = few_run(c, n, R_cap, safe_rows, t_arr, env_arr, c->mod);
     r.x = x_rows; r.d_R = d_R; r.eps_out = eps_out;
     tick(c, 1, 0, s);
@@ -924,13 +955,12 @@ int tsdp_load_weights(tsdp_ctx* c, int which, const float* h_blob, size_t nbytes
   HIPCHK(c, hipMemcpy(n.modb, modb.data(), modb.size() * sizeof(float), hipMemcpyHostToDevice));
   n.loaded = true;
   c->cond_set = false;
-  n.fused = false;
+  n.fused = n.few = n.few_roll = false;
   n.path = "f32-ops";
   if (!std::getenv("TSDP_DISABLE_FUSED")) {
     FusedKernels fk;
-    if (find_fused(cf.dtype, n.d, cf.H, n.heads, cf.cond_mode, cf.cond_tokens, n.m / n.d, n.L, fk) &&
-        (rc = build_fused(c, n, w, modw, fk)))
-      return rc;
+    if (!find_fused(cf.dtype, n.d, cf.H, n.heads, cf.cond_mode, cf.cond_tokens, n.m / n.d, n.L, fk)) HIPCHK(c, find_few_dyn(cf, n, fk));
+    if (fk.few_forward && (rc = build_fused(c, n, w, modw, fk))) return rc;
   }
   if (!n.fused && cf.cond_mode == 1 && !n.kc) {        // fp32 keys / values of the operator kernels
     const size_t cnt = (size_t)L * cf.B_max * cf.cond_tokens * d;
@@ -1023,9 +1053,9 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
   hipLaunchKernelGGL(k_rows, dim3(B), dim3(128), 0, s, d_x, d_t0, (const int32_t*)d_row_ptr, cf.T, D, d_row_t,
                      d_row_env, d_y_last, d_states, d_eps_p, d_xi, gated ? (const int32_t*)c->n_draft : nullptr);
   Net& dn = c->net[1];
-  if (dn.fused) {
+  if (dn.fused || dn.few_roll) {
     // persistent drafter kernel (or the spread launches): pick the tile (environments per workgroup) that fills the chip best
-    const bool big = (B + dn.draft_rpt_big - 1) / dn.draft_rpt_big >= 192;
+    const bool big = dn.fused && (B + dn.draft_rpt_big - 1) / dn.draft_rpt_big >= 192;
     const int rpt = big ? dn.draft_rpt_big : dn.draft_rpt_small;
     const size_t lds = fused_draft_lds(dn, cf, rpt);
     if (dn.few_roll || lds <= 160 * 1024) {

@@ -162,6 +162,19 @@ def test_forward_of_few_rows_at_its_edges(base, B, K_max):
     _stage_parity(wl, B, t0, K, s, clip=1.5 if B == 9 else None, norm=B == 3, bonus=B == 17 and K_max == 1)
 
 
+@pytest.mark.parametrize("dtype, H, base, draft, B", [
+    ("fp32", 16, ti.NetShape(2, 112, 7), ti.NetShape(1, 48, 3), 1),      # seven k-steps, heads of one fragment
+    ("fp32", 32, ti.NetShape(1, 144, 3, 3), ti.NetShape(1, 16, 1, 1), 3),   # nine k-steps, hidden width 27 fragments; one fragment in all
+    ("fp32", 16, ti.NetShape(1, 272, 17), ti.NetShape(1, 96, 3), 2),     # 272 features: a second vector on some lanes
+    ("bf16", 16, ti.NetShape(1, 320, 5), ti.NetShape(1, 64, 2), 9),      # bf16 weights, fp32 operands
+])
+def test_few_rows_of_run_time_sizes(dtype, H, base, draft, B):
+    wl = ti.small_variant(ti.C2, dtype=dtype, H=H, A=6, cond_dim=32, K_max=3, base=base, draft=draft)
+    t0 = np.full(B, 60); t0[-1] = 2
+    K = np.full(B, 3); K[0] = 2
+    _stage_parity(wl, B, t0, K, np.full(B, 1.1), bonus=B == 2, paths=("f32-ops", "f32-ops"))
+
+
 @pytest.mark.parametrize("wl", [ti.small_variant(ti.C3, base=ti.NetShape(2, 256, 4), draft=ti.NetShape(2, 256, 4), K_max=3),
                                 ti.small_variant(ti.C4, base=ti.NetShape(1, 512, 8), draft=ti.NetShape(1, 512, 8), K_max=3)])
 def test_few_rows_of_equal_networks_give_equal_predictions(wl):
