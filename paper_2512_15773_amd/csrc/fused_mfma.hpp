@@ -319,7 +319,8 @@ struct FusedCfg {
   static constexpr bool LN_STAGE = true;                // FiLM vectors come from global memory: fetch them cooperatively
   static constexpr int WAVES_PER_SIMD = (WG_PER_CU * NW + 3) / 4;
   static constexpr int BD = WAVES_PER_SIMD >= 2 ? 1 : 2; // LDS operand buffers: a second wave on the SIMD hides LDS latency
-  static constexpr bool XPF = WAVES_PER_SIMD == 1;      // request the first weight fragments of a phase one phase early
+  static constexpr bool XPF = WAVES_PER_SIMD == 1;      // request the first weights of the MLP's products one phase early
+                                                         // (those of the attention blocks always: C3 -1 %, C4 and C5 -0.5 %)
   static_assert(D % (16 * NW) == 0 && NT % 16 == 0 && H % 16 == 0 && NT % H == 0 && DH % KSTEP == 0, "shape");
   static_assert(D % KSTEP == 0 && CH % KSTEP == 0, "shape");
   static_assert((HEADS % HP) == 0 && (HP * 3 * DH) % (16 * NW) == 0 && (CM == 0 || (HPX * DH) % (16 * NW) == 0) &&
@@ -648,6 +649,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
   for (int layer = 0; layer < net.L; ++layer) {
     const FusedLayer& W = net.layer[layer];
     // ================= self-attention block =================
+    if (!XPF) gq.issue(W.qkv, KD, wave, 0, lane, NW);
     write_ln(layer, 0);
     if constexpr (BSTAGE) {
       // The layer's biases that are added outside a product's own latency shadow go to LDS: the MLP's GELU runs inside
@@ -675,9 +677,8 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0, 0, 0, 0};
         }
-        if (!XPF) gq.issue(W.qkv, KD, g * (HP * 3 * DH / 16) + wave, 0, lane, NW);
         gq.run(act, AS, acc, lane);
-        if (XPF) go.issue(W.o, KD, wave * MBH, g * HP * KH, lane);      // needed only after the attention
+        go.issue(W.o, KD, wave * MBH, g * HP * KH, lane);      // needed only after the attention
         if (g > 0) lds_barrier();                     // previous group's O-projection has read qbuf
 #pragma unroll
         for (int mb = 0; mb < MBQ; ++mb) {
@@ -704,8 +705,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
       for (int task = wave; task < RPT * HP * NKF; task += NW)
           self_attention((task / NKF) % RPT, task / (NKF * RPT), task % NKF);
       lds_barrier();
-      if (XPF && g + 1 < NG) gq.issue(W.qkv, KD, (g + 1) * (HP * 3 * DH / 16) + wave, 0, lane, NW);
-      if (!XPF) go.issue(W.o, KD, wave * MBH, g * HP * KH, lane);
+      if (g + 1 < NG) gq.issue(W.qkv, KD, (g + 1) * (HP * 3 * DH / 16) + wave, 0, lane, NW);
       go.run(qbuf, QTS, h, lane);                        // one product over the heads of the group
     }
     add_bias_h(W.o_b, layer, 0);
@@ -719,7 +719,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
       constexpr int NTASK = RPT * HPX * NKF, TPW = (NTASK + NW - 1) / NW;
       typedef FragGemm<TT, MBH, NB, HPX * KH, BD> GOX;
       GC gc;
-      if (XPF) gc.issue(W.cq, KD, wave * MBC, 0, lane);
+      gc.issue(W.cq, KD, wave * MBC, 0, lane);
       write_ln(layer, -1);                               // its barriers order the O-projection reads before qbuf writes
       for (int g = 0; g < NGX; ++g) {
         FENCE_LANE_IDS();
@@ -749,9 +749,8 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0, 0, 0, 0};
           }
-          if (!XPF) gc.issue(W.cq, KD, g * (HPX * DH / 16) + wave * MBC, 0, lane);
           gc.run(act, AS, acc, lane);
-          if (XPF) go.issue(W.co, KD, wave * MBH, g * HPX * KH, lane);
+          go.issue(W.co, KD, wave * MBH, g * HPX * KH, lane);
           if (g > 0) lds_barrier();
 #pragma unroll
           for (int mb = 0; mb < MBC; ++mb) {
@@ -788,8 +787,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
           }
         }
         lds_barrier();
-        if (XPF && g + 1 < NGX) gc.issue(W.cq, KD, (g + 1) * (HPX * DH / 16) + wave * MBC, 0, lane);
-        if (!XPF) go.issue(W.co, KD, wave * MBH, g * HPX * KH, lane);
+        if (g + 1 < NGX) gc.issue(W.cq, KD, (g + 1) * (HPX * DH / 16) + wave * MBC, 0, lane);
         go.run(qbuf, QXS, h, lane);
       }
       add_bias_h(W.co_b, layer, 1);
@@ -800,11 +798,12 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
       // matrix pipeline leaves free.  Its first half is spread over the k-steps of the down-projection of chunk
       // c-1, its second half over those of the up-projection of chunk c+1 (all of it in one product would need
       // more vector slots than that product leaves); one barrier per chunk.
+      GU gu;
+      gu.issue(W.up, KD, wave * MBU, 0, lane);
       write_ln(layer, 2);
       f32x4 accA[MBU][NB], accB[MBU][NB];
       constexpr int PARTS = MBU * NB;
       constexpr int HALF = PARTS / 2;                         // parts done under the previous down-projection
-      GU gu;
       GD gd;
       constexpr bool PRIME = KD >= GD::PF && KC >= GU::PF;
       typedef std::integral_constant<int, GU::PF> UFULL;
@@ -872,7 +871,6 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
         }
       };
       zero(accA);
-      gu.issue(W.up, KD, wave * MBU, 0, lane);
       gu.run(act, AS, accA, lane);
 #pragma unroll
       for (int idx = 0; idx < HALF; ++idx) gelu_part(0, accA, idx);
