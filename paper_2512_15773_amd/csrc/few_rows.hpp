@@ -234,12 +234,13 @@ __device__ __forceinline__ void few_embed(const FewIO& io, const float* xr, int 
       for (int u = 0; u < 8; ++u) w[u] = *reinterpret_cast<const f32x4*>(io.tok_wt + (size_t)min(a0 + u, A - 1) * D + c);
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        if (a0 + u >= A) break;
+        if (a0 + u < A) {
 #pragma unroll
-        for (int p = 0; p < W::NPASS; ++p) {
-          const float xv = xr[min(W::tok(p, wave, lane), C::H - 1) * A + a0 + u];
+          for (int p = 0; p < W::NPASS; ++p) {
+            const float xv = xr[min(W::tok(p, wave, lane), C::H - 1) * A + a0 + u];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) v[p][j][i] = fmaf(xv, w[u][i], v[p][j][i]);
+            for (int i = 0; i < 4; ++i) v[p][j][i] = fmaf(xv, w[u][i], v[p][j][i]);
+          }
         }
       }
     }
@@ -471,7 +472,7 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_attn(FewIO io, std::conditiona
   typedef typename TT::elem elem;
   typedef typename TT::vec4 vec4;
   typedef typename TT::frag frag;
-  constexpr int H = C::H, NB = C::NB, KSTEP = TT::KSTEP, VW = TT::VW, VS = H + 4;
+  constexpr int H = C::H, NB = C::NB, KSTEP = TT::KSTEP, VW = TT::VW, VS = H + 4, UNR = C::DYN ? 1 : 8;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int D = few_d<C>(io), DH = C::DYN ? io.DH : C::DH, heads = C::DYN ? io.heads : C::HEADS;
   const int AS = D + TT::PAD, QS = DH + TT::PAD, KD = D / KSTEP, KH = DH / KSTEP;
@@ -579,7 +580,7 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_attn(FewIO io, std::conditiona
     f32x4 s[NB];
 #pragma unroll
     for (int kf = 0; kf < NB; ++kf) s[kf] = f32x4{0, 0, 0, 0};
-#pragma unroll
+#pragma unroll UNR
     for (int ks = 0; ks < KH; ++ks) {
       const frag qb = *reinterpret_cast<const frag*>(qp + l16 * QS + ks * KSTEP + lg * VW);
 #pragma unroll
@@ -588,7 +589,7 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_attn(FewIO io, std::conditiona
     }
     vec4 p[NB];
     softmax_keys<TT, NB, C::DYN>(s, p, DH);
-#pragma unroll
+#pragma unroll UNR
     for (int cf = 0; cf < DH / 16; ++cf) {
       f32x4 o = f32x4{0, 0, 0, 0};
 #pragma unroll

@@ -77,7 +77,8 @@ struct DraftIO {               // drafter rollout
   int mod_cols;                // columns of one in-kernel FiLM product: a multiple of RPT up to 16 (mod_cols/RPT steps at once)
   float* y;                    // [B,H,A]  in: the latents, out: the latents after the last drafted step
   float* states; float* eps_p; float* xi;   // [R,H,A] retained per drafted transition
-  const int32_t* gate;         // chain driver: live row count of the round (0 = every environment finished), or null
+  const int32_t* gate;         // 0: no environment drafts in this round
+  int bonus;                   // also write the bonus row of every running environment (k_bonus_rows)
 };
 
 __device__ __forceinline__ float gelu_fast(float x) {
@@ -1024,7 +1025,7 @@ __global__ __launch_bounds__(C::THREADS) void k_fused_draft(FusedNet net, DraftI
   float* dbias = reinterpret_cast<float*>(sgbuf + 16 * SGS);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, lg = lane >> 4;
   const int env0 = blockIdx.x * RPT;
-  if (io.gate && *io.gate == 0) return;
+  if (*io.gate == 0 && !io.bonus) return;
   if (threadIdx.x == 0) s_kmax = 0;
   lds_barrier();
   if (threadIdx.x < RPT) {
@@ -1039,8 +1040,9 @@ __global__ __launch_bounds__(C::THREADS) void k_fused_draft(FusedNet net, DraftI
     s_rowp[threadIdx.x] = live ? io.row_ptr[b] : 0;
     atomicMax(&s_kmax, ke);
   }
-  for (int i = threadIdx.x; i < 16 * SGS; i += TH) sgbuf[i] = (elem)0.0f;
-  for (int i = threadIdx.x; i < net.L * 3 * D; i += TH) {
+  const bool any = *io.gate != 0;
+  if (any) for (int i = threadIdx.x; i < 16 * SGS; i += TH) sgbuf[i] = (elem)0.0f;
+  if (any) for (int i = threadIdx.x; i < net.L * 3 * D; i += TH) {
     const int l = i / (3 * D), which = (i / D) % 3, c = i % D;
     const float* src = which == 0 ? net.layer[l].o_b : (which == 1 ? net.layer[l].co_b : net.layer[l].dn_b);
     dbias[i] = src ? src[c] : 0.0f;
@@ -1127,9 +1129,23 @@ __global__ __launch_bounds__(C::THREADS) void k_fused_draft(FusedNet net, DraftI
     }
     lds_barrier();
   }
-  for (int i = threadIdx.x; i < NT * A; i += TH) {
+  if (any) for (int i = threadIdx.x; i < NT * A; i += TH) {
     const int b = env0 + i / DE;
     if (b < io.B) io.y[(size_t)env0 * DE + i] = yt[i];
+  }
+  if (io.bonus) {                                       // the state reached by the last draft, with a base step's noise
+    const int nblk = DE >> 2;
+    for (int i = threadIdx.x; i < RPT * nblk; i += TH) {
+      const int r = i / nblk, blk = i % nblk, b = env0 + r;
+      if (s_t0[r] < 0) continue;
+      const int t = s_t0[r] - s_keff[r];
+      const size_t row = (size_t)s_rowp[r] + s_keff[r];
+      float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (t > 0) z = xi_block(io.seed, io.env_id ? io.env_id[b] : b, t, blk);
+      *reinterpret_cast<f32x4*>(io.states + row * DE + 4 * blk) = *reinterpret_cast<const f32x4*>(yt + r * DE + 4 * blk);
+      *reinterpret_cast<f32x4*>(io.eps_p + row * DE + 4 * blk) = f32x4{0, 0, 0, 0};
+      if (io.xi) *reinterpret_cast<f32x4*>(io.xi + row * DE + 4 * blk) = f32x4{z.x, z.y, z.z, z.w};
+    }
   }
 }
 

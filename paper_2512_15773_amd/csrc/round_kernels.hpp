@@ -19,7 +19,7 @@ __global__ __launch_bounds__(1024) void k_plan(const int32_t* __restrict__ t0, c
                                                const float* __restrict__ sigma_scale,
                                                int B, int K_max, int T, int bonus, int32_t* __restrict__ K_eff,
                                                int32_t* __restrict__ row_ptr, int32_t* __restrict__ status,
-                                               int32_t* __restrict__ n_draft) {
+                                               int32_t* __restrict__ n_draft, int32_t* __restrict__ live) {
   __shared__ int32_t part[1024];
   __shared__ int32_t carry;
   if (threadIdx.x == 0) carry = 0;
@@ -53,9 +53,72 @@ __global__ __launch_bounds__(1024) void k_plan(const int32_t* __restrict__ t0, c
     __syncthreads();
   }
   if (threadIdx.x == 0) {
+    if (live) *live = 0;                            // chain driver: counted by this round's k_accept
     row_ptr[B] = carry;
     n_draft[0] = carry > 0 ? B : 0;                 // environments with rows: none once all have finished
     n_draft[1] = any_draft ? B : 0;                 // environments the drafter has to look at: none in a round of plain base steps
+  }
+}
+
+// k_plan and k_rows in one launch: one workgroup per environment counts the rows of all of them (two words each, from
+// the L2) to find its own first row.  Up to PLAN_ROWS_B environments that costs less than the launch it saves (a chain of
+// one environment: 4.5 us of a 330 us round); beyond it the counting grows with B^2.
+constexpr int PLAN_ROWS_B = 1024;
+__global__ __launch_bounds__(128) void k_plan_rows(const float* __restrict__ x, const int32_t* __restrict__ t0,
+                                                   const int32_t* __restrict__ K, const float* __restrict__ sigma_scale, int B,
+                                                   int K_max, int T, int D, int bonus, int gated, int32_t* __restrict__ K_eff,
+                                                   int32_t* __restrict__ row_ptr, int32_t* __restrict__ status,
+                                                   int32_t* __restrict__ n_draft, int32_t* __restrict__ live,
+                                                   int32_t* __restrict__ row_t, int32_t* __restrict__ row_env,
+                                                   float* __restrict__ y, float* __restrict__ states, float* __restrict__ eps_p,
+                                                   float* __restrict__ xi) {
+  __shared__ int32_t part[3][2];
+  const int b = blockIdx.x, k_min = bonus ? 0 : 1;
+  auto plan = [&](int kk, int tt, int& ke) {            // rows of an environment
+    const int k = min(max(kk, k_min), K_max), t = min(tt, T - 1);
+    ke = t < 0 ? 0 : min(k, t);
+    return t < 0 ? 0 : (bonus ? ke + 1 : max(ke, 1));
+  };
+  const int my_k = K[b], my_t = t0[b];
+  int before = 0, total = 0, drafts = 0;
+  for (int e = threadIdx.x; e < B; e += 128) {
+    int ke;
+    const int n = plan(K[e], t0[e], ke);
+    total += n; drafts |= ke;
+    if (e < b) before += n;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) { before += __shfl_xor(before, o); total += __shfl_xor(total, o); drafts |= __shfl_xor(drafts, o); }
+  if ((threadIdx.x & 63) == 0) {
+    const int w = threadIdx.x >> 6;
+    part[0][w] = before; part[1][w] = total; part[2][w] = drafts;
+  }
+  __syncthreads();
+  const int r0 = part[0][0] + part[0][1], R = part[1][0] + part[1][1];
+  int ke;
+  const int n = plan(my_k, my_t, ke);
+  if (threadIdx.x == 0) {
+    if (my_k < k_min || my_k > K_max) atomicOr(status, 1);
+    if (my_t >= T) atomicOr(status, 2);
+    if (my_t >= 0 && !(sigma_scale[b] > 0.0f)) atomicOr(status, 4);
+    K_eff[b] = ke; row_ptr[b] = r0;
+    if (b == B - 1) row_ptr[B] = R;
+    if (b == 0) {
+      n_draft[0] = R > 0 ? B : 0; n_draft[1] = part[2][0] | part[2][1] ? B : 0;
+      if (live) *live = 0;
+    }
+  }
+  if (gated && R == 0) return;                          // chain driver: no environment is running any more
+  const int t = min(my_t, T - 1);
+  for (int j = threadIdx.x; j < n; j += 128) { row_t[r0 + j] = t - j; row_env[r0 + j] = b; }
+  for (int e = threadIdx.x; e < D; e += 128) {
+    const float v = x[(long long)b * D + e];
+    y[(long long)b * D + e] = v;
+    if (t == 0) {
+      states[(long long)r0 * D + e] = v;
+      eps_p[(long long)r0 * D + e] = 0.0f;
+      if (xi) xi[(long long)r0 * D + e] = 0.0f;
+    }
   }
 }
 
@@ -193,6 +256,18 @@ __device__ __forceinline__ double group_sum(double v) {
 
 __device__ __forceinline__ double group16_sum(double v) { return group_sum<16>(v); }
 
+// Chain bookkeeping, done by the acceptance kernel as it finishes an environment: per-environment totals, the number of
+// environments still running and the number of rounds that had rows (any of the pointers may be null).
+struct ChainAcc {
+  int32_t* tot_accept; int32_t* tot_drafts; int32_t* tot_rounds; int32_t* live; int32_t* rounds_run;
+  __device__ __forceinline__ void add(int b, int n_acc, int K_eff, int t_next) const {
+    if (tot_accept) tot_accept[b] += n_acc;
+    if (tot_drafts) tot_drafts[b] += K_eff;
+    if (tot_rounds) tot_rounds[b] += 1;
+    if (live && t_next >= 0) atomicAdd(live, 1);
+  }
+};
+
 // Acceptance: one wavefront per environment, 64/G rows at a time (one row per group of G lanes; the host picks G so
 // that the D/4 16-byte vectors of a row fill the lanes: 8 lanes x 5 vectors at D = 160, 16 x 7 at D = 448).  Each
 // group streams eps_p, eps_q, xi (and the state when x0 is clamped) of its row with 16-byte loads, all of them
@@ -216,7 +291,7 @@ __global__ __launch_bounds__(256) void k_accept(int B, int D, const int32_t* __r
                                                 float* __restrict__ x_out, int32_t* __restrict__ t_next,
                                                 int32_t* __restrict__ n_accept, int32_t* __restrict__ n_adv,
                                                 uint8_t* __restrict__ flags, float* __restrict__ logratio,
-                                                float* __restrict__ logu_out, const int32_t* __restrict__ gate) {
+                                                float* __restrict__ logu_out, const int32_t* __restrict__ gate, ChainAcc chain) {
   // chain driver: once no environment is running, latents, timesteps and counters stay as they are
   if (gate && *gate == 0) return;
   // MAXI = 16-byte vectors per lane and row: rows of up to G*MAXI*4 elements
@@ -224,6 +299,7 @@ __global__ __launch_bounds__(256) void k_accept(int B, int D, const int32_t* __r
   const int lane = threadIdx.x & 63, grp = lane / G, gl = lane % G;
   const int b = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (b >= B) return;
+  if (chain.rounds_run && b == 0 && lane == 0 && row_ptr[B] > 0) *chain.rounds_run += 1;
   const int r0 = row_ptr[b], r1 = row_ptr[b + 1];
   const int nb = D >> 2;
   float4* xo = reinterpret_cast<float4*>(x_out + (long long)b * D);
@@ -338,13 +414,13 @@ __global__ __launch_bounds__(256) void k_accept(int B, int D, const int32_t* __r
       }
       xo[i] = make_float4(o[0], o[1], o[2], o[3]);
     }
-    if (lane == 0) { t_next[b] = t - 1; n_accept[b] = K_eff; if (n_adv) n_adv[b] = K_eff + 1; }
+    if (lane == 0) { t_next[b] = t - 1; n_accept[b] = K_eff; if (n_adv) n_adv[b] = K_eff + 1; chain.add(b, K_eff, K_eff, t - 1); }
     return;
   }
   if (jstar == 0) {                                 // every draft accepted: commit y_{K_eff}
     const float4* yl = reinterpret_cast<const float4*>(y_last + (long long)b * D);
     for (int i = lane; i < nb; i += 64) xo[i] = yl[i];
-    if (lane == 0) { t_next[b] = t0 - K_eff; n_accept[b] = K_eff; if (n_adv) n_adv[b] = K_eff; }
+    if (lane == 0) { t_next[b] = t0 - K_eff; n_accept[b] = K_eff; if (n_adv) n_adv[b] = K_eff; chain.add(b, K_eff, K_eff, t0 - K_eff); }
     return;
   }
   {                                                 // reflect the first rejected draft about the target mean
@@ -373,26 +449,8 @@ __global__ __launch_bounds__(256) void k_accept(int B, int D, const int32_t* __r
       }
       xo[i] = make_float4(o[0], o[1], o[2], o[3]);
     }
-    if (lane == 0) { t_next[b] = t0 - jstar; n_accept[b] = jstar - 1; if (n_adv) n_adv[b] = jstar; }
+    if (lane == 0) { t_next[b] = t0 - jstar; n_accept[b] = jstar - 1; if (n_adv) n_adv[b] = jstar; chain.add(b, jstar - 1, K_eff, t0 - jstar); }
   }
-}
-
-// Chain bookkeeping after a round: per-environment totals and the number of environments still running.
-__global__ void k_chain_accum(int B, const int32_t* __restrict__ t, const int32_t* __restrict__ K_eff,
-                              const int32_t* __restrict__ n_acc, const int32_t* __restrict__ n_adv,
-                              const int32_t* __restrict__ row_ptr, int32_t* __restrict__ tot_accept,
-                              int32_t* __restrict__ tot_drafts, int32_t* __restrict__ tot_rounds, int32_t* __restrict__ live,
-                              int32_t* __restrict__ rounds_run) {
-  if (rounds_run && blockIdx.x == 0 && threadIdx.x == 0 && row_ptr[B] > 0) *rounds_run += 1;   // a round that had rows
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  const bool ran = row_ptr[b + 1] > row_ptr[b];      // the environment had rows in this round
-  if (ran) {
-    if (tot_accept) tot_accept[b] += n_acc[b];
-    if (tot_drafts) tot_drafts[b] += K_eff[b];
-    if (tot_rounds) tot_rounds[b] += 1;
-  }
-  if (live && t[b] >= 0) atomicAdd(live, 1);
 }
 
 __global__ void k_fill_i32(int32_t* p, int n, int32_t v) {

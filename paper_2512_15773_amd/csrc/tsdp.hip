@@ -1030,7 +1030,8 @@ int tsdp_set_cond(tsdp_ctx* c, const float* d_cond, int B, void* stream) {
 static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0, const int32_t* d_K,
                       const float* d_sigma_scale, const int32_t* d_env_id, int32_t* d_row_ptr, int32_t* d_row_t,
                       int32_t* d_row_env, float* d_states, float* d_eps_p, float* d_xi, float* d_y_last, bool gated,
-                      void* stream, int base_mod_rows = 0, bool* base_mod_started = nullptr) {
+                      void* stream, int base_mod_rows = 0, bool* base_mod_started = nullptr, int32_t* live = nullptr) {
+  // live: word that the round's k_accept counts the running environments in (cleared here), or null
   // base_mod_rows > 0 (whole rounds): once the row table exists, the base network's per-row FiLM vectors of up to that
   // many rows are computed on the auxiliary stream, beside the rollout; *base_mod_started tells the caller to join
   int rc = check_ready(c, B, true);
@@ -1043,15 +1044,21 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
   hipStream_t s = (hipStream_t)stream;
   const tsdp_config& cf = c->cfg;
   const int D = c->D;
-  hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, d_t0, d_K, d_sigma_scale, B, cf.K_max, cf.T, cf.bonus_row, c->K_eff,
-                     d_row_ptr, c->status, c->n_draft);
+  if (B <= PLAN_ROWS_B) {
+    hipLaunchKernelGGL(k_plan_rows, dim3(B), dim3(128), 0, s, d_x, d_t0, d_K, d_sigma_scale, B, cf.K_max, cf.T, D, cf.bonus_row,
+                       gated ? 1 : 0, c->K_eff, d_row_ptr, c->status, c->n_draft, live, d_row_t, d_row_env, d_y_last, d_states,
+                       d_eps_p, d_xi);
+  } else {
+    hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, d_t0, d_K, d_sigma_scale, B, cf.K_max, cf.T, cf.bonus_row, c->K_eff,
+                       d_row_ptr, c->status, c->n_draft, live);
+    hipLaunchKernelGGL(k_rows, dim3(B), dim3(128), 0, s, d_x, d_t0, (const int32_t*)d_row_ptr, cf.T, D, d_row_t,
+                       d_row_env, d_y_last, d_states, d_eps_p, d_xi, gated ? (const int32_t*)c->n_draft : nullptr);
+  }
   auto bonus_rows = [&]() {
     if (cf.bonus_row)
       hipLaunchKernelGGL(k_bonus_rows, dim3(B), dim3(128), 0, s, d_t0, (const int32_t*)c->K_eff, (const int32_t*)d_row_ptr,
                          d_env_id, cf.T, D, cf.seed, (const float*)d_y_last, d_states, d_eps_p, d_xi);
   };
-  hipLaunchKernelGGL(k_rows, dim3(B), dim3(128), 0, s, d_x, d_t0, (const int32_t*)d_row_ptr, cf.T, D, d_row_t,
-                     d_row_env, d_y_last, d_states, d_eps_p, d_xi, gated ? (const int32_t*)c->n_draft : nullptr);
   Net& dn = c->net[1];
   if (dn.fused || dn.few_roll) {
     // persistent drafter kernel (or the spread launches): pick the tile (environments per workgroup) that fills the chip best
@@ -1075,6 +1082,7 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
       io.clip = cf.clip_x0; io.clip_val = cf.clip_val; io.seed = cf.seed;
       io.y = d_y_last; io.states = d_states; io.eps_p = d_eps_p; io.xi = d_xi;
       io.gate = c->n_draft + 1;
+      io.bonus = cf.bonus_row;
       tick(c, 0, 0, s);
       if (dn.few_roll) {
         if (!dn.fnet.modtab) dn.few_film(dn.fnet, d_t0, 0, nullptr, cf.K_max, cf.T, nullptr, B * cf.K_max, c->few_mod, s);
@@ -1084,7 +1092,7 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
         HIPCHK(c, (big ? dn.fused_draft_big : dn.fused_draft_small)(dn.fnet, io, cf.A, s));
       }
       tick(c, 0, 1, s);
-      bonus_rows();
+      if (dn.few_roll) bonus_rows();
       HIPCHK(c, hipGetLastError());
       return TSDP_OK;
     }
@@ -1143,7 +1151,7 @@ static int accept_impl(tsdp_ctx* c, int B, const int32_t* d_row_ptr, const int32
                        const float* d_sigma_scale, const float* d_lambda, const float* d_states, const float* d_eps_p,
                        const float* d_eps_q, const float* d_xi, const float* d_y_last, float* d_x_out, int32_t* d_t_next,
                        int32_t* d_n_accept, int32_t* d_n_adv, uint8_t* d_flags, float* d_logratio, float* d_logu,
-                       const int32_t* d_gate, void* stream) {
+                       const int32_t* d_gate, void* stream, const ChainAcc& chain = ChainAcc{}) {
   int rc = check_ready(c, B, false);
   if (rc) return rc;
   if (B == 0) return TSDP_OK;
@@ -1165,7 +1173,7 @@ static int accept_impl(tsdp_ctx* c, int B, const int32_t* d_row_ptr, const int32
 #define TSDP_ACCEPT_X(CL, RG, GG, MI)                                                                           \
   hipLaunchKernelGGL((k_accept<CL, RG, GG, MI>), g, blk, 0, s, B, c->D, d_row_ptr, d_row_t, d_env_id, d_sigma_scale, \
                      d_states, d_eps_p, d_eps_q, d_xi, d_y_last, c->tb, cf.clip_val, cf.seed, d_lambda, cf.bonus_row, d_x_out, d_t_next, \
-                     d_n_accept, d_n_adv, d_flags, d_logratio, d_logu, d_gate)
+                     d_n_accept, d_n_adv, d_flags, d_logratio, d_logu, d_gate, chain)
 #define TSDP_ACCEPT_MI(MI)                                                       \
   case MI:                                                                       \
     if (cf.clip_x0) { if (g8) TSDP_ACCEPT(true, 8, MI); else TSDP_ACCEPT(true, 16, MI); }    \
@@ -1205,7 +1213,7 @@ int tsdp_accept_threshold(tsdp_ctx* c, int B, const int32_t* d_row_ptr, const in
 
 static int round_impl(tsdp_ctx* c, int B, float* d_x, int32_t* d_t, const int32_t* d_K, const float* d_sigma_scale,
                       const int32_t* d_env_id, const float* d_lambda, int32_t* d_n_accept, int32_t* d_n_advanced,
-                      bool gated, void* stream) {
+                      bool gated, void* stream, const ChainAcc& chain = ChainAcc{}) {
   int rc = check_ready(c, B, true);
   if (rc) return rc;
   if (B == 0) return TSDP_OK;
@@ -1214,14 +1222,14 @@ static int round_impl(tsdp_ctx* c, int B, float* d_x, int32_t* d_t, const int32_
   const int R_cap = B * (c->cfg.K_max + (c->cfg.bonus_row ? 1 : 0));
   bool mod_started = false;
   if ((rc = draft_impl(c, B, d_x, d_t, d_K, d_sigma_scale, d_env_id, c->row_ptr, c->row_t, c->row_env, c->states,
-                       c->eps_p, c->xi, c->y_last, gated, stream, R_cap, &mod_started)))
+                       c->eps_p, c->xi, c->y_last, gated, stream, R_cap, &mod_started, chain.live)))
     return rc;
   if ((rc = verify_impl(c, B, R_cap, c->row_ptr, c->row_t, c->row_env, c->states, c->eps_q, true, stream, mod_started)))
     return rc;
   // x and t are overwritten in place: the acceptance kernel reads only the round's own buffers
   return accept_impl(c, B, c->row_ptr, c->row_t, d_env_id, d_sigma_scale, d_lambda, c->states, c->eps_p, c->eps_q, c->xi,
                      c->y_last, d_x, d_t, d_n_accept ? d_n_accept : c->n_acc, d_n_advanced ? d_n_advanced : c->n_adv,
-                     nullptr, nullptr, nullptr, gated ? (const int32_t*)c->n_draft : nullptr, stream);
+                     nullptr, nullptr, nullptr, gated ? (const int32_t*)c->n_draft : nullptr, stream, chain);
 }
 
 int tsdp_round(tsdp_ctx* c, int B, float* d_x, int32_t* d_t, const int32_t* d_K, const float* d_sigma_scale,
@@ -1270,6 +1278,7 @@ static int chain_impl(tsdp_ctx* c, int B, float* d_x, int32_t* d_t, const int32_
   const dim3 gb((B + 255) / 256), blk(256);
   for (int32_t* p : {d_tot_accept, d_tot_drafts, d_tot_rounds})
     if (p) hipLaunchKernelGGL(k_fill_i32, gb, blk, 0, s, p, B, 0);
+  const ChainAcc chain{d_tot_accept, d_tot_drafts, d_tot_rounds, host_checked ? c->live : nullptr, d_rounds_run};
   int rounds = 0;
   while (rounds < max_rounds) {
     if (staged) {
@@ -1277,16 +1286,12 @@ static int chain_impl(tsdp_ctx* c, int B, float* d_x, int32_t* d_t, const int32_
       hipLaunchKernelGGL(k_stage_select, gb, blk, 0, s, B, (const int32_t*)d_t, t_hi, t_lo, d_K, d_sigma_scale, d_lambda,
                          c->K_sel, c->s_sel, c->lam_sel);
       rc = round_impl(c, B, d_x, d_t, c->K_sel, c->s_sel, d_env_id, d_lambda ? c->lam_sel : nullptr, c->n_acc, c->n_adv,
-                      !host_checked, stream);
+                      !host_checked, stream, chain);
     } else {
-      rc = round_impl(c, B, d_x, d_t, d_K, d_sigma_scale, d_env_id, d_lambda, c->n_acc, c->n_adv, !host_checked, stream);
+      rc = round_impl(c, B, d_x, d_t, d_K, d_sigma_scale, d_env_id, d_lambda, c->n_acc, c->n_adv, !host_checked, stream, chain);
     }
     if (rc) return rc;
     ++rounds;
-    if (host_checked) hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(1), 0, s, c->live, 1, 0);
-    hipLaunchKernelGGL(k_chain_accum, gb, blk, 0, s, B, (const int32_t*)d_t, (const int32_t*)c->K_eff,
-                       (const int32_t*)c->n_acc, (const int32_t*)c->n_adv, (const int32_t*)c->row_ptr, d_tot_accept,
-                       d_tot_drafts, d_tot_rounds, host_checked ? c->live : nullptr, d_rounds_run);
     if (host_checked && (rounds % check_every == 0 || rounds == max_rounds)) {
       int32_t live = 0;
       HIPCHK(c, hipMemcpyAsync(&live, c->live, sizeof(int32_t), hipMemcpyDeviceToHost, s));

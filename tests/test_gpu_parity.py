@@ -191,6 +191,34 @@ def test_few_rows_of_equal_networks_give_equal_predictions(wl):
     ctx.close()
 
 
+@pytest.mark.parametrize("B", [127, 129, 1024, 1025])
+@pytest.mark.parametrize("bonus", [False, True])
+def test_row_table_and_chain_totals_over_the_batch_size(B, bonus):
+    # the row table is one launch up to 1024 environments and two beyond; a chain counts in its acceptance kernel
+    import torch
+    wl = ti.small_variant(ti.C1, B=B)
+    rng = np.random.default_rng(B)
+    t0 = rng.integers(-1, wl.T, B).astype(np.int32); K = rng.integers(0 if bonus else 1, wl.K_max + 1, B).astype(np.int32)
+    ctx = gpu_side(wl, ti.make_weights(wl, "base"), ti.make_weights(wl, "draft"), ti.make_cond(wl, B), B_max=B, bonus_row=bonus)
+    rows = ctx.alloc_rows(B)
+    x = to_dev(ti.make_latents(wl, B)); s = to_dev(np.ones(B, np.float32))
+    ctx.tsdp_draft(x, to_dev(t0), to_dev(K), s, None, rows)
+    ke, ptr = sr.plan_rows(t0, K, bonus)[:2]
+    np.testing.assert_array_equal(rows["row_ptr"].cpu().numpy(), ptr)
+    first = np.repeat(np.asarray(ptr)[:-1], np.diff(ptr))
+    np.testing.assert_array_equal(rows["row_t"].cpu().numpy()[:ptr[-1]], np.repeat(t0, np.diff(ptr)) - (np.arange(ptr[-1]) - first))
+    assert ctx.tsdp_status() == 0
+    td = to_dev(t0)
+    rounds, tot = ctx.tsdp_chain(x, td, to_dev(np.maximum(K, 1)), s, None, check_every=1)
+    live = np.asarray(t0) >= 0
+    assert bool((td < 0).all().item()) and rounds == int(tot["rounds"].max().item())
+    assert bool((tot["rounds"][~torch.from_numpy(live).cuda()] == 0).all().item())
+    # every step is an accepted draft, a reflected one or a base step, at most one of the latter two a round
+    adv = (tot["accept"] + tot["rounds"]).cpu().numpy()
+    assert (adv[live] >= t0[live] + 1).all() and (tot["accept"].cpu().numpy() <= tot["drafts"].cpu().numpy()).all()
+    ctx.close()
+
+
 def _round_parity(wl, B, t0, K, s, env, head_scale=1.0):
     """tsdp_round against the oracle's round.  The same inputs also go through the three stages with diagnostics,
     which gives the GPU's own log alpha of every row: the fused round must equal the stages bit for bit, accept
