@@ -11,6 +11,39 @@
 
 namespace tsdp {
 
+// Conditioning vectors: both networks' embeddings W cond + b in one launch.  One wavefront per
+// output feature and eight environments: it reads its weight row once, 16 bytes a lane, and sums over the lanes.  Bound by
+// the latency of two dependent reads, in large batches by the environments each wavefront reads again.  C = 1024, both
+// networks of d = 256 + 128 (384 + 192): 1, 64, 256, 1024 environments 6.9 (6.5), 7.9 (10), 19 (27), 66 (94) us; the tiled
+// product (C / 16 barrier steps whatever the batch) 117 us, so beyond 1024 environments that one stays.
+constexpr int COND_VEC_B = 1024;
+struct CondVecNet { const float* w; const float* b; float* out; int d; };
+__global__ __launch_bounds__(256) void k_cond_vec(const float* __restrict__ cond, CondVecNet n0, CondVecNet n1, int B, int C) {
+  constexpr int NE = 8;
+  const int lane = threadIdx.x & 63;
+  int f = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const CondVecNet n = f < n0.d ? n0 : n1;
+  if (f >= n0.d) f -= n0.d;
+  if (f >= n.d) return;
+  const int e0 = blockIdx.y * NE;
+  float acc[NE] = {};
+  for (int c = lane * 4; c < C; c += 256) {             // (C is a multiple of 4)
+    const f32x4 w = *reinterpret_cast<const f32x4*>(n.w + (size_t)f * C + c);
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(cond + (size_t)min(e0 + e, B - 1) * C + c);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[e] = fmaf(w[j], x[j], acc[e]);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) acc[e] += __shfl_xor(acc[e], o);
+    if (lane == 0 && e0 + e < B) n.out[(size_t)(e0 + e) * n.d + f] = acc[e] + n.b[f];
+  }
+}
+
 // cond [M, C] fp32 -> planes [ceil(M/16)][KS][3][64][8] bf16 in MFMA operand order (lane l: row l%16, columns
 // ks*32 + (l/16)*8 ..), zero beyond M and C.  One thread per (fragment, k-step, lane); C is a multiple of 4.
 __global__ __launch_bounds__(256) void k_split_cond(const float* __restrict__ cond, int M, int C, int KS,

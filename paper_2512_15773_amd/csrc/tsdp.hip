@@ -993,6 +993,16 @@ int tsdp_set_cond(tsdp_ctx* c, const float* d_cond, int B, void* stream) {
   if (!c->net[0].loaded || !c->net[1].loaded) return fail(c, TSDP_E_STATE, "weights of both networks must be loaded");
   hipStream_t s = (hipStream_t)stream;
   const tsdp_config& cf = c->cfg;
+  if (cf.cond_mode == 0 && B <= COND_VEC_B) {
+    const Net &a = c->net[0], &b = c->net[1];
+    hipLaunchKernelGGL(k_cond_vec, dim3((a.d + b.d + 3) / 4, (B + 7) / 8), dim3(256), 0, s, d_cond,
+                       CondVecNet{a.blob + a.c_w, a.blob + a.c_b, a.cemb, a.d}, CondVecNet{b.blob + b.c_w, b.blob + b.c_b, b.cemb, b.d},
+                       B, cf.cond_dim);
+    HIPCHK(c, hipGetLastError());
+    c->cond_set = true;
+    c->cond_B = B;
+    return TSDP_OK;
+  }
   CondIO io{};
   for (int which = 0; which < 2; ++which) {
     Net& n = c->net[which];

@@ -191,6 +191,26 @@ def test_few_rows_of_equal_networks_give_equal_predictions(wl):
     ctx.close()
 
 
+@pytest.mark.parametrize("B, cond_dim", [(1, 4), (9, 260), (1024, 64), (1025, 64)])
+def test_conditioning_vectors_at_the_edges_of_their_kernel(B, cond_dim):
+    # eight environments a wavefront, 256 components a step, another kernel beyond 1024 environments
+    wl = ti.small_variant(ti.C1, B=B, cond_dim=cond_dim)
+    wb = ti.make_weights(wl, "base", b_std=0.02); wd = ti.make_weights(wl, "draft", b_std=0.02)
+    cond = ti.make_cond(wl, B)
+    ctx = gpu_side(wl, wb, wd, cond, B_max=B)
+    rows = ctx.alloc_rows(B)
+    t0 = np.full(B, 5, np.int32); one = np.ones(B, np.int32)
+    ctx.tsdp_draft(to_dev(ti.make_latents(wl, B)), to_dev(t0), to_dev(one), to_dev(np.ones(B, np.float32)), None, rows)
+    ctx.tsdp_verify(B, rows)
+    pick = np.unique([0, B // 2, B - 1])
+    base, drafter, _ = oracle_side(wl, wb, wd)
+    st = rows["states"].cpu().numpy()[pick]
+    for net, name in ((drafter, "eps_p"), (base, "eps_q")):
+        ref = sr.verify(net, pick, t0[pick], st, cond)
+        assert scaled_err(rows[name].cpu().numpy()[pick], ref) < TOL["fp32"], name
+    ctx.close()
+
+
 @pytest.mark.parametrize("B", [127, 129, 1024, 1025])
 @pytest.mark.parametrize("bonus", [False, True])
 def test_row_table_and_chain_totals_over_the_batch_size(B, bonus):
