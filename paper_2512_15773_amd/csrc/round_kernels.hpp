@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 #include "philox.hpp"
 
 namespace tsdp {
@@ -19,7 +20,7 @@ __global__ __launch_bounds__(1024) void k_plan(const int32_t* __restrict__ t0, c
                                                const float* __restrict__ sigma_scale,
                                                int B, int K_max, int T, int bonus, int32_t* __restrict__ K_eff,
                                                int32_t* __restrict__ row_ptr, int32_t* __restrict__ status,
-                                               int32_t* __restrict__ n_draft, int32_t* __restrict__ live) {
+                                               int32_t* __restrict__ n_draft, int32_t* __restrict__ live, int32_t* __restrict__ rounds_run) {
   __shared__ int32_t part[1024];
   __shared__ int32_t carry;
   if (threadIdx.x == 0) carry = 0;
@@ -54,6 +55,7 @@ __global__ __launch_bounds__(1024) void k_plan(const int32_t* __restrict__ t0, c
   }
   if (threadIdx.x == 0) {
     if (live) *live = 0;                            // chain driver: counted by this round's k_accept
+    if (rounds_run && carry > 0) *rounds_run += 1;  // chain driver: rounds that had rows
     row_ptr[B] = carry;
     n_draft[0] = carry > 0 ? B : 0;                 // environments with rows: none once all have finished
     n_draft[1] = any_draft ? B : 0;                 // environments the drafter has to look at: none in a round of plain base steps
@@ -69,7 +71,7 @@ __global__ __launch_bounds__(128) void k_plan_rows(const float* __restrict__ x, 
                                                    int K_max, int T, int D, int bonus, int gated, int32_t* __restrict__ K_eff,
                                                    int32_t* __restrict__ row_ptr, int32_t* __restrict__ status,
                                                    int32_t* __restrict__ n_draft, int32_t* __restrict__ live,
-                                                   int32_t* __restrict__ row_t, int32_t* __restrict__ row_env,
+                                                   int32_t* __restrict__ rounds_run, int32_t* __restrict__ row_t, int32_t* __restrict__ row_env,
                                                    float* __restrict__ y, float* __restrict__ states, float* __restrict__ eps_p,
                                                    float* __restrict__ xi) {
   __shared__ int32_t part[3][2];
@@ -106,6 +108,7 @@ __global__ __launch_bounds__(128) void k_plan_rows(const float* __restrict__ x, 
     if (b == 0) {
       n_draft[0] = R > 0 ? B : 0; n_draft[1] = part[2][0] | part[2][1] ? B : 0;
       if (live) *live = 0;
+      if (rounds_run && R > 0) *rounds_run += 1;
     }
   }
   if (gated && R == 0) return;                          // chain driver: no environment is running any more
@@ -256,10 +259,12 @@ __device__ __forceinline__ double group_sum(double v) {
 
 __device__ __forceinline__ double group16_sum(double v) { return group_sum<16>(v); }
 
-// Chain bookkeeping, done by the acceptance kernel as it finishes an environment: per-environment totals, the number of
-// environments still running and the number of rounds that had rows (any of the pointers may be null).
+// Chain bookkeeping, done by the acceptance kernel as it finishes an environment: per-environment totals and the number of
+// environments still running (any of the pointers may be null).  Its own instantiation: a call of tsdp_accept carries none
+// of it.
+struct NoChain { __device__ __forceinline__ void add(int, int, int, int) const {} };
 struct ChainAcc {
-  int32_t* tot_accept; int32_t* tot_drafts; int32_t* tot_rounds; int32_t* live; int32_t* rounds_run;
+  int32_t* tot_accept; int32_t* tot_drafts; int32_t* tot_rounds; int32_t* live;
   __device__ __forceinline__ void add(int b, int n_acc, int K_eff, int t_next) const {
     if (tot_accept) tot_accept[b] += n_acc;
     if (tot_drafts) tot_drafts[b] += K_eff;
@@ -279,7 +284,7 @@ struct ChainAcc {
 // environment's rows and its value is masked out of the sums): a load under a lane-dependent condition becomes a
 // branch with its own wait, which serialises the stream.  The row data is read exactly once: non-temporal loads
 // (2^20-row shape: 0.426 -> 0.391 ms).
-template <bool CLIP, bool REGEN, int G, int MAXI>
+template <bool CLIP, bool REGEN, int G, int MAXI, bool CHAIN = false>
 __global__ __launch_bounds__(256) void k_accept(int B, int D, const int32_t* __restrict__ row_ptr,
                                                 const int32_t* __restrict__ row_t, const int32_t* __restrict__ env_id,
                                                 const float* __restrict__ sigma_scale, const float* __restrict__ states,
@@ -291,7 +296,8 @@ __global__ __launch_bounds__(256) void k_accept(int B, int D, const int32_t* __r
                                                 float* __restrict__ x_out, int32_t* __restrict__ t_next,
                                                 int32_t* __restrict__ n_accept, int32_t* __restrict__ n_adv,
                                                 uint8_t* __restrict__ flags, float* __restrict__ logratio,
-                                                float* __restrict__ logu_out, const int32_t* __restrict__ gate, ChainAcc chain) {
+                                                float* __restrict__ logu_out, const int32_t* __restrict__ gate,
+                                                std::conditional_t<CHAIN, ChainAcc, NoChain> chain) {
   // chain driver: once no environment is running, latents, timesteps and counters stay as they are
   if (gate && *gate == 0) return;
   // MAXI = 16-byte vectors per lane and row: rows of up to G*MAXI*4 elements
@@ -299,7 +305,6 @@ __global__ __launch_bounds__(256) void k_accept(int B, int D, const int32_t* __r
   const int lane = threadIdx.x & 63, grp = lane / G, gl = lane % G;
   const int b = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (b >= B) return;
-  if (chain.rounds_run && b == 0 && lane == 0 && row_ptr[B] > 0) *chain.rounds_run += 1;
   const int r0 = row_ptr[b], r1 = row_ptr[b + 1];
   const int nb = D >> 2;
   float4* xo = reinterpret_cast<float4*>(x_out + (long long)b * D);

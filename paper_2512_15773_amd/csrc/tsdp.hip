@@ -1040,8 +1040,9 @@ int tsdp_set_cond(tsdp_ctx* c, const float* d_cond, int B, void* stream) {
 static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0, const int32_t* d_K,
                       const float* d_sigma_scale, const int32_t* d_env_id, int32_t* d_row_ptr, int32_t* d_row_t,
                       int32_t* d_row_env, float* d_states, float* d_eps_p, float* d_xi, float* d_y_last, bool gated,
-                      void* stream, int base_mod_rows = 0, bool* base_mod_started = nullptr, int32_t* live = nullptr) {
-  // live: word that the round's k_accept counts the running environments in (cleared here), or null
+                      void* stream, int base_mod_rows = 0, bool* base_mod_started = nullptr, int32_t* live = nullptr,
+                      int32_t* rounds_run = nullptr) {
+  // live: word that the round's k_accept counts the running environments in (cleared here), rounds_run: rounds that had rows, or null
   // base_mod_rows > 0 (whole rounds): once the row table exists, the base network's per-row FiLM vectors of up to that
   // many rows are computed on the auxiliary stream, beside the rollout; *base_mod_started tells the caller to join
   int rc = check_ready(c, B, true);
@@ -1056,11 +1057,11 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
   const int D = c->D;
   if (B <= PLAN_ROWS_B) {
     hipLaunchKernelGGL(k_plan_rows, dim3(B), dim3(128), 0, s, d_x, d_t0, d_K, d_sigma_scale, B, cf.K_max, cf.T, D, cf.bonus_row,
-                       gated ? 1 : 0, c->K_eff, d_row_ptr, c->status, c->n_draft, live, d_row_t, d_row_env, d_y_last, d_states,
+                       gated ? 1 : 0, c->K_eff, d_row_ptr, c->status, c->n_draft, live, rounds_run, d_row_t, d_row_env, d_y_last, d_states,
                        d_eps_p, d_xi);
   } else {
     hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, d_t0, d_K, d_sigma_scale, B, cf.K_max, cf.T, cf.bonus_row, c->K_eff,
-                       d_row_ptr, c->status, c->n_draft, live);
+                       d_row_ptr, c->status, c->n_draft, live, rounds_run);
     hipLaunchKernelGGL(k_rows, dim3(B), dim3(128), 0, s, d_x, d_t0, (const int32_t*)d_row_ptr, cf.T, D, d_row_t,
                        d_row_env, d_y_last, d_states, d_eps_p, d_xi, gated ? (const int32_t*)c->n_draft : nullptr);
   }
@@ -1178,12 +1179,15 @@ static int accept_impl(tsdp_ctx* c, int B, const int32_t* d_row_ptr, const int32
   const int maxi8 = (nb + 7) / 8, maxi16 = (nb + 15) / 16;
   const bool g8 = maxi8 <= 8 && nb * 16 * maxi16 > nb * 8 * maxi8;   // the 8-lane mapping fits and idles fewer lanes
   const int maxi = g8 ? maxi8 : maxi16;
+  const bool chained = chain.tot_accept || chain.tot_drafts || chain.tot_rounds || chain.live;   // (a chain stores its noise)
 #define TSDP_ACCEPT(CL, GG, MI)                                                                                 \
-  if (d_xi) TSDP_ACCEPT_X(CL, false, GG, MI); else TSDP_ACCEPT_X(CL, true, GG, MI)
-#define TSDP_ACCEPT_X(CL, RG, GG, MI)                                                                           \
-  hipLaunchKernelGGL((k_accept<CL, RG, GG, MI>), g, blk, 0, s, B, c->D, d_row_ptr, d_row_t, d_env_id, d_sigma_scale, \
+  if (chained) TSDP_ACCEPT_X(CL, false, GG, MI, true, chain);                                                   \
+  else if (d_xi) TSDP_ACCEPT_X(CL, false, GG, MI, false, NoChain{});                                            \
+  else TSDP_ACCEPT_X(CL, true, GG, MI, false, NoChain{})
+#define TSDP_ACCEPT_X(CL, RG, GG, MI, CH, ACC)                                                                           \
+  hipLaunchKernelGGL((k_accept<CL, RG, GG, MI, CH>), g, blk, 0, s, B, c->D, d_row_ptr, d_row_t, d_env_id, d_sigma_scale, \
                      d_states, d_eps_p, d_eps_q, d_xi, d_y_last, c->tb, cf.clip_val, cf.seed, d_lambda, cf.bonus_row, d_x_out, d_t_next, \
-                     d_n_accept, d_n_adv, d_flags, d_logratio, d_logu, d_gate, chain)
+                     d_n_accept, d_n_adv, d_flags, d_logratio, d_logu, d_gate, ACC)
 #define TSDP_ACCEPT_MI(MI)                                                       \
   case MI:                                                                       \
     if (cf.clip_x0) { if (g8) TSDP_ACCEPT(true, 8, MI); else TSDP_ACCEPT(true, 16, MI); }    \
@@ -1223,7 +1227,7 @@ int tsdp_accept_threshold(tsdp_ctx* c, int B, const int32_t* d_row_ptr, const in
 
 static int round_impl(tsdp_ctx* c, int B, float* d_x, int32_t* d_t, const int32_t* d_K, const float* d_sigma_scale,
                       const int32_t* d_env_id, const float* d_lambda, int32_t* d_n_accept, int32_t* d_n_advanced,
-                      bool gated, void* stream, const ChainAcc& chain = ChainAcc{}) {
+                      bool gated, void* stream, const ChainAcc& chain = ChainAcc{}, int32_t* rounds_run = nullptr) {
   int rc = check_ready(c, B, true);
   if (rc) return rc;
   if (B == 0) return TSDP_OK;
@@ -1232,7 +1236,7 @@ static int round_impl(tsdp_ctx* c, int B, float* d_x, int32_t* d_t, const int32_
   const int R_cap = B * (c->cfg.K_max + (c->cfg.bonus_row ? 1 : 0));
   bool mod_started = false;
   if ((rc = draft_impl(c, B, d_x, d_t, d_K, d_sigma_scale, d_env_id, c->row_ptr, c->row_t, c->row_env, c->states,
-                       c->eps_p, c->xi, c->y_last, gated, stream, R_cap, &mod_started, chain.live)))
+                       c->eps_p, c->xi, c->y_last, gated, stream, R_cap, &mod_started, chain.live, rounds_run)))
     return rc;
   if ((rc = verify_impl(c, B, R_cap, c->row_ptr, c->row_t, c->row_env, c->states, c->eps_q, true, stream, mod_started)))
     return rc;
@@ -1288,7 +1292,7 @@ static int chain_impl(tsdp_ctx* c, int B, float* d_x, int32_t* d_t, const int32_
   const dim3 gb((B + 255) / 256), blk(256);
   for (int32_t* p : {d_tot_accept, d_tot_drafts, d_tot_rounds})
     if (p) hipLaunchKernelGGL(k_fill_i32, gb, blk, 0, s, p, B, 0);
-  const ChainAcc chain{d_tot_accept, d_tot_drafts, d_tot_rounds, host_checked ? c->live : nullptr, d_rounds_run};
+  const ChainAcc chain{d_tot_accept, d_tot_drafts, d_tot_rounds, host_checked ? c->live : nullptr};
   int rounds = 0;
   while (rounds < max_rounds) {
     if (staged) {
@@ -1296,9 +1300,9 @@ static int chain_impl(tsdp_ctx* c, int B, float* d_x, int32_t* d_t, const int32_
       hipLaunchKernelGGL(k_stage_select, gb, blk, 0, s, B, (const int32_t*)d_t, t_hi, t_lo, d_K, d_sigma_scale, d_lambda,
                          c->K_sel, c->s_sel, c->lam_sel);
       rc = round_impl(c, B, d_x, d_t, c->K_sel, c->s_sel, d_env_id, d_lambda ? c->lam_sel : nullptr, c->n_acc, c->n_adv,
-                      !host_checked, stream, chain);
+                      !host_checked, stream, chain, d_rounds_run);
     } else {
-      rc = round_impl(c, B, d_x, d_t, d_K, d_sigma_scale, d_env_id, d_lambda, c->n_acc, c->n_adv, !host_checked, stream, chain);
+      rc = round_impl(c, B, d_x, d_t, d_K, d_sigma_scale, d_env_id, d_lambda, c->n_acc, c->n_adv, !host_checked, stream, chain, d_rounds_run);
     }
     if (rc) return rc;
     ++rounds;
