@@ -1,9 +1,12 @@
 // Cross-attention keys / values of new observations, for the fused bf16 networks: every layer's K and V projection of
 // both networks in one launch, written straight in the fragment order the attention reads.
 //
-// The observations are fp32 and stay so: a float is the exact sum of three bf16 numbers (3 x 8 significant bits), the
-// weights are bf16 already, so three bf16 MFMAs per fragment pair give the fp32 x bf16 products exactly and add them
-// in fp32 -- at a third of the bf16 matrix rate, five times the fp32 matrix rate.
+// The sums are k_linear's, bit for bit: fp32 fused multiply-adds over the features in ascending order, then the bias,
+// then one rounding to bf16.  mfma_f32_16x16x4_f32 adds its four products to the accumulator one after the other, each
+// with one rounding, in the order of the lane groups (checked on hardware, denormals included), so a chain of them over
+// ascending features is that sum.  Another order (three bf16 planes per observation: 0.93 ms instead of 3.04) rounds a few
+// keys to the other bf16 number, and at the first timesteps of a squared-cosine chain, where a noise prediction is
+// multiplied by 31, that is enough for a nearly tied draft to fall on the other side of its test.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -44,94 +47,69 @@ __global__ __launch_bounds__(256) void k_cond_vec(const float* __restrict__ cond
   }
 }
 
-// cond [M, C] fp32 -> planes [ceil(M/16)][KS][3][64][8] bf16 in MFMA operand order (lane l: row l%16, columns
-// ks*32 + (l/16)*8 ..), zero beyond M and C.  One thread per (fragment, k-step, lane); C is a multiple of 4.
-__global__ __launch_bounds__(256) void k_split_cond(const float* __restrict__ cond, int M, int C, int KS,
-                                                    bf16x8* __restrict__ planes) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  const int MF = (M + 15) / 16;
-  if (i >= (long long)MF * KS * 64) return;
-  const int lane = (int)(i & 63);
-  const long long fk = i >> 6;
-  const int ks = (int)(fk % KS), mf = (int)(fk / KS);
-  const int row = mf * 16 + (lane & 15), col = ks * 32 + (lane >> 4) * 8;
-  float v[8];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    f32x4 x = f32x4{0, 0, 0, 0};
-    if (row < M && col + 4 * h < C) x = *reinterpret_cast<const f32x4*>(cond + (size_t)row * C + col + 4 * h);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[4 * h + j] = x[j];
-  }
-  bf16x8 p[3];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const __bf16 a = (__bf16)v[j];
-    const float r1 = v[j] - (float)a;
-    const __bf16 b = (__bf16)r1;
-    p[0][j] = a; p[1][j] = b; p[2][j] = (__bf16)(r1 - (float)b);
-  }
-  bf16x8* out = planes + fk * 3 * 64 + lane;
-#pragma unroll
-  for (int q = 0; q < 3; ++q) out[q * 64] = p[q];
-}
-
 struct CondNet {                 // one network's share of the launch
   const bf16x8* w;               // [L*2*d/16][KS][64] fragments: per layer the key rows, then the value rows
   const float* bias;             // [L*2*d]
   __bf16* kc; __bf16* vct;       // FusedNet::kc / vct
   int L, d, heads, tiles;        // tiles = L*2*d / 256
 };
-struct CondIO { CondNet net[2]; const bf16x8* planes; int MF, KS, SF; };   // MF = B*SF token fragments
+struct CondIO { CondNet net[2]; const float* cond; int M, C, KS, SF; };   // cond [M = B*S, C]
 
 // Tile: 256 features (16 fragments, all keys or all values of one layer because d is a multiple of 256) x 128 tokens
-// (8 fragments, three planes each).  8 waves as 4 x 2, each 64 features x 64 tokens.  Per k-step the workgroup brings
-// 16 KB of weights and 24 KB of planes into LDS and does 384 MFMAs (1536 cycles): 27 B per cycle and CU, half of what
-// the L2 delivers, so the matrix cores bound it.  Two LDS buffers, the next k-step travels through registers while
-// the current one is multiplied; one barrier per k-step.
+// (8 fragments).  8 waves as 4 x 2, each 64 features x 64 tokens.  Per k-step the workgroup brings 16 KB of weights and
+// 16 KB of observations into LDS and does 1024 MFMAs, 8192 cycles of each matrix core: they bound it.  Two LDS buffers,
+// the next k-step travels through registers while the current one is multiplied; one barrier per k-step.
+// Lane group g supplies features 4m + g of a k-step to MFMA m: the weights are packed in that order (build_fused).
 // Keys are computed features x tokens, values tokens x features, so that in both cases a lane's four accumulators are
 // the neighbouring entries of one 8-byte piece of the attention operand.
-// Measured, 256 environments x 64 tokens x 768, 12 layers of d = 512 and 2 of d = 256: 0.90 ms = 1.12 PFLOP/s of bf16
-// products (k_split_cond before it: 0.024 ms), against 4.9 ms of fp32 products on the vector units in 28 launches, each
-// followed by two that rounded and reordered its output.
-constexpr int COND_FF = 16, COND_TF = 8, COND_STAGE = (COND_FF + 3 * COND_TF) * 64;   // stage size in 16-byte units
-constexpr int COND_LDS = 2 * COND_STAGE * 16;
+// Measured, 256 environments x 64 tokens x 768, 12 layers of d = 512 and 2 of d = 256: 3.04 ms = 110 TFLOP/s (nominal fp32
+// matrix rate 157), against 4.9 ms of fp32 products on the vector units in 28 launches, each followed by two that rounded
+// and reordered its output.
+constexpr int COND_FF = 16, COND_TF = 8, COND_XS = 36;   // floats per token in LDS: 32 and the bank padding
+constexpr int COND_W_B = COND_FF * 64 * 16, COND_STAGE_B = COND_W_B + COND_TF * 16 * COND_XS * 4, COND_LDS = 2 * COND_STAGE_B;
 
 __global__ __launch_bounds__(512, 1) void k_cond_kv(CondIO io) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  bf16x8* lds = reinterpret_cast<bf16x8*>(lds_raw);
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wf = wave & 3, wt = wave >> 2, l16 = lane & 15, lg = lane >> 4;
   // consecutive workgroups share the feature tile and walk the tokens
-  const int tt = (io.MF + COND_TF - 1) / COND_TF;
+  const int MF = io.M / 16, tt = (MF + COND_TF - 1) / COND_TF;
   int ft = blockIdx.x / tt;
   const int tf0 = (blockIdx.x % tt) * COND_TF;
   const int which = ft >= io.net[0].tiles ? 1 : 0;
   const CondNet& n = io.net[which];
   if (which) ft -= io.net[0].tiles;
   const int KS = io.KS;
-  const bf16x8* wsrc = n.w + (size_t)ft * COND_FF * KS * 64;
-  // a wave fetches 5 of the 40 fragments of a stage: fragment id 0..15 weights, 16.. planes (token fragment, plane)
-  constexpr int PW = (COND_FF + 3 * COND_TF) / 8;
-  const bf16x8* src[PW];
-  int step[PW];
+  // a thread fetches two pieces of weights (fragments 2 wave, 2 wave + 1) and of observations (tokens xr, xr + 64)
+  const bf16x8* wsrc = n.w + ((size_t)ft * COND_FF + wave * 2) * KS * 64 + lane;
+  const int xr = threadIdx.x >> 3, xc = (threadIdx.x & 7) * 4;
+  const float* xsrc[2];
 #pragma unroll
-  for (int j = 0; j < PW; ++j) {
-    const int id = wave * PW + j;
-    if (id < COND_FF) {
-      src[j] = wsrc + (size_t)id * KS * 64 + lane; step[j] = 64;
-    } else {
-      const int tf = min(tf0 + (id - COND_FF) / 3, io.MF - 1), q = (id - COND_FF) % 3;
-      src[j] = io.planes + ((size_t)tf * KS * 3 + q) * 64 + lane; step[j] = 3 * 64;
+  for (int j = 0; j < 2; ++j) xsrc[j] = io.cond + (size_t)min(tf0 * 16 + xr + j * 64, io.M - 1) * io.C;
+  bf16x8 rw[2];
+  f32x4 rx[2];
+  auto request = [&](int k) {
+    k = min(k, KS - 1);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      rw[j] = wsrc[((size_t)j * KS + k) * 64];
+      rx[j] = *reinterpret_cast<const f32x4*>(xsrc[j] + min(k * 32 + xc, io.C - 4));
     }
-  }
-  bf16x8 r[PW];
+    __builtin_amdgcn_sched_barrier(0);                  // (the scheduler would sink the loads to their use)
+  };
+  auto deposit = [&](int k) {
+    unsigned char* st = lds + (k & 1) * COND_STAGE_B;
+    const bool in = k * 32 + xc < io.C;                 // (C is a multiple of 4; features beyond it are zero)
 #pragma unroll
-  for (int j = 0; j < PW; ++j) r[j] = src[j][0];
-#pragma unroll
-  for (int j = 0; j < PW; ++j) lds[(wave * PW + j) * 64 + lane] = r[j];
-#pragma unroll
-  for (int j = 0; j < PW; ++j) r[j] = src[j][(size_t)min(1, KS - 1) * step[j]];
+    for (int j = 0; j < 2; ++j) {
+      reinterpret_cast<bf16x8*>(st)[(wave * 2 + j) * 64 + lane] = rw[j];
+      *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(st + COND_W_B) + (xr + j * 64) * COND_XS + xc) =
+          in ? rx[j] : f32x4{0, 0, 0, 0};
+    }
+  };
+  request(0);
+  deposit(0);
+  request(1);
   f32x4 acc[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -143,28 +121,24 @@ __global__ __launch_bounds__(512, 1) void k_cond_kv(CondIO io) {
     constexpr bool keys = decltype(KEYS)::value;
     for (int k = 0; k < KS; ++k) {
       __syncthreads();                                  // stage k is in LDS; stage k-1 has been read by every wave
-      const bf16x8* st = lds + (k & 1) * COND_STAGE;
+      const unsigned char* st = lds + (k & 1) * COND_STAGE_B;
+      const float* xs = reinterpret_cast<const float*>(st + COND_W_B) + (wt * 64 + l16) * COND_XS + lg;
       bf16x8 a[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = st[(wf * 4 + i) * 64 + lane];
+      for (int i = 0; i < 4; ++i) a[i] = reinterpret_cast<const bf16x8*>(st)[(wf * 4 + i) * 64 + lane];
+      deposit(k + 1);
+      request(k + 2);
 #pragma unroll
-      for (int q = 2; q >= 0; --q) {                    // small pieces first
-        bf16x8 b[4];
+      for (int m = 0; m < 8; ++m) {
+        float b[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] = st[(COND_FF + (wt * 4 + j) * 3 + q) * 64 + lane];
-        if (q == 2) {
-          bf16x8* nx = lds + ((k + 1) & 1) * COND_STAGE;
-#pragma unroll
-          for (int j = 0; j < PW; ++j) nx[(wave * PW + j) * 64 + lane] = r[j];
-#pragma unroll
-          for (int j = 0; j < PW; ++j) r[j] = src[j][(size_t)min(k + 2, KS - 1) * step[j]];
-        }
+        for (int j = 0; j < 4; ++j) b[j] = xs[j * 16 * COND_XS + 4 * m];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            acc[i][j] = keys ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0)
-                             : __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
+            acc[i][j] = keys ? __builtin_amdgcn_mfma_f32_16x16x4f32((float)a[i][m], b[j], acc[i][j], 0, 0, 0)
+                             : __builtin_amdgcn_mfma_f32_16x16x4f32(b[j], (float)a[i][m], acc[i][j], 0, 0, 0);
       }
     }
   };
@@ -177,7 +151,7 @@ __global__ __launch_bounds__(512, 1) void k_cond_kv(CondIO io) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int tf = tf0 + wt * 4 + j;
-      if (tf >= io.MF) continue;
+      if (tf >= MF) continue;
       const int env = tf / SF, sf = tf % SF;
       const size_t eh = ((size_t)env * n.L + layer) * n.heads + head;
       if (cls == 0) {

@@ -93,7 +93,6 @@ struct tsdp_ctx {
   Net net[2];
   bool cond_set = false;
   int cond_B = 0;
-  uint8_t* cond_planes = nullptr;   // bf16 planes of the observation tokens (k_split_cond), shared by both networks
   int32_t* status = nullptr;
   int32_t* live = nullptr;      // environments still running (chain driver)
   int32_t* K_sel = nullptr;     // [B_max] per-round picks from the stage tables (staged chain driver)
@@ -576,13 +575,21 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
     const size_t S = cf.cond_tokens, cnt = (size_t)cf.B_max * L * S * d;
     if (!n.kc_pk && (rc = dev_alloc(c, &n.kc_pk, cnt))) return rc;
     if (!n.vct_pk && (rc = dev_alloc(c, &n.vct_pk, cnt))) return rc;
-    // key / value projections, per layer the key rows then the value rows (k_cond_kv)
+    // key / value projections, per layer the key rows then the value rows; inside a k-step entry i of lane group g is
+    // feature 4i + g (k_cond_kv)
     std::vector<uint8_t> kv;
     std::vector<float> kvb;
+    const int C = cf.cond_dim, CP = (C + 31) / 32 * 32;
+    std::vector<float> ord((size_t)d * CP, 0.0f);
+    auto pack_kv = [&](const float* src) {
+      for (int r = 0; r < d; ++r)
+        for (int k = 0; k < C; ++k) ord[(size_t)r * CP + k / 32 * 32 + k % 4 * 8 + k % 32 / 4] = src[(size_t)r * C + k];
+      pack_frags(kv, false, ord.data(), CP, d, ident);
+    };
     for (int l = 0; l < L; ++l) {
       const LayerOff& o = n.lay[l];
-      pack_frags(kv, f32, &w[o.ck_w], cf.cond_dim, d, ident);
-      pack_frags(kv, f32, &w[o.cv_w], cf.cond_dim, d, ident);
+      pack_kv(&w[o.ck_w]);
+      pack_kv(&w[o.cv_w]);
       kvb.insert(kvb.end(), &w[o.ck_b], &w[o.ck_b] + d);
       kvb.insert(kvb.end(), &w[o.cv_b], &w[o.cv_b] + d);
     }
@@ -590,8 +597,6 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
     if (!n.kv_b && (rc = dev_alloc(c, &n.kv_b, kvb.size()))) return rc;
     HIPCHK(c, hipMemcpy(n.kv_w, kv.data(), kv.size(), hipMemcpyHostToDevice));
     HIPCHK(c, hipMemcpy(n.kv_b, kvb.data(), kvb.size() * sizeof(float), hipMemcpyHostToDevice));
-    if (!c->cond_planes && (rc = dev_alloc(c, &c->cond_planes, (size_t)cf.B_max * S * ((cf.cond_dim + 31) / 32) * 32 * 6)))
-      return rc;
     HIPCHK(c, hipFuncSetAttribute(reinterpret_cast<const void*>(k_cond_kv), hipFuncAttributeMaxDynamicSharedMemorySize, COND_LDS));
     f.kc = reinterpret_cast<const bf16x8*>(n.kc_pk);
     f.vct = reinterpret_cast<const bf16x4*>(n.vct_pk);
@@ -1022,12 +1027,9 @@ int tsdp_set_cond(tsdp_ctx* c, const float* d_cond, int B, void* stream) {
     }
   }
   if (const int tiles = io.net[0].tiles + io.net[1].tiles) {
-    const int M = B * cf.cond_tokens;
-    io.planes = reinterpret_cast<const bf16x8*>(c->cond_planes);
-    io.MF = M / 16; io.KS = (cf.cond_dim + 31) / 32; io.SF = cf.cond_tokens / 16;
-    hipLaunchKernelGGL(k_split_cond, grid1((long long)io.MF * io.KS * 64, 256), dim3(256), 0, s, d_cond, M, cf.cond_dim, io.KS,
-                       reinterpret_cast<bf16x8*>(c->cond_planes));
-    hipLaunchKernelGGL(k_cond_kv, dim3(tiles * ((io.MF + COND_TF - 1) / COND_TF)), dim3(512), COND_LDS, s, io);
+    io.cond = d_cond;
+    io.M = B * cf.cond_tokens; io.C = cf.cond_dim; io.KS = (cf.cond_dim + 31) / 32; io.SF = cf.cond_tokens / 16;
+    hipLaunchKernelGGL(k_cond_kv, dim3(tiles * ((io.M / 16 + COND_TF - 1) / COND_TF)), dim3(512), COND_LDS, s, io);
   }
   HIPCHK(c, hipGetLastError());
   c->cond_set = true;

@@ -146,6 +146,30 @@ def test_cross_attention_operands_at_tile_edges(B, cond_dim, S):
     _stage_parity(wl, B, t0, K, s, paths=("bf16-mfma-fused", "bf16-mfma-fused"))
 
 
+@pytest.mark.parametrize("cond_dim, S", [(36, 64), (768, 64)])
+def test_keys_and_values_add_the_observation_features_in_order(cond_dim, S):
+    # 2^24 + 1 + ... + 1 - 2^24 is zero in fp32 in ascending order (a tie to even every time), and cond_dim - 2 or something
+    # between in any other order: an observation of these numbers must give the bits of an observation of zeros
+    import torch
+    wl = ti.small_variant(ti.C4, B=2, K_max=1, cond_dim=cond_dim, cond_tokens=S, base=ti.NetShape(1, 512, 8), draft=ti.NetShape(1, 256, 8))
+    nets = [ti.make_weights(wl, which, b_std=0.02) for which in ("base", "draft")]
+    for w in nets:
+        for name in w:
+            if name.endswith(("ck_w", "cv_w")):
+                w[name][:] = 1.0
+    cond = np.zeros((2, S, cond_dim), np.float32)
+    cond[1, :, 1:-1] = 1.0; cond[1, :, 0] = 2.0 ** 24; cond[1, :, -1] = -2.0 ** 24
+    ctx = gpu_side(wl, *nets, cond, B_max=2)
+    rows = ctx.alloc_rows(2)
+    x = np.repeat(ti.make_latents(wl, 2)[:1], 2, axis=0)
+    one = np.ones(2, np.int32)
+    ctx.tsdp_draft(to_dev(x), to_dev(50 * one), to_dev(one), to_dev(np.ones(2, np.float32)), to_dev(7 * one), rows)
+    ctx.tsdp_verify(2, rows)
+    for name in ("eps_p", "eps_q"):
+        assert bool(torch.isfinite(rows[name]).all()) and torch.equal(rows[name][0], rows[name][1]), name
+    ctx.close()
+
+
 @pytest.mark.parametrize("base, B, K_max", [
     (ti.replace(ti.C2, base=ti.NetShape(2, 256, 4)), 1, 1),       # one row
     (ti.replace(ti.C2, base=ti.NetShape(2, 256, 4)), 9, 1),       # rows not a multiple of the eight XCDs
