@@ -14,37 +14,55 @@
 
 namespace tsdp {
 
-// Conditioning vectors: both networks' embeddings W cond + b in one launch.  One wavefront per
-// output feature and eight environments: it reads its weight row once, 16 bytes a lane, and sums over the lanes.  Bound by
-// the latency of two dependent reads, in large batches by the environments each wavefront reads again.  C = 1024, both
-// networks of d = 256 + 128 (384 + 192): 1, 64, 256, 1024 environments 6.9 (6.5), 7.9 (10), 19 (27), 66 (94) us; the tiled
-// product (C / 16 barrier steps whatever the batch) 117 us, so beyond 1024 environments that one stays.
-constexpr int COND_VEC_B = 1024;
+// Conditioning vectors: both networks' embeddings W cond + b in one launch.  A workgroup takes 16 output features and 16
+// environments, one thread per number: fp32 fused multiply-adds over the components in ascending order, then the bias --
+// k_linear's sum, bit for bit, so an environment's embedding does not depend on which of the two a batch takes.  Weights
+// and vectors come through LDS in pieces of 256 components, the next piece travels in registers meanwhile.  Bound in small
+// batches by the chain of dependent multiply-adds, in large ones by the LDS (two 16-byte reads per four of them).
+// C = 1024, both networks of d = 256 + 128 (384 + 192): 1, 64, 256, 1024 environments 7.7 (7.6), 8.9 (9.0), 13 (18),
+// 31 (43) us; k_linear, whose C / 16 barrier steps take the same time for any batch up to 1024, 117 (131) us, so beyond 1024
+// environments that one stays.
+constexpr int COND_VEC_B = 1024, COND_VEC_C = 256, COND_VEC_S = COND_VEC_C + 4;   // (stride: 16 rows on different banks)
 struct CondVecNet { const float* w; const float* b; float* out; int d; };
 __global__ __launch_bounds__(256) void k_cond_vec(const float* __restrict__ cond, CondVecNet n0, CondVecNet n1, int B, int C) {
-  constexpr int NE = 8;
-  const int lane = threadIdx.x & 63;
-  int f = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const CondVecNet n = f < n0.d ? n0 : n1;
-  if (f >= n0.d) f -= n0.d;
-  if (f >= n.d) return;
-  const int e0 = blockIdx.y * NE;
-  float acc[NE] = {};
-  for (int c = lane * 4; c < C; c += 256) {             // (C is a multiple of 4)
-    const f32x4 w = *reinterpret_cast<const f32x4*>(n.w + (size_t)f * C + c);
+  __shared__ __attribute__((aligned(16))) float ws[16 * COND_VEC_S], xs[16 * COND_VEC_S];
+  const int tiles0 = (n0.d + 15) / 16;
+  const bool second = (int)blockIdx.x >= tiles0;
+  const CondVecNet n = second ? n1 : n0;
+  const int f0 = ((int)blockIdx.x - (second ? tiles0 : 0)) * 16, e0 = blockIdx.y * 16;
+  const int fl = threadIdx.x & 15, el = threadIdx.x >> 4, f = f0 + fl, e = e0 + el;
+  f32x4 rw[4], rx[4];                                   // thread i brings 16 bytes of rows i / 64 + 0, 4, 8, 12
+  const int row = threadIdx.x >> 6, col = (threadIdx.x & 63) * 4;
+  auto request = [&](int c0) {
+    const int c = min(c0 + col, C - 4);                 // (C is a multiple of 4; what lies beyond it is not summed)
 #pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      const f32x4 x = *reinterpret_cast<const f32x4*>(cond + (size_t)min(e0 + e, B - 1) * C + c);
+    for (int j = 0; j < 4; ++j) {
+      rw[j] = *reinterpret_cast<const f32x4*>(n.w + (size_t)min(f0 + row + 4 * j, n.d - 1) * C + c);
+      rx[j] = *reinterpret_cast<const f32x4*>(cond + (size_t)min(e0 + row + 4 * j, B - 1) * C + c);
+    }
+  };
+  float acc = 0.0f;
+  request(0);
+  for (int c0 = 0; c0 < C; c0 += COND_VEC_C) {
+    if (c0) __syncthreads();                            // the piece before has been read
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[e] = fmaf(w[j], x[j], acc[e]);
+    for (int j = 0; j < 4; ++j) {
+      *reinterpret_cast<f32x4*>(ws + (row + 4 * j) * COND_VEC_S + col) = rw[j];
+      *reinterpret_cast<f32x4*>(xs + (row + 4 * j) * COND_VEC_S + col) = rx[j];
+    }
+    __syncthreads();
+    if (c0 + COND_VEC_C < C) request(c0 + COND_VEC_C);
+    if (e0 + (el & ~3) < B) {                           // (a wavefront without an environment only brings data)
+      const int nc = min(COND_VEC_C, C - c0);
+#pragma unroll 8
+      for (int c = 0; c < nc; c += 4) {
+        const f32x4 w = *reinterpret_cast<const f32x4*>(ws + fl * COND_VEC_S + c), x = *reinterpret_cast<const f32x4*>(xs + el * COND_VEC_S + c);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc = fmaf(x[j], w[j], acc);
+      }
     }
   }
-#pragma unroll
-  for (int e = 0; e < NE; ++e) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc[e] += __shfl_xor(acc[e], o);
-    if (lane == 0 && e0 + e < B) n.out[(size_t)(e0 + e) * n.d + f] = acc[e] + n.b[f];
-  }
+  if (e < B && f < n.d) n.out[(size_t)e * n.d + f] = acc + n.b[f];
 }
 
 struct CondNet {                 // one network's share of the launch

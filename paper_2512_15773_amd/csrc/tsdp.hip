@@ -1000,7 +1000,7 @@ int tsdp_set_cond(tsdp_ctx* c, const float* d_cond, int B, void* stream) {
   const tsdp_config& cf = c->cfg;
   if (cf.cond_mode == 0 && B <= COND_VEC_B) {
     const Net &a = c->net[0], &b = c->net[1];
-    hipLaunchKernelGGL(k_cond_vec, dim3((a.d + b.d + 3) / 4, (B + 7) / 8), dim3(256), 0, s, d_cond,
+    hipLaunchKernelGGL(k_cond_vec, dim3((a.d + 15) / 16 + (b.d + 15) / 16, (B + 15) / 16), dim3(256), 0, s, d_cond,
                        CondVecNet{a.blob + a.c_w, a.blob + a.c_b, a.cemb, a.d}, CondVecNet{b.blob + b.c_w, b.blob + b.c_b, b.cemb, b.d},
                        B, cf.cond_dim);
     HIPCHK(c, hipGetLastError());

@@ -235,6 +235,39 @@ def test_conditioning_vectors_at_the_edges_of_their_kernel(B, cond_dim):
     ctx.close()
 
 
+@pytest.mark.parametrize("cond_dim, few", [(64, 3), (36, 17), (1024, 1)])
+def test_conditioning_vectors_do_not_depend_on_the_batch(cond_dim, few):
+    # batches of up to 1024 and larger ones take different kernels: the same environments give the same bits in both, and
+    # both add the components in ascending order (2^24 + 1 + ... + 1 - 2^24 is zero in fp32 in that order only)
+    import torch
+    B = 1025
+    wl = ti.small_variant(ti.C1, B=B, cond_dim=cond_dim)
+    nets = [ti.make_weights(wl, which, b_std=0.02) for which in ("base", "draft")]
+    cond = ti.make_cond(wl, B)
+    cond[:2] = 0.0
+    cond[1, 1:-1] = 1.0; cond[1, 0] = 2.0 ** 24; cond[1, -1] = -2.0 ** 24
+    x = ti.make_latents(wl, B); x[1] = x[0]
+
+    def predictions(ctx, n):
+        ctx.tsdp_set_cond(to_dev(cond[:n]))
+        rows = ctx.alloc_rows(n)
+        one = np.ones(n, np.int32)
+        ctx.tsdp_draft(to_dev(x[:n]), to_dev(5 * one), to_dev(one), to_dev(np.ones(n, np.float32)), None, rows)
+        ctx.tsdp_verify(n, rows)
+        return torch.stack([rows["eps_p"][:n], rows["eps_q"][:n]])
+
+    ctx = gpu_side(wl, *nets, cond, B_max=B)
+    assert torch.equal(predictions(ctx, B)[:, :few], predictions(ctx, few))
+    for w in nets:
+        w["c_w"][:] = 1.0
+    for which, w in enumerate(nets):
+        ctx.tsdp_load_weights(which, ti.pack_blob(w))
+    for n in (2, B):
+        got = predictions(ctx, n)
+        assert torch.equal(got[:, 0], got[:, 1]), n
+    ctx.close()
+
+
 @pytest.mark.parametrize("B", [127, 129, 1024, 1025])
 @pytest.mark.parametrize("bonus", [False, True])
 def test_row_table_and_chain_totals_over_the_batch_size(B, bonus):
