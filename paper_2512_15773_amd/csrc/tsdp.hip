@@ -14,6 +14,7 @@
 #include "kernels_f32.hpp"
 #include "fused_mfma.hpp"
 #include "cond_kernels.hpp"
+#include "few_plan.hpp"
 #include "few_rows.hpp"
 #include "round_kernels.hpp"
 
@@ -677,7 +678,7 @@ void forward_f32(tsdp_ctx* c, Net& n, const float* x_rows, int R_cap, const int3
 
 FewRun few_run(tsdp_ctx* c, const Net& n, int R_cap, int safe_rows, const int32_t* t_arr, const int32_t* env_arr, const float* mod) {
   FewRun r{};
-  r.row_t = t_arr; r.row_env = env_arr; r.R_cap = R_cap; r.safe_rows = std::min(safe_rows, R_cap);
+  r.row_t = t_arr; r.row_env = env_arr; r.R_cap = R_cap; r.safe_rows = safe_rows;
   r.A = c->cfg.A; r.T = c->cfg.T; r.mod = n.fnet.modtab ? n.fnet.modtab : mod;
   for (int i = 0; i < 2; ++i) { r.h[i] = c->few_h[i]; r.part[i] = c->few_part[i]; }
   r.pstride = (size_t)R_cap * c->cfg.H * n.d;
@@ -1099,7 +1100,7 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
       tick(c, 0, 0, s);
       if (dn.few_roll) {
         if (!dn.fnet.modtab) dn.few_film(dn.fnet, d_t0, 0, nullptr, cf.K_max, cf.T, nullptr, B * cf.K_max, c->few_mod, s);
-        const FewRun r = few_run(c, dn, B, B, d_t0, nullptr, c->few_mod);
+        const FewRun r = few_run(c, dn, B, few_safe_rows(true, B, B), d_t0, nullptr, c->few_mod);   // (K_eff is the context's; d_y_last has B rows)
         dn.few_draft(dn.fnet, r, io, cf.K_max, c->few_y, s);
       } else {
         HIPCHK(c, (big ? dn.fused_draft_big : dn.fused_draft_small)(dn.fnet, io, cf.A, s));
@@ -1150,7 +1151,9 @@ static int verify_impl(tsdp_ctx* c, int B, int R_cap, const int32_t* d_row_ptr, 
     d_row_env = c->row_env_chk;
   }
   if (mod_ready) HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));   // join: the FiLM vectors computed beside the rollout
-  if ((rc = forward(c, c->net[0], d_states, R_cap, d_row_ptr + B, d_row_t, 0, d_row_env, d_eps_q, s, mod_ready, B))) return rc;
+  if ((rc = forward(c, c->net[0], d_states, R_cap, d_row_ptr + B, d_row_t, 0, d_row_env, d_eps_q, s, mod_ready,
+                    few_safe_rows(own_table, B, R_cap))))
+    return rc;
   HIPCHK(c, hipGetLastError());
   return TSDP_OK;
 }
