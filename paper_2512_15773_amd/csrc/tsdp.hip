@@ -106,6 +106,7 @@ struct tsdp_ctx {
   bool ws_ready = false;
   float *h = nullptr, *a = nullptr, *qkv = nullptr, *ao = nullptr, *u = nullptr, *sg = nullptr, *mod = nullptr;
   // k_few_*: residual, partial sums, latents between two transitions, FiLM vectors of all transitions of a rollout
+  FewSize few_have;             // floats of few_h / few_part
   float *few_h[2] = {nullptr, nullptr}, *few_part[2] = {nullptr, nullptr}, *few_y[2] = {nullptr, nullptr}, *few_mod = nullptr;
   float* eps_tmp = nullptr;     // [B_max, D] drafter output of the current step
   int32_t *row_t_chk = nullptr, *row_env_chk = nullptr;   // [rows] range-checked copy of a caller's row table (tsdp_verify)
@@ -735,21 +736,20 @@ size_t fused_draft_lds(const Net& n, const tsdp_config& cf, int rpt) {
 
 int ensure_few(tsdp_ctx* c) {
   const tsdp_config& cf = c->cfg;
-  size_t h = 0, part = 0;
   int rc;
-  for (const Net& n : c->net) {
-    if (!n.few) continue;
-    h = std::max(h, rows_max(cf) * cf.H * n.d);
-    part = std::max(part, rows_max(cf) * cf.H * n.d * n.few_slices);
-  }
-  if (h && !c->few_h[0]) {
+  const Net &bn = c->net[0], &dn = c->net[1];
+  const FewSize need = few_size(rows_max(cf) * cf.H, {bn.few, (size_t)bn.d, (size_t)bn.few_slices}, {dn.few, (size_t)dn.d, (size_t)dn.few_slices});
+  if (!few_fits(c->few_have, need)) {                  // (buffers that are replaced live as long as the context: a graph may hold them)
+    const FewSize z{std::max(need.h, c->few_have.h), std::max(need.part, c->few_have.part)};
+    float *h[2], *part[2];
     for (int i = 0; i < 2; ++i) {
-      if ((rc = dev_alloc(c, &c->few_h[i], h))) return rc;
-      if ((rc = dev_alloc(c, &c->few_part[i], part))) return rc;
-      if ((rc = dev_alloc(c, &c->few_y[i], (size_t)cf.B_max * c->D))) return rc;
+      if ((rc = dev_alloc(c, &h[i], z.h))) return rc;
+      if ((rc = dev_alloc(c, &part[i], z.part))) return rc;
+      if (!c->few_y[i] && (rc = dev_alloc(c, &c->few_y[i], (size_t)cf.B_max * c->D))) return rc;
     }
+    for (int i = 0; i < 2; ++i) { c->few_h[i] = h[i]; c->few_part[i] = part[i]; }
+    c->few_have = z;
   }
-  const Net& dn = c->net[1];
   if (dn.few_roll && cf.cond_mode == 0 && !c->few_mod &&
       (rc = dev_alloc(c, &c->few_mod, (size_t)cf.B_max * cf.K_max * dn.L * 4 * dn.d)))
     return rc;
@@ -989,7 +989,7 @@ int tsdp_load_weights(tsdp_ctx* c, int which, const float* h_blob, size_t nbytes
     HIPCHK(c, hipDeviceSynchronize());
     n.fnet.modtab = n.modtab;
   }
-  return TSDP_OK;
+  return c->ws_ready ? ensure_few(c) : TSDP_OK;         // a context in use: the network may need larger buffers than before
 }
 
 int tsdp_set_cond(tsdp_ctx* c, const float* d_cond, int B, void* stream) {

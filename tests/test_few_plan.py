@@ -11,6 +11,18 @@ SHIM = """
 using namespace tsdp;
 extern "C" {
 int safe_rows(int own, int B, int R_cap) { return few_safe_rows(own != 0, B, R_cap); }
+// the context's buffers after a sequence of loads: flags[2 * i] / [2 * i + 1] = base / drafter takes the spread path then
+int buffers_hold(long tokens, long d0, long s0, long d1, long s1, const int* flags, int loads) {
+  FewSize have;
+  for (int i = 0; i < loads; ++i) {
+    const FewSize need = few_size(tokens, {flags[2 * i] != 0, (size_t)d0, (size_t)s0}, {flags[2 * i + 1] != 0, (size_t)d1, (size_t)s1});
+    if (!few_fits(have, need)) have = {std::max(have.h, need.h), std::max(have.part, need.part)};
+    const long d[2] = {d0, d1}, s[2] = {s0, s1};
+    for (int n = 0; n < 2; ++n)
+      if (flags[2 * i + n] && (have.h < (size_t)(tokens * d[n]) || have.part < (size_t)(tokens * d[n] * s[n]))) return 0;
+  }
+  return 1;
+}
 }
 """
 
@@ -34,3 +46,12 @@ def test_rows_of_a_callers_buffer_are_not_read_beyond_the_live_ones(plan):
                 early = [r for r in range(R_cap) if r < plan.safe_rows(0, B, R_cap)]
                 assert all(r < live for r in early), (B, R_cap, live)
             assert plan.safe_rows(1, B, R_cap) <= R_cap           # the context's own buffers hold R_cap rows
+
+
+def test_buffers_hold_whatever_networks_take_the_spread_path(plan):
+    # a reload can move either network to the spread path: the larger one after the smaller one, and back
+    L = C.c_long
+    for d0, s0, d1, s1 in ((256, 16, 128, 8), (128, 8, 256, 16), (512, 8, 512, 8)):
+        for flags in ([0, 1, 1, 1], [1, 0, 1, 1], [0, 0, 0, 1, 1, 0], [1, 1, 0, 1, 1, 1]):
+            a = (C.c_int * len(flags))(*flags)
+            assert plan.buffers_hold(L(2048), L(d0), L(s0), L(d1), L(s1), a, len(flags) // 2), (d0, d1, flags)

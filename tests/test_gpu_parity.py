@@ -235,6 +235,37 @@ def test_conditioning_vectors_at_the_edges_of_their_kernel(B, cond_dim):
     ctx.close()
 
 
+@pytest.mark.parametrize("which", [0, 1])
+def test_reload_of_a_network_onto_the_spread_path(which, monkeypatch):
+    # TSDP_DISABLE_FUSED is read by every load: a context that has already run with one network on the operator kernels gets
+    # larger buffers when that network returns, and then gives the bits of a fresh context
+    import torch
+    wl = ti.C2
+    nets = [ti.make_weights(wl, name, b_std=0.02) for name in ("base", "draft")]
+    cond = ti.make_cond(wl, 1)
+
+    def predictions(ctx):
+        rows = ctx.alloc_rows(1)
+        ctx.tsdp_draft(to_dev(ti.make_latents(wl, 1)), to_dev(np.array([70], np.int32)), to_dev(np.array([8], np.int32)),
+                       to_dev(np.ones(1, np.float32)), None, rows)
+        ctx.tsdp_verify(1, rows)
+        return torch.stack([rows["eps_p"], rows["eps_q"], rows["states"]])
+
+    fresh = gpu_side(wl, *nets, cond, B_max=1)
+    ref = predictions(fresh)
+    fresh.close()
+    monkeypatch.setenv("TSDP_DISABLE_FUSED", "1")
+    ctx = gpu_side(wl, *nets, cond, B_max=1)
+    monkeypatch.delenv("TSDP_DISABLE_FUSED")
+    for load in (1 - which, which):
+        ctx.tsdp_load_weights(load, ti.pack_blob(nets[load]))
+        ctx.tsdp_set_cond(to_dev(cond))
+        got = predictions(ctx)
+        assert scaled_err(got.cpu().numpy(), ref.cpu().numpy()) < TOL[wl.dtype]
+    assert torch.equal(got, ref)
+    ctx.close()
+
+
 @pytest.mark.parametrize("cond_dim, few", [(64, 3), (36, 17), (1024, 1)])
 def test_conditioning_vectors_do_not_depend_on_the_batch(cond_dim, few):
     # batches of up to 1024 and larger ones take different kernels: the same environments give the same bits in both, and
