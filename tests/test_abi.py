@@ -65,3 +65,12 @@ def test_bench_refuses_more_than_one_gpu():
     assert r.returncode != 0
     assert "one GPU" in (r.stdout + r.stderr)
     assert not any(line.startswith("{") for line in r.stdout.splitlines())      # no result line
+
+
+def test_environment_switches_are_the_documented_ones():
+    src = os.path.join(ROOT, "paper_2512_15773_amd", "csrc")
+    read = set()
+    for name in os.listdir(src):
+        read |= set(re.findall(r"getenv\s*\(\s*\"(\w+)\"", open(os.path.join(src, name)).read()))
+    header = open(os.path.join(ROOT, "include", "tsdp.h")).read()
+    assert read == set(re.findall(r"Environment: (\w+)", header)) == {"TSDP_DISABLE_FUSED"}
