@@ -5,11 +5,26 @@
 
 namespace tsdp {
 
-// Rows below this one a launch may start to read before it knows how many rows are live.  In the context's own row
-// buffers any row up to their capacity exists, and every running environment has one: the loads of the first B rows travel
-// together with the live row count.  A caller's buffers hold the live rows and no more -- finished environments own none,
-// so not even the first B need exist -- and nothing of them is read before the count is known.
-inline int few_safe_rows(bool own_rows, int B, int R_cap) { return own_rows ? std::min(B, R_cap) : 0; }
+// Rows below this one a launch may start to read before it knows how many rows are live (`ahead`).  In the context's own
+// row buffers any row up to their capacity exists, and every running environment has one: the loads of the first B rows
+// travel together with the live row count, which is worth 1 % of a round.  Not so
+//  - in a caller's buffers: they hold the live rows and no more -- finished environments own none, so not even the first B
+//    need exist -- and nothing of them is read before the count is known;
+//  - in the rounds of an enqueued chain, most of which have no live row: a launch without one costs 1.5 us where it asks
+//    first and 2.6 us where it first requests the row's data and weights (one C2 environment, a round of 54 launches 85 us, 142).
+inline int few_safe_rows(bool ahead, int B, int R_cap) { return ahead ? std::min(B, R_cap) : 0; }
+
+// Launches of a spread rollout: every transition up to K_max has its own, whether drafted or not (the draft counts are on
+// the device).  A drafted transition of the fp32 d = 128 network takes 23 us instead of the persistent kernel's 39, an
+// undrafted one 6 to 15 instead of none: with half of K_max or more the spread rollout is the faster one, and what fewer
+// drafts lose grows with K_max.  Rounds of one C2 environment, us, persistent / spread rollout: K = 1, 4, 8 of 8 226 / 277,
+// 344 / 331, 495 / 396; K = 1, 4, 16 of 16 226 / 363, 344 / 413, 788 / 595; K = 4, 64 of 64 344 / 1085, 2673 / 1888.  So up
+// to 40 launches (two layers: K_max = 9) the rollout is spread -- the loss stays below a quarter of a round, and below what
+// the spread verify saves of it (one workgroup per row: 545, 663, 812 with K = 1, 4, 8) -- and beyond it is one launch.
+constexpr int FEW_ROLL_LAUNCHES = 40;
+inline bool few_rollout_pays(int layers, bool wide, bool cross, int K_max) {
+  return layers * (wide ? 2 : 1) * (cross ? 3 : 2) * K_max + 1 <= FEW_ROLL_LAUNCHES;
+}
 
 // Floats of the two residual and of the two partial-sum buffers, shared by both networks.  Which networks take the spread
 // path can change with every tsdp_load_weights, so what a context holds is compared with what its networks need now, and

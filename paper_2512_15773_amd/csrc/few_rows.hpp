@@ -31,15 +31,16 @@ namespace tsdp {
 // registers hold weights in flight; eight for wide rows.
 // Slices: one unit's fp32 matrix rate bounds a slice of d = 256 (16 slices of 64 instead of 8 of 128: round of one C2
 // environment 402 -> 389 us), in bf16 the sums that the next launch reads do (4 instead of 8: 128 rows 172 instead of 232 us).
+constexpr int FEW_WIDE = 16384;                   // numbers of a wide row's residual
 template <class TT, int D, int H>
-constexpr int few_slices() { return D * H >= 16384 ? 8 : sizeof(typename TT::elem) == 2 ? 4 : D >= 256 ? 16 : 8; }
+constexpr int few_slices() { return D * H >= FEW_WIDE ? 8 : sizeof(typename TT::elem) == 2 ? 4 : D >= 256 ? 16 : 8; }
 
 template <class TT_, int D_, int H_, int HEADS_, int SX_ = 0, int NCH_ = few_slices<TT_, D_, H_>()>
 struct FewCfg {
   typedef TT_ TT;
   static constexpr bool DYN = false;
   static constexpr int D = D_, H = H_, HEADS = HEADS_, SX = SX_, NCH = NCH_, DH = D / HEADS, CH = 4 * D / NCH, NB = H / 16;
-  static constexpr bool WIDE = D * H >= 16384;
+  static constexpr bool WIDE = D * H >= FEW_WIDE;
   static constexpr int NW = WIDE ? 8 : 4, TH = NW * 64;
   static constexpr int NPA = WIDE ? 0 : HEADS, NPM = WIDE ? 0 : NCH;   // partial sums an attention / MLP block leaves
   static constexpr int JV = (D / 4 + 63) / 64;    // 16-byte vectors per lane and token
@@ -489,7 +490,10 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_attn(FewIO io, std::conditiona
   int head, row;
   few_place(io, heads, head, row);
   const FewRow me = few_row(io, row);
-  if (row >= io.safe_rows && !me.live) return;           // (below that: decided once the first loads are under way)
+  // STEP: transition `done` ends here, if it was drafted at all; below safe_rows the others decide once the first loads
+  // are under way
+  const int ke = me.k_eff, done = io.step - 1;
+  if (STEP ? ke < done || (ke == done && head != 0) : row >= io.safe_rows && !me.live) return;
   constexpr bool ST = !C::DYN;
   typedef FewGemm<C, ST ? 3 * C::DH / 16 : 4, ST ? C::D / KSTEP : 1> GQ;
   typedef FewGemm<C, ST ? C::D / 16 : 4, ST ? C::DH / KSTEP : 1> GO;
@@ -499,8 +503,6 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_attn(FewIO io, std::conditiona
   FewFilm<C> fm;
   fm.load(io, row, me.t, lane);
   if constexpr (STEP) {
-    const int ke = me.k_eff, k = io.step - 1;       // transition k ends here, if it was drafted at all
-    if (ke < k || (ke == k && head != 0)) return;
     few_residual<C, NP>(io, row, wave, lane, v, weights);
     FewFilm<C> none;
     none.none();
@@ -510,7 +512,7 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_attn(FewIO io, std::conditiona
     float* yt = et + 512;
     float* zt = yt + 512;
     int t = dr.t0[row];
-    t = (t >= dr.tb.T ? dr.tb.T - 1 : t) - k + 1;
+    t = (t >= dr.tb.T ? dr.tb.T - 1 : t) - done + 1;
     lds_barrier();
     for (int i = (threadIdx.x + C::TH - 64) % C::TH; i < nblk; i += C::TH) {   // beside the product of wave 0
       const float4 z = xi_block(dr.seed, dr.env_id ? dr.env_id[row] : row, t, i);
@@ -518,7 +520,7 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_attn(FewIO io, std::conditiona
     }
     few_head<C>(io, act, AS, wave, lane, [&](int i, float e) { et[i] = e; });
     lds_barrier();
-    const size_t o_row = ((size_t)dr.row_ptr[row] + k - 1) * DE, o_env = (size_t)row * DE;
+    const size_t o_row = ((size_t)dr.row_ptr[row] + done - 1) * DE, o_env = (size_t)row * DE;
     const float sa = dr.tb.sqrt_abar[t], s1 = dr.tb.sqrt_1m[t], c0 = dr.tb.c0[t], cx = dr.tb.cx[t], ce = dr.tb.ce[t];
     const float sig = dr.sigma_scale[row] * dr.tb.sigma[t];
     for (int i = threadIdx.x; i < nblk; i += C::TH) {
@@ -536,10 +538,10 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_attn(FewIO io, std::conditiona
         *reinterpret_cast<f32x4*>(dr.states + o_row + 4 * i) = y;
         *reinterpret_cast<f32x4*>(dr.eps_p + o_row + 4 * i) = e;
         if (dr.xi) *reinterpret_cast<f32x4*>(dr.xi + o_row + 4 * i) = z;
-        *reinterpret_cast<f32x4*>((ke == k ? dr.y : io.y_out) + o_env + 4 * i) = o;
+        *reinterpret_cast<f32x4*>((ke == done ? dr.y : io.y_out) + o_env + 4 * i) = o;
       }
     }
-    if (ke == k) return;                                 // the environment's last drafted transition
+    if (ke == done) return;                              // the environment's last drafted transition
     lds_barrier();
     few_embed<C>(io, yt, wave, lane, v);
   } else if constexpr (NP == FEW_EMBED) {
@@ -817,20 +819,21 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_out(FewIO io) {
 // FiLM vectors of a few rows, all layers at once: mod[r, :] = W_mod SiLU(temb[t_r] + cemb[env_r]) + b_mod.  A workgroup
 // takes 16 rows and four fragment rows (64 outputs), so that one row tile already puts L*D/16 workgroups on the chip.
 // k_max > 0: the rows are the transitions of a rollout, r = env * k_max + (k - 1) at timestep t_arr[env] - (k - 1).
-// DC = 0: run-time D.
+// gate: 0 = nothing to do (no environment drafts), or null.  DC = 0: run-time D.
 template <class TT, int DC>
 __global__ __launch_bounds__(256, 1) void k_few_film(const void* __restrict__ modw, const float* __restrict__ modb,
                                                         const float* __restrict__ temb, const float* __restrict__ cemb,
                                                         const int32_t* __restrict__ t_arr, int t_sub,
                                                         const int32_t* __restrict__ env_arr, int k_max, int T, int Drt, int Nm,
-                                                        const int32_t* __restrict__ d_R, int R_cap, float* __restrict__ mod) {
+                                                        const int32_t* __restrict__ d_R, const int32_t* __restrict__ gate,
+                                                        int R_cap, float* __restrict__ mod) {
   typedef typename TT::elem elem;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   elem* sg = reinterpret_cast<elem*>(lds);
   const int D = DC ? DC : Drt, AS = D + TT::PAD, KD = D / TT::KSTEP;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, lg = lane >> 4;
   const int R = d_R ? min(*d_R, R_cap) : R_cap, row0 = blockIdx.y * 16;
-  if (row0 >= R) return;
+  if (row0 >= R || (gate && *gate == 0)) return;
   const int f = min((int)blockIdx.x * 4 + wave, Nm / 16 - 1);   // (a wave past the last fragment row repeats it)
   typedef FragGemm<TT, 1, 1, (DC ? DC / TT::KSTEP : 1), 2, 16> G;
   G g;

@@ -64,7 +64,7 @@ struct Net {
   bool few_roll = false;        // so is the drafter's rollout
   void (*few_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr;
   void (*few_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;
-  void (*few_film)(const FusedNet&, const int32_t*, int, const int32_t*, int, int, const int32_t*, int, float*, hipStream_t) = nullptr;
+  void (*few_film)(const FusedNet&, const int32_t*, int, const int32_t*, int, int, const int32_t*, const int32_t*, int, float*, hipStream_t) = nullptr;
   int few_slices = 0;           // partial sums per row
   float* tok_wt = nullptr;      // [A, d] token embedding, transposed
   uint16_t* kc_pk = nullptr;    // fragment-ordered bf16 keys / transposed values of every (env, layer, head)
@@ -262,8 +262,8 @@ inline int few_slices_dyn(int M) {
   return n;
 }
 
-// From eight rows on all workgroups of a row sit on one XCD, whose L2 then holds the row's partial sums (16 rows of
-// 32 x 512: round 2279 -> 1368 us; 16 x 256: no change); fewer rows are dealt over all of them.
+// From eight rows on all workgroups of a row sit on one XCD, whose L2 then holds the row's partial sums (32 rows of
+// 32 x 512 with partial sums: round 2279 -> 1368 us; 8 rows of 16 x 256: no change); fewer rows are dealt over all of them.
 constexpr int FEW_BY_ROW = 8;
 
 // The launches of one spread forward pass: every kernel reads the residual and the partial sums its predecessor left
@@ -384,17 +384,17 @@ void few_draft(const FusedNet& n, const FewRun& r, const DraftIO& dr, int k_max,
 
 template <class TT, int D>
 void launch_few_film(const FusedNet& n, const int32_t* t_arr, int t_sub, const int32_t* env_arr, int k_max, int T,
-                     const int32_t* d_R, int R_cap, float* mod, hipStream_t s) {
+                     const int32_t* d_R, const int32_t* gate, int R_cap, float* mod, hipStream_t s) {
   const int d = D ? D : n.D, Nm = n.L * 4 * d;
   hipLaunchKernelGGL((k_few_film<TT, D>), dim3((Nm / 16 + 3) / 4, (R_cap + 15) / 16), dim3(256),
                      16 * (d + TT::PAD) * (int)sizeof(typename TT::elem), s, n.modw, n.modb, n.temb, n.cemb, t_arr, t_sub, env_arr,
-                     k_max, T, d, Nm, d_R, R_cap, mod);
+                     k_max, T, d, Nm, d_R, gate, R_cap, mod);
 }
 
 struct FusedKernels {
   void (*few_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr;
   void (*few_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;
-  void (*few_film)(const FusedNet&, const int32_t*, int, const int32_t*, int, int, const int32_t*, int, float*, hipStream_t) = nullptr;
+  void (*few_film)(const FusedNet&, const int32_t*, int, const int32_t*, int, int, const int32_t*, const int32_t*, int, float*, hipStream_t) = nullptr;
   int few_slices = 0;
   // variant for batches of at most one tile per CU: one 8-wave workgroup per CU instead of two 4-wave ones
   hipError_t (*verify_few)(const FusedNet&, const FusedIO&, int, int, hipStream_t) = nullptr;
@@ -623,11 +623,14 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   // of the context decides, not the call: an environment's result must not depend on the batch it is computed in.
   const size_t layer_bytes = (size_t)(cf.cond_mode == 1 ? 14 : 12) * d * d * (f32 ? 4 : 2);
   n.few = dyn ? rows_max(cf) * cf.H <= FEW_TOKENS_DYN : rows_max(cf) * cf.H <= (f32 ? FEW_TOKENS_F32 : FEW_TOKENS_BF16) && layer_bytes >= FEW_LAYER_BYTES;
-  // The rollout: fp32 layers are bound by one unit's matrix rate (d = 128: 39 us per transition, spread 27), bf16 drafters
+  // The rollout: fp32 layers are bound by one unit's matrix rate (d = 128: 39 us per transition, spread 23), bf16 drafters
   // of this size are not (d = 192: spread 2 us per transition slower).  A drafter of the base network's own shape takes
-  // the base network's kernels, so that equal weights give equal predictions.
+  // the base network's kernels, so that equal weights give equal predictions: both spread or neither.
   const bool twin = cf.base_d == cf.draft_d && cf.base_layers == cf.draft_layers && cf.base_heads == cf.draft_heads;
-  n.few_roll = n.few && (twin || f32);
+  const bool pays = dyn || few_rollout_pays(cf.draft_layers, (size_t)cf.draft_d * cf.H >= FEW_WIDE, cf.cond_mode == 1, cf.K_max);
+  if (twin && !pays) n.few = false;
+  n.few_roll = n.few && pays && (twin || f32);
+  if (&n == &c->net[1]) n.few = n.few_roll;
   if (!dyn) n.path = f32 ? "f32-mfma-fused" : "bf16-mfma-fused";
   return TSDP_OK;
 }
@@ -702,16 +705,15 @@ int forward(tsdp_ctx* c, Net& n, const float* x_rows, int R_cap, const int32_t* 
   const tsdp_config& cf = c->cfg;
   if (n.fnet.modtab || mod_ready) {
     // token conditioning: the FiLM vectors are a function of the timestep only and were tabulated at load time
-  } else if (n.fused_mod) {
-    const bool base = &n == &c->net[0];
-    if (base) tick(c, 3, 0, s);
-    n.fused_mod(n.fnet, t_arr, t_sub, env_arr, cf.T, d_R, R_cap, c->mod, s);
-    if (base) tick(c, 3, 1, s);
-  } else {                                            // fp32 networks: fp32 products
-    n.few_film(n.fnet, t_arr, t_sub, env_arr, 0, cf.T, d_R, R_cap, c->mod, s);
+  } else {
+    const bool timed = &n == &c->net[0] && n.fused_mod;
+    if (timed) tick(c, 3, 0, s);
+    if (n.fused_mod && !n.few) n.fused_mod(n.fnet, t_arr, t_sub, env_arr, cf.T, d_R, R_cap, c->mod, s);
+    else n.few_film(n.fnet, t_arr, t_sub, env_arr, 0, cf.T, d_R, nullptr, R_cap, c->mod, s);   // few rows; fp32 networks
+    if (timed) tick(c, 3, 1, s);
   }
   const int stage = (&n == &c->net[0]) ? 1 : -1;          // only the base network's forward is the verify stage
-  if (n.few && (stage == 1 || !n.fused)) {
+  if (n.few) {                                        // (the base network: a drafter that is `few` rolls out in draft_impl)
     FewRun r = few_run(c, n, R_cap, safe_rows, t_arr, env_arr, c->mod);
     r.x = x_rows; r.d_R = d_R; r.eps_out = eps_out;
     tick(c, 1, 0, s);
@@ -1085,8 +1087,9 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
     const size_t lds = fused_draft_lds(dn, cf, rpt);
     if (dn.few_roll || lds <= 160 * 1024) {
       Net& bn = c->net[0];
-      if (base_mod_rows > 0 && bn.fused && bn.fused_mod && !bn.fnet.modtab) {
-        // fork: the fused rollout keeps its FiLM vectors in LDS, so the shared buffer is free for the base network's
+      if (base_mod_rows > 0 && bn.fused && bn.fused_mod && !bn.few && !bn.fnet.modtab) {
+        // fork: a rollout keeps its FiLM vectors in LDS or in few_mod, so the shared buffer is free for the base network's.
+        // (Not for few rows: their product takes 7 us, the fork and join 20 to 30 us of every round of a chain.)
         HIPCHK(c, hipEventRecord(c->ev_fork, s));
         HIPCHK(c, hipStreamWaitEvent(c->aux, c->ev_fork, 0));
         bn.fused_mod(bn.fnet, d_row_t, 0, d_row_env, cf.T, d_row_ptr + B, base_mod_rows, c->mod, c->aux);
@@ -1103,8 +1106,8 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
       io.bonus = cf.bonus_row;
       tick(c, 0, 0, s);
       if (dn.few_roll) {
-        if (!dn.fnet.modtab) dn.few_film(dn.fnet, d_t0, 0, nullptr, cf.K_max, cf.T, nullptr, B * cf.K_max, c->few_mod, s);
-        const FewRun r = few_run(c, dn, B, few_safe_rows(true, B, B), d_t0, nullptr, c->few_mod);   // (K_eff is the context's; d_y_last has B rows)
+        if (!dn.fnet.modtab) dn.few_film(dn.fnet, d_t0, 0, nullptr, cf.K_max, cf.T, nullptr, c->n_draft + 1, B * cf.K_max, c->few_mod, s);
+        const FewRun r = few_run(c, dn, B, few_safe_rows(!gated, B, B), d_t0, nullptr, c->few_mod);   // (d_y_last has B rows)
         dn.few_draft(dn.fnet, r, io, cf.K_max, c->few_y, s);
       } else {
         HIPCHK(c, (big ? dn.fused_draft_big : dn.fused_draft_small)(dn.fnet, io, cf.A, s));
@@ -1136,7 +1139,7 @@ int tsdp_draft(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0, const 
 
 static int verify_impl(tsdp_ctx* c, int B, int R_cap, const int32_t* d_row_ptr, const int32_t* d_row_t,
                        const int32_t* d_row_env, const float* d_states, float* d_eps_q, bool own_table, void* stream,
-                       bool mod_ready = false) {
+                       bool mod_ready = false, bool gated = false) {
   int rc = check_ready(c, B, true);
   if (rc) return rc;
   if (B == 0 || R_cap == 0) return TSDP_OK;
@@ -1156,7 +1159,7 @@ static int verify_impl(tsdp_ctx* c, int B, int R_cap, const int32_t* d_row_ptr, 
   }
   if (mod_ready) HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));   // join: the FiLM vectors computed beside the rollout
   if ((rc = forward(c, c->net[0], d_states, R_cap, d_row_ptr + B, d_row_t, 0, d_row_env, d_eps_q, s, mod_ready,
-                    few_safe_rows(own_table, B, R_cap))))
+                    few_safe_rows(own_table && !gated, B, R_cap))))
     return rc;
   HIPCHK(c, hipGetLastError());
   return TSDP_OK;
@@ -1247,7 +1250,7 @@ static int round_impl(tsdp_ctx* c, int B, float* d_x, int32_t* d_t, const int32_
   if ((rc = draft_impl(c, B, d_x, d_t, d_K, d_sigma_scale, d_env_id, c->row_ptr, c->row_t, c->row_env, c->states,
                        c->eps_p, c->xi, c->y_last, gated, stream, R_cap, &mod_started, chain.live, rounds_run)))
     return rc;
-  if ((rc = verify_impl(c, B, R_cap, c->row_ptr, c->row_t, c->row_env, c->states, c->eps_q, true, stream, mod_started)))
+  if ((rc = verify_impl(c, B, R_cap, c->row_ptr, c->row_t, c->row_env, c->states, c->eps_q, true, stream, mod_started, gated)))
     return rc;
   // x and t are overwritten in place: the acceptance kernel reads only the round's own buffers
   return accept_impl(c, B, c->row_ptr, c->row_t, d_env_id, d_sigma_scale, d_lambda, c->states, c->eps_p, c->eps_q, c->xi,

@@ -11,6 +11,7 @@ SHIM = """
 using namespace tsdp;
 extern "C" {
 int safe_rows(int own, int B, int R_cap) { return few_safe_rows(own != 0, B, R_cap); }
+int rollout_pays(int layers, int wide, int cross, int K_max) { return few_rollout_pays(layers, wide != 0, cross != 0, K_max); }
 // the context's buffers after a sequence of loads: flags[2 * i] / [2 * i + 1] = base / drafter takes the spread path then
 int buffers_hold(long tokens, long d0, long s0, long d1, long s1, const int* flags, int loads) {
   FewSize have;
@@ -55,3 +56,13 @@ def test_buffers_hold_whatever_networks_take_the_spread_path(plan):
         for flags in ([0, 1, 1, 1], [1, 0, 1, 1], [0, 0, 0, 1, 1, 0], [1, 1, 0, 1, 1, 1]):
             a = (C.c_int * len(flags))(*flags)
             assert plan.buffers_hold(L(2048), L(d0), L(s0), L(d1), L(s1), a, len(flags) // 2), (d0, d1, flags)
+
+
+def test_rollouts_of_many_possible_drafts_stay_in_one_launch(plan):
+    # every transition up to K_max is launched, drafted or not: a context for 64 drafts that asks for four would pay for 64
+    assert plan.rollout_pays(2, 0, 0, 8) and not plan.rollout_pays(2, 0, 0, 16)
+    for layers in (1, 2, 8):
+        for wide in (0, 1):
+            for cross in (0, 1):
+                pays = [plan.rollout_pays(layers, wide, cross, k) for k in range(1, 65)]
+                assert pays == sorted(pays, reverse=True) and not pays[-1]

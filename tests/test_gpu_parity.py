@@ -991,6 +991,26 @@ def test_enqueue_only_chain_is_bit_identical_to_the_host_checked_chain():
         S["ctx"].close()
 
 
+@pytest.mark.parametrize("wl, B, bonus", [
+    (ti.small_variant(ti.C2, T=30, base=ti.NetShape(2, 256, 4)), 5, False),                                 # spread rollout
+    (ti.small_variant(ti.C2, T=30, base=ti.NetShape(2, 256, 4)), 5, True),
+    (ti.small_variant(ti.C3, T=30, K_max=4, base=ti.NetShape(2, 256, 4), draft=ti.NetShape(2, 256, 4)), 3, True),   # bf16
+    (ti.small_variant(ti.C3, T=30, K_max=4), 3, False),                                                     # persistent rollout
+    (ti.small_variant(ti.C4, T=20, K_max=3, base=ti.NetShape(1, 512, 8)), 2, False),                        # wide rows
+    (ti.small_variant(ti.C2, T=30, A=4, cond_dim=64, base=ti.NetShape(2, 96, 3), draft=ti.NetShape(1, 48, 3)), 5, True),
+])
+def test_enqueue_only_chain_of_few_rows(wl, B, bonus):
+    # an enqueued chain looks at the live word before anything else, the host-checked one loads ahead of it; draft counts
+    # from 0 or 1 to K_max end the rollouts at different transitions, and the last rounds have no live row
+    rng = np.random.default_rng(B)
+    S = _setup(wl, B, head_scale=0.3, bonus=bonus)
+    t0 = rng.integers(-1, wl.T, B); t0[0] = wl.T - 1; t0[1] = 0
+    K = rng.integers(0 if bonus else 1, wl.K_max + 1, B); K[0] = wl.K_max
+    _chain_both_ways(S["ctx"], S["x"], t0, K, rng.uniform(1.0, 1.3, B), None, None, None, wl.T + 3, wl.T)
+    assert S["ctx"].tsdp_status() == 0
+    S["ctx"].close()
+
+
 def test_layernorm_statistics_survive_a_large_mean_in_fp32():
     # a residual stream whose mean is 12x its spread (token-embedding bias 0.5 on features of spread 0.04): the
     # one-pass variance E[x^2] - mean^2 loses 2^-24 mean^2 / var = 1e-5 of the variance in fp32, at the fp32
