@@ -416,7 +416,7 @@ constexpr int F256_CH = 256;
 constexpr int FEW_TILES = 288;   // up to this many tiles the 8-wave verify variant (one workgroup per CU) is used
 constexpr int V512_HPX = 8;      // heads per cross-attention phase of the d = 512 verify kernel
 constexpr int V512_CH = 256;     // hidden-chunk width of the d = 512 verify kernel
-constexpr size_t FEW_TOKENS_BF16 = 2176, FEW_TOKENS_F32 = 2048, FEW_TOKENS_DYN = 32768, FEW_LAYER_BYTES = 700000;   // build_fused
+constexpr size_t FEW_TOKENS_BF16 = 2176, FEW_TOKENS_F32 = 2048, FEW_LAYER_BYTES = 700000;   // build_fused
 // shapes with compiled fused kernels
 bool find_fused(int dtype, int D, int H, int heads, int cm, int S, int mlp_ratio, int L, FusedKernels& k) {
   if (mlp_ratio != 4 || L > FUSED_MAX_LAYERS) return false;
@@ -456,9 +456,20 @@ bool find_fused(int dtype, int D, int H, int heads, int cm, int S, int mlp_ratio
   return false;
 }
 
-// Shapes without a compiled kernel: up to FEW_TOKENS_DYN tokens the spread kernels (d = 96 / 48, rounds of 64, 512, 2048 rows:
-// 235, 408, 1108 us; one launch per operator 816, 934, 1359; equal at 8192 rows) with run-time sizes (vector conditioning, sizes in fragments of
-// 16, a row's operands in the LDS; 48 and 64 tokens would spill the residual).
+// rows of the ragged batch a context must hold: K_max per environment, one more with the bonus row
+inline size_t rows_max(const tsdp_config& cf) { return (size_t)cf.B_max * (cf.K_max + (cf.bonus_row ? 1 : 0)); }
+
+// A drafter of the base network's own shape takes the base network's kernels, so that equal weights give equal predictions.
+inline bool twin_nets(const tsdp_config& cf) {
+  return cf.base_d == cf.draft_d && cf.base_layers == cf.draft_layers && cf.base_heads == cf.draft_heads;
+}
+// tokens of the largest spread launch of a network with run-time sizes: the rollout has one row per environment
+inline size_t dyn_tokens(const tsdp_config& cf, int which) {
+  return (which == 1 && !twin_nets(cf) ? (size_t)cf.B_max : rows_max(cf)) * cf.H;
+}
+
+// Shapes without a compiled kernel: the spread kernels with run-time sizes where few_dyn_pays says so (vector conditioning,
+// sizes in fragments of 16, a row's operands in the LDS; 48 and 64 tokens would spill the residual).
 template <class C>
 hipError_t few_dyn_kernels(FusedKernels& k) {
   k.few_forward = few_forward<C>; k.few_draft = few_draft<C>; k.few_film = launch_few_film<TF32, 0>;
@@ -468,17 +479,15 @@ hipError_t few_dyn_kernels(FusedKernels& k) {
   return hipSuccess;
 }
 
-hipError_t find_few_dyn(const tsdp_config& cf, const Net& n, FusedKernels& k) {
+hipError_t find_few_dyn(const tsdp_config& cf, int which, const Net& n, FusedKernels& k) {
   const int dh = n.d / n.heads, ch = n.m % 16 ? 0 : n.m / few_slices_dyn(n.m);
   if (cf.cond_mode != 0 || (cf.H != 16 && cf.H != 32) || n.d % 16 || dh % 16 || n.m % 16 || n.L > FUSED_MAX_LAYERS ||
-      few_lds_attn<TF32>(n.d, cf.H, dh) + FEW_STEP_LDS > 160 * 1024 || few_lds_mlp<TF32>(n.d, cf.H, ch) > 160 * 1024)
+      few_lds_attn<TF32>(n.d, cf.H, dh) + FEW_STEP_LDS > 160 * 1024 || few_lds_mlp<TF32>(n.d, cf.H, ch) > 160 * 1024 ||
+      !few_dyn_pays(dyn_tokens(cf, which), n.heads, 4 * ((size_t)4 * n.d * n.d + (size_t)2 * n.d * n.m)))
     return hipSuccess;
   k.few_slices = std::max(n.heads, few_slices_dyn(n.m));
   return cf.H == 16 ? few_dyn_kernels<FewDyn<1>>(k) : few_dyn_kernels<FewDyn<2>>(k);
 }
-
-// rows of the ragged batch a context must hold: K_max per environment, one more with the bonus row
-inline size_t rows_max(const tsdp_config& cf) { return (size_t)cf.B_max * (cf.K_max + (cf.bonus_row ? 1 : 0)); }
 
 size_t layout_net(const tsdp_config& cf, int which, Net& n) {
   n.L = which == 0 ? cf.base_layers : cf.draft_layers;
@@ -622,11 +631,10 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   // through one compute unit faster than through two launches (fp32 d = 64, 393 KB in all: 21 us against 25).  The capacity
   // of the context decides, not the call: an environment's result must not depend on the batch it is computed in.
   const size_t layer_bytes = (size_t)(cf.cond_mode == 1 ? 14 : 12) * d * d * (f32 ? 4 : 2);
-  n.few = dyn ? rows_max(cf) * cf.H <= FEW_TOKENS_DYN : rows_max(cf) * cf.H <= (f32 ? FEW_TOKENS_F32 : FEW_TOKENS_BF16) && layer_bytes >= FEW_LAYER_BYTES;
+  n.few = dyn || (rows_max(cf) * cf.H <= (f32 ? FEW_TOKENS_F32 : FEW_TOKENS_BF16) && layer_bytes >= FEW_LAYER_BYTES);
   // The rollout: fp32 layers are bound by one unit's matrix rate (d = 128: 39 us per transition, spread 23), bf16 drafters
-  // of this size are not (d = 192: spread 2 us per transition slower).  A drafter of the base network's own shape takes
-  // the base network's kernels, so that equal weights give equal predictions: both spread or neither.
-  const bool twin = cf.base_d == cf.draft_d && cf.base_layers == cf.draft_layers && cf.base_heads == cf.draft_heads;
+  // of this size are not (d = 192: spread 2 us per transition slower).  Twins are both spread or neither.
+  const bool twin = twin_nets(cf);
   const bool pays = dyn || few_rollout_pays(cf.draft_layers, (size_t)cf.draft_d * cf.H >= FEW_WIDE, cf.cond_mode == 1, cf.K_max);
   if (twin && !pays) n.few = false;
   n.few_roll = n.few && pays && (twin || f32);
@@ -744,7 +752,10 @@ int ensure_few(tsdp_ctx* c) {
   const tsdp_config& cf = c->cfg;
   int rc;
   const Net &bn = c->net[0], &dn = c->net[1];
-  const FewSize need = few_size(rows_max(cf) * cf.H, {bn.few, (size_t)bn.d, (size_t)bn.few_slices}, {dn.few, (size_t)dn.d, (size_t)dn.few_slices});
+  auto shape = [&](const Net& n, int which) {
+    return FewShape{n.few, n.fused ? rows_max(cf) * cf.H : dyn_tokens(cf, which), (size_t)n.d, (size_t)n.few_slices};
+  };
+  const FewSize need = few_size(shape(bn, 0), shape(dn, 1));
   if (!few_fits(c->few_have, need)) {                  // (buffers that are replaced live as long as the context: a graph may hold them)
     const FewSize z{std::max(need.h, c->few_have.h), std::max(need.part, c->few_have.part)};
     float *h[2], *part[2];
@@ -971,7 +982,7 @@ int tsdp_load_weights(tsdp_ctx* c, int which, const float* h_blob, size_t nbytes
   n.path = "f32-ops";
   if (!std::getenv("TSDP_DISABLE_FUSED")) {
     FusedKernels fk;
-    if (!find_fused(cf.dtype, n.d, cf.H, n.heads, cf.cond_mode, cf.cond_tokens, n.m / n.d, n.L, fk)) HIPCHK(c, find_few_dyn(cf, n, fk));
+    if (!find_fused(cf.dtype, n.d, cf.H, n.heads, cf.cond_mode, cf.cond_tokens, n.m / n.d, n.L, fk)) HIPCHK(c, find_few_dyn(cf, which, n, fk));
     if (fk.few_forward && (rc = build_fused(c, n, w, modw, fk))) return rc;
   }
   if (!n.fused && cf.cond_mode == 1 && !n.kc) {        // fp32 keys / values of the operator kernels

@@ -12,11 +12,12 @@ using namespace tsdp;
 extern "C" {
 int safe_rows(int own, int B, int R_cap) { return few_safe_rows(own != 0, B, R_cap); }
 int rollout_pays(int layers, int wide, int cross, int K_max) { return few_rollout_pays(layers, wide != 0, cross != 0, K_max); }
+int dyn_pays(long tokens, long heads, long layer_bytes) { return few_dyn_pays(tokens, heads, layer_bytes); }
 // the context's buffers after a sequence of loads: flags[2 * i] / [2 * i + 1] = base / drafter takes the spread path then
 int buffers_hold(long tokens, long d0, long s0, long d1, long s1, const int* flags, int loads) {
   FewSize have;
   for (int i = 0; i < loads; ++i) {
-    const FewSize need = few_size(tokens, {flags[2 * i] != 0, (size_t)d0, (size_t)s0}, {flags[2 * i + 1] != 0, (size_t)d1, (size_t)s1});
+    const FewSize need = few_size({flags[2 * i] != 0, (size_t)tokens, (size_t)d0, (size_t)s0}, {flags[2 * i + 1] != 0, (size_t)tokens, (size_t)d1, (size_t)s1});
     if (!few_fits(have, need)) have = {std::max(have.h, need.h), std::max(have.part, need.part)};
     const long d[2] = {d0, d1}, s[2] = {s0, s1};
     for (int n = 0; n < 2; ++n)
@@ -66,3 +67,14 @@ def test_rollouts_of_many_possible_drafts_stay_in_one_launch(plan):
             for cross in (0, 1):
                 pays = [plan.rollout_pays(layers, wide, cross, k) for k in range(1, 65)]
                 assert pays == sorted(pays, reverse=True) and not pays[-1]
+
+
+def test_run_time_sizes_are_spread_only_where_that_is_faster(plan):
+    # (d, heads, rows of 16 tokens, spread was the faster one): both sides measured on networks of two layers
+    layer = lambda d: 12 * d * d * 4
+    pays = lambda d, heads, rows: bool(plan.dyn_pays(C.c_long(16 * rows), C.c_long(heads), C.c_long(layer(d))))
+    for d, heads, rows in ((96, 3, 512), (96, 3, 576), (320, 5, 512), (256, 8, 256), (320, 10, 128), (512, 16, 128), (512, 32, 64), (1024, 16, 64)):
+        assert pays(d, heads, rows), (d, heads, rows)
+    for d, heads, rows in ((64, 4, 1024), (96, 3, 1024), (256, 16, 1024), (320, 20, 256), (512, 32, 256), (640, 20, 256),
+                           (1024, 32, 64), (1024, 8, 128), (1024, 16, 512), (1024, 64, 2048)):
+        assert not pays(d, heads, rows), (d, heads, rows)

@@ -199,6 +199,31 @@ def test_few_rows_of_run_time_sizes(dtype, H, base, draft, B):
     _stage_parity(wl, B, t0, K, np.full(B, 1.1), bonus=B == 2, paths=("f32-ops", "f32-ops"))
 
 
+def _runs_timed_kernel(ctx, stage):
+    # operator sequences are not bracketed by events, every other path of a network is
+    from paper_2512_15773_amd.binding import TsdpError
+    try:
+        ctx.tsdp_kernel_ms(stage)
+        return True
+    except TsdpError:
+        return False
+
+
+@pytest.mark.parametrize("B, K_max, spread", [(587, 1, (True, True)), (588, 1, (False, False)), (293, 2, (True, True)), (294, 2, (False, True))])
+def test_run_time_sizes_on_both_sides_of_their_line(B, K_max, spread):
+    # three heads: up to 9400 tokens, of the ragged batch for the base network and of the environments for the drafter
+    wl = ti.small_variant(ti.C2, A=4, cond_dim=32, B=B, K_max=K_max, base=ti.NetShape(1, 96, 3), draft=ti.NetShape(1, 48, 3))
+    S = _setup(wl, B)
+    t0 = np.full(B, -1); t0[[0, B // 2, B - 1]] = (70, 0, 3)
+    K = np.full(B, K_max); s = np.full(B, 1.1)
+    S["ctx"].tsdp_kernel_timing(True)
+    rows = _gpu_draft(S, t0, K, s, None)
+    o = _check_draft(S, rows, t0, K, s, None, TOL["fp32"])
+    _check_verify(S, rows, o, TOL["fp32"])
+    assert (_runs_timed_kernel(S["ctx"], 1), _runs_timed_kernel(S["ctx"], 0)) == spread
+    S["ctx"].close()
+
+
 @pytest.mark.parametrize("wl", [ti.small_variant(ti.C3, base=ti.NetShape(2, 256, 4), draft=ti.NetShape(2, 256, 4), K_max=3),
                                 ti.small_variant(ti.C4, base=ti.NetShape(1, 512, 8), draft=ti.NetShape(1, 512, 8), K_max=3)])
 def test_few_rows_of_equal_networks_give_equal_predictions(wl):
