@@ -27,6 +27,11 @@
  *  - Ragged row table: environment b owns rows row_ptr[b] .. row_ptr[b+1]-1; row row_ptr[b]+k-1 holds the
  *    input state y_{k-1} of drafted transition k at timestep t0[b]-k+1.  K_eff = min(K, t0).  An
  *    environment at t0 = 0 owns one row (the deterministic last base step); a finished one owns none.
+ *  - An environment's results do not depend on the batch it is computed in, bit for bit, within one context and between
+ *    contexts whose capacity is on the same side of the line up to which a forward pass is spread over the chip
+ *    (compiled shapes: B_max * (K_max + bonus_row) * H of at most 2048 tokens in fp32, 2176 in bf16, and K_max of at
+ *    most 9 with two layers for a spread rollout).  Across that line they differ by rounding, and an accept decision
+ *    that nearly ties can differ.
  *  - H*A must be a multiple of 4 and at most 512.  The context owns weights, tables and workspace; calls on one
  *    context must not overlap in time (they share the workspace).
  */
@@ -81,8 +86,8 @@ int tsdp_create(const tsdp_config* cfg, tsdp_ctx** out_ctx);
 /* Frees everything the context owns.  Synchronises the device.  NULL is allowed. */
 void tsdp_destroy(tsdp_ctx* ctx);
 
-/* Environment: TSDP_DISABLE_FUSED (any value), read by tsdp_load_weights, keeps a network on the general fp32
- * operator kernels even where a fused kernel exists for its shape (a diagnostic; tsdp_path_name reports the path). */
+/* Environment: TSDP_DISABLE_FUSED (any value), read by every tsdp_load_weights, keeps that network on the general fp32
+ * operator kernels even where a faster kernel exists for its shape (a diagnostic). */
 
 /* Loads one denoiser (which: 0 = base, 1 = drafter) from a HOST blob of fp32 values: the tensors
  * tok_w[d,A] tok_b[d] pos[H,d] t_w1[d,d] t_b1[d] t_w2[d,d] t_b2[d] (mode 0: c_w[d,C] c_b[d]) then per
@@ -186,9 +191,10 @@ int tsdp_chain_staged(tsdp_ctx* ctx, int B, float* d_x, int32_t* d_t, const int3
  * synchronises.  Every kernel of a round reads the round's live row count on the device and returns at once when no
  * environment is running any more, so rounds past the end of the chain cost their launches without work -- about 1.5 us
  * each: 6 launches a round, or 2 to 6 more per layer where few rows are spread over the chip (one environment, fp32,
- * d = 256 x 8 and 128 x 2 layers, K_max = 8: 54 launches, 83 us) -- and leave latents, timesteps and totals untouched.  A round advances every running environment by at least one step, so
- * n_rounds = (largest t) + 1 <= T always completes the chain.  Finished environments own no rows: the ragged verify
- * batch of a round holds the running environments only, and tiles beyond its live row count exit.
+ * d = 256 x 8 and 128 x 2 layers, K_max = 8: 54 launches, 83 us) -- and leave latents, timesteps and totals untouched.
+ * A round advances every running environment by at least one step, so n_rounds = (largest t) + 1 <= T always completes
+ * the chain.  Finished environments own no rows: the ragged verify batch of a round holds the running environments only,
+ * and tiles beyond its live row count exit.
  * staged = 0: d_K[B], d_sigma_scale[B], d_lambda[B] (NULL = stochastic test) as in tsdp_chain; staged = 1: [B,3] stage
  * tables with the bounds t_hi >= t_lo >= 0 as in tsdp_chain_staged.  Totals as in tsdp_chain (device, NULL to skip);
  * d_rounds_run (device int32, NULL to skip) receives the number of rounds in which some environment ran.
@@ -241,7 +247,9 @@ int tsdp_status(tsdp_ctx* ctx, void* stream, int32_t* h_status);
 int tsdp_kernel_timing(tsdp_ctx* ctx, int enable);
 int tsdp_kernel_ms(tsdp_ctx* ctx, int stage, float* h_ms);
 
-/* Name of the kernel path used for a network ("f32-ops", "bf16-mfma-fused", ...). which: 0 base, 1 drafter. */
+/* Kernels of a network (which: 0 base, 1 drafter): "bf16-mfma-fused" / "f32-mfma-fused" where kernels are compiled for
+ * its shape, "f32-ops" otherwise.  In contexts of few rows the forward pass is spread over the chip instead of one
+ * workgroup per tile (compiled shapes), or instead of one launch per operator (others); the name stays the same. */
 const char* tsdp_path_name(const tsdp_ctx* ctx, int which);
 
 const char* tsdp_last_error(const tsdp_ctx* ctx);

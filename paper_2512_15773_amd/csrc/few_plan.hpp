@@ -14,6 +14,15 @@ namespace tsdp {
 //    first and 2.6 us where it first requests the row's data and weights (one C2 environment, a round of 54 launches 85 us, 142).
 inline int few_safe_rows(bool ahead, int B, int R_cap) { return ahead ? std::min(B, R_cap) : 0; }
 
+// Networks with compiled kernels.  One workgroup per tile takes the same time from 1 to 256 tiles, the spread launches grow
+// with the rows; they meet at about 2100 tokens.  Rounds, us, tile / spread at 64, 128, 144 rows of 16 tokens: bf16 d = 256
+// 498 / 409, 498 / 443, 497 / 511; bf16 d = 384 880 / 729, 881 / 869, -; fp32 d = 256 799 / 504, 800 / 724, and at 136 rows
+// 797 / 835; at 64, 128 rows of 32 tokens, d = 512: 1577 / 1252, 1591 / 1856.  A layer of less than 700 KB passes through one
+// compute unit faster than through two launches (fp32 d = 64, 393 KB in all: 21 us against 25).
+inline bool few_pays(size_t tokens, bool f32, size_t layer_bytes) {
+  return tokens <= (f32 ? 2048 : 2176) && layer_bytes >= 700000;
+}
+
 // Launches of a spread rollout: every transition up to K_max has its own, whether drafted or not (the draft counts are on
 // the device).  A drafted transition of the fp32 d = 128 network takes 23 us instead of the persistent kernel's 39, an
 // undrafted one 6 to 15 instead of none: with half of K_max or more the spread rollout is the faster one, and what fewer

@@ -416,7 +416,6 @@ constexpr int F256_CH = 256;
 constexpr int FEW_TILES = 288;   // up to this many tiles the 8-wave verify variant (one workgroup per CU) is used
 constexpr int V512_HPX = 8;      // heads per cross-attention phase of the d = 512 verify kernel
 constexpr int V512_CH = 256;     // hidden-chunk width of the d = 512 verify kernel
-constexpr size_t FEW_TOKENS_BF16 = 2176, FEW_TOKENS_F32 = 2048, FEW_LAYER_BYTES = 700000;   // build_fused
 // shapes with compiled fused kernels
 bool find_fused(int dtype, int D, int H, int heads, int cm, int S, int mlp_ratio, int L, FusedKernels& k) {
   if (mlp_ratio != 4 || L > FUSED_MAX_LAYERS) return false;
@@ -624,14 +623,9 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   n.fused_draft_small = fk.draft_small; n.fused_draft_big = fk.draft_big;
   n.draft_rpt_small = fk.rpt_small; n.draft_rpt_big = fk.rpt_big;
   n.few_forward = fk.few_forward; n.few_draft = fk.few_draft; n.few_film = fk.few_film; n.few_slices = fk.few_slices;
-  // Few rows: the spread kernels.  One workgroup per tile takes the same time from 1 to 256 tiles, the spread launches
-  // grow with the rows; they meet at about 2100 tokens.  Rounds, us, tile / spread at 64, 128, 144 rows of 16 tokens: bf16
-  // d = 256 498 / 409, 498 / 443, 497 / 511; bf16 d = 384 880 / 729, 881 / 869, -; fp32 d = 256 799 / 504, 800 / 724, and at
-  // 136 rows 797 / 835; at 64, 128 rows of 32 tokens, d = 512: 1577 / 1252, 1591 / 1856.  A layer of less than 700 KB passes
-  // through one compute unit faster than through two launches (fp32 d = 64, 393 KB in all: 21 us against 25).  The capacity
-  // of the context decides, not the call: an environment's result must not depend on the batch it is computed in.
-  const size_t layer_bytes = (size_t)(cf.cond_mode == 1 ? 14 : 12) * d * d * (f32 ? 4 : 2);
-  n.few = dyn || (rows_max(cf) * cf.H <= (f32 ? FEW_TOKENS_F32 : FEW_TOKENS_BF16) && layer_bytes >= FEW_LAYER_BYTES);
+  // Few rows: the spread kernels.  The capacity of the context decides, not the call: an environment's result must not
+  // depend on the batch it is computed in.
+  n.few = dyn || few_pays(rows_max(cf) * cf.H, f32, (size_t)(cf.cond_mode == 1 ? 14 : 12) * d * d * (f32 ? 4 : 2));
   // The rollout: fp32 layers are bound by one unit's matrix rate (d = 128: 39 us per transition, spread 23), bf16 drafters
   // of this size are not (d = 192: spread 2 us per transition slower).  Twins are both spread or neither.
   const bool twin = twin_nets(cf);

@@ -12,6 +12,7 @@ using namespace tsdp;
 extern "C" {
 int safe_rows(int own, int B, int R_cap) { return few_safe_rows(own != 0, B, R_cap); }
 int rollout_pays(int layers, int wide, int cross, int K_max) { return few_rollout_pays(layers, wide != 0, cross != 0, K_max); }
+int pays(long tokens, int f32, long layer_bytes) { return few_pays(tokens, f32 != 0, layer_bytes); }
 int dyn_pays(long tokens, long heads, long layer_bytes) { return few_dyn_pays(tokens, heads, layer_bytes); }
 // the context's buffers after a sequence of loads: flags[2 * i] / [2 * i + 1] = base / drafter takes the spread path then
 int buffers_hold(long tokens, long d0, long s0, long d1, long s1, const int* flags, int loads) {
@@ -78,3 +79,12 @@ def test_run_time_sizes_are_spread_only_where_that_is_faster(plan):
     for d, heads, rows in ((64, 4, 1024), (96, 3, 1024), (256, 16, 1024), (320, 20, 256), (512, 32, 256), (640, 20, 256),
                            (1024, 32, 64), (1024, 8, 128), (1024, 16, 512), (1024, 64, 2048)):
         assert not pays(d, heads, rows), (d, heads, rows)
+
+
+def test_compiled_kernels_are_spread_up_to_2048_and_2176_tokens(plan):
+    # the GPU tests of the tile kernels take contexts just above these lines
+    L = C.c_long
+    big = L(12 * 256 * 256 * 2)
+    assert plan.pays(L(2048), 1, big) and not plan.pays(L(2064), 1, big)
+    assert plan.pays(L(2176), 0, big) and not plan.pays(L(2192), 0, big)
+    assert not plan.pays(L(16), 1, L(12 * 64 * 64 * 4))

@@ -224,6 +224,44 @@ def test_run_time_sizes_on_both_sides_of_their_line(B, K_max, spread):
     S["ctx"].close()
 
 
+@pytest.mark.parametrize("dtype, H, base, draft", [
+    ("fp32", 8, ti.NetShape(2, 96, 3), ti.NetShape(1, 48, 3)),         # eight tokens
+    ("fp32", 16, ti.NetShape(1, 100, 5), ti.NetShape(1, 36, 3)),       # sizes that are not multiples of 16
+    ("fp32", 48, ti.NetShape(1, 64, 4, 2), ti.NetShape(1, 32, 2)),     # 48 tokens
+    ("bf16", 8, ti.NetShape(1, 256, 4), ti.NetShape(1, 128, 4)),       # bf16 weights
+])
+@pytest.mark.parametrize("bonus, clip, norm", [(False, None, 0), (True, 1.5, 1)])
+def test_operator_kernels_with_vector_conditioning(dtype, H, base, draft, bonus, clip, norm):
+    # shapes that neither a compiled nor a spread kernel takes: one launch per operator, one pass per drafted transition
+    wl = ti.small_variant(ti.C2, dtype=dtype, H=H, A=5, cond_dim=32, B=4, K_max=3, base=base, draft=draft)
+    S = _setup(wl, 4, clip=clip, bonus=bonus, norm=norm)
+    assert (S["ctx"].path_name(0), S["ctx"].path_name(1)) == ("f32-ops", "f32-ops")
+    t0 = np.array([99, 0, -1, 2]); K = np.array([3, 2, 3, 3]); s = np.full(4, 1.1)
+    S["ctx"].tsdp_kernel_timing(True)
+    rows = _gpu_draft(S, t0, K, s, None)
+    o = _check_draft(S, rows, t0, K, s, None, TOL[dtype])
+    _check_verify(S, rows, o, TOL[dtype])
+    assert not _runs_timed_kernel(S["ctx"], 0) and not _runs_timed_kernel(S["ctx"], 1)
+    _check_accept(S, rows, o, s, None, 1e-9)
+    S["ctx"].close()
+
+
+@pytest.mark.parametrize("wl, B", [
+    (ti.small_variant(ti.C2, base=ti.NetShape(2, 256, 4)), 129),                        # fp32: 2064 tokens with K_max = 1
+    (ti.small_variant(ti.C3, base=ti.NetShape(2, 256, 4)), 137),                        # bf16: 2192
+    (ti.small_variant(ti.C5, ragged=False, base=ti.NetShape(2, 384, 6)), 137),
+    (ti.small_variant(ti.C4, base=ti.NetShape(1, 512, 8)), 69),                         # 2208 tokens of 32-token rows
+])
+@pytest.mark.parametrize("bonus, clip, norm", [(False, None, 1), (True, 1.5, 1)])
+def test_tile_kernels_just_above_the_few_rows(wl, B, bonus, clip, norm):
+    # the smallest contexts whose base network keeps one workgroup per tile; most environments are finished, so that the
+    # live rows end inside a tile
+    wl = ti.replace(wl, B=B, K_max=1)
+    t0 = np.full(B, -1); t0[:5] = (wl.T - 1, 0, 60, 1, 30)
+    K = np.ones(B, int); s = np.full(B, 1.1)
+    _stage_parity(wl, B, t0, K, s, clip=clip, bonus=bonus, norm=norm)
+
+
 @pytest.mark.parametrize("wl", [ti.small_variant(ti.C3, base=ti.NetShape(2, 256, 4), draft=ti.NetShape(2, 256, 4), K_max=3),
                                 ti.small_variant(ti.C4, base=ti.NetShape(1, 512, 8), draft=ti.NetShape(1, 512, 8), K_max=3)])
 def test_few_rows_of_equal_networks_give_equal_predictions(wl):
@@ -1103,3 +1141,34 @@ def test_prepare_makes_a_fresh_context_capturable_and_short_chains_stop_where_as
     torch.cuda.synchronize()
     assert int(run.item()) == 0 and torch.equal(xa, xb)
     ref_ctx.close(); ctx.close()
+
+
+@pytest.mark.parametrize("wl", [
+    ti.small_variant(ti.C2, B=3, K_max=4, base=ti.NetShape(2, 256, 4)),
+    ti.small_variant(ti.C4, B=2, K_max=3, base=ti.NetShape(1, 512, 8)),
+    ti.small_variant(ti.C2, B=3, K_max=4, A=4, cond_dim=64, base=ti.NetShape(2, 96, 3), draft=ti.NetShape(1, 48, 3)),
+])
+def test_first_round_of_few_rows_can_be_captured(wl):
+    # after tsdp_prepare the spread kernels need no allocation and no launch attribute: their first launch is recorded
+    import torch
+    B = wl.B
+    nets = [ti.make_weights(wl, which, head_scale=0.3) for which in ("base", "draft")]
+    cond, x0 = ti.make_cond(wl, B), to_dev(ti.make_latents(wl, B))
+    t0 = to_dev(np.array([50, 2, 0][:B], np.int32)); K = to_dev(np.array([wl.K_max, 3, 1][:B], np.int32)); s = torch.ones(B, device="cuda")
+    ctx = gpu_side(wl, *nets, cond)
+    ctx.tsdp_prepare()
+    x, t = x0.clone(), t0.clone()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.tsdp_round(x, t, K, s, None)
+    eager = gpu_side(wl, *nets, cond)
+    for i in range(3):
+        x.copy_(x0); t.copy_(t0)
+        graph.replay()
+        torch.cuda.synchronize()
+        xe, te = x0.clone(), t0.clone()
+        eager.tsdp_round(xe, te, K, s, None)
+        assert torch.equal(x, xe) and torch.equal(t, te), i
+    del graph
+    eager.close(); ctx.close()
