@@ -17,8 +17,8 @@
 //
 // What bounds it: with R rows the one-workgroup-per-tile kernels keep R / rows-per-tile compute units busy, each of
 // which streams every weight of the network (or, fp32, multiplies at one unit's matrix rate).  Here a launch has
-// R x heads or R x slices workgroups that read each weight once per row, request their weights before anything else
-// and do a few microseconds of work; the rest is the launch itself.
+// R x heads or R x slices workgroups that read each weight once per row, request their weights right behind the residual
+// and its partial sums, before the first of these is used, and do a few microseconds of work; the rest is the launch itself.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

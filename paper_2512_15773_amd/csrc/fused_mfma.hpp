@@ -321,7 +321,7 @@ struct FusedCfg {
   static constexpr int WAVES_PER_SIMD = (WG_PER_CU * NW + 3) / 4;
   static constexpr int BD = WAVES_PER_SIMD >= 2 ? 1 : 2; // LDS operand buffers: a second wave on the SIMD hides LDS latency
   static constexpr bool XPF = WAVES_PER_SIMD == 1;      // request the first weights of the MLP's products one phase early
-                                                         // (those of the attention blocks always: C3 -1 %, C4 and C5 -0.5 %)
+                                                         // (those of the attention blocks always: C3 -1 %, C4, C5 no change beyond the noise)
   static_assert(D % (16 * NW) == 0 && NT % 16 == 0 && H % 16 == 0 && NT % H == 0 && DH % KSTEP == 0, "shape");
   static_assert(D % KSTEP == 0 && CH % KSTEP == 0, "shape");
   static_assert((HEADS % HP) == 0 && (HP * 3 * DH) % (16 * NW) == 0 && (CM == 0 || (HPX * DH) % (16 * NW) == 0) &&

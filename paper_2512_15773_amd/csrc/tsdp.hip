@@ -116,8 +116,9 @@ struct tsdp_ctx {
   int32_t *row_ptr = nullptr, *row_t = nullptr, *row_env = nullptr, *t_next = nullptr, *n_acc = nullptr, *n_adv = nullptr;
   float *states = nullptr, *eps_p = nullptr, *eps_q = nullptr, *xi = nullptr, *y_last = nullptr;
   std::vector<void*> owned;
-  // A round computes the base network's per-row FiLM vectors (k_mod_gemm, bound by its output stream) on a second
-  // stream of the same priority while the drafter rolls out: forked after the row table, joined before the verify.
+  // A round of more than a few rows computes the base network's per-row FiLM vectors (k_mod_gemm, bound by its output
+  // stream) on a second stream of the same priority while the drafter rolls out: forked after the row table, joined
+  // before the verify.
   hipStream_t aux = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   // optional kernel timing: events recorded around the dominant kernel of each stage
@@ -1094,7 +1095,7 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
       Net& bn = c->net[0];
       if (base_mod_rows > 0 && bn.fused && bn.fused_mod && !bn.few && !bn.fnet.modtab) {
         // fork: a rollout keeps its FiLM vectors in LDS or in few_mod, so the shared buffer is free for the base network's.
-        // (Not for few rows: their product takes 7 us, the fork and join 20 to 30 us of every round of a chain.)
+        // (Not for few rows: their product takes 6 us, the fork and join about 30 us of every round of an enqueued chain.)
         HIPCHK(c, hipEventRecord(c->ev_fork, s));
         HIPCHK(c, hipStreamWaitEvent(c->aux, c->ev_fork, 0));
         bn.fused_mod(bn.fnet, d_row_t, 0, d_row_env, cf.T, d_row_ptr + B, base_mod_rows, c->mod, c->aux);
