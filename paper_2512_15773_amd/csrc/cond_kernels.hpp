@@ -4,7 +4,7 @@
 // The sums are k_linear's, bit for bit: fp32 fused multiply-adds over the features in ascending order, then the bias,
 // then one rounding to bf16.  mfma_f32_16x16x4_f32 adds its four products to the accumulator one after the other, each
 // with one rounding, in the order of the lane groups (checked on hardware, denormals included), so a chain of them over
-// ascending features is that sum.  Another order (three bf16 planes per observation: 0.93 ms instead of 3.04) rounds a few
+// ascending features is that sum.  Another order (three bf16 planes per observation: 0.92 ms instead of 2.83) rounds a few
 // keys to the other bf16 number, and at the first timesteps of a squared-cosine chain, where a noise prediction is
 // multiplied by 31, that is enough for a nearly tied draft to fall on the other side of its test.
 #pragma once
@@ -76,17 +76,19 @@ struct CondIO { CondNet net[2]; const float* cond; int M, C, KS, SF; };   // con
 // Tile: 256 features (16 fragments, all keys or all values of one layer because d is a multiple of 256) x 128 tokens
 // (8 fragments).  8 waves as 4 x 2, each 64 features x 64 tokens.  Per k-step the workgroup brings 16 KB of weights and
 // 16 KB of observations into LDS and does 1024 MFMAs, 8192 cycles of each matrix core: they bound it.  Two LDS buffers,
-// the next k-step travels through registers while the current one is multiplied; one barrier per k-step.
+// the next k-step travels through registers while the current one is multiplied; one barrier per k-step.  Two workgroups
+// per CU (128 registers, a few spilled before the loop and read back after it), one multiplies while the other waits at
+// its barrier: 2.83 ms instead of 3.04.
 // Lane group g supplies features 4m + g of a k-step to MFMA m: the weights are packed in that order (build_fused).
 // Keys are computed features x tokens, values tokens x features, so that in both cases a lane's four accumulators are
 // the neighbouring entries of one 8-byte piece of the attention operand.
-// Measured, 256 environments x 64 tokens x 768, 12 layers of d = 512 and 2 of d = 256: 3.04 ms = 110 TFLOP/s (nominal fp32
+// Measured, 256 environments x 64 tokens x 768, 12 layers of d = 512 and 2 of d = 256: 2.83 ms = 118 TFLOP/s (nominal fp32
 // matrix rate 157), against 4.9 ms of fp32 products on the vector units in 28 launches, each followed by two that rounded
 // and reordered its output.
 constexpr int COND_FF = 16, COND_TF = 8, COND_XS = 36;   // floats per token in LDS: 32 and the bank padding
 constexpr int COND_W_B = COND_FF * 64 * 16, COND_STAGE_B = COND_W_B + COND_TF * 16 * COND_XS * 4, COND_LDS = 2 * COND_STAGE_B;
 
-__global__ __launch_bounds__(512, 1) void k_cond_kv(CondIO io) {
+__global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wf = wave & 3, wt = wave >> 2, l16 = lane & 15, lg = lane >> 4;
