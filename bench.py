@@ -551,7 +551,7 @@ def measure_workload(wl, point, steps, warmup, torch, Tsdp, dev, full):
     if fused:
         k_ms, k_med = time_kernel(ctx, lambda: ctx.tsdp_verify(wl.B, rows), 1, n_it)
         kd_ms, _ = time_kernel(ctx, lambda: ctx.tsdp_draft(x0d, t0d, Kd, sd, None, rows), 0, n_it)
-        kname = "k_fused_forward (verify forward, all layers in one launch)"
+        kname = "verify forward (k_fused_forward, all layers in one launch; few rows: k_few_*, two launches per layer and more)"
     else:
         k_ms, k_med, kd_ms, kname = t_verify[0], t_verify[1], None, "tsdp_verify (sequence of fp32 operator kernels)"
     lat["drafter_kernel"] = kd_ms
@@ -611,7 +611,7 @@ def measure_workload(wl, point, steps, warmup, torch, Tsdp, dev, full):
         wbytes = drafter_weight_bytes(wl)
         kmax = int(keff.max(initial=0))
         stream_gbs = wbytes * kmax * wgs / (kd_ms * 1e-3) / 1e9
-        res["drafter"] = {"kernel": "k_fused_draft (persistent rollout, K sequential steps in one launch)",
+        res["drafter"] = {"kernel": "drafter rollout (k_fused_draft, K sequential steps in one launch; few fp32 rows: k_few_*)",
                           "kernel_ms": kd_ms, "steps": kmax, "us_per_step": 1e3 * kd_ms / max(kmax, 1),
                           "workgroups": wgs, "environments_per_workgroup": rpt,
                           "weight_bytes_per_step_and_workgroup": wbytes,
