@@ -37,14 +37,15 @@ inline bool few_rollout_pays(int layers, bool wide, bool cross, int K_max) {
 
 // Networks with run-time sizes: `tokens` a launch covers at most (the ragged batch's, the rollout's one row per environment).
 // A spread launch streams its weights once per row and adds max(heads, slices) partial sums of the whole row in every
-// workgroup, one launch per operator does neither but has six times the launches.  Rows of 16 tokens at which both take
-// the same time (two layers, 64 .. 2048 rows measured): three heads d = 96 ~950; 8 heads d = 256 ~850; 10 d = 320 ~500;
-// 16 d = 512 ~420; 20 d = 640 ~230; 32 d = 512 ~200; up to six heads at d = 512 .. 768, beyond 2048; of 32
-// tokens: 8 d = 512 ~240, 12 d = 768 ~115 -- tokens x heads of 44 000 and more, near whose lower end the line is.  (64 rows, us, operators / spread: d = 96 187 / 57, d = 512 663 / 309,
-// 16 heads; 2048 rows 671 / 800, 7164 / 8634.)  A layer of more than the 32 MB of all L2s comes from beyond them for every
-// row: d = 1024 meets at 90 rows (8 or 16 heads), 64 rows 1369 / 1182, 512 rows 6434 / 9794.
+// workgroup; one launch per operator does neither but has six times the launches.  Rows at which both take the same time
+// (two layers, 64 .. 2048 rows measured), 16 tokens: 3 heads d = 96 ~950, 8 d = 256 ~850, 10 d = 320 ~500, 16 d = 512 ~420,
+// 20 d = 640 ~230, 32 d = 512 ~200, up to six heads at d = 512 .. 768 beyond 2048; 32 tokens: 8 d = 512 ~240, 12 d = 768 ~115.
+// That is tokens x heads of 44 000 and more, near whose lower end the line is.  (64 rows, us, operators / spread: d = 96
+// 187 / 57, d = 512 with 16 heads 663 / 309; 2048 rows 671 / 800, 7164 / 8634.)  A layer of more than the 32 MB of all L2s
+// comes from beyond them for every row: d = 1024 meets at 90 rows (8 or 16 heads), 64 rows 1369 / 1182, 512 6434 / 9794.
 inline bool few_dyn_pays(size_t tokens, size_t heads, size_t layer_bytes) {
-  return layer_bytes <= (32u << 20) ? tokens * std::max<size_t>(heads, 5) <= 47000 : tokens * std::max<size_t>(heads, 16) <= 16384;
+  return layer_bytes <= (32u << 20) ? tokens * std::max<size_t>(heads, 5) <= 47000
+                                    : tokens * std::max<size_t>(heads, 16) <= 16384;
 }
 
 // Floats of the two residual and of the two partial-sum buffers, shared by both networks.  Which networks take the spread
