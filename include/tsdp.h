@@ -29,9 +29,9 @@
  *    environment at t0 = 0 owns one row (the deterministic last base step); a finished one owns none.
  *  - An environment's results do not depend on the batch it is computed in, bit for bit, within one context and between
  *    contexts whose capacity is on the same side of the line up to which a forward pass is spread over the chip
- *    (compiled shapes: B_max * (K_max + bonus_row) * H of at most 2048 tokens in fp32, 2176 in bf16, and K_max of at
- *    most 9 with two layers for a spread rollout).  Across that line they differ by rounding, and an accept decision
- *    that nearly ties can differ.
+ *    (compiled shapes: B_max * (K_max + bonus_row) * H of at most 2048 tokens in fp32, 2176 in bf16; rollouts with
+ *    cross-attention B_max of at most 24; two bf16 networks of one shape K_max of at most 9 with two layers).  Across
+ *    that line they differ by rounding, and an accept decision that nearly ties can differ.
  *  - H*A must be a multiple of 4 and at most 512.  The context owns weights, tables and workspace; calls on one
  *    context must not overlap in time (they share the workspace).
  */
@@ -233,7 +233,8 @@ int tsdp_distill_loss_noalloc(tsdp_ctx* ctx, int R, const int32_t* d_row_t, cons
  * bit 0 = some K was outside 0..K_max (clamped), bit 1 = some t0 was >= T (treated as T-1) or a row timestep given to
  * tsdp_verify was outside 0..T-1 (clamped), bit 2 = some running environment had sigma_scale <= 0 or NaN (not
  * corrected: the outputs of that environment are undefined, no memory is touched out of bounds), bit 3 = a row
- * environment index given to tsdp_verify was outside the batch of tsdp_set_cond (clamped). */
+ * environment index given to tsdp_verify was outside the batch of tsdp_set_cond (clamped), bit 4 = a kernel gave up waiting
+ * for another workgroup of its launch (cannot happen; the results are undefined, tsdp_load_weights restores the context). */
 int tsdp_status(tsdp_ctx* ctx, void* stream, int32_t* h_status);
 
 /* Measurement aid.  tsdp_kernel_timing(ctx, 1) makes the following calls record a pair of HIP events on the

@@ -16,15 +16,15 @@ inline int few_safe_rows(bool ahead, int B, int R_cap) { return ahead ? std::min
 
 // Networks with compiled kernels.  One workgroup per tile takes the same time from 1 to 256 tiles, the spread launches grow
 // with the rows; they meet at about 2100 tokens.  Rounds, us, tile / spread at 64, 128, 144 rows of 16 tokens: bf16 d = 256
-// 498 / 409, 498 / 443, 497 / 511; bf16 d = 384 880 / 729, 881 / 869, -; fp32 d = 256 799 / 504, 800 / 724, and at 136 rows
-// 797 / 835; at 64, 128 rows of 32 tokens, d = 512: 1577 / 1252, 1591 / 1856.  A layer of less than 700 KB passes through one
+// 498 / 409, 498 / 443, 497 / 511; bf16 d = 384 880 / 729, 881 / 869, -; fp32 d = 256 (one launch, k_flow) 799 / 461, 800 / 727;
+// at 64, 128 rows of 32 tokens, d = 512: 1577 / 1252, 1591 / 1856.  A layer of less than 700 KB passes through one
 // compute unit faster than through two launches (fp32 d = 64, 393 KB in all: 21 us against 25).
 inline bool few_pays(size_t tokens, bool f32, size_t layer_bytes) {
   return tokens <= (f32 ? 2048 : 2176) && layer_bytes >= 700000;
 }
 
-// Launches of a spread rollout: every transition up to K_max has its own, whether drafted or not (the draft counts are on
-// the device).  A drafted transition of the fp32 d = 128 network takes 23 us instead of the persistent kernel's 39, an
+// Launches of a spread rollout (two bf16 networks of one shape): every transition up to K_max has its own, whether drafted or
+// not (the draft counts are on the device).  With the fp32 d = 128 network, before it was one launch (k_flow), a drafted transition took 23 us instead of the persistent kernel's 39, an
 // undrafted one 6 to 15 instead of none: with half of K_max or more the spread rollout is the faster one, and what fewer
 // drafts lose grows with K_max.  Rounds of one C2 environment, us, persistent / spread rollout: K = 1, 4, 8 of 8 226 / 277,
 // 344 / 331, 495 / 396; K = 1, 4, 16 of 16 226 / 363, 344 / 413, 788 / 595; K = 4, 64 of 64 344 / 1085, 2673 / 1888.  So up
@@ -34,6 +34,10 @@ constexpr int FEW_ROLL_LAUNCHES = 40;
 inline bool few_rollout_pays(int layers, bool wide, bool cross, int K_max) {
   return layers * (wide ? 2 : 1) * (cross ? 3 : 2) * K_max + 1 <= FEW_ROLL_LAUNCHES;
 }
+
+// Rollout in one launch (k_flow) of a drafter with cross-attention, d = 256, 32 tokens: us for eight transitions of 1, 4, 8, 16, 32
+// environments 317, 346, 350, 373, 518, the persistent kernel (one workgroup an environment) 425 to 463.
+inline bool flow_draft_pays(int environments) { return environments <= 24; }
 
 // Networks with run-time sizes: `tokens` a launch covers at most (the ragged batch's, the rollout's one row per environment).
 // A spread launch streams its weights once per row and adds max(heads, slices) partial sums of the whole row in every

@@ -12,6 +12,13 @@ struct SchedTables {          // device pointers, fp32[T] each; posterior mean =
   int T;
 };
 
+// Tickets and counters of the one-launch passes (k_flow): one word per line of the L2, zero before their launch.
+constexpr int SYNC_LINE = 32;
+__device__ __forceinline__ void clear_sync(int32_t* sync, int lines, int thread, int threads) {
+  if (sync)
+    for (int i = thread; i < lines; i += threads) sync[(size_t)i * SYNC_LINE] = 0;
+}
+
 // K_eff = min(clamp(K), t0), rows per env = live ? (bonus ? K_eff + 1 : max(K_eff,1)) : 0, exclusive scan into
 // row_ptr[B+1].  K is clamped to 1..K_max (0..K_max with the bonus row, where K = 0 is a plain base step).
 // n_draft[0] receives B if any environment has rows, else 0; n_draft[1] receives B if any environment drafts
@@ -73,9 +80,10 @@ __global__ __launch_bounds__(128) void k_plan_rows(const float* __restrict__ x, 
                                                    int32_t* __restrict__ n_draft, int32_t* __restrict__ live,
                                                    int32_t* __restrict__ rounds_run, int32_t* __restrict__ row_t, int32_t* __restrict__ row_env,
                                                    float* __restrict__ y, float* __restrict__ states, float* __restrict__ eps_p,
-                                                   float* __restrict__ xi) {
+                                                   float* __restrict__ xi, int32_t* __restrict__ sync, int lines) {
   __shared__ int32_t part[3][2];
   const int b = blockIdx.x, k_min = bonus ? 0 : 1;
+  clear_sync(sync, lines, b * 128 + threadIdx.x, B * 128);
   auto plan = [&](int kk, int tt, int& ke) {            // rows of an environment
     const int k = min(max(kk, k_min), K_max), t = min(tt, T - 1);
     ke = t < 0 ? 0 : min(k, t);
@@ -129,8 +137,9 @@ __global__ __launch_bounds__(128) void k_plan_rows(const float* __restrict__ x, 
 // environment index to 0..n_env-1; status bit 1 / bit 3 report a clamp.
 __global__ void k_check_rows(const int32_t* __restrict__ d_R, int R_cap, const int32_t* __restrict__ row_t,
                              const int32_t* __restrict__ row_env, int T, int n_env, int32_t* __restrict__ row_t_out,
-                             int32_t* __restrict__ row_env_out, int32_t* __restrict__ status) {
+                             int32_t* __restrict__ row_env_out, int32_t* __restrict__ status, int32_t* __restrict__ sync, int lines) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  clear_sync(sync, lines, r, gridDim.x * blockDim.x);
   const int R = min(*d_R, R_cap);
   if (r >= R) return;
   int t = row_t[r], e = row_env[r];
@@ -145,7 +154,8 @@ __global__ void k_check_rows(const int32_t* __restrict__ d_R, int R_cap, const i
 __global__ void k_rows(const float* __restrict__ x, const int32_t* __restrict__ t0, const int32_t* __restrict__ row_ptr,
                        int T, int D, int32_t* __restrict__ row_t, int32_t* __restrict__ row_env,
                        float* __restrict__ y, float* __restrict__ states, float* __restrict__ eps_p,
-                       float* __restrict__ xi, const int32_t* __restrict__ gate) {
+                       float* __restrict__ xi, int32_t* __restrict__ sync, int lines, const int32_t* __restrict__ gate) {
+  clear_sync(sync, lines, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
   if (gate && *gate == 0) return;                   // chain driver: no environment is running any more
   const int b = blockIdx.x;
   const int r0 = row_ptr[b], n = row_ptr[b + 1] - r0;

@@ -16,6 +16,7 @@
 #include "cond_kernels.hpp"
 #include "few_plan.hpp"
 #include "few_rows.hpp"
+#include "flow_rows.hpp"
 #include "round_kernels.hpp"
 
 using namespace tsdp;
@@ -28,6 +29,7 @@ struct FewRun {                 // one forward pass of k_few_*
   const float* mod;             // [R][L*4D], or the network's table over timesteps
   float* eps_out;
   float* h[2]; float* part[2]; size_t pstride;
+  unsigned char* buf; int32_t* sync; int32_t* status;   // k_flow: buffers of the rows, tickets and counters
 };
 
 struct LayerOff {
@@ -65,7 +67,8 @@ struct Net {
   void (*few_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr;
   void (*few_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;
   void (*few_film)(const FusedNet&, const int32_t*, int, const int32_t*, int, int, const int32_t*, const int32_t*, int, float*, hipStream_t) = nullptr;
-  int few_slices = 0;           // partial sums per row
+  int few_slices = 0;           // partial sums per row (run-time sizes)
+  size_t flow_row = 0;          // bytes of a row's buffers (k_flow)
   float* tok_wt = nullptr;      // [A, d] token embedding, transposed
   uint16_t* kc_pk = nullptr;    // fragment-ordered bf16 keys / transposed values of every (env, layer, head)
   uint16_t* vct_pk = nullptr;
@@ -107,6 +110,8 @@ struct tsdp_ctx {
   float *h = nullptr, *a = nullptr, *qkv = nullptr, *ao = nullptr, *u = nullptr, *sg = nullptr, *mod = nullptr;
   // k_few_*: residual, partial sums, latents between two transitions, FiLM vectors of all transitions of a rollout
   FewSize few_have;             // floats of few_h / few_part
+  unsigned char* flow_buf = nullptr; size_t flow_have = 0;   // k_flow: buffers of the rows, empty between launches
+  int32_t* sync = nullptr;      // k_flow: tickets and counters of the verify rows, then of the rollout's environments
   float *few_h[2] = {nullptr, nullptr}, *few_part[2] = {nullptr, nullptr}, *few_y[2] = {nullptr, nullptr}, *few_mod = nullptr;
   float* eps_tmp = nullptr;     // [B_max, D] drafter output of the current step
   int32_t *row_t_chk = nullptr, *row_env_chk = nullptr;   // [rows] range-checked copy of a caller's row table (tsdp_verify)
@@ -357,7 +362,7 @@ void few_forward(const FusedNet& n, const FewRun& r, hipStream_t s) {
   p.head();
 }
 
-// The drafter's rollout: 2 L launches per transition (3 L with cross-attention) and one that ends the last.  r.mod holds
+// The drafter's rollout as launches: 2 L per transition (3 L with cross-attention) and one that ends the last.  r.mod holds
 // the FiLM vectors of every transition, [env][k_max] rows (unless they come from the table).
 template <class C>
 void few_draft(const FusedNet& n, const FewRun& r, const DraftIO& dr, int k_max, float* const* y, hipStream_t s) {
@@ -392,11 +397,50 @@ void launch_few_film(const FusedNet& n, const int32_t* t_arr, int t_sub, const i
                      k_max, T, d, Nm, d_R, gate, R_cap, mod);
 }
 
+// Workgroups of a one-launch pass, per XCD: four phases of its rows (one at work, the next ones waiting with their weights in
+// registers; one C2 environment with 2, 3, 4 phases 282, 262, 260 us a round), two per compute unit at most.
+// Up to eight rows (one per XCD) and in rollouts a workgroup asks for half a unit's LDS, so that no two share its matrix cores
+// (8 rows 106 us a pass, 138 with two); with more rows the second one works while the first waits (64 rows 486 -> 300 us).
+// The rows of an XCD are dealt to four groups of tasks: fewer leave units idle, eight have no row left to take in turn
+// (64 rows of two layers 342, 385, 300, 351 us with 1, 2, 4, 8).
+constexpr int FLOW_WGS = 64, FLOW_GROUPS = 4, FLOW_ALONE = 84 * 1024;
+template <class C, bool ROLL>
+void flow_launch(const FusedNet& n, const FewRun& r, FlowIO& io, const std::conditional_t<ROLL, DraftIO, FewNone>& dr, int phases, hipStream_t s) {
+  const int per_xcd = (r.R_cap + 7) / 8, lds = C::lds(r.A);
+  io.R_cap = r.R_cap; io.phases = phases; io.groups = std::min(per_xcd, FLOW_GROUPS);
+  io.ticket = r.sync; io.cnt = r.sync + 8 * SYNC_LINE; io.status = r.status;
+  io.x = r.x; io.row_t = r.row_t; io.row_env = r.row_env; io.T = r.T; io.A = r.A;
+  io.mod = r.mod; io.mod_row = n.L * 4 * C::D; io.by_t = n.modtab != nullptr;
+  io.buf = r.buf; io.eps_out = r.eps_out;
+  static const hipError_t attr = hipFuncSetAttribute((const void*)k_flow<C, ROLL>, hipFuncAttributeMaxDynamicSharedMemorySize, 140 * 1024);
+  (void)attr;                                            // (a launch that this failed for fails itself)
+  if (r.R_cap > 0)
+    hipLaunchKernelGGL((k_flow<C, ROLL>), dim3(8 * std::min(4 * io.groups * C::G, FLOW_WGS)), dim3(C::TH),
+                       ROLL || r.R_cap <= 8 ? std::max(lds, FLOW_ALONE) : lds, s, n, io, dr);
+}
+
+template <class C>
+void flow_forward(const FusedNet& n, const FewRun& r, hipStream_t s) {
+  FlowIO io{};
+  io.word = r.d_R;
+  flow_launch<C, false>(n, r, io, FewNone{}, n.L * C::NPH + 1, s);
+}
+
+template <class C>
+void flow_draft(const FusedNet& n, const FewRun& r, const DraftIO& dr, int k_max, float* const* y, hipStream_t s) {
+  FlowIO io{};
+  io.word = dr.K_eff; io.k_max = k_max; io.y[0] = y[0]; io.y[1] = y[1];
+  FewRun rr = r;
+  rr.x = dr.y;
+  flow_launch<C, true>(n, rr, io, dr, k_max * n.L * C::NPH + 1, s);
+}
+
 struct FusedKernels {
   void (*few_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr;
   void (*few_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;
   void (*few_film)(const FusedNet&, const int32_t*, int, const int32_t*, int, int, const int32_t*, const int32_t*, int, float*, hipStream_t) = nullptr;
-  int few_slices = 0;
+  int few_slices = 0; size_t flow_row = 0, flow_draft_row = 0;
+  void (*flow_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;   // of a drafter that is no twin
   // variant for batches of at most one tile per CU: one 8-wave workgroup per CU instead of two 4-wave ones
   hipError_t (*verify_few)(const FusedNet&, const FusedIO&, int, int, hipStream_t) = nullptr;
   int rpt_verify = 0;
@@ -406,6 +450,22 @@ struct FusedKernels {
   hipError_t (*draft_big)(const FusedNet&, const DraftIO&, int, hipStream_t) = nullptr;
   int rpt_small = 0, rpt_big = 0;
 };
+
+// The spread kernels of a compiled shape.
+template <class TT, int D, int H, int HEADS, int SX>
+void spread_kernels(FusedKernels& k) {
+  if constexpr (std::is_same<TT, TF32>::value) {
+    typedef FlowCfg<TT, D, H, HEADS, SX> F;
+    k.few_forward = flow_forward<F>; k.few_draft = flow_draft<F>; k.flow_row = 2 * F::SET_B;
+  } else {
+    typedef FewCfg<TT, D, H, HEADS, SX> F;
+    k.few_forward = few_forward<F>; k.few_draft = few_draft<F>; k.few_slices = std::max(F::NCH, F::HEADS);
+    if constexpr (SX > 0 && D * H < FEW_WIDE) {
+      typedef FlowCfg<TT, D, H, HEADS, SX> X;
+      k.flow_draft = flow_draft<X>; k.flow_draft_row = 2 * X::SET_B;
+    }
+  }
+}
 
 // Measured tile choices of the compiled shapes.
 constexpr int NWS128 = 8;        // waves of the one-environment drafter tile, d = 128
@@ -424,8 +484,7 @@ bool find_fused(int dtype, int D, int H, int heads, int cm, int S, int mlp_ratio
   if (dtype == DT_ && D == D_ && H == H_ && heads == HD_ && cm == CM_ && (CM_ == 0 || S == SX_)) {             \
     k.verify = launch_verify<FusedCfg<TT_, D_, NTV, H_, HD_, CM_, CHV, SX_, HPV, NWV, HPXV>>;                  \
     k.rpt_verify = NTV / H_;                                                                                   \
-    typedef FewCfg<TT_, D_, H_, HD_, SX_> F_;                                                                   \
-    k.few_forward = few_forward<F_>; k.few_draft = few_draft<F_>; k.few_slices = std::max(F_::NCH, F_::HEADS);   \
+    spread_kernels<TT_, D_, H_, HD_, SX_>(k);                                                                  \
     k.few_film = launch_few_film<TT_, D_>;                                                                       \
     k.mod = DT_ == 1 ? launch_mod<D_> : nullptr;                                                               \
     k.draft_small = launch_draft<FusedCfg<TT_, D_, NTS, H_, HD_, CM_, CHS, SX_, HPS, NWS>>; k.rpt_small = NTS / H_; \
@@ -623,16 +682,21 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   n.fused_mod = fk.mod;
   n.fused_draft_small = fk.draft_small; n.fused_draft_big = fk.draft_big;
   n.draft_rpt_small = fk.rpt_small; n.draft_rpt_big = fk.rpt_big;
-  n.few_forward = fk.few_forward; n.few_draft = fk.few_draft; n.few_film = fk.few_film; n.few_slices = fk.few_slices;
+  n.few_forward = fk.few_forward; n.few_draft = fk.few_draft; n.few_film = fk.few_film; n.few_slices = fk.few_slices; n.flow_row = fk.flow_row;
   // Few rows: the spread kernels.  The capacity of the context decides, not the call: an environment's result must not
   // depend on the batch it is computed in.
   n.few = dyn || few_pays(rows_max(cf) * cf.H, f32, (size_t)(cf.cond_mode == 1 ? 14 : 12) * d * d * (f32 ? 4 : 2));
-  // The rollout: fp32 layers are bound by one unit's matrix rate (d = 128: 39 us per transition, spread 23), bf16 drafters
-  // of this size are not (d = 192: spread 2 us per transition slower).  Twins are both spread or neither.
+  // The rollout: fp32 layers are bound by one unit's matrix rate (d = 128: 39 us per transition, spread 17), and so are those
+  // with cross-attention by one unit's weight stream; bf16 drafters with a conditioning vector are not (d = 192: spread 2 us per
+  // transition slower).  Twins are both spread or neither.
   const bool twin = twin_nets(cf);
-  const bool pays = dyn || few_rollout_pays(cf.draft_layers, (size_t)cf.draft_d * cf.H >= FEW_WIDE, cf.cond_mode == 1, cf.K_max);
+  const bool pays = dyn || n.flow_row || few_rollout_pays(cf.draft_layers, (size_t)cf.draft_d * cf.H >= FEW_WIDE, cf.cond_mode == 1, cf.K_max);
   if (twin && !pays) n.few = false;
   n.few_roll = n.few && pays && (twin || f32);
+  if (&n == &c->net[1] && !twin && fk.flow_draft && flow_draft_pays(cf.B_max)) {
+    n.few_draft = fk.flow_draft; n.flow_row = fk.flow_draft_row;
+    n.few_roll = true;
+  }
   if (&n == &c->net[1]) n.few = n.few_roll;
   if (!dyn) n.path = f32 ? "f32-mfma-fused" : "bf16-mfma-fused";
   return TSDP_OK;
@@ -693,6 +757,8 @@ FewRun few_run(tsdp_ctx* c, const Net& n, int R_cap, int safe_rows, const int32_
   r.A = c->cfg.A; r.T = c->cfg.T; r.mod = n.fnet.modtab ? n.fnet.modtab : mod;
   for (int i = 0; i < 2; ++i) { r.h[i] = c->few_h[i]; r.part[i] = c->few_part[i]; }
   r.pstride = (size_t)R_cap * c->cfg.H * n.d;
+  r.sync = c->sync + (&n == &c->net[1] ? (size_t)flow_lines(rows_max(c->cfg)) * SYNC_LINE : 0);
+  r.buf = c->flow_buf; r.status = c->status;
   return r;
 }
 
@@ -743,13 +809,13 @@ size_t fused_draft_lds(const Net& n, const tsdp_config& cf, int rpt) {
   return act + scr + 2 * 8 * NT * 4 + 2 * NT * cf.A * 4 + (size_t)rpt * n.L * 4 * D * 4 + 16 * (D + PAD) * ES;  // upper bound
 }
 
+int sync_lines(const tsdp_ctx* c) { return flow_lines(rows_max(c->cfg)) + flow_lines(c->cfg.B_max); }
+
 int ensure_few(tsdp_ctx* c) {
   const tsdp_config& cf = c->cfg;
   int rc;
   const Net &bn = c->net[0], &dn = c->net[1];
-  auto shape = [&](const Net& n, int which) {
-    return FewShape{n.few, n.fused ? rows_max(cf) * cf.H : dyn_tokens(cf, which), (size_t)n.d, (size_t)n.few_slices};
-  };
+  auto shape = [&](const Net& n, int which) { return FewShape{n.few && !n.flow_row, n.fused ? rows_max(cf) * cf.H : dyn_tokens(cf, which), (size_t)n.d, (size_t)n.few_slices}; };
   const FewSize need = few_size(shape(bn, 0), shape(dn, 1));
   if (!few_fits(c->few_have, need)) {                  // (buffers that are replaced live as long as the context: a graph may hold them)
     const FewSize z{std::max(need.h, c->few_have.h), std::max(need.part, c->few_have.part)};
@@ -757,10 +823,21 @@ int ensure_few(tsdp_ctx* c) {
     for (int i = 0; i < 2; ++i) {
       if ((rc = dev_alloc(c, &h[i], z.h))) return rc;
       if ((rc = dev_alloc(c, &part[i], z.part))) return rc;
-      if (!c->few_y[i] && (rc = dev_alloc(c, &c->few_y[i], (size_t)cf.B_max * c->D))) return rc;
     }
     for (int i = 0; i < 2; ++i) { c->few_h[i] = h[i]; c->few_part[i] = part[i]; }
     c->few_have = z;
+  }
+  for (float*& y : c->few_y)
+    if (dn.few_roll && !y && (rc = dev_alloc(c, &y, (size_t)cf.B_max * c->D))) return rc;
+  const size_t flow = std::max(bn.few ? rows_max(cf) * bn.flow_row : 0, dn.few ? cf.B_max * dn.flow_row : 0);
+  if (flow > c->flow_have) {
+    unsigned char* buf;
+    if ((rc = dev_alloc(c, &buf, flow))) return rc;
+    HIPCHK(c, hipMemset(buf, 0xFF, flow));               // FLOW_EMPTY
+    HIPCHK(c, hipStreamSynchronize(nullptr));
+    if (!c->sync && (rc = dev_alloc(c, &c->sync, (size_t)sync_lines(c) * SYNC_LINE))) return rc;
+    c->flow_buf = buf;
+    c->flow_have = flow;
   }
   if (dn.few_roll && cf.cond_mode == 0 && !c->few_mod &&
       (rc = dev_alloc(c, &c->few_mod, (size_t)cf.B_max * cf.K_max * dn.L * 4 * dn.d)))
@@ -971,6 +1048,7 @@ int tsdp_load_weights(tsdp_ctx* c, int which, const float* h_blob, size_t nbytes
   HIPCHK(c, hipMemcpy(n.temb, temb.data(), temb.size() * sizeof(float), hipMemcpyHostToDevice));
   HIPCHK(c, hipMemcpy(n.modw, modw.data(), modw.size() * sizeof(float), hipMemcpyHostToDevice));
   HIPCHK(c, hipMemcpy(n.modb, modb.data(), modb.size() * sizeof(float), hipMemcpyHostToDevice));
+  if (c->flow_buf) HIPCHK(c, hipMemset(c->flow_buf, 0xFF, c->flow_have));   // FLOW_EMPTY, as every launch leaves it
   n.loaded = true;
   c->cond_set = false;
   n.fused = n.few = n.few_roll = false;
@@ -1073,12 +1151,12 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
   if (B <= PLAN_ROWS_B) {
     hipLaunchKernelGGL(k_plan_rows, dim3(B), dim3(128), 0, s, d_x, d_t0, d_K, d_sigma_scale, B, cf.K_max, cf.T, D, cf.bonus_row,
                        gated ? 1 : 0, c->K_eff, d_row_ptr, c->status, c->n_draft, live, rounds_run, d_row_t, d_row_env, d_y_last, d_states,
-                       d_eps_p, d_xi);
+                       d_eps_p, d_xi, c->sync, sync_lines(c));
   } else {
     hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, d_t0, d_K, d_sigma_scale, B, cf.K_max, cf.T, cf.bonus_row, c->K_eff,
                        d_row_ptr, c->status, c->n_draft, live, rounds_run);
     hipLaunchKernelGGL(k_rows, dim3(B), dim3(128), 0, s, d_x, d_t0, (const int32_t*)d_row_ptr, cf.T, D, d_row_t,
-                       d_row_env, d_y_last, d_states, d_eps_p, d_xi, gated ? (const int32_t*)c->n_draft : nullptr);
+                       d_row_env, d_y_last, d_states, d_eps_p, d_xi, c->sync, sync_lines(c), gated ? (const int32_t*)c->n_draft : nullptr);
   }
   auto bonus_rows = [&]() {
     if (cf.bonus_row)
@@ -1159,7 +1237,7 @@ static int verify_impl(tsdp_ctx* c, int B, int R_cap, const int32_t* d_row_ptr, 
     // a caller's row table: timesteps and environment indices are clamped into range (the kernels index tables
     // with them) and the status word reports it
     hipLaunchKernelGGL(k_check_rows, grid1(R_cap, 256), dim3(256), 0, s, d_row_ptr + B, R_cap, d_row_t, d_row_env, c->cfg.T,
-                       c->cond_B, c->row_t_chk, c->row_env_chk, c->status);
+                       c->cond_B, c->row_t_chk, c->row_env_chk, c->status, c->sync, flow_lines(R_cap));
     d_row_t = c->row_t_chk;
     d_row_env = c->row_env_chk;
   }
@@ -1369,6 +1447,12 @@ int tsdp_prepare(tsdp_ctx* c) {
   FusedIO io{};
   DraftIO dio{};
   Net& bn = c->net[0];
+  for (Net* n : {&c->net[0], &c->net[1]})
+    if (n->few && n->flow_row) {
+      const FewRun none = few_run(c, *n, 0, 0, nullptr, nullptr, nullptr);
+      if (n == &bn) n->few_forward(n->fnet, none, nullptr);
+      else n->few_draft(n->fnet, none, dio, c->cfg.K_max, c->few_y, nullptr);
+    }
   if (bn.fused) {
     if (bn.fused_verify) HIPCHK(c, bn.fused_verify(bn.fnet, io, c->cfg.A, 0, nullptr));
     if (bn.fused_verify_few) HIPCHK(c, bn.fused_verify_few(bn.fnet, io, c->cfg.A, 0, nullptr));

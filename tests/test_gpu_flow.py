@@ -1,0 +1,57 @@
+"""Forward passes and rollouts in one launch (csrc/flow_rows.hpp): row counts where the tasks are dealt differently, and the
+buffers that every launch has to leave empty."""
+import numpy as np
+import pytest
+
+import tsdp_inputs as ti
+from tests.helpers import gpu_side, to_dev
+from tests.test_gpu_parity import _stage_parity
+
+pytestmark = pytest.mark.gpu
+STATE = ti.replace(ti.C2, base=ti.NetShape(2, 256, 4))
+
+
+@pytest.mark.parametrize("wl, B, K_max", [
+    (STATE, 7, 1), (STATE, 8, 1),                     # one row per XCD at most: a workgroup per unit
+    (STATE, 33, 1), (STATE, 43, 3),                   # five tiles of rows for four groups; groups of four and five
+    (ti.replace(ti.C2, base=ti.NetShape(1, 256, 4), draft=ti.NetShape(1, 128, 4)), 2, 5),   # one layer: both sets of buffers in turn
+    (ti.replace(ti.C2, base=ti.NetShape(3, 128, 4), draft=ti.NetShape(3, 256, 4)), 2, 4),   # an odd number of layers
+    (ti.replace(ti.C4, base=ti.NetShape(1, 512, 8)), 24, 2), (ti.replace(ti.C4, base=ti.NetShape(1, 512, 8)), 25, 2),   # rollout with
+])                                                    # cross-attention: the largest in one launch, the smallest beyond it
+def test_rows_are_dealt_to_the_tasks(wl, B, K_max):
+    wl = ti.small_variant(wl, B=B, K_max=K_max)
+    rng = np.random.default_rng(B)
+    t0 = rng.integers(0, wl.T, B); K = rng.integers(1, K_max + 1, B); s = rng.uniform(1.0, 1.5, B)
+    t0[0] = wl.T - 1; K[0] = K_max; t0[-1] = 1
+    _stage_parity(wl, B, t0, K, s, norm=B % 2)
+
+
+@pytest.mark.parametrize("payload", [0xFFFFFFFF, 0x7FC00000])
+def test_not_a_number_passes_through_and_leaves_nothing_behind(payload):
+    # the pattern of an empty buffer, as a latent: its environment's results are not numbers, the others' and those of the
+    # next calls have the same bits as without it
+    import torch
+    wl = ti.small_variant(STATE, B=3, K_max=4)
+    nets = [ti.make_weights(wl, which, b_std=0.02) for which in ("base", "draft")]
+    ctx = gpu_side(wl, *nets, ti.make_cond(wl, 3), B_max=3)
+    x = to_dev(ti.make_latents(wl, 3)); bad = x.clone()
+    bad[1].view(torch.int32).fill_(payload - (1 << 32) if payload >= 1 << 31 else payload)
+    t0 = to_dev(np.array([99, 50, 3], np.int32)); K = to_dev(np.array([4, 3, 4], np.int32)); s = to_dev(np.ones(3, np.float32))
+
+    def stages(latents):
+        rows = ctx.alloc_rows(3)
+        ctx.tsdp_draft(latents, t0, K, s, None, rows)
+        ctx.tsdp_verify(3, rows)
+        return {k: rows[k][:10].clone() for k in ("states", "eps_p", "eps_q")}
+    ref = stages(x)
+    for latents in (bad, x, bad, bad, x):
+        got = stages(latents)
+        keep = [0, 1, 2, 3, 7, 8, 9]                  # rows of environments 0 and 2
+        for name in got:
+            assert torch.equal(got[name][keep], ref[name][keep]), name
+            if latents is bad:
+                assert bool(torch.isnan(got[name][4:7]).all()), name
+            else:
+                assert torch.equal(got[name], ref[name]), name
+    assert ctx.tsdp_status() == 0
+    ctx.close()
