@@ -186,12 +186,6 @@ __device__ __forceinline__ void flow_signal(const FlowIO& io, int row, int kind)
 // of every k-step, which is the layout of an MFMA operand.
 template <class C> using FlowV = f32x4[C::KW][C::NB][C::VQ];
 
-#ifndef SAMPLE_R
-#define SAMPLE_R 0
-#endif
-#ifndef SAMPLE_B
-#define SAMPLE_B 0
-#endif
 template <class C>
 struct FlowTask {
   typedef typename C::TT TT;
@@ -227,7 +221,6 @@ struct FlowTask {
       for (int k = 0; k < NK; ++k) w[m][k] = reinterpret_cast<const frag*>(p)[((size_t)row[m] * ks_total + ks0 + k) * 64 + lane];
   }
   __device__ void residual(__amdgpu_buffer_rsrc_t r, int at, FlowV<C>& v) const {
-    if (SAMPLE_R) flow_sample<CF, H * 64>(r, at + wave * CF * H * 64, lane);
     flow_poll(io, lane, [&]() {
 #pragma unroll
       for (int ks = 0; ks < KW; ++ks)
@@ -648,7 +641,6 @@ __global__ __launch_bounds__(C::TH) void k_flow(FusedNet net, FlowIO io, std::co
           frag kk[KW][NB];
           vec4 vv[CF][NB];
           wait(row);
-          if (SAMPLE_B) flow_sample<CF * NB, 256 * ES>(r, C::O_Q + 2 * C::XB + wave * CF * NB * 256 * ES, lane);
           flow_poll(io, lane, [&]() {
 #pragma unroll
             for (int ks = 0; ks < KW; ++ks)
