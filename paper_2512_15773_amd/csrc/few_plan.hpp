@@ -39,6 +39,12 @@ inline bool few_rollout_pays(int layers, bool wide, bool cross, int K_max) {
 // environments 317, 346, 350, 373, 518, the persistent kernel (one workgroup an environment) 425 to 463.
 inline bool flow_draft_pays(int environments) { return environments <= 24; }
 
+// Forward pass in one launch (k_flow) of a bf16 network: its dependent steps are shorter, but a row costs it more of the chip
+// (registers for one workgroup per unit) than the spread launches.  Rounds, us, spread / one launch at 8, 16, 32, 64, 128 rows
+// of 16 tokens: d = 256 250 / 214, 253 / 228, 256 / 273, 264 / 345, 311 / 490; d = 384 at 4, 16, 32 rows 317 / 243, 634 / 579,
+// 642 / 675 (328 / 363 with four drafts).  Two workgroups per unit at d = 256 meet at 32 rows (256 / 251) and lose 5 % at 16.
+inline bool flow_forward_pays(size_t tokens) { return tokens <= 256; }
+
 // Networks with run-time sizes: `tokens` a launch covers at most (the ragged batch's, the rollout's one row per environment).
 // A spread launch streams its weights once per row and adds max(heads, slices) partial sums of the whole row in every
 // workgroup; one launch per operator does neither but has six times the launches.  Rows at which both take the same time

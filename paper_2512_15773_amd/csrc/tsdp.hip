@@ -441,6 +441,7 @@ struct FusedKernels {
   void (*few_film)(const FusedNet&, const int32_t*, int, const int32_t*, int, int, const int32_t*, const int32_t*, int, float*, hipStream_t) = nullptr;
   int few_slices = 0; size_t flow_row = 0, flow_draft_row = 0;
   void (*flow_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;   // of a drafter that is no twin
+  void (*flow_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr; size_t flow_forward_row = 0;        // of a bf16 base that is no twin
   // variant for batches of at most one tile per CU: one 8-wave workgroup per CU instead of two 4-wave ones
   hipError_t (*verify_few)(const FusedNet&, const FusedIO&, int, int, hipStream_t) = nullptr;
   int rpt_verify = 0;
@@ -460,6 +461,10 @@ void spread_kernels(FusedKernels& k) {
   } else {
     typedef FewCfg<TT, D, H, HEADS, SX> F;
     k.few_forward = few_forward<F>; k.few_draft = few_draft<F>; k.few_slices = std::max(F::NCH, F::HEADS);
+    if constexpr (SX == 0 && D >= 256 && D * H < FEW_WIDE) {
+      typedef FlowCfg<TT, D, H, HEADS, SX> X;
+      k.flow_forward = flow_forward<X>; k.flow_forward_row = 2 * X::SET_B;
+    }
     if constexpr (SX > 0 && D * H < FEW_WIDE) {
       typedef FlowCfg<TT, D, H, HEADS, SX> X;
       k.flow_draft = flow_draft<X>; k.flow_draft_row = 2 * X::SET_B;
@@ -693,6 +698,9 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   const bool pays = dyn || n.flow_row || few_rollout_pays(cf.draft_layers, (size_t)cf.draft_d * cf.H >= FEW_WIDE, cf.cond_mode == 1, cf.K_max);
   if (twin && !pays) n.few = false;
   n.few_roll = n.few && pays && (twin || f32);
+  if (&n == &c->net[0] && n.few && !twin && fk.flow_forward && flow_forward_pays(rows_max(cf) * cf.H)) {
+    n.few_forward = fk.flow_forward; n.flow_row = fk.flow_forward_row;
+  }
   if (&n == &c->net[1] && !twin && fk.flow_draft && flow_draft_pays(cf.B_max)) {
     n.few_draft = fk.flow_draft; n.flow_row = fk.flow_draft_row;
     n.few_roll = true;

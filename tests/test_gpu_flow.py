@@ -17,7 +17,11 @@ STATE = ti.replace(ti.C2, base=ti.NetShape(2, 256, 4))
     (ti.replace(ti.C2, base=ti.NetShape(1, 256, 4), draft=ti.NetShape(1, 128, 4)), 2, 5),   # one layer: both sets of buffers in turn
     (ti.replace(ti.C2, base=ti.NetShape(3, 128, 4), draft=ti.NetShape(3, 256, 4)), 2, 4),   # an odd number of layers
     (ti.replace(ti.C4, base=ti.NetShape(1, 512, 8)), 24, 2), (ti.replace(ti.C4, base=ti.NetShape(1, 512, 8)), 25, 2),   # rollout with
-])                                                    # cross-attention: the largest in one launch, the smallest beyond it
+    # cross-attention: the largest in one launch, the smallest beyond it; bf16 bases up to 16 rows, and the first beyond
+    (ti.replace(ti.C3, base=ti.NetShape(2, 256, 4)), 1, 9), (ti.replace(ti.C3, base=ti.NetShape(1, 256, 4)), 8, 2),
+    (ti.replace(ti.C3, base=ti.NetShape(2, 256, 4)), 17, 1), (ti.replace(ti.C5, base=ti.NetShape(1, 384, 6)), 5, 3),
+    (ti.replace(ti.C5, base=ti.NetShape(3, 384, 6)), 16, 1),
+])
 def test_rows_are_dealt_to_the_tasks(wl, B, K_max):
     wl = ti.small_variant(wl, B=B, K_max=K_max)
     rng = np.random.default_rng(B)
