@@ -24,12 +24,13 @@ inline bool few_pays(size_t tokens, bool f32, size_t layer_bytes) {
 }
 
 // Launches of a spread rollout (two bf16 networks of one shape): every transition up to K_max has its own, whether drafted or
-// not (the draft counts are on the device).  With the fp32 d = 128 network, before it was one launch (k_flow), a drafted transition took 23 us instead of the persistent kernel's 39, an
-// undrafted one 6 to 15 instead of none: with half of K_max or more the spread rollout is the faster one, and what fewer
-// drafts lose grows with K_max.  Rounds of one C2 environment, us, persistent / spread rollout: K = 1, 4, 8 of 8 226 / 277,
-// 344 / 331, 495 / 396; K = 1, 4, 16 of 16 226 / 363, 344 / 413, 788 / 595; K = 4, 64 of 64 344 / 1085, 2673 / 1888.  So up
-// to 40 launches (two layers: K_max = 9) the rollout is spread -- the loss stays below a quarter of a round, and below what
-// the spread verify saves of it (one workgroup per row: 545, 663, 812 with K = 1, 4, 8) -- and beyond it is one launch.
+// not (the draft counts are on the device).  With the fp32 d = 128 network, before it was one launch (k_flow), a drafted
+// transition took 23 us instead of the persistent kernel's 39, an undrafted one 6 to 15 instead of none: with half of K_max or
+// more the spread rollout is the faster one, and what fewer drafts lose grows with K_max.  Rounds of one C2 environment, us,
+// persistent / spread rollout: K = 1, 4, 8 of 8 226 / 277, 344 / 331, 495 / 396; K = 1, 4, 16 of 16 226 / 363, 344 / 413,
+// 788 / 595; K = 4, 64 of 64 344 / 1085, 2673 / 1888.  So up to 40 launches (two layers: K_max = 9) the rollout is spread --
+// the loss stays below a quarter of a round, and below what the spread verify saves of it (one workgroup per row: 545, 663,
+// 812 with K = 1, 4, 8) -- and beyond it is one launch.
 constexpr int FEW_ROLL_LAUNCHES = 40;
 inline bool few_rollout_pays(int layers, bool wide, bool cross, int K_max) {
   return layers * (wide ? 2 : 1) * (cross ? 3 : 2) * K_max + 1 <= FEW_ROLL_LAUNCHES;
