@@ -23,22 +23,32 @@ inline bool few_pays(size_t tokens, bool f32, size_t layer_bytes) {
   return tokens <= (f32 ? 2048 : 2176) && layer_bytes >= 700000;
 }
 
-// Launches of a spread rollout (two bf16 networks of one shape): every transition up to K_max has its own, whether drafted or
-// not (the draft counts are on the device).  With the fp32 d = 128 network, before it was one launch (k_flow), a drafted
-// transition took 23 us instead of the persistent kernel's 39, an undrafted one 6 to 15 instead of none: with half of K_max or
-// more the spread rollout is the faster one, and what fewer drafts lose grows with K_max.  Rounds of one C2 environment, us,
-// persistent / spread rollout: K = 1, 4, 8 of 8 226 / 277, 344 / 331, 495 / 396; K = 1, 4, 16 of 16 226 / 363, 344 / 413,
-// 788 / 595; K = 4, 64 of 64 344 / 1085, 2673 / 1888.  So up to 40 launches (two layers: K_max = 9) the rollout is spread --
-// the loss stays below a quarter of a round, and below what the spread verify saves of it (one workgroup per row: 545, 663,
-// 812 with K = 1, 4, 8) -- and beyond it is one launch.
+// Launches of a spread rollout: every transition up to K_max has its own, whether drafted or not (the draft counts are on
+// the device).  A drafted transition of the fp32 d = 128 network takes 23 us instead of the persistent kernel's 39, an
+// undrafted one 6 to 15 instead of none: with half of K_max or more the spread rollout is the faster one, and what fewer
+// drafts lose grows with K_max.  Rounds of one C2 environment, us, persistent / spread rollout: K = 1, 4, 8 of 8 226 / 277,
+// 344 / 331, 495 / 396; K = 1, 4, 16 of 16 226 / 363, 344 / 413, 788 / 595; K = 4, 64 of 64 344 / 1085, 2673 / 1888.  So up
+// to 40 launches (two layers: K_max = 9) the rollout is spread -- the loss stays below a quarter of a round, and below what
+// the spread verify saves of it (one workgroup per row: 545, 663, 812 with K = 1, 4, 8) -- and beyond it is one launch.
 constexpr int FEW_ROLL_LAUNCHES = 40;
 inline bool few_rollout_pays(int layers, bool wide, bool cross, int K_max) {
   return layers * (wide ? 2 : 1) * (cross ? 3 : 2) * K_max + 1 <= FEW_ROLL_LAUNCHES;
 }
 
-// Rollout in one launch (k_flow) of a drafter with cross-attention, d = 256, 32 tokens: us for eight transitions of 1, 4, 8, 16, 32
-// environments 317, 346, 350, 373, 518, the persistent kernel (one workgroup an environment) 425 to 463.
-inline bool flow_draft_pays(int environments) { return environments <= 24; }
+// Rollout in one launch (k_flow) instead of in launches (where that pays, `launches`) or in the persistent kernel.
+// fp32: the XCDs work side by side, and from the third environment of an XCD on a transition grows by about a quarter with
+// every other one, where the launches fill the chip at the same time.  tsdp_draft, us, launches / one launch, four transitions of
+// 8, 12, 16, 18, 24, 32 environments, two layers: d = 128 105 / 87, 107 / 95, 107 / 96, 108 / 113, 108 / 113, 109 / 137 (one
+// transition of 64, 128: 40 / 69, 57 / 115); d = 256 197 / 124, 202 / 182, 202 / 183, 231 / 257, 232 / 256, 239 / 336.  One layer of
+// d = 128 is too short for the exchanges unless there are several transitions: 16 environments, K_max = 1, 2, 4, 7 23 / 27, 37 /
+// 39, 64 / 63, 105 / 98.  Against the persistent kernel (four layers, K_max = 7, 8 / 18 environments) d = 128 515 / 249, 515 / 335,
+// d = 256 1992 / 357, 1972 / 797; it does not grow with the environments, and at 32 one launch takes 0.83 (0.55) of its time.
+// bf16 with cross-attention, d = 256, 32 tokens: eight transitions of 1, 4, 8, 16, 32 environments 317, 346, 350, 373, 518, the
+// persistent kernel (one workgroup an environment) 425 to 463.
+inline bool flow_draft_pays(int environments, bool f32, size_t d, int layers, int K_max, bool launches) {
+  if (!f32) return environments <= 24;
+  return launches ? environments <= 16 && (layers * d >= 256 || K_max >= 4) : environments <= 32;
+}
 
 // Forward pass in one launch (k_flow) of a bf16 network: its dependent steps are shorter, but a row costs it more of the chip
 // (registers for one workgroup per unit) than the spread launches.  Rounds, us, spread / one launch at 8, 16, 32, 64, 128 rows

@@ -29,11 +29,13 @@ namespace tsdp {
 
 // Compile-time sizes of a network; NCH slices of the MLP's hidden layer.  Four wavefronts, one per SIMD, whose up to 512
 // registers hold weights in flight; eight for wide rows.
-// Slices: the sums that the next launch reads bound them (4 instead of 8: 128 rows of d = 256 172 instead of 232 us).
+// Slices: one unit's fp32 matrix rate bounds a slice of d = 256 (16 slices of 64 instead of 8 of 128: round of one C2
+// environment 402 -> 389 us), in bf16 the sums that the next launch reads do (4 instead of 8: 128 rows 172 instead of 232 us).
 constexpr int FEW_WIDE = 16384;                   // numbers of a wide row's residual
-template <int D, int H> constexpr int few_slices() { return D * H >= FEW_WIDE ? 8 : 4; }
+template <class TT, int D, int H>
+constexpr int few_slices() { return D * H >= FEW_WIDE ? 8 : sizeof(typename TT::elem) == 2 ? 4 : D >= 256 ? 16 : 8; }
 
-template <class TT_, int D_, int H_, int HEADS_, int SX_ = 0, int NCH_ = few_slices<D_, H_>()>
+template <class TT_, int D_, int H_, int HEADS_, int SX_ = 0, int NCH_ = few_slices<TT_, D_, H_>()>
 struct FewCfg {
   typedef TT_ TT;
   static constexpr bool DYN = false;

@@ -67,8 +67,8 @@ struct Net {
   void (*few_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr;
   void (*few_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;
   void (*few_film)(const FusedNet&, const int32_t*, int, const int32_t*, int, int, const int32_t*, const int32_t*, int, float*, hipStream_t) = nullptr;
-  int few_slices = 0;           // partial sums per row (run-time sizes)
-  size_t flow_row = 0;          // bytes of a row's buffers (k_flow)
+  int few_slices = 0;           // partial sums per row
+  size_t flow_row = 0;          // bytes of a row's buffers (k_flow), 0: two launches per layer (k_few_*)
   float* tok_wt = nullptr;      // [A, d] token embedding, transposed
   uint16_t* kc_pk = nullptr;    // fragment-ordered bf16 keys / transposed values of every (env, layer, head)
   uint16_t* vct_pk = nullptr;
@@ -439,9 +439,11 @@ struct FusedKernels {
   void (*few_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr;
   void (*few_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;
   void (*few_film)(const FusedNet&, const int32_t*, int, const int32_t*, int, int, const int32_t*, const int32_t*, int, float*, hipStream_t) = nullptr;
-  int few_slices = 0; size_t flow_row = 0, flow_draft_row = 0;
-  void (*flow_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;   // of a drafter that is no twin
-  void (*flow_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr; size_t flow_forward_row = 0;        // of a bf16 base that is no twin
+  int few_slices = 0;
+  // the same in one launch, where a shape has it; bytes of a row's buffers
+  void (*flow_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr;
+  void (*flow_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;
+  size_t flow_row = 0;
   // variant for batches of at most one tile per CU: one 8-wave workgroup per CU instead of two 4-wave ones
   hipError_t (*verify_few)(const FusedNet&, const FusedIO&, int, int, hipStream_t) = nullptr;
   int rpt_verify = 0;
@@ -455,20 +457,15 @@ struct FusedKernels {
 // The spread kernels of a compiled shape.
 template <class TT, int D, int H, int HEADS, int SX>
 void spread_kernels(FusedKernels& k) {
-  if constexpr (std::is_same<TT, TF32>::value) {
-    typedef FlowCfg<TT, D, H, HEADS, SX> F;
-    k.few_forward = flow_forward<F>; k.few_draft = flow_draft<F>; k.flow_row = 2 * F::SET_B;
-  } else {
-    typedef FewCfg<TT, D, H, HEADS, SX> F;
-    k.few_forward = few_forward<F>; k.few_draft = few_draft<F>; k.few_slices = std::max(F::NCH, F::HEADS);
-    if constexpr (SX == 0 && D >= 256 && D * H < FEW_WIDE) {
-      typedef FlowCfg<TT, D, H, HEADS, SX> X;
-      k.flow_forward = flow_forward<X>; k.flow_forward_row = 2 * X::SET_B;
-    }
-    if constexpr (SX > 0 && D * H < FEW_WIDE) {
-      typedef FlowCfg<TT, D, H, HEADS, SX> X;
-      k.flow_draft = flow_draft<X>; k.flow_draft_row = 2 * X::SET_B;
-    }
+  typedef FewCfg<TT, D, H, HEADS, SX> F;
+  k.few_forward = few_forward<F>; k.few_draft = few_draft<F>; k.few_slices = std::max(F::NCH, F::HEADS);
+  constexpr bool F32 = std::is_same<TT, TF32>::value, NARROW = D * H < FEW_WIDE;
+  constexpr bool FORWARD = F32 || (SX == 0 && D >= 256 && NARROW), DRAFT = F32 || (SX > 0 && NARROW);
+  if constexpr (FORWARD || DRAFT) {
+    typedef FlowCfg<TT, D, H, HEADS, SX> X;
+    if constexpr (FORWARD) k.flow_forward = flow_forward<X>;
+    if constexpr (DRAFT) k.flow_draft = flow_draft<X>;
+    k.flow_row = 2 * X::SET_B;
   }
 }
 
@@ -687,25 +684,26 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   n.fused_mod = fk.mod;
   n.fused_draft_small = fk.draft_small; n.fused_draft_big = fk.draft_big;
   n.draft_rpt_small = fk.rpt_small; n.draft_rpt_big = fk.rpt_big;
-  n.few_forward = fk.few_forward; n.few_draft = fk.few_draft; n.few_film = fk.few_film; n.few_slices = fk.few_slices; n.flow_row = fk.flow_row;
+  n.few_forward = fk.few_forward; n.few_draft = fk.few_draft; n.few_film = fk.few_film; n.few_slices = fk.few_slices; n.flow_row = 0;
   // Few rows: the spread kernels.  The capacity of the context decides, not the call: an environment's result must not
   // depend on the batch it is computed in.
   n.few = dyn || few_pays(rows_max(cf) * cf.H, f32, (size_t)(cf.cond_mode == 1 ? 14 : 12) * d * d * (f32 ? 4 : 2));
-  // The rollout: fp32 layers are bound by one unit's matrix rate (d = 128: 39 us per transition, spread 17), and so are those
-  // with cross-attention by one unit's weight stream; bf16 drafters with a conditioning vector are not (d = 192: spread 2 us per
-  // transition slower).  Twins are both spread or neither.
-  const bool twin = twin_nets(cf);
-  const bool pays = dyn || n.flow_row || few_rollout_pays(cf.draft_layers, (size_t)cf.draft_d * cf.H >= FEW_WIDE, cf.cond_mode == 1, cf.K_max);
-  if (twin && !pays) n.few = false;
-  n.few_roll = n.few && pays && (twin || f32);
-  if (&n == &c->net[0] && n.few && !twin && fk.flow_forward && flow_forward_pays(rows_max(cf) * cf.H)) {
-    n.few_forward = fk.flow_forward; n.flow_row = fk.flow_forward_row;
+  // The rollout: fp32 layers are bound by one unit's matrix rate (d = 128: 37 us per transition, in launches 23, in one launch
+  // 17), and so are those with cross-attention by one unit's weight stream; bf16 drafters with a conditioning vector are not
+  // (d = 192: spread 2 us per transition slower).  Twins are both in one launch, both in two launches per layer or neither.
+  const bool base = &n == &c->net[0], twin = twin_nets(cf);
+  const bool launches = dyn || few_rollout_pays(cf.draft_layers, (size_t)cf.draft_d * cf.H >= FEW_WIDE, cf.cond_mode == 1, cf.K_max);
+  const bool one_forward = n.few && fk.flow_forward;
+  const bool one_draft = (n.few || !f32) && fk.flow_draft && flow_draft_pays(cf.B_max, f32, d, L, cf.K_max, launches);
+  const bool one = twin ? one_forward && one_draft : base ? one_forward : one_draft;
+  if (one) {
+    if (fk.flow_forward) n.few_forward = fk.flow_forward;
+    if (fk.flow_draft) n.few_draft = fk.flow_draft;
+    n.flow_row = fk.flow_row;
   }
-  if (&n == &c->net[1] && !twin && fk.flow_draft && flow_draft_pays(cf.B_max)) {
-    n.few_draft = fk.flow_draft; n.flow_row = fk.flow_draft_row;
-    n.few_roll = true;
-  }
-  if (&n == &c->net[1]) n.few = n.few_roll;
+  if (twin && !launches && !one) n.few = false;
+  n.few_roll = !base && (one || (n.few && launches && (twin || f32)));
+  if (!base) n.few = n.few_roll;
   if (!dyn) n.path = f32 ? "f32-mfma-fused" : "bf16-mfma-fused";
   return TSDP_OK;
 }

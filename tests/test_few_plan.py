@@ -13,6 +13,7 @@ extern "C" {
 int safe_rows(int own, int B, int R_cap) { return few_safe_rows(own != 0, B, R_cap); }
 int rollout_pays(int layers, int wide, int cross, int K_max) { return few_rollout_pays(layers, wide != 0, cross != 0, K_max); }
 int pays(long tokens, int f32, long layer_bytes) { return few_pays(tokens, f32 != 0, layer_bytes); }
+int draft_pays(int environments, int f32, long d, int layers, int K_max, int launches) { return flow_draft_pays(environments, f32 != 0, d, layers, K_max, launches != 0); }
 int dyn_pays(long tokens, long heads, long layer_bytes) { return few_dyn_pays(tokens, heads, layer_bytes); }
 // the context's buffers after a sequence of loads: flags[2 * i] / [2 * i + 1] = base / drafter takes the spread path then
 int buffers_hold(long tokens, long d0, long s0, long d1, long s1, const int* flags, int loads) {
@@ -88,3 +89,17 @@ def test_compiled_kernels_are_spread_up_to_2048_and_2176_tokens(plan):
     assert plan.pays(L(2048), 1, big) and not plan.pays(L(2064), 1, big)
     assert plan.pays(L(2176), 0, big) and not plan.pays(L(2192), 0, big)
     assert not plan.pays(L(16), 1, L(12 * 64 * 64 * 4))
+
+
+def test_rollouts_in_one_launch_only_where_that_is_faster(plan):
+    # (d, layers, K_max, environments): tsdp_draft measured on every side of the line, in fp32 against the launches (all of K_max
+    # up to 40 launches) and against the persistent kernel beyond, in bf16 (cross-attention) against the persistent kernel
+    L = C.c_long
+    pays = lambda f32, d, layers, K_max, B: bool(plan.draft_pays(B, f32, L(d), layers, K_max, plan.rollout_pays(layers, 0, 1 - f32, K_max)))
+    for d, layers, K_max, B in ((128, 1, 7, 16), (128, 1, 4, 12), (128, 2, 1, 8), (128, 2, 4, 16), (128, 4, 2, 16), (256, 1, 1, 8), (256, 2, 7, 16), (256, 4, 1, 16),
+                                (128, 2, 64, 2), (128, 2, 16, 8), (128, 4, 7, 18), (256, 4, 7, 18)):
+        assert pays(1, d, layers, K_max, B), (d, layers, K_max, B)
+    for d, layers, K_max, B in ((128, 1, 1, 8), (128, 1, 2, 16), (128, 1, 4, 18), (128, 2, 1, 24), (128, 2, 4, 18), (128, 2, 2, 64), (128, 2, 1, 128), (128, 4, 4, 32),
+                                (256, 1, 1, 18), (256, 2, 4, 24), (256, 4, 4, 32), (256, 4, 2, 64)):
+        assert not pays(1, d, layers, K_max, B), (d, layers, K_max, B)
+    assert pays(0, 256, 2, 8, 24) and not pays(0, 256, 2, 8, 25)
