@@ -29,10 +29,12 @@
  *    environment at t0 = 0 owns one row (the deterministic last base step); a finished one owns none.
  *  - An environment's results do not depend on the batch it is computed in, bit for bit, within one context and between
  *    contexts whose capacity is on the same side of the line up to which a forward pass is spread over the chip
- *    (compiled shapes: B_max * (K_max + bonus_row) * H of at most 2048 tokens in fp32, 2176 in bf16, where there
- *    is a second line at 256 for networks with a conditioning vector; fp32 rollouts B_max of at most 16 (32 where they
- *    would be more than 40 launches), with cross-attention 24; two bf16 networks of one shape K_max of at most 9 with
- *    two layers).  Across such a line they differ by rounding, and an accept decision that nearly ties can differ.
+ *    (compiled shapes: B_max * (K_max + bonus_row) * H of at most 2048 tokens in fp32, 2176 in bf16) and, within it, of
+ *    the line up to which it is one launch (forward passes with a conditioning vector: 256 tokens in bf16; fp32
+ *    d = 256 896 with four layers or more, 640 with fewer, d = 128 256 and 128; rollouts: fp32 B_max of at most 16, or 32
+ *    where they would be more than 40 launches, with cross-attention 24; two bf16 networks of one shape K_max of at
+ *    most 9 with two layers).  Across such a line they differ by rounding, and an accept decision that nearly ties can
+ *    differ.
  *  - H*A must be a multiple of 4 and at most 512.  The context owns weights, tables and workspace; calls on one
  *    context must not overlap in time (they share the workspace).
  */

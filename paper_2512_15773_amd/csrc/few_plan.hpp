@@ -16,8 +16,8 @@ inline int few_safe_rows(bool ahead, int B, int R_cap) { return ahead ? std::min
 
 // Networks with compiled kernels.  One workgroup per tile takes the same time from 1 to 256 tiles, the spread launches grow
 // with the rows; they meet at about 2100 tokens.  Rounds, us, tile / spread at 64, 128, 144 rows of 16 tokens: bf16 d = 256
-// 498 / 409, 498 / 443, 497 / 511; bf16 d = 384 880 / 729, 881 / 869, -; fp32 d = 256 (one launch, k_flow) 799 / 461, 800 / 727;
-// at 64, 128 rows of 32 tokens, d = 512: 1577 / 1252, 1591 / 1856.  A layer of less than 700 KB passes through one
+// 498 / 409, 498 / 443, 497 / 511; bf16 d = 384 880 / 729, 881 / 869, -; fp32 d = 256 799 / 504, 800 / 724, and at 136 rows
+// 797 / 835; at 64, 128 rows of 32 tokens, d = 512: 1577 / 1252, 1591 / 1856.  A layer of less than 700 KB passes through one
 // compute unit faster than through two launches (fp32 d = 64, 393 KB in all: 21 us against 25).
 inline bool few_pays(size_t tokens, bool f32, size_t layer_bytes) {
   return tokens <= (f32 ? 2048 : 2176) && layer_bytes >= 700000;
@@ -50,11 +50,20 @@ inline bool flow_draft_pays(int environments, bool f32, size_t d, int layers, in
   return launches ? environments <= 16 && (layers * d >= 256 || K_max >= 4) : environments <= 32;
 }
 
-// Forward pass in one launch (k_flow) of a bf16 network: its dependent steps are shorter, but a row costs it more of the chip
-// (registers for one workgroup per unit) than the spread launches.  Rounds, us, spread / one launch at 8, 16, 32, 64, 128 rows
-// of 16 tokens: d = 256 250 / 214, 253 / 228, 256 / 273, 264 / 345, 311 / 490; d = 384 at 4, 16, 32 rows 317 / 243, 634 / 579,
-// 642 / 675 (328 / 363 with four drafts).  Two workgroups per unit at d = 256 meet at 32 rows (256 / 251) and lose 5 % at 16.
-inline bool flow_forward_pays(size_t tokens) { return tokens <= 256; }
+// Forward pass in one launch (k_flow): its dependent steps are shorter than two launches per layer, but a row costs it more of
+// the chip (registers for one workgroup per unit, tasks that take their rows in turn).
+// fp32, tsdp_verify, us, launches / one launch: d = 256, one layer, 32, 40, 48, 64 rows of 16 tokens 41 / 39, 45 / 43, 45 / 49, 49 / 56;
+// two 66 / 64, 73 / 69, 76 / 77, 83 / 93; four 117 / 104, 131 / 118, 135 / 133, 151 / 161; eight 219 / 186, 250 / 215, 254 / 244,
+// 288 / 300, at 56 rows four 148 / 145, eight 284 / 271, eight at 80, 96, 112, 128 rows 401 / 357, 432 / 415, 468 / 471, 509 / 531.
+// d = 128, 8, 12, 16, 20 rows: one layer 21.4 / 21.2, 22.0 / 22.7, 21.3 / 23.1, 21.8 / 25.0; two 32 / 29, 31.7 / 32.4, 31.9 / 32.7, 32 / 37;
+// four 50 / 45, 53 / 53, 53 / 53, 52 / 59; eight 97 / 79, 98 / 93, 99 / 98, 99 / 106 (128 rows, four layers: 89 / 157).
+// bf16, rounds, us, 8, 16, 32, 64, 128 rows of 16 tokens: d = 256 250 / 214, 253 / 228, 256 / 273, 264 / 345, 311 / 490; d = 384 at
+// 4, 16, 32 rows 317 / 243, 634 / 579, 642 / 675 (328 / 363 with four drafts).  Two workgroups per unit at d = 256 meet at 32 rows
+// (256 / 251) and lose 5 % at 16.
+inline bool flow_forward_pays(size_t tokens, bool f32, size_t d, int layers) {
+  if (!f32) return tokens <= 256;
+  return tokens <= 16 * (d >= 256 ? (layers >= 4 ? 56 : 40) : (layers >= 4 ? 16 : 8));
+}
 
 // Networks with run-time sizes: `tokens` a launch covers at most (the ragged batch's, the rollout's one row per environment).
 // A spread launch streams its weights once per row and adds max(heads, slices) partial sums of the whole row in every

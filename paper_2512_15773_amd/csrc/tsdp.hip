@@ -693,9 +693,11 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   // (d = 192: spread 2 us per transition slower).  Twins are both in one launch, both in two launches per layer or neither.
   const bool base = &n == &c->net[0], twin = twin_nets(cf);
   const bool launches = dyn || few_rollout_pays(cf.draft_layers, (size_t)cf.draft_d * cf.H >= FEW_WIDE, cf.cond_mode == 1, cf.K_max);
-  const bool one_forward = n.few && fk.flow_forward;
+  const bool one_forward = n.few && fk.flow_forward && flow_forward_pays(rows_max(cf) * cf.H, f32, d, L);
   const bool one_draft = (n.few || !f32) && fk.flow_draft && flow_draft_pays(cf.B_max, f32, d, L, cf.K_max, launches);
-  const bool one = twin ? one_forward && one_draft : base ? one_forward : one_draft;
+  // (twins whose rollout would be the persistent kernel: it gains a multiple of what the forward pass can lose -- four layers of
+  // d = 256, 16 environments, K = 8: tsdp_draft 2240 -> 644 us, tsdp_verify 243 -> 279)
+  const bool one = twin ? fk.flow_forward && one_draft && (one_forward || !launches) : base ? one_forward : one_draft;
   if (one) {
     if (fk.flow_forward) n.few_forward = fk.flow_forward;
     if (fk.flow_draft) n.few_draft = fk.flow_draft;

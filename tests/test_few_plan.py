@@ -14,6 +14,7 @@ int safe_rows(int own, int B, int R_cap) { return few_safe_rows(own != 0, B, R_c
 int rollout_pays(int layers, int wide, int cross, int K_max) { return few_rollout_pays(layers, wide != 0, cross != 0, K_max); }
 int pays(long tokens, int f32, long layer_bytes) { return few_pays(tokens, f32 != 0, layer_bytes); }
 int draft_pays(int environments, int f32, long d, int layers, int K_max, int launches) { return flow_draft_pays(environments, f32 != 0, d, layers, K_max, launches != 0); }
+int forward_pays(long tokens, int f32, long d, int layers) { return flow_forward_pays(tokens, f32 != 0, d, layers); }
 int dyn_pays(long tokens, long heads, long layer_bytes) { return few_dyn_pays(tokens, heads, layer_bytes); }
 // the context's buffers after a sequence of loads: flags[2 * i] / [2 * i + 1] = base / drafter takes the spread path then
 int buffers_hold(long tokens, long d0, long s0, long d1, long s1, const int* flags, int loads) {
@@ -103,3 +104,15 @@ def test_rollouts_in_one_launch_only_where_that_is_faster(plan):
                                 (256, 1, 1, 18), (256, 2, 4, 24), (256, 4, 4, 32), (256, 4, 2, 64)):
         assert not pays(1, d, layers, K_max, B), (d, layers, K_max, B)
     assert pays(0, 256, 2, 8, 24) and not pays(0, 256, 2, 8, 25)
+
+
+def test_forward_passes_in_one_launch_only_where_that_is_faster(plan):
+    # (fp32, d, layers, rows of 16 tokens): tsdp_verify measured against two launches per layer
+    L = C.c_long
+    pays = lambda f32, d, layers, rows: bool(plan.forward_pays(L(16 * rows), f32, L(d), layers))
+    for f32, d, layers, rows in ((1, 256, 1, 40), (1, 256, 2, 40), (1, 256, 4, 56), (1, 256, 8, 56), (1, 128, 1, 8), (1, 128, 2, 8), (1, 128, 4, 16),
+                                 (1, 128, 8, 16), (0, 256, 2, 16), (0, 384, 1, 16), (0, 384, 8, 16)):
+        assert pays(f32, d, layers, rows), (f32, d, layers, rows)
+    for f32, d, layers, rows in ((1, 256, 1, 48), (1, 256, 2, 64), (1, 256, 4, 64), (1, 256, 8, 64), (1, 256, 8, 128), (1, 128, 1, 12), (1, 128, 2, 20), (1, 128, 4, 20),
+                                 (1, 128, 8, 24), (1, 128, 4, 128), (0, 256, 8, 32), (0, 384, 8, 32)):
+        assert not pays(f32, d, layers, rows), (f32, d, layers, rows)

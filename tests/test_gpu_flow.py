@@ -14,6 +14,9 @@ STATE = ti.replace(ti.C2, base=ti.NetShape(2, 256, 4))
 @pytest.mark.parametrize("wl, B, K_max", [
     (STATE, 7, 1), (STATE, 8, 1),                     # one row per XCD at most: a workgroup per unit
     (STATE, 33, 1), (STATE, 43, 3),                   # five tiles of rows for four groups; groups of four and five
+    (STATE, 40, 1), (STATE, 41, 1), (ti.replace(ti.C2, base=ti.NetShape(4, 256, 4)), 14, 4), (ti.replace(ti.C2, base=ti.NetShape(4, 256, 4)), 19, 3),
+    (ti.replace(ti.C2, base=ti.NetShape(4, 128, 4)), 8, 2), (ti.replace(ti.C2, base=ti.NetShape(4, 128, 4)), 17, 1),   # fp32 forward passes: the most rows
+    # in one launch, the fewest in two launches per layer
     (STATE, 16, 2), (STATE, 17, 2),                   # fp32 rollouts: the most environments in one launch, the fewest in launches
     (ti.replace(ti.C2, base=ti.NetShape(3, 128, 4), draft=ti.NetShape(4, 256, 4)), 18, 7),   # so many launches: in one beyond that too
     (ti.replace(ti.C2, base=ti.NetShape(1, 256, 4), draft=ti.NetShape(4, 128, 4)), 33, 3),   # and in launches
