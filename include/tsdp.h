@@ -28,13 +28,15 @@
  *    input state y_{k-1} of drafted transition k at timestep t0[b]-k+1.  K_eff = min(K, t0).  An
  *    environment at t0 = 0 owns one row (the deterministic last base step); a finished one owns none.
  *  - An environment's results do not depend on the batch it is computed in, bit for bit, within one context and between
- *    contexts whose capacity is on the same side of the line up to which a forward pass is spread over the chip
- *    (compiled shapes: B_max * (K_max + bonus_row) * H of at most 2048 tokens in fp32, 2176 in bf16) and, within it, of
- *    the line up to which it is one launch (forward passes with a conditioning vector: 256 tokens in bf16; fp32
- *    d = 256 896 with four layers or more, 640 with fewer, d = 128 256 and 128; rollouts: fp32 B_max of at most 16, or 32
- *    where they would be more than 40 launches, with cross-attention 24; two bf16 networks of one shape K_max of at
- *    most 9 with two layers).  Across such a line they differ by rounding, and an accept decision that nearly ties can
- *    differ.
+ *    contexts whose capacity is on the same side of the lines at which the kernels change (compiled shapes; tokens are
+ *    B_max * (K_max + bonus_row) * H):
+ *      a forward pass is spread over the chip   up to 2048 tokens in fp32, 2176 in bf16
+ *      and is one launch                        bf16 with a conditioning vector up to 256 tokens (one layer of d = 256: 160);
+ *                                               fp32 d = 256 up to 896 (640 with fewer than four layers), d = 128 256 (128)
+ *      a rollout is one launch                  fp32 up to B_max = 16, or 32 where it would be more than 40 launches (one
+ *                                               layer of d = 128 only from K_max = 4 on); with cross-attention B_max = 24
+ *      two networks of one shape are spread     bf16 up to 40 launches a rollout (two layers: K_max = 9)
+ *    Across such a line they differ by rounding, and an accept decision that nearly ties can differ.
  *  - H*A must be a multiple of 4 and at most 512.  The context owns weights, tables and workspace; calls on one
  *    context must not overlap in time (they share the workspace).
  */

@@ -59,9 +59,10 @@ inline bool flow_draft_pays(int environments, bool f32, size_t d, int layers, in
 // four 50 / 45, 53 / 53, 53 / 53, 52 / 59; eight 97 / 79, 98 / 93, 99 / 98, 99 / 106 (128 rows, four layers: 89 / 157).
 // bf16, rounds, us, 8, 16, 32, 64, 128 rows of 16 tokens: d = 256 250 / 214, 253 / 228, 256 / 273, 264 / 345, 311 / 490; d = 384 at
 // 4, 16, 32 rows 317 / 243, 634 / 579, 642 / 675 (328 / 363 with four drafts).  Two workgroups per unit at d = 256 meet at 32 rows
-// (256 / 251) and lose 5 % at 16.
+// (256 / 251) and lose 5 % at 16.  tsdp_verify of one layer, d = 256, 8, 10, 12, 16 rows 24.3 / 22.6, 24.2 / 23.8, 23.9 / 24.1, 24.1 / 24.9
+// (two layers, 16 rows 37 / 34), d = 384, 16 rows 36 / 31.
 inline bool flow_forward_pays(size_t tokens, bool f32, size_t d, int layers) {
-  if (!f32) return tokens <= 256;
+  if (!f32) return tokens <= (layers * d >= 384 ? 256 : 160);
   return tokens <= 16 * (d >= 256 ? (layers >= 4 ? 56 : 40) : (layers >= 4 ? 16 : 8));
 }
 

@@ -111,8 +111,8 @@ def test_forward_passes_in_one_launch_only_where_that_is_faster(plan):
     L = C.c_long
     pays = lambda f32, d, layers, rows: bool(plan.forward_pays(L(16 * rows), f32, L(d), layers))
     for f32, d, layers, rows in ((1, 256, 1, 40), (1, 256, 2, 40), (1, 256, 4, 56), (1, 256, 8, 56), (1, 128, 1, 8), (1, 128, 2, 8), (1, 128, 4, 16),
-                                 (1, 128, 8, 16), (0, 256, 2, 16), (0, 384, 1, 16), (0, 384, 8, 16)):
+                                 (1, 128, 8, 16), (0, 256, 1, 10), (0, 256, 2, 16), (0, 384, 1, 16), (0, 384, 8, 16)):
         assert pays(f32, d, layers, rows), (f32, d, layers, rows)
     for f32, d, layers, rows in ((1, 256, 1, 48), (1, 256, 2, 64), (1, 256, 4, 64), (1, 256, 8, 64), (1, 256, 8, 128), (1, 128, 1, 12), (1, 128, 2, 20), (1, 128, 4, 20),
-                                 (1, 128, 8, 24), (1, 128, 4, 128), (0, 256, 8, 32), (0, 384, 8, 32)):
+                                 (1, 128, 8, 24), (1, 128, 4, 128), (0, 256, 1, 16), (0, 256, 8, 32), (0, 384, 8, 32)):
         assert not pays(f32, d, layers, rows), (f32, d, layers, rows)
