@@ -34,7 +34,8 @@
  *      and is one launch                        bf16 with a conditioning vector up to 256 tokens (one layer of d = 256: 160);
  *                                               fp32 d = 256 up to 896 (640 with fewer than four layers), d = 128 256 (128)
  *      a rollout is one launch                  fp32 up to B_max = 16, or 32 where it would be more than 40 launches (one
- *                                               layer of d = 128 only from K_max = 4 on); with cross-attention B_max = 24
+ *                                               layer of d = 128 only from K_max = 4 on); with cross-attention up to
+ *                                               B_max = 24 (one layer: 16, and 8 with K_max = 1)
  *      two networks of one shape are spread     bf16 up to 40 launches a rollout (two layers: K_max = 9)
  *    Across such a line they differ by rounding, and an accept decision that nearly ties can differ.
  *  - H*A must be a multiple of 4 and at most 512.  The context owns weights, tables and workspace; calls on one

@@ -44,9 +44,10 @@ inline bool few_rollout_pays(int layers, bool wide, bool cross, int K_max) {
 // 39, 64 / 63, 105 / 98.  Against the persistent kernel (four layers, K_max = 7, 8 / 18 environments) d = 128 515 / 249, 515 / 335,
 // d = 256 1992 / 357, 1972 / 797; it does not grow with the environments, and at 32 one launch takes 0.83 (0.55) of its time.
 // bf16 with cross-attention, d = 256, 32 tokens: eight transitions of 1, 4, 8, 16, 32 environments 317, 346, 350, 373, 518, the
-// persistent kernel (one workgroup an environment) 425 to 463.
+// persistent kernel (one workgroup an environment) 425 to 463; tsdp_draft, persistent / one launch, 24 environments, K_max = 1, 2, 8, one
+// layer 38 / 42, 66 / 71, 236 / 236, two 67 / 66, 122 / 117, 459 / 420; one layer, 16 environments 36.8 / 38.5, 65 / 63, 235 / 208.
 inline bool flow_draft_pays(int environments, bool f32, size_t d, int layers, int K_max, bool launches) {
-  if (!f32) return environments <= 24;
+  if (!f32) return environments <= (layers >= 2 ? 24 : K_max >= 2 ? 16 : 8);
   return launches ? environments <= 16 && (layers * d >= 256 || K_max >= 4) : environments <= 32;
 }
 

@@ -103,7 +103,8 @@ def test_rollouts_in_one_launch_only_where_that_is_faster(plan):
     for d, layers, K_max, B in ((128, 1, 1, 8), (128, 1, 2, 16), (128, 1, 4, 18), (128, 2, 1, 24), (128, 2, 4, 18), (128, 2, 2, 64), (128, 2, 1, 128), (128, 4, 4, 32),
                                 (256, 1, 1, 18), (256, 2, 4, 24), (256, 4, 4, 32), (256, 4, 2, 64)):
         assert not pays(1, d, layers, K_max, B), (d, layers, K_max, B)
-    assert pays(0, 256, 2, 8, 24) and not pays(0, 256, 2, 8, 25)
+    assert pays(0, 256, 2, 1, 24) and not pays(0, 256, 2, 8, 25)
+    assert pays(0, 256, 1, 1, 8) and pays(0, 256, 1, 2, 16) and not pays(0, 256, 1, 1, 16) and not pays(0, 256, 1, 2, 24)
 
 
 def test_forward_passes_in_one_launch_only_where_that_is_faster(plan):
