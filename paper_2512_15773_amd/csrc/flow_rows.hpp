@@ -72,7 +72,7 @@ struct FlowCfg {
   static constexpr int O_E = 0, O_H0 = HB, O_H1 = 2 * HB, O_H2 = SX ? 3 * HB : O_H1, O_Q = O_H2 + HB, O_U = O_Q + 3 * XB, O_XQ = O_U + 4 * XB,
                        SET_B = O_XQ + (SX ? XB : 0);
   static constexpr int STAT_B = 2 * NW * H * 4, RED_B = NW * 4 * FS * NB * 1024, STEP_B = 2 * 512 * 4;
-  static int lds(int A) { return STAT_B + RED_B + STEP_B + D * A * 4; }
+  static constexpr int lds(int A) { return STAT_B + RED_B + STEP_B + D * A * 4; }
   static_assert(DH % TT::KSTEP == 0 && H % 16 == 0 && D % (16 * FS) == 0, "shape");
 };
 

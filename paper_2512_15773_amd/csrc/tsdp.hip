@@ -404,19 +404,24 @@ void launch_few_film(const FusedNet& n, const int32_t* t_arr, int t_sub, const i
 // The rows of an XCD are dealt to four groups of tasks: fewer leave units idle, eight have no row left to take in turn
 // (64 rows of two layers 342, 385, 300, 351 us with 1, 2, 4, 8).
 constexpr int FLOW_WGS = 64, FLOW_GROUPS = 4, FLOW_ALONE = 84 * 1024;
+template <class C, bool ROLL> int flow_lds(int A, int R_cap) { return ROLL || R_cap <= 8 ? std::max(C::lds(A), FLOW_ALONE) : C::lds(A); }
 template <class C, bool ROLL>
 void flow_launch(const FusedNet& n, const FewRun& r, FlowIO& io, const std::conditional_t<ROLL, DraftIO, FewNone>& dr, int phases, hipStream_t s) {
-  const int per_xcd = (r.R_cap + 7) / 8, lds = C::lds(r.A);
+  const int per_xcd = (r.R_cap + 7) / 8, lds = flow_lds<C, ROLL>(r.A, r.R_cap);
   io.R_cap = r.R_cap; io.phases = phases; io.groups = std::min(per_xcd, FLOW_GROUPS);
   io.ticket = r.sync; io.cnt = r.sync + 8 * SYNC_LINE; io.status = r.status;
   io.x = r.x; io.row_t = r.row_t; io.row_env = r.row_env; io.T = r.T; io.A = r.A;
   io.mod = r.mod; io.mod_row = n.L * 4 * C::D; io.by_t = n.modtab != nullptr;
   io.buf = r.buf; io.eps_out = r.eps_out;
-  static const hipError_t attr = hipFuncSetAttribute((const void*)k_flow<C, ROLL>, hipFuncAttributeMaxDynamicSharedMemorySize, 140 * 1024);
-  (void)attr;                                            // (a launch that this failed for fails itself)
   if (r.R_cap > 0)
-    hipLaunchKernelGGL((k_flow<C, ROLL>), dim3(8 * std::min(4 * io.groups * C::G, FLOW_WGS)), dim3(C::TH),
-                       ROLL || r.R_cap <= 8 ? std::max(lds, FLOW_ALONE) : lds, s, n, io, dr);
+    hipLaunchKernelGGL((k_flow<C, ROLL>), dim3(8 * std::min(4 * io.groups * C::G, FLOW_WGS)), dim3(C::TH), lds, s, n, io, dr);
+}
+// Declares the largest LDS request of any context (H A <= 512) on the device that is current: at every load, so that a launch has
+// nothing to set and contexts on several devices or with several A do not depend on each other.
+template <class C, bool ROLL>
+hipError_t flow_declare() {
+  static_assert(C::lds(512 / C::H) + 16 <= 160 * 1024, "LDS");   // (16: the drawn ticket)
+  return hipFuncSetAttribute((const void*)k_flow<C, ROLL>, hipFuncAttributeMaxDynamicSharedMemorySize, flow_lds<C, ROLL>(512 / C::H, 1));
 }
 
 template <class C>
@@ -443,6 +448,7 @@ struct FusedKernels {
   // the same in one launch, where a shape has it; bytes of a row's buffers
   void (*flow_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr;
   void (*flow_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;
+  hipError_t (*flow_declare_forward)() = nullptr; hipError_t (*flow_declare_draft)() = nullptr;
   size_t flow_row = 0;
   // variant for batches of at most one tile per CU: one 8-wave workgroup per CU instead of two 4-wave ones
   hipError_t (*verify_few)(const FusedNet&, const FusedIO&, int, int, hipStream_t) = nullptr;
@@ -463,8 +469,8 @@ void spread_kernels(FusedKernels& k) {
   constexpr bool FORWARD = F32 || (SX == 0 && D >= 256 && NARROW), DRAFT = F32 || (SX > 0 && NARROW);
   if constexpr (FORWARD || DRAFT) {
     typedef FlowCfg<TT, D, H, HEADS, SX> X;
-    if constexpr (FORWARD) k.flow_forward = flow_forward<X>;
-    if constexpr (DRAFT) k.flow_draft = flow_draft<X>;
+    if constexpr (FORWARD) { k.flow_forward = flow_forward<X>; k.flow_declare_forward = flow_declare<X, false>; }
+    if constexpr (DRAFT) { k.flow_draft = flow_draft<X>; k.flow_declare_draft = flow_declare<X, true>; }
     k.flow_row = 2 * X::SET_B;
   }
 }
@@ -699,8 +705,13 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   // d = 256, 16 environments, K = 8: tsdp_draft 2240 -> 644 us, tsdp_verify 243 -> 279)
   const bool one = twin ? fk.flow_forward && one_draft && (one_forward || !launches) : base ? one_forward : one_draft;
   if (one) {
-    if (fk.flow_forward) n.few_forward = fk.flow_forward;
-    if (fk.flow_draft) n.few_draft = fk.flow_draft;
+    if (base) {
+      n.few_forward = fk.flow_forward;
+      HIPCHK(c, fk.flow_declare_forward());
+    } else {
+      n.few_draft = fk.flow_draft;
+      HIPCHK(c, fk.flow_declare_draft());
+    }
     n.flow_row = fk.flow_row;
   }
   if (twin && !launches && !one) n.few = false;
@@ -1455,12 +1466,6 @@ int tsdp_prepare(tsdp_ctx* c) {
   FusedIO io{};
   DraftIO dio{};
   Net& bn = c->net[0];
-  for (Net* n : {&c->net[0], &c->net[1]})
-    if (n->few && n->flow_row) {
-      const FewRun none = few_run(c, *n, 0, 0, nullptr, nullptr, nullptr);
-      if (n == &bn) n->few_forward(n->fnet, none, nullptr);
-      else n->few_draft(n->fnet, none, dio, c->cfg.K_max, c->few_y, nullptr);
-    }
   if (bn.fused) {
     if (bn.fused_verify) HIPCHK(c, bn.fused_verify(bn.fnet, io, c->cfg.A, 0, nullptr));
     if (bn.fused_verify_few) HIPCHK(c, bn.fused_verify_few(bn.fnet, io, c->cfg.A, 0, nullptr));

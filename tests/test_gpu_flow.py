@@ -1,5 +1,7 @@
 """Forward passes and rollouts in one launch (csrc/flow_rows.hpp): row counts where the tasks are dealt differently, and the
 buffers that every launch has to leave empty."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -65,3 +67,35 @@ def test_not_a_number_passes_through_and_leaves_nothing_behind(payload):
                 assert torch.equal(got[name], ref[name]), name
     assert ctx.tsdp_status() == 0
     ctx.close()
+
+
+class _FuncAttributes(ctypes.Structure):              # hipFuncAttributes
+    _fields_ = [(n, t) for n, t in (("binaryVersion", ctypes.c_int), ("cacheModeCA", ctypes.c_int), ("constSizeBytes", ctypes.c_size_t),
+                                    ("localSizeBytes", ctypes.c_size_t), ("maxDynamicSharedSizeBytes", ctypes.c_int), ("maxThreadsPerBlock", ctypes.c_int),
+                                    ("numRegs", ctypes.c_int), ("preferredShmemCarveout", ctypes.c_int), ("ptxVersion", ctypes.c_int), ("sharedSizeBytes", ctypes.c_size_t))]
+
+
+def _declared(lib, symbol):
+    attr = _FuncAttributes()
+    assert ctypes.CDLL("libamdhip64.so").hipFuncGetAttributes(ctypes.byref(attr), ctypes.c_void_p(ctypes.addressof(ctypes.c_void_p.in_dll(lib, symbol)))) == 0
+    return attr.maxDynamicSharedSizeBytes
+
+
+def test_launches_declare_the_lds_that_they_ask_for():
+    # the rollout of d = 256 with cross-attention asks for 134 KB and one KB per component of an action: more for A = 16, the most
+    # that 32 tokens allow, than for the context that is loaded last
+    from paper_2512_15773_amd import load_library
+    wl = ti.replace(ti.C4, base=ti.NetShape(1, 512, 8))
+    for A in (16, 2):
+        wl = ti.small_variant(wl, B=2, K_max=2, A=A)
+        ctx = gpu_side(wl, *(ti.make_weights(wl, which) for which in ("base", "draft")), ti.make_cond(wl, 2))
+        ctx.tsdp_prepare()
+        ctx.close()
+    symbol = "_ZN4tsdp6k_flowINS_7FlowCfgINS_5TBF16ELi256ELi32ELi8ELi64ELi2EEELb1EEEvNS_8FusedNetENS_6FlowIOENSt11conditionalIXT0_ENS_7DraftIOENS_7FewNoneEE4typeE"
+    assert _declared(load_library(), symbol) >= 2 * 8 * 32 * 4 + 8 * 4 * 2 * 2 * 1024 + 2 * 512 * 4 + 256 * 16 * 4
+
+
+@pytest.mark.parametrize("A", [16, 6])
+def test_rollouts_with_cross_attention_and_the_most_lds(A):
+    wl = ti.small_variant(ti.C4, B=3, K_max=3, A=A, base=ti.NetShape(1, 512, 8))
+    _stage_parity(wl, 3, np.array([99, 40, 2]), np.array([3, 1, 3]), np.ones(3))
