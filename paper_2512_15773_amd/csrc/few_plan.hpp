@@ -67,6 +67,13 @@ inline bool flow_forward_pays(size_t tokens, bool f32, size_t d, int layers) {
   return tokens <= 16 * (d >= 256 ? (layers >= 4 ? 56 : 40) : (layers >= 4 ? 16 : 8));
 }
 
+// Waits of the one-launch kernels.  No wait polls more than FLOW_SPINS times (about half a microsecond each); every FLOW_LOOK
+// polls it looks whether another wait of its launch has run into that bound, and ends if so: a launch whose data cannot arrive
+// drains within one bound and FLOW_LOOK polls of every later wait, not one bound each.
+constexpr int FLOW_SPINS = 1 << 22, FLOW_LOOK = 64;
+enum FlowTurn { FLOW_POLL, FLOW_ASK, FLOW_GIVE_UP };   // behind poll n that found its data missing
+constexpr FlowTurn flow_turn(int n) { return n >= FLOW_SPINS ? FLOW_GIVE_UP : n % FLOW_LOOK == FLOW_LOOK - 1 ? FLOW_ASK : FLOW_POLL; }
+
 // Networks with run-time sizes: `tokens` a launch covers at most (the ragged batch's, the rollout's one row per environment).
 // A spread launch streams its weights once per row and adds max(heads, slices) partial sums of the whole row in every
 // workgroup; one launch per operator does neither but has six times the launches.  Rows at which both take the same time

@@ -35,24 +35,25 @@
 // Tasks are drawn from a ticket per XCD in the order of the phases, and depend on earlier tickets only.  The earliest
 // unfinished task has been drawn by a workgroup that is running, and waits for nothing: the launch makes progress with any
 // number of resident workgroups, also beside other launches of this kind.  The rows of an XCD's tickets are their own, so the
-// XCDs do not wait for each other.  Every wait is bounded all the same (FLOW_SPINS): past the bound the status word reports
-// it and the launch drains.
+// XCDs do not wait for each other.  Every wait is bounded all the same (flow_turn): past the bound the status word reports it,
+// the waits of the other tasks end too, and the launch drains.
 // Visibility: what one workgroup writes for another in the same launch goes through loads and stores of device scope
 // (sc1), which do not stay in an L1 or in the L2 of one XCD.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "fused_mfma.hpp"
+#include "few_plan.hpp"
 #include "few_rows.hpp"
 #include "round_kernels.hpp"
 
 namespace tsdp {
 
-constexpr int FLOW_SPINS = 1 << 22;               // polls of one wait (about half a microsecond each)
 constexpr int FLOW_NAP = 3;                       // x 64 cycles between the first words of a store and all of them
 constexpr int FLOW_KINDS = 6;                     // counters of a row: one per kind of phase
-// lines of the tickets (one per XCD) and of the counters of `rows` rows
-inline int flow_lines(size_t rows) { return (int)(8 + rows * FLOW_KINDS); }
+// lines of the tickets (one per XCD), of the word that ends all waits and of the counters of `rows` rows
+constexpr int FLOW_OVER_LINE = 8, FLOW_CNT_LINE = 9;
+inline int flow_lines(size_t rows) { return (int)(FLOW_CNT_LINE + rows * FLOW_KINDS); }
 constexpr int FLOW_STATUS = 16;                   // status bit: a wait ran into its bound
 
 // Feature blocks of a task.  fp32: one, its products are bound by a unit's matrix rate (one C2 environment 260 us a round, with two
@@ -79,7 +80,7 @@ struct FlowCfg {
 struct FlowIO {
   int R_cap, groups, phases;     // groups: the rows of an XCD (every eighth) are dealt to this many tasks of a phase and slice
   const int32_t* word;           // live row count; rollout: K_eff of every environment
-  int32_t* ticket; int32_t* cnt; int32_t* status;
+  int32_t* ticket; int32_t* over; int32_t* cnt; int32_t* status;
   const float* x;                // latents of the rows
   const int32_t* row_t; const int32_t* row_env; int T;
   const float* mod; int mod_row, by_t;           // FiLM vectors: floats between rows; by_t: rows are timesteps
@@ -125,15 +126,26 @@ template <class F> __device__ __forceinline__ void flow_max(unsigned& m, const F
     m = max(max(m, w[0]), w[1]);
   }
 }
+// behind poll n of a wait that found its data missing: true ends the wait (cannot happen; lets the launch drain)
+__device__ __forceinline__ bool flow_over(const FlowIO& io, int n, int lane) {
+  const FlowTurn turn = flow_turn(n);
+  if (turn == FLOW_POLL) return false;
+  if (turn == FLOW_ASK) return __builtin_amdgcn_readfirstlane(__hip_atomic_load(io.over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0;
+  if (lane == 0) {
+    atomicOr(io.status, FLOW_STATUS);
+    __hip_atomic_store(io.over, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  return true;
+}
 // Waits for N pieces of BYTES each at off (what one store instruction writes, or several): every lane looks at one word, so that
 // 64 / N lanes look at each piece.  Cheap to repeat, where reading everything is not; who reads the pieces afterwards still checks them whole.
 template <int N, int BYTES>
-__device__ __forceinline__ void flow_sample(__amdgpu_buffer_rsrc_t r, int off, int lane) {
+__device__ __forceinline__ void flow_sample(const FlowIO& io, __amdgpu_buffer_rsrc_t r, int off, int lane) {
   static_assert(64 % N == 0 && BYTES % (64 / N) == 0, "lanes per piece");
   const int at = off + lane % N * BYTES + lane / N * (BYTES / (64 / N)) + 4 * (lane & 1);
-  for (int n = 0; n < FLOW_SPINS; ++n) {
+  for (int n = 0;; ++n) {
     asm volatile("" ::: "memory");
-    if (!__any(__builtin_amdgcn_raw_buffer_load_b32(r, at, 0, FLOW_SC1) == FLOW_EMPTY)) break;
+    if (!__any(__builtin_amdgcn_raw_buffer_load_b32(r, at, 0, FLOW_SC1) == FLOW_EMPTY) || flow_over(io, n, lane)) break;
   }
   __builtin_amdgcn_s_sleep(FLOW_NAP);
 }
@@ -149,10 +161,7 @@ __device__ __forceinline__ void flow_guard(const FlowIO& io, int row, int kind, 
     int32_t* c = io.cnt + (row * FLOW_KINDS + kind) * SYNC_LINE;
     for (int n = 0;; ++n) {
       if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >= target) break;
-      if (n >= FLOW_SPINS) {                             // cannot happen; lets the launch drain
-        if (lane == 0) { atomicOr(io.status, FLOW_STATUS); __hip_atomic_fetch_add(c, 1 << 24, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-        break;
-      }
+      if (flow_over(io, n, lane)) break;
       __builtin_amdgcn_s_sleep(2);
     }
   }
@@ -169,10 +178,7 @@ __device__ __forceinline__ void flow_poll(const FlowIO& io, int lane, F&& load, 
     unsigned m = 0;
     (flow_max(m, v), ...);
     if (!__any(m == FLOW_EMPTY)) break;
-    if (n >= FLOW_SPINS) {                               // cannot happen; lets the launch drain
-      if (lane == 0) atomicOr(io.status, FLOW_STATUS);
-      break;
-    }
+    if (flow_over(io, n, lane)) break;
   }
 }
 // the task's stores are complete: count it
@@ -770,7 +776,7 @@ __global__ __launch_bounds__(C::TH) void k_flow(FusedNet net, FlowIO io, std::co
         frag a[KWM][NB];
         f32x4 acc[FS][NB];
         wait(row);
-        flow_sample<KWM * NB, 64 * VW * ES>(r, C::O_U + wave * KWM * NB * 64 * VW * ES, lane);
+        flow_sample<KWM * NB, 64 * VW * ES>(io, r, C::O_U + wave * KWM * NB * 64 * VW * ES, lane);
         flow_poll(io, lane, [&]() {
 #pragma unroll
           for (int ks = 0; ks < KWM; ++ks)

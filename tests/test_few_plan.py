@@ -16,6 +16,19 @@ int pays(long tokens, int f32, long layer_bytes) { return few_pays(tokens, f32 !
 int draft_pays(int environments, int f32, long d, int layers, int K_max, int launches) { return flow_draft_pays(environments, f32 != 0, d, layers, K_max, launches != 0); }
 int forward_pays(long tokens, int f32, long d, int layers) { return flow_forward_pays(tokens, f32 != 0, d, layers); }
 int dyn_pays(long tokens, long heads, long layer_bytes) { return few_dyn_pays(tokens, heads, layer_bytes); }
+// polls of one workgroup's `waits` waits, one after the other, for data that never arrives
+long drain(int waits) {
+  long polls = 0;
+  bool over = false;
+  for (int w = 0; w < waits; ++w)
+    for (int n = 0;; ++n) {
+      ++polls;
+      const FlowTurn turn = flow_turn(n);
+      if (turn == FLOW_GIVE_UP) over = true;
+      if (turn == FLOW_GIVE_UP || (turn == FLOW_ASK && over)) break;
+    }
+  return polls;
+}
 // the context's buffers after a sequence of loads: flags[2 * i] / [2 * i + 1] = base / drafter takes the spread path then
 int buffers_hold(long tokens, long d0, long s0, long d1, long s1, const int* flags, int loads) {
   FewSize have;
@@ -39,7 +52,9 @@ def plan(tmp_path_factory):
     with open(src, "w") as f:
         f.write(SHIM)
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC", "-I", CSRC, src, "-o", lib], check=True)
-    return C.CDLL(lib)
+    plan = C.CDLL(lib)
+    plan.drain.restype = C.c_long
+    return plan
 
 
 def test_rows_of_a_callers_buffer_are_not_read_beyond_the_live_ones(plan):
@@ -117,3 +132,11 @@ def test_forward_passes_in_one_launch_only_where_that_is_faster(plan):
     for f32, d, layers, rows in ((1, 256, 1, 48), (1, 256, 2, 64), (1, 256, 4, 64), (1, 256, 8, 64), (1, 256, 8, 128), (1, 128, 1, 12), (1, 128, 2, 20), (1, 128, 4, 20),
                                  (1, 128, 8, 24), (1, 128, 4, 128), (0, 256, 1, 16), (0, 256, 8, 32), (0, 384, 8, 32)):
         assert not pays(f32, d, layers, rows), (f32, d, layers, rows)
+
+
+def test_a_launch_whose_data_cannot_arrive_drains_after_one_bound(plan):
+    # one wait may take its bound (about two seconds), the hundreds that follow in the same launch may not
+    bound = plan.drain(1)
+    assert 1 << 20 <= bound <= (1 << 22) + 1
+    for waits in (2, 97, 10000):
+        assert plan.drain(waits) <= bound + 64 * (waits - 1), waits
