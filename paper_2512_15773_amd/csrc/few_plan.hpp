@@ -19,8 +19,10 @@ inline int few_safe_rows(bool ahead, int B, int R_cap) { return ahead ? std::min
 // 498 / 409, 498 / 443, 497 / 511; bf16 d = 384 880 / 729, 881 / 869, -; fp32 d = 256 799 / 504, 800 / 724, and at 136 rows
 // 797 / 835; at 64, 128 rows of 32 tokens, d = 512: 1577 / 1252, 1591 / 1856.  A layer of less than 700 KB passes through one
 // compute unit faster than through two launches (fp32 d = 64, 393 KB in all: 21 us against 25).
+constexpr size_t FEW_LAYER_BYTES = 700000;
+constexpr size_t layer_bytes(size_t d, bool f32, bool cross) { return (cross ? 14 : 12) * d * d * (f32 ? 4 : 2); }
 inline bool few_pays(size_t tokens, bool f32, size_t layer_bytes) {
-  return tokens <= (f32 ? 2048 : 2176) && layer_bytes >= 700000;
+  return tokens <= (f32 ? 2048 : 2176) && layer_bytes >= FEW_LAYER_BYTES;
 }
 
 // Launches of a spread rollout: every transition up to K_max has its own, whether drafted or not (the draft counts are on

@@ -460,18 +460,20 @@ struct FusedKernels {
   int rpt_small = 0, rpt_big = 0;
 };
 
-// The spread kernels of a compiled shape.
+// The spread kernels of a compiled shape, where few_pays can choose them.
 template <class TT, int D, int H, int HEADS, int SX>
 void spread_kernels(FusedKernels& k) {
-  typedef FewCfg<TT, D, H, HEADS, SX> F;
-  k.few_forward = few_forward<F>; k.few_draft = few_draft<F>; k.few_slices = std::max(F::NCH, F::HEADS);
   constexpr bool F32 = std::is_same<TT, TF32>::value, NARROW = D * H < FEW_WIDE;
-  constexpr bool FORWARD = F32 || (SX == 0 && D >= 256 && NARROW), DRAFT = F32 || (SX > 0 && NARROW);
-  if constexpr (FORWARD || DRAFT) {
-    typedef FlowCfg<TT, D, H, HEADS, SX> X;
-    if constexpr (FORWARD) { k.flow_forward = flow_forward<X>; k.flow_declare_forward = flow_declare<X, false>; }
-    if constexpr (DRAFT) { k.flow_draft = flow_draft<X>; k.flow_declare_draft = flow_declare<X, true>; }
-    k.flow_row = 2 * X::SET_B;
+  if constexpr (layer_bytes(D, F32, SX > 0) >= FEW_LAYER_BYTES) {
+    typedef FewCfg<TT, D, H, HEADS, SX> F;
+    k.few_forward = few_forward<F>; k.few_draft = few_draft<F>; k.few_slices = std::max(F::NCH, F::HEADS);
+    constexpr bool FORWARD = F32 || (SX == 0 && D >= 256 && NARROW), DRAFT = F32 || (SX > 0 && NARROW);
+    if constexpr (FORWARD || DRAFT) {
+      typedef FlowCfg<TT, D, H, HEADS, SX> X;
+      if constexpr (FORWARD) { k.flow_forward = flow_forward<X>; k.flow_declare_forward = flow_declare<X, false>; }
+      if constexpr (DRAFT) { k.flow_draft = flow_draft<X>; k.flow_declare_draft = flow_declare<X, true>; }
+      k.flow_row = 2 * X::SET_B;
+    }
   }
 }
 
@@ -693,7 +695,7 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   n.few_forward = fk.few_forward; n.few_draft = fk.few_draft; n.few_film = fk.few_film; n.few_slices = fk.few_slices; n.flow_row = 0;
   // Few rows: the spread kernels.  The capacity of the context decides, not the call: an environment's result must not
   // depend on the batch it is computed in.
-  n.few = dyn || few_pays(rows_max(cf) * cf.H, f32, (size_t)(cf.cond_mode == 1 ? 14 : 12) * d * d * (f32 ? 4 : 2));
+  n.few = dyn || few_pays(rows_max(cf) * cf.H, f32, layer_bytes(d, f32, cf.cond_mode == 1));
   // The rollout: fp32 layers are bound by one unit's matrix rate (d = 128: 37 us per transition, in launches 23, in one launch
   // 17), and so are those with cross-attention by one unit's weight stream; bf16 drafters with a conditioning vector are not
   // (d = 192: spread 2 us per transition slower).  Twins are both in one launch, both in two launches per layer or neither.
@@ -1075,7 +1077,7 @@ int tsdp_load_weights(tsdp_ctx* c, int which, const float* h_blob, size_t nbytes
   if (!std::getenv("TSDP_DISABLE_FUSED")) {
     FusedKernels fk;
     if (!find_fused(cf.dtype, n.d, cf.H, n.heads, cf.cond_mode, cf.cond_tokens, n.m / n.d, n.L, fk)) HIPCHK(c, find_few_dyn(cf, which, n, fk));
-    if (fk.few_forward && (rc = build_fused(c, n, w, modw, fk))) return rc;
+    if (fk.few_film && (rc = build_fused(c, n, w, modw, fk))) return rc;
   }
   if (!n.fused && cf.cond_mode == 1 && !n.kc) {        // fp32 keys / values of the operator kernels
     const size_t cnt = (size_t)L * cf.B_max * cf.cond_tokens * d;

@@ -140,3 +140,15 @@ def test_a_launch_whose_data_cannot_arrive_drains_after_one_bound(plan):
     assert 1 << 20 <= bound <= (1 << 22) + 1
     for waits in (2, 97, 10000):
         assert plan.drain(waits) <= bound + 64 * (waits - 1), waits
+
+
+def test_no_kernel_is_compiled_that_no_network_reaches():
+    # a layer of less than FEW_LAYER_BYTES never takes the spread kernels: fp32 d = 32, 64 and bf16 d = 128 have none
+    lib = os.path.join(os.path.dirname(CSRC), "libtsdp.so")
+    if not os.path.exists(lib):
+        pytest.skip("the library is not built")
+    names = subprocess.run(["nm", "-D", "--defined-only", lib], capture_output=True, text=True, check=True).stdout
+    assert "FlowCfgINS_4TF32ELi256E" in names and "FewCfgINS_4TF32ELi128E" in names
+    for cfg in ("FlowCfg", "FewCfg"):
+        for shape in ("INS_4TF32ELi32E", "INS_4TF32ELi64E", "INS_5TBF16ELi128E"):
+            assert cfg + shape not in names, cfg + shape
