@@ -1055,8 +1055,10 @@ def test_enqueue_only_chain_is_bit_identical_to_the_host_checked_chain():
 
 
 @pytest.mark.parametrize("wl, B, bonus", [
-    (ti.small_variant(ti.C2, T=30, base=ti.NetShape(2, 256, 4)), 5, False),                                 # spread rollout
+    (ti.small_variant(ti.C2, T=30, base=ti.NetShape(2, 256, 4)), 5, False),                                 # one launch each
     (ti.small_variant(ti.C2, T=30, base=ti.NetShape(2, 256, 4)), 5, True),
+    (ti.small_variant(ti.C2, T=30, K_max=4, base=ti.NetShape(2, 256, 4)), 18, False),                       # launches
+    (ti.small_variant(ti.C2, T=30, K_max=4, base=ti.NetShape(2, 256, 4)), 17, True),
     (ti.small_variant(ti.C3, T=30, K_max=4, base=ti.NetShape(2, 256, 4), draft=ti.NetShape(2, 256, 4)), 3, True),   # bf16
     (ti.small_variant(ti.C3, T=30, K_max=4), 3, False),                                                     # persistent rollout
     (ti.small_variant(ti.C4, T=20, K_max=3, base=ti.NetShape(1, 512, 8)), 2, False),                        # wide rows
@@ -1145,6 +1147,7 @@ def test_prepare_makes_a_fresh_context_capturable_and_short_chains_stop_where_as
 
 @pytest.mark.parametrize("wl", [
     ti.small_variant(ti.C2, B=3, K_max=4, base=ti.NetShape(2, 256, 4)),
+    ti.small_variant(ti.C2, B=18, K_max=3, base=ti.NetShape(2, 256, 4)),
     ti.small_variant(ti.C4, B=2, K_max=3, base=ti.NetShape(1, 512, 8)),
     ti.small_variant(ti.C2, B=3, K_max=4, A=4, cond_dim=64, base=ti.NetShape(2, 96, 3), draft=ti.NetShape(1, 48, 3)),
 ])
@@ -1154,7 +1157,7 @@ def test_first_round_of_few_rows_can_be_captured(wl):
     B = wl.B
     nets = [ti.make_weights(wl, which, head_scale=0.3) for which in ("base", "draft")]
     cond, x0 = ti.make_cond(wl, B), to_dev(ti.make_latents(wl, B))
-    t0 = to_dev(np.array([50, 2, 0][:B], np.int32)); K = to_dev(np.array([wl.K_max, 3, 1][:B], np.int32)); s = torch.ones(B, device="cuda")
+    t0 = to_dev(np.resize([50, 2, 0], B).astype(np.int32)); K = to_dev(np.resize([wl.K_max, 3, 1], B).astype(np.int32)); s = torch.ones(B, device="cuda")
     ctx = gpu_side(wl, *nets, cond)
     ctx.tsdp_prepare()
     x, t = x0.clone(), t0.clone()
