@@ -551,7 +551,7 @@ def measure_workload(wl, point, steps, warmup, torch, Tsdp, dev, full):
     if fused:
         k_ms, k_med = time_kernel(ctx, lambda: ctx.tsdp_verify(wl.B, rows), 1, n_it)
         kd_ms, _ = time_kernel(ctx, lambda: ctx.tsdp_draft(x0d, t0d, Kd, sd, None, rows), 0, n_it)
-        kname = "verify forward (k_fused_forward, all layers in one launch; few rows: k_few_*, two launches per layer and more)"
+        kname = "verify forward (k_fused_forward, all layers in one launch; few rows: k_flow in one launch, or k_few_* in two per layer and more)"
     else:
         k_ms, k_med, kd_ms, kname = t_verify[0], t_verify[1], None, "tsdp_verify (sequence of fp32 operator kernels)"
     lat["drafter_kernel"] = kd_ms
@@ -611,12 +611,14 @@ def measure_workload(wl, point, steps, warmup, torch, Tsdp, dev, full):
         wbytes = drafter_weight_bytes(wl)
         kmax = int(keff.max(initial=0))
         stream_gbs = wbytes * kmax * wgs / (kd_ms * 1e-3) / 1e9
-        res["drafter"] = {"kernel": "drafter rollout (k_fused_draft, K sequential steps in one launch; few fp32 rows: k_few_*)",
+        # few fp32 environments with layers of 700 KB and more: tasks spread over the chip, no stream per workgroup
+        spread = not bf16 and 12 * wl.draft.d ** 2 * 4 >= 700000 and wl.B * wl.K_max * wl.H <= 2048
+        res["drafter"] = {"kernel": "drafter rollout, K sequential steps in one launch (" + ("k_flow)" if spread else "k_fused_draft)"),
                           "kernel_ms": kd_ms, "steps": kmax, "us_per_step": 1e3 * kd_ms / max(kmax, 1),
-                          "workgroups": wgs, "environments_per_workgroup": rpt,
-                          "weight_bytes_per_step_and_workgroup": wbytes,
-                          "l2_weight_stream_GBps": stream_gbs, "l2_stream_ceiling_GBps": L2_STREAM_GBS,
-                          "frac_of_l2_stream_ceiling": stream_gbs / L2_STREAM_GBS,
+                          "workgroups": None if spread else wgs, "environments_per_workgroup": None if spread else rpt,
+                          "weight_bytes_per_step_and_workgroup": None if spread else wbytes,
+                          "l2_weight_stream_GBps": None if spread else stream_gbs, "l2_stream_ceiling_GBps": L2_STREAM_GBS,
+                          "frac_of_l2_stream_ceiling": None if spread else stream_gbs / L2_STREAM_GBS,
                           "note": "sequential by construction: bound by per-step latency, not by the stream; the "
                                   "ceiling is a measured streaming rate of this part, not a published peak"}
     state = dict(ctx=ctx, x0d=x0d, t0d=t0d, Kd=Kd, sd=sd, rows=rows, problem=(wb, wd, cond, x, t0, K, s), t_round=t_round)

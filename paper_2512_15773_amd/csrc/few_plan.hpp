@@ -11,27 +11,28 @@ namespace tsdp {
 //  - in a caller's buffers: they hold the live rows and no more -- finished environments own none, so not even the first B
 //    need exist -- and nothing of them is read before the count is known;
 //  - in the rounds of an enqueued chain, most of which have no live row: a launch without one costs 1.5 us where it asks
-//    first and 2.6 us where it first requests the row's data and weights (one C2 environment, a round of 54 launches 85 us, 142).
+//    first and 2.6 us where it first requests the row's data and weights (an empty round of 54 launches 85 us, 142).
 inline int few_safe_rows(bool ahead, int B, int R_cap) { return ahead ? std::min(B, R_cap) : 0; }
 
 // Networks with compiled kernels.  One workgroup per tile takes the same time from 1 to 256 tiles, the spread launches grow
 // with the rows; they meet at about 2100 tokens.  Rounds, us, tile / spread at 64, 128, 144 rows of 16 tokens: bf16 d = 256
 // 498 / 409, 498 / 443, 497 / 511; bf16 d = 384 880 / 729, 881 / 869, -; fp32 d = 256 799 / 504, 800 / 724, and at 136 rows
 // 797 / 835; at 64, 128 rows of 32 tokens, d = 512: 1577 / 1252, 1591 / 1856.  A layer of less than 700 KB passes through one
-// compute unit faster than through two launches (fp32 d = 64, 393 KB in all: 21 us against 25).
+// compute unit faster than through two launches (fp32 d = 64, 393 KB in all: 21 us against 25); one launch was not measured there.
 constexpr size_t FEW_LAYER_BYTES = 700000;
 constexpr size_t layer_bytes(size_t d, bool f32, bool cross) { return (cross ? 14 : 12) * d * d * (f32 ? 4 : 2); }
 inline bool few_pays(size_t tokens, bool f32, size_t layer_bytes) {
   return tokens <= (f32 ? 2048 : 2176) && layer_bytes >= FEW_LAYER_BYTES;
 }
 
-// Launches of a spread rollout: every transition up to K_max has its own, whether drafted or not (the draft counts are on
-// the device).  A drafted transition of the fp32 d = 128 network takes 23 us instead of the persistent kernel's 39, an
-// undrafted one 6 to 15 instead of none: with half of K_max or more the spread rollout is the faster one, and what fewer
-// drafts lose grows with K_max.  Rounds of one C2 environment, us, persistent / spread rollout: K = 1, 4, 8 of 8 226 / 277,
-// 344 / 331, 495 / 396; K = 1, 4, 16 of 16 226 / 363, 344 / 413, 788 / 595; K = 4, 64 of 64 344 / 1085, 2673 / 1888.  So up
-// to 40 launches (two layers: K_max = 9) the rollout is spread -- the loss stays below a quarter of a round, and below what
-// the spread verify saves of it (one workgroup per row: 545, 663, 812 with K = 1, 4, 8) -- and beyond it is one launch.
+// Launches of a spread rollout (two bf16 networks of one shape; fp32 drafters beyond flow_draft_pays): every transition up to
+// K_max has its own, whether drafted or not (the draft counts are on the device).  With half of K_max or more the spread rollout
+// is the faster one, and what fewer drafts lose grows with K_max.  Rounds of one environment, two bf16 networks of d = 256, us,
+// persistent rollout and tile kernels / all spread: two layers, K = 1, 4, 8 of 8 170 / 164, 296 / 220, 464 / 293; 1, 4, 9 of 9 169 / 178,
+// 296 / 232, 507 / 321; 1, 8, 16 of 16 170 / 279, 464 / 390, 802 / 532; four layers 1, 2, 4 of 4 283 / 213, 384 / 244, 589 / 307, 1, 8
+// of 8 282 / 310, 1031 / 531.  With the fp32 drafter of d = 128, two layers (spread 23 us a drafted and 6 to 15 an undrafted transition,
+// persistent 39), K = 1, 4, 8 of 8 226 / 277, 344 / 331, 495 / 396; 4, 64 of 64 344 / 1085, 2673 / 1888.  So up to 40 launches (two layers:
+// K_max = 9) the rollout is spread -- the loss stays below a quarter of a round -- and beyond it is one launch.
 constexpr int FEW_ROLL_LAUNCHES = 40;
 inline bool few_rollout_pays(int layers, bool wide, bool cross, int K_max) {
   return layers * (wide ? 2 : 1) * (cross ? 3 : 2) * K_max + 1 <= FEW_ROLL_LAUNCHES;

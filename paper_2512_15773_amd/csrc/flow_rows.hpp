@@ -8,8 +8,8 @@
 //   phase D  down projection of 16 features, added to the residual
 //   head     LayerNorm -> output projection; in a rollout the sampler step, done by phase A of the next transition
 //
-// For the fp32 networks, whose products are worth sixteen units a row, for rollouts with cross-attention and for bf16
-// networks with a conditioning vector up to 16 rows (one environment, d = 256, K = 8: round 250 -> 214 us).
+// For the fewest rows (flow_forward_pays, flow_draft_pays): fp32 networks, whose products are worth sixteen units a row, rollouts
+// with cross-attention, and bf16 networks with a conditioning vector (one environment, d = 256, K = 8: round 250 -> 214 us).
 // What bounds a few rows is the chain of dependent steps, not their work.  With two launches per layer a step was 6 to
 // 12 us: 2.4 us between dependent launches, the weights requested only then, and partial sums of the whole row (up to 272 KB)
 // read by every workgroup.  Here a step is an exchange of 16 to 64 KB through the L2 (1 to 1.5 us), workgroups of the
