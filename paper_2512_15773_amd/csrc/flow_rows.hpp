@@ -32,13 +32,17 @@
 // one phase that is next, and is why nobody meets data of pass i - 2: what a task of pass i polls or writes was emptied by C / X
 // of pass i - 2 or A of pass i - 1 at the latest, A of pass i starts behind the counter of C(i-1), C(i-1) behind A(i-1)
 // (X(i-1)), and every other task of pass i behind data or a counter of A(i).
-// Tasks are drawn from a ticket per XCD in the order of the phases, and depend on earlier tickets only.  The earliest
-// unfinished task has been drawn by a workgroup that is running, and waits for nothing: the launch makes progress with any
-// number of resident workgroups, also beside other launches of this kind.  The rows of an XCD's tickets are their own, so the
-// XCDs do not wait for each other.  Every wait is bounded all the same (flow_turn): past the bound the status word reports it,
-// the waits of the other tasks end too, and the launch drains.
-// Visibility: what one workgroup writes for another in the same launch goes through loads and stores of device scope
-// (sc1), which do not stay in an L1 or in the L2 of one XCD.
+// Every eighth row is a set; a set belongs to one XCD, and its tasks are drawn from the set's ticket in the order of the
+// phases and depend on earlier tickets only.  The earliest unfinished task has been drawn by a workgroup that is running, and
+// waits for nothing: the launch makes progress with any number of resident workgroups, also beside other launches of this
+// kind.  The rows of a set are its own, so the XCDs do not wait for each other.  Every wait is bounded all the same
+// (flow_turn): past the bound the status word reports it, the waits of the other tasks end too, and the launch drains.
+// A workgroup asks the hardware which XCD it is on and takes the set of that number for it (owner word); a set whose XCD has
+// no workgroup of this launch for FLOW_LATE looks (another partition mode, an XCD busy with other work) is taken by one that
+// has none left, so every set is worked off, each by one XCD.
+// Visibility: what one workgroup writes for another in the same launch therefore meets in one L2.  Stores are plain (the L1
+// writes through), loads of device scope (sc1) pass the L1 by.  One way between two units of an XCD 0.26 us; with stores of
+// device scope, which go on to memory, 0.49 (0.65 to another XCD): one C2 environment 258 -> 230 us a round, four C4 914 -> 862.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -51,8 +55,9 @@ namespace tsdp {
 
 constexpr int FLOW_NAP = 3;                       // x 64 cycles between the first words of a store and all of them
 constexpr int FLOW_KINDS = 6;                     // counters of a row: one per kind of phase
-// lines of the tickets (one per XCD), of the word that ends all waits and of the counters of `rows` rows
-constexpr int FLOW_OVER_LINE = 8, FLOW_CNT_LINE = 9;
+constexpr int FLOW_LATE = 64;                     // looks at a set that nobody has taken (about half a microsecond each) before another XCD takes it
+// lines of the tickets (one per set), of the word that ends all waits, of the sets' owners and of the counters of `rows` rows
+constexpr int FLOW_SETS = 8, FLOW_OVER_LINE = 8, FLOW_OWNER_LINE = 9, FLOW_CNT_LINE = 17;
 inline int flow_lines(size_t rows) { return (int)(FLOW_CNT_LINE + rows * FLOW_KINDS); }
 constexpr int FLOW_STATUS = 16;                   // status bit: a wait ran into its bound
 
@@ -78,9 +83,9 @@ struct FlowCfg {
 };
 
 struct FlowIO {
-  int R_cap, groups, phases;     // groups: the rows of an XCD (every eighth) are dealt to this many tasks of a phase and slice
+  int R_cap, groups, phases;     // groups: the rows of a set are dealt to this many tasks of a phase and slice
   const int32_t* word;           // live row count; rollout: K_eff of every environment
-  int32_t* ticket; int32_t* over; int32_t* cnt; int32_t* status;
+  int32_t* ticket; int32_t* over; int32_t* owner; int32_t* cnt; int32_t* status;
   const float* x;                // latents of the rows
   const int32_t* row_t; const int32_t* row_env; int T;
   const float* mod; int mod_row, by_t;           // FiLM vectors: floats between rows; by_t: rows are timesteps
@@ -102,12 +107,12 @@ __device__ __forceinline__ void flow_st(__amdgpu_buffer_rsrc_t r, int off, f32x4
   flow_u4 w = __builtin_bit_cast(flow_u4, v);
 #pragma unroll
   for (int i = 0; i < 4; ++i) w[i] = flow_word(w[i]);
-  __builtin_amdgcn_raw_buffer_store_b128(w, r, off, 0, FLOW_SC1);
+  __builtin_amdgcn_raw_buffer_store_b128(w, r, off, 0, 0);
 }
 __device__ __forceinline__ void flow_st(__amdgpu_buffer_rsrc_t r, int off, bf16x4 v) {
   flow_u2 w = __builtin_bit_cast(flow_u2, v);
   w[0] = flow_word(w[0]); w[1] = flow_word(w[1]);
-  __builtin_amdgcn_raw_buffer_store_b64(w, r, off, 0, FLOW_SC1);
+  __builtin_amdgcn_raw_buffer_store_b64(w, r, off, 0, 0);
 }
 template <class F> __device__ __forceinline__ F flow_ld(__amdgpu_buffer_rsrc_t r, int off) {   // 16 or 8 bytes
   if constexpr (sizeof(F) == 16) return __builtin_bit_cast(F, (flow_u4)__builtin_amdgcn_raw_buffer_load_b128(r, off, 0, FLOW_SC1));
@@ -152,7 +157,33 @@ __device__ __forceinline__ void flow_sample(const FlowIO& io, __amdgpu_buffer_rs
 // empties `bytes` (a multiple of 16) at off
 __device__ __forceinline__ void flow_clear(__amdgpu_buffer_rsrc_t r, int off, int bytes, int tid, int threads) {
   for (int i = tid * 16; i < bytes; i += threads * 16)
-    __builtin_amdgcn_raw_buffer_store_b128(flow_u4{FLOW_EMPTY, FLOW_EMPTY, FLOW_EMPTY, FLOW_EMPTY}, r, off + i, 0, FLOW_SC1);
+    __builtin_amdgcn_raw_buffer_store_b128(flow_u4{FLOW_EMPTY, FLOW_EMPTY, FLOW_EMPTY, FLOW_EMPTY}, r, off + i, 0, 0);
+}
+
+__device__ __forceinline__ int flow_xcc() { return __builtin_amdgcn_s_getreg(20 | 3 << 11); }   // HW_REG_XCC_ID, 4 bits
+__device__ __forceinline__ int32_t flow_word_at(const int32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// (one thread) takes the set for the XCD: true if it is the XCD's now
+__device__ __forceinline__ bool flow_take(const FlowIO& io, int set, int xcc) {
+  int32_t had = 0;
+  __hip_atomic_compare_exchange_strong(io.owner + set * SYNC_LINE, &had, xcc + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return had == 0 || had == xcc + 1;
+}
+// (wavefront 0, all lanes) sets that have rows and no owner yet, as a mask
+__device__ __forceinline__ unsigned flow_free_sets(const FlowIO& io, int rows, int lane) {
+  const int n = min(rows, FLOW_SETS);
+  return (unsigned)__ballot(lane < n && flow_word_at(io.owner + min(lane, FLOW_SETS - 1) * SYNC_LINE) == 0);
+}
+// (wavefront 0) a set that nobody has taken although its own XCD had time to, or -1: all sets are in hand
+__device__ __forceinline__ int flow_late_set(const FlowIO& io, int rows, int xcc, int lane) {
+  for (int n = 0;; ++n) {
+    const unsigned open = flow_free_sets(io, rows, lane);
+    if (open == 0) return -1;
+    if (n >= FLOW_LATE) {
+      const int set = __ffs(open) - 1;
+      if (__builtin_amdgcn_readfirstlane(lane == 0 ? flow_take(io, set, xcc) : 0)) return set;
+    }
+    __builtin_amdgcn_s_sleep(8);
+  }
 }
 
 // wavefront 0 waits until counter `kind` of the row has reached `target`, the others at the barrier
@@ -425,25 +456,49 @@ __global__ __launch_bounds__(C::TH) void k_flow(FusedNet net, FlowIO io, std::co
   constexpr int D = C::D, H = C::H, DH = C::DH, NB = C::NB, KW = C::KW, KWM = C::KWM, CF = C::CF, VQ = C::VQ, VW = TT::VW, KSTEP = TT::KSTEP,
                 FS = C::FS, ES = sizeof(elem), KD = D / KSTEP, G = C::G;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  __shared__ int32_t drawn;
-  const int xcd = blockIdx.x % 8, rows = ROLL ? io.R_cap : min(*io.word, io.R_cap);
-  if (xcd >= rows) return;
-  int phases = io.phases;
-  if (ROLL) {                                            // the XCD's longest rollout and the phase that ends it
-    int k_max = 0;
-    for (int row = xcd; row < rows; row += 8) k_max = max(k_max, io.word[row]);
-    if (k_max == 0) return;
-    phases = min(phases, k_max * net.L * C::NPH + 1);
-  }
-  const int n_tasks = phases * io.groups * G, A = io.A;
+  __shared__ int32_t drawn[2];
+  const int xcc = flow_xcc();
+  const bool first_wave = threadIdx.x < 64;
+  int set = xcc % FLOW_SETS;
+  if (threadIdx.x == 0) drawn[1] = flow_take(io, set, xcc);
+  const int rows = ROLL ? io.R_cap : min(*io.word, io.R_cap), A = io.A;
+  if (rows == 0) return;
+  int phases = io.phases, n_tasks = 0;
+  auto enter = [&]() {                                   // the set's tasks; rollout: its longest one and the phase that ends it
+    if (ROLL) {
+      int k_max = 0;
+      for (int row = set; row < rows; row += FLOW_SETS) k_max = max(k_max, io.word[row]);
+      phases = k_max == 0 ? 0 : min(io.phases, k_max * net.L * C::NPH + 1);
+    }
+    n_tasks = set < rows ? phases * io.groups * G : 0;
+  };
+  lds_barrier();
+  if (__builtin_amdgcn_readfirstlane(drawn[1])) enter();
   for (;;) {
     lds_barrier();                                       // the task before has read its LDS
-    if (threadIdx.x == 0) drawn = __hip_atomic_fetch_add(io.ticket + xcd * SYNC_LINE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (first_wave) {
+      int ticket = 0;
+      if (threadIdx.x == 0 && n_tasks) ticket = __hip_atomic_fetch_add(io.ticket + set * SYNC_LINE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned open = flow_free_sets(io, rows, threadIdx.x);     // (travels with the ticket)
+      if (threadIdx.x == 0) { drawn[0] = ticket; drawn[1] = open; }
+    }
     lds_barrier();
-    const int ticket = __builtin_amdgcn_readfirstlane(drawn);
-    if (ticket >= n_tasks) return;
+    const int ticket = __builtin_amdgcn_readfirstlane(drawn[0]);
+    if (ticket >= n_tasks) {
+      if (__builtin_amdgcn_readfirstlane(drawn[1]) == 0) return;
+      lds_barrier();
+      if (first_wave) {
+        const int late = flow_late_set(io, rows, xcc, threadIdx.x);
+        if (threadIdx.x == 0) drawn[1] = late;
+      }
+      lds_barrier();
+      set = __builtin_amdgcn_readfirstlane(drawn[1]);
+      if (set < 0) return;
+      enter();
+      continue;
+    }
     const int slice = ticket % G, group = ticket / G % io.groups, phase = ticket / G / io.groups;
-    const int row0 = xcd + 8 * group, row_step = 8 * io.groups;
+    const int row0 = set + FLOW_SETS * group, row_step = FLOW_SETS * io.groups;
     if (row0 >= rows) continue;
     const int pass = phase / C::NPH, layer = pass % net.L, k = ROLL ? pass / net.L + 1 : 1;   // k: the drafted transition
     const bool end = !ROLL && pass == net.L;             // behind the last layer
@@ -558,7 +613,7 @@ __global__ __launch_bounds__(C::TH) void k_flow(FusedNet net, FlowIO io, std::co
                   *reinterpret_cast<f32x4*>(dr.eps_p + o_row + 4 * i) = ev;
                   if (dr.xi) *reinterpret_cast<f32x4*>(dr.xi + o_row + 4 * i) = zv;
                   float* yo = (ends ? dr.y : io.y[k & 1]) + (size_t)row * (H * A);
-                  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(flow_u4, o), flow_rsrc(yo, H * A * 4), i * 16, 0, FLOW_SC1);
+                  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(flow_u4, o), flow_rsrc(yo, H * A * 4), i * 16, 0, 0);
                   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // complete before this task's q | k | v (barriers between)
                 }
               }

@@ -409,7 +409,7 @@ template <class C, bool ROLL>
 void flow_launch(const FusedNet& n, const FewRun& r, FlowIO& io, const std::conditional_t<ROLL, DraftIO, FewNone>& dr, int phases, hipStream_t s) {
   const int per_xcd = (r.R_cap + 7) / 8, lds = flow_lds<C, ROLL>(r.A, r.R_cap);
   io.R_cap = r.R_cap; io.phases = phases; io.groups = std::min(per_xcd, FLOW_GROUPS);
-  io.ticket = r.sync; io.over = r.sync + FLOW_OVER_LINE * SYNC_LINE; io.cnt = r.sync + FLOW_CNT_LINE * SYNC_LINE; io.status = r.status;
+  io.ticket = r.sync; io.over = r.sync + FLOW_OVER_LINE * SYNC_LINE; io.owner = r.sync + FLOW_OWNER_LINE * SYNC_LINE; io.cnt = r.sync + FLOW_CNT_LINE * SYNC_LINE; io.status = r.status;
   io.x = r.x; io.row_t = r.row_t; io.row_env = r.row_env; io.T = r.T; io.A = r.A;
   io.mod = r.mod; io.mod_row = n.L * 4 * C::D; io.by_t = n.modtab != nullptr;
   io.buf = r.buf; io.eps_out = r.eps_out;
