@@ -90,6 +90,19 @@ inline bool few_dyn_pays(size_t tokens, size_t heads, size_t layer_bytes) {
                                     : tokens * std::max<size_t>(heads, 16) <= 16384;
 }
 
+// One workgroup per row or environment through all layers (k_row) instead of launches, for networks with run-time sizes.
+// A unit's time for a layer grows with its weights times the fragments of 16 tokens (fp32 matrix rate), and not with the rows
+// until every unit has one; a launch costs the same for any small layer, and grows with the rows.  Two layers, us, launches / one
+// workgroup a row; tsdp_verify of 8, 256, 512 rows of 16 tokens: d = 48 (0.1 MB a layer) 43 / 23, 68 / 23, 111 / 31; d = 96 (0.44 MB)
+// 51 / 40, 122 / 42, 222 / 62; d = 128 (0.79 MB) 56 / 50, 125 / 54, 230 / 83; d = 160 (1.2 MB) 65 / 77, 213 / 82, 381 / 126;
+// d = 256 (3.1 MB) 90 / 164, 304 / 165.  tsdp_draft of one layer, eight transitions of 1, 64 environments: 170 / 76, 167 / 79;
+// 214 / 134, 215 / 137; 234 / 178, 239 / 182; d = 160 272 / 285, 301 / 291.  32 tokens, verify of 8, 256 rows: d = 96 72 / 62,
+// 287 / 65, d = 128 82 / 86, 290 / 88.
+inline bool row_pays(size_t tokens, size_t H, size_t layer_bytes) {
+  const size_t work = layer_bytes * H / 16;
+  return work <= 900000 || (work <= 1600000 && tokens >= 1024);
+}
+
 // Floats of the two residual and of the two partial-sum buffers, shared by both networks.  Which networks take the spread
 // path can change with every tsdp_load_weights, so what a context holds is compared with what its networks need now, and
 // replaced by a larger buffer where it is too small.

@@ -16,6 +16,7 @@
 #include "cond_kernels.hpp"
 #include "few_plan.hpp"
 #include "few_rows.hpp"
+#include "row_dyn.hpp"
 #include "flow_rows.hpp"
 #include "round_kernels.hpp"
 
@@ -67,7 +68,7 @@ struct Net {
   void (*few_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr;
   void (*few_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;
   void (*few_film)(const FusedNet&, const int32_t*, int, const int32_t*, int, int, const int32_t*, const int32_t*, int, float*, hipStream_t) = nullptr;
-  int few_slices = 0;           // partial sums per row
+  int few_slices = 0;           // partial sums per row, 0: none (k_row)
   size_t flow_row = 0;          // bytes of a row's buffers (k_flow), 0: two launches per layer (k_few_*)
   float* tok_wt = nullptr;      // [A, d] token embedding, transposed
   uint16_t* kc_pk = nullptr;    // fragment-ordered bf16 keys / transposed values of every (env, layer, head)
@@ -440,6 +441,23 @@ void flow_draft(const FusedNet& n, const FewRun& r, const DraftIO& dr, int k_max
   flow_launch<C, true>(n, rr, io, dr, k_max * n.L * C::NPH + 1, s);
 }
 
+// Run-time sizes, one workgroup per row or environment (k_row)
+template <int NB>
+RowIO row_io(const FusedNet& n, const FewRun& r, int k_max) {
+  const unsigned cf = n.D / n.heads / 16;
+  return RowIO{RowDiv(cf), RowDiv(3 * cf), RowDiv(n.D / 4), r.d_R, r.R_cap, r.A, NB * 16, n.D / n.heads, k_max, r.x, r.mod, r.eps_out};
+}
+template <int NB>
+void row_forward(const FusedNet& n, const FewRun& r, hipStream_t s) {
+  hipLaunchKernelGGL((k_row<NB, false>), dim3(r.R_cap), dim3(ROW_TH), row_lds(n.D, NB * 16, n.M, r.A, false).total * 4, s, n,
+                     row_io<NB>(n, r, 0), FewNone{});
+}
+template <int NB>
+void row_draft(const FusedNet& n, const FewRun& r, const DraftIO& dr, int k_max, float* const*, hipStream_t s) {
+  hipLaunchKernelGGL((k_row<NB, true>), dim3(r.R_cap), dim3(ROW_TH), row_lds(n.D, NB * 16, n.M, r.A, true).total * 4, s, n,
+                     row_io<NB>(n, r, k_max), dr);
+}
+
 struct FusedKernels {
   void (*few_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr;
   void (*few_draft)(const FusedNet&, const FewRun&, const DraftIO&, int, float* const*, hipStream_t) = nullptr;
@@ -537,8 +555,16 @@ inline size_t dyn_tokens(const tsdp_config& cf, int which) {
   return (which == 1 && !twin_nets(cf) ? (size_t)cf.B_max : rows_max(cf)) * cf.H;
 }
 
-// Shapes without a compiled kernel: the spread kernels with run-time sizes where few_dyn_pays says so (vector conditioning,
-// sizes in fragments of 16, a row's operands in the LDS; 48 and 64 tokens would spill the residual).
+// Shapes without a compiled kernel: the kernels with run-time sizes where few_dyn_pays says so (vector conditioning, sizes in
+// fragments of 16, a row's operands in the LDS; 48 and 64 tokens would spill the residual): one workgroup per row where row_pays
+// says so, else the spread ones.
+template <int NB>
+hipError_t row_kernels(FusedKernels& k) {
+  k.few_forward = row_forward<NB>; k.few_draft = row_draft<NB>; k.few_film = launch_few_film<TF32, 0>;
+  for (const void* f : {(const void*)k_row<NB, false>, (const void*)k_row<NB, true>, (const void*)k_few_film<TF32, 0>})
+    if (hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)) return e;
+  return hipSuccess;
+}
 template <class C>
 hipError_t few_dyn_kernels(FusedKernels& k) {
   k.few_forward = few_forward<C>; k.few_draft = few_draft<C>; k.few_film = launch_few_film<TF32, 0>;
@@ -550,10 +576,15 @@ hipError_t few_dyn_kernels(FusedKernels& k) {
 
 hipError_t find_few_dyn(const tsdp_config& cf, int which, const Net& n, FusedKernels& k) {
   const int dh = n.d / n.heads, ch = n.m % 16 ? 0 : n.m / few_slices_dyn(n.m);
+  const size_t bytes = 4 * ((size_t)4 * n.d * n.d + (size_t)2 * n.d * n.m);
   if (cf.cond_mode != 0 || (cf.H != 16 && cf.H != 32) || n.d % 16 || dh % 16 || n.m % 16 || n.L > FUSED_MAX_LAYERS ||
       few_lds_attn<TF32>(n.d, cf.H, dh) + FEW_STEP_LDS > 160 * 1024 || few_lds_mlp<TF32>(n.d, cf.H, ch) > 160 * 1024 ||
-      !few_dyn_pays(dyn_tokens(cf, which), n.heads, 4 * ((size_t)4 * n.d * n.d + (size_t)2 * n.d * n.m)))
+      !few_dyn_pays(dyn_tokens(cf, which), n.heads, bytes))
     return hipSuccess;
+  // (twins: both of them or neither)
+  if (row_pays(dyn_tokens(cf, which), cf.H, bytes) && n.d <= ROW_MAX_D && 5 * n.d + n.m <= ROW_MAX_BIAS &&
+      row_lds(n.d, cf.H, n.m, cf.A, true).total * 4 <= 160 * 1024)
+    return cf.H == 16 ? row_kernels<1>(k) : row_kernels<2>(k);
   k.few_slices = std::max(n.heads, few_slices_dyn(n.m));
   return cf.H == 16 ? few_dyn_kernels<FewDyn<1>>(k) : few_dyn_kernels<FewDyn<2>>(k);
 }
@@ -597,7 +628,9 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   const int d = n.d, m = n.m, L = n.L, DH = d / n.heads;
   const bool dyn = !fk.verify, f32 = dyn || cf.dtype == 0;   // run-time sizes: fp32 operands, as in the operator kernels
   std::vector<uint8_t> pk;
-  std::vector<float> qb((size_t)L * 3 * d);
+  // q|k|v biases of a layer; run-time sizes: the other biases behind them (output projection, down, up)
+  const size_t nb = dyn ? 5 * (size_t)d + m : 3 * (size_t)d;
+  std::vector<float> qb(L * nb);
   struct Off { size_t qkv, o, up, dn, cq, co; };
   std::vector<Off> off(L);
   auto ident = [](int r) { return r; };
@@ -609,7 +642,12 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
       return cls * d + head * DH + cdim;
     };
     off[l].qkv = pk.size(); pack_frags(pk, f32, &w[o.qkv_w], d, 3 * d, qkv_row);
-    for (int lr = 0; lr < 3 * d; ++lr) qb[(size_t)l * 3 * d + lr] = w[o.qkv_b + qkv_row(lr)];
+    for (int lr = 0; lr < 3 * d; ++lr) qb[l * nb + lr] = w[o.qkv_b + qkv_row(lr)];
+    if (dyn) {
+      std::copy_n(&w[o.o_b], d, &qb[l * nb + 3 * d]);
+      std::copy_n(&w[o.dn_b], d, &qb[l * nb + 4 * d]);
+      std::copy_n(&w[o.up_b], m, &qb[l * nb + 5 * d]);
+    }
     off[l].o = pk.size(); pack_frags(pk, f32, &w[o.o_w], d, d, ident);
     off[l].up = pk.size(); pack_frags(pk, f32, &w[o.up_w], d, m, ident);
     off[l].dn = pk.size(); pack_frags(pk, f32, &w[o.dn_w], m, d, ident);
@@ -637,7 +675,7 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
     const LayerOff& o = n.lay[l];
     FusedLayer& fl = f.layer[l];
     fl.qkv = P(off[l].qkv); fl.o = P(off[l].o); fl.up = P(off[l].up); fl.dn = P(off[l].dn);
-    fl.qkv_b = dqb + (size_t)l * 3 * d;
+    fl.qkv_b = dqb + l * nb;
     fl.o_b = n.blob + o.o_b; fl.up_b = n.blob + o.up_b; fl.dn_b = n.blob + o.dn_b;
     if (cf.cond_mode == 1) {
       fl.cq = P(off[l].cq); fl.co = P(off[l].co);
@@ -836,7 +874,7 @@ int ensure_few(tsdp_ctx* c) {
   const tsdp_config& cf = c->cfg;
   int rc;
   const Net &bn = c->net[0], &dn = c->net[1];
-  auto shape = [&](const Net& n, int which) { return FewShape{n.few && !n.flow_row, n.fused ? rows_max(cf) * cf.H : dyn_tokens(cf, which), (size_t)n.d, (size_t)n.few_slices}; };
+  auto shape = [&](const Net& n, int which) { return FewShape{n.few && !n.flow_row && n.few_slices, n.fused ? rows_max(cf) * cf.H : dyn_tokens(cf, which), (size_t)n.d, (size_t)n.few_slices}; };
   const FewSize need = few_size(shape(bn, 0), shape(dn, 1));
   if (!few_fits(c->few_have, need)) {                  // (buffers that are replaced live as long as the context: a graph may hold them)
     const FewSize z{std::max(need.h, c->few_have.h), std::max(need.part, c->few_have.part)};

@@ -16,6 +16,7 @@ int pays(long tokens, int f32, long layer_bytes) { return few_pays(tokens, f32 !
 int draft_pays(int environments, int f32, long d, int layers, int K_max, int launches) { return flow_draft_pays(environments, f32 != 0, d, layers, K_max, launches != 0); }
 int forward_pays(long tokens, int f32, long d, int layers) { return flow_forward_pays(tokens, f32 != 0, d, layers); }
 int dyn_pays(long tokens, long heads, long layer_bytes) { return few_dyn_pays(tokens, heads, layer_bytes); }
+int one_workgroup_pays(long tokens, long H, long layer_bytes) { return row_pays(tokens, H, layer_bytes); }
 // polls of one workgroup's `waits` waits, one after the other, for data that never arrives
 long drain(int waits) {
   long polls = 0;
@@ -96,6 +97,13 @@ def test_run_time_sizes_are_spread_only_where_that_is_faster(plan):
     for d, heads, rows in ((64, 4, 1024), (96, 3, 1024), (256, 16, 1024), (320, 20, 256), (512, 32, 256), (640, 20, 256),
                            (1024, 32, 64), (1024, 8, 128), (1024, 16, 512), (1024, 64, 2048)):
         assert not pays(d, heads, rows), (d, heads, rows)
+
+
+def test_a_row_per_workgroup_only_where_that_is_faster(plan):
+    # (d, tokens of a row, rows, one workgroup per row was the faster one): both sides measured on networks of two layers
+    for d, H, rows, faster in ((48, 16, 8, 1), (96, 16, 512, 1), (128, 16, 8, 1), (160, 16, 8, 0), (160, 16, 256, 1), (256, 16, 8, 0),
+                               (96, 32, 8, 1), (128, 32, 8, 0), (128, 32, 256, 1)):
+        assert plan.one_workgroup_pays(C.c_long(H * rows), C.c_long(H), C.c_long(12 * d * d * 4)) == faster, (d, H, rows)
 
 
 def test_compiled_kernels_are_spread_up_to_2048_and_2176_tokens(plan):

@@ -1,0 +1,42 @@
+"""One workgroup per row for networks with run-time sizes (csrc/row_dyn.hpp), at the sizes where its blocks, fragments and
+vectors end, against the fp64 oracle."""
+import numpy as np
+import pytest
+
+import tsdp_inputs as ti
+from tests.helpers import gpu_side, to_dev
+from tests.test_gpu_parity import _stage_parity
+
+pytestmark = pytest.mark.gpu
+N = ti.NetShape
+
+
+@pytest.mark.parametrize("H, A, base, draft, B, K_max", [
+    (16, 4, N(2, 96, 3), N(1, 48, 3), 5, 8),             # six and three k-steps; more wavefronts than fragment rows
+    (16, 30, N(1, 112, 7), N(3, 16, 1), 3, 5),           # seven k-steps, heads of one fragment, two fragment rows of the head; one k-step
+    (16, 5, N(1, 144, 3, 2), N(1, 128, 1), 2, 3),        # nine k-steps: a block and one; a head of eight fragments
+    (32, 16, N(2, 80, 5, 3), N(1, 64, 2), 4, 4),         # two token fragments, hidden width of 15 fragments; the most latents of a row
+    (16, 4, N(2, 160, 5), N(1, 160, 2), 64, 1),          # tokens enough for larger layers: a second vector on some lanes
+    (16, 4, N(16, 32, 2), N(16, 48, 3), 1, 2),           # the most layers
+])
+@pytest.mark.parametrize("bonus, clip, norm", [(False, None, 0), (True, 1.5, 1)])
+def test_one_workgroup_per_row(H, A, base, draft, B, K_max, bonus, clip, norm):
+    wl = ti.small_variant(ti.C2, H=H, A=A, cond_dim=32, B=B, K_max=K_max, base=base, draft=draft)
+    rng = np.random.default_rng(B)
+    t0 = rng.integers(0, wl.T, B); K = rng.integers(1, K_max + 1, B); s = rng.uniform(1.0, 1.5, B)
+    t0[0] = wl.T - 1; K[0] = K_max
+    if B > 2:
+        t0[1], t0[2] = 0, -1                             # a lone base step; a finished environment
+    _stage_parity(wl, B, t0, K, s, clip=clip, norm=norm, bonus=bonus)
+
+
+def test_equal_networks_predict_the_same():
+    wl = ti.small_variant(ti.C2, A=6, cond_dim=32, B=3, K_max=5, base=N(2, 96, 3), draft=N(2, 96, 3))
+    w = ti.make_weights(wl, "base", b_std=0.02)
+    ctx = gpu_side(wl, w, w, ti.make_cond(wl, 3), B_max=3)
+    rows = ctx.alloc_rows(3)
+    ctx.tsdp_draft(to_dev(ti.make_latents(wl, 3)), to_dev(np.array([99, 50, 9], np.int32)), to_dev(np.full(3, 5, np.int32)),
+                   to_dev(np.ones(3, np.float32)), None, rows)
+    ctx.tsdp_verify(3, rows)
+    assert bool((rows["eps_p"][:15] == rows["eps_q"][:15]).all())
+    ctx.close()
