@@ -44,6 +44,8 @@ struct FewCfg {
   static constexpr int NW = WIDE ? 8 : 4, TH = NW * 64;
   static constexpr int NPA = WIDE ? 0 : HEADS, NPM = WIDE ? 0 : NCH;   // partial sums an attention / MLP block leaves
   static constexpr int JV = (D / 4 + 63) / 64;    // 16-byte vectors per lane and token
+  // MLP workgroups of a unit: two where they fit (136 rows are 544 of them; d = 256 in bf16 with 264 registers 435 us a round, 256 425)
+  static constexpr int MLP_WGS = sizeof(typename TT::elem) == 2 && H == 16 && D <= 256 ? 2 : 1;
   static_assert(D % 32 == 0 && H % 16 == 0 && CH % TT_::KSTEP == 0 && CH % 16 == 0 && DH % TT_::KSTEP == 0, "shape");
 };
 
@@ -53,7 +55,7 @@ template <int NB_>
 struct FewDyn {
   typedef TF32 TT;
   static constexpr bool DYN = true, WIDE = false;
-  static constexpr int D = 0, H = NB_ * 16, HEADS = 0, SX = 0, NCH = 0, DH = 0, CH = 0, NB = NB_, JV = 4, NW = 4, TH = 256;
+  static constexpr int D = 0, H = NB_ * 16, HEADS = 0, SX = 0, NCH = 0, DH = 0, CH = 0, NB = NB_, JV = 4, NW = 4, TH = 256, MLP_WGS = 1;
   static constexpr int NPA = 1, NPM = 1;           // (the number is in FewIO)
 };
 
@@ -360,6 +362,13 @@ struct FewGemm {
   static constexpr int DEEP0 = (C::NW == 4 ? 40 : 20) / MB, DEEP = DEEP0 < 1 ? 1 : DEEP0;
   typedef FragGemm<TT, MB, C::NB, NKS, 2, DEEP> G;
   G g;
+  f32x4 bias[MB];
+  // requested ahead of the weights: in the epilogue nothing covers its way through the L2 (with k_few_out's residual: rounds of
+  // four C4 environments 846 -> 765 us, eight C2 448 -> 424, a plain chain of eight C3 13.05 -> 12.37 ms)
+  __device__ __forceinline__ void with_bias(const float* b, int wave, int lane) {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) bias[mb] = *reinterpret_cast<const f32x4*>(b + min(wave + mb * C::NW, MF - 1) * 16 + (lane >> 4) * 4);
+  }
   __device__ __forceinline__ void begin(const void* w, int ks_total, int mf0, int ks0, int wave, int lane) {
     // a wave without a last fragment repeats its first one (its result is dropped): every load stays inside the slice
     g.prime_begin(w, ks_total, mf0 + min(wave, MF - 1), ks0, lane, wave + (MB - 1) * C::NW < MF ? C::NW : 0);
@@ -367,7 +376,7 @@ struct FewGemm {
     for (int p = 0; p < G::PF; ++p) g.prime_stage(p);
     asm volatile("" ::: "memory");
   }
-  template <class E>
+  template <bool BIAS = false, class E>
   __device__ __forceinline__ void run(const typename TT::elem* act, int stride, int wave, int lane, E&& epi) {
     f32x4 acc[MB][C::NB];
 #pragma unroll
@@ -378,6 +387,10 @@ struct FewGemm {
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       const int f = wave + mb * C::NW;
+      if (BIAS) {
+#pragma unroll
+        for (int nb = 0; nb < C::NB; ++nb) acc[mb][nb] += bias[mb];
+      }
       if (MF % C::NW == 0 || f < MF) epi(f, acc[mb]);
     }
   }
@@ -498,7 +511,13 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_attn(FewIO io, std::conditiona
   typedef FewGemm<C, ST ? 3 * C::DH / 16 : 4, ST ? C::D / KSTEP : 1> GQ;
   typedef FewGemm<C, ST ? C::D / 16 : 4, ST ? C::DH / KSTEP : 1> GO;
   GQ gq;
-  auto weights = [&]() { if constexpr (ST) gq.begin(io.w1, KD, head * (3 * DH / 16), 0, wave, lane); };
+  const float* bq = io.b1 + head * 3 * DH;
+  auto weights = [&]() {
+    if constexpr (ST) {
+      gq.with_bias(bq, wave, lane);
+      gq.begin(io.w1, KD, head * (3 * DH / 16), 0, wave, lane);
+    }
+  };
   FewRes<C> v;
   FewFilm<C> fm;
   fm.load(io, row, me.t, lane);
@@ -558,13 +577,11 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_attn(FewIO io, std::conditiona
   few_norm<C>(io, fm, wave, lane, v, act, AS);
   if (head == 0 && (NP != 0 || STEP)) few_store_residual<C>(io, row, wave, lane, v);
   lds_barrier();
-  const float* bq = io.b1 + head * 3 * DH;
   auto epi_qkv = [&](int f, const f32x4 (&acc)[NB]) {
     const int lr = f * 16, cls = lr / DH, c0 = lr % DH + lg * 4;
-    const f32x4 b = *reinterpret_cast<const f32x4*>(bq + lr + lg * 4);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const f32x4 r = acc[nb] + b;
+      const f32x4 r = C::DYN ? acc[nb] + *reinterpret_cast<const f32x4*>(bq + lr + lg * 4) : acc[nb];
       const int t = nb * 16 + l16;
       if (cls < 2) {
         *reinterpret_cast<vec4*>((cls ? k : q) + t * QS + c0) = TT::cvt(r);
@@ -576,7 +593,7 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_attn(FewIO io, std::conditiona
   };
   GO go;
   if constexpr (ST) {
-    gq.run(act, AS, wave, lane, epi_qkv);
+    gq.template run<true>(act, AS, wave, lane, epi_qkv);
     if constexpr (!C::WIDE) go.begin(io.w2, KD, 0, head * KH, wave, lane);   // travels during the attention
   } else {
     few_gemm_dyn<NB>(io.w1, KD, head * (3 * DH / 16), 3 * DH / 16, 0, KD, reinterpret_cast<const float*>(act), AS, wave, lane, epi_qkv);
@@ -629,7 +646,10 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_cross(FewIO io) {
   FewGemm<C, DH / 16, KD> gq;
   FewGemm<C, D / 16, KH> go;
   FewRes<C> v;
-  few_residual<C, NP>(io, row, wave, lane, v, [&]() { gq.begin(io.w1, KD, head * (DH / 16), 0, wave, lane); });
+  few_residual<C, NP>(io, row, wave, lane, v, [&]() {
+    gq.with_bias(io.b1 + head * DH, wave, lane);
+    gq.begin(io.w1, KD, head * (DH / 16), 0, wave, lane);
+  });
   if (!me.live) return;
   FewFilm<C> fm;
   fm.none();
@@ -652,11 +672,10 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_cross(FewIO io) {
       for (int kf = 0; kf < SF; ++kf) va[cf][kf] = vp[(cf * SF + kf) * 64];
   }
   lds_barrier();
-  gq.run(act, AS, wave, lane, [&](int f, const f32x4 (&acc)[NB]) {
-    const f32x4 b = *reinterpret_cast<const f32x4*>(io.b1 + head * DH + f * 16 + lg * 4);
+  gq.template run<true>(act, AS, wave, lane, [&](int f, const f32x4 (&acc)[NB]) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
-      *reinterpret_cast<bf16x4*>(q + (nb * 16 + l16) * QS + f * 16 + lg * 4) = to_bf16x4(acc[nb] + b);
+      *reinterpret_cast<bf16x4*>(q + (nb * 16 + l16) * QS + f * 16 + lg * 4) = to_bf16x4(acc[nb]);
   });
   if constexpr (!C::WIDE) go.begin(io.w2, KD, 0, head * KH, wave, lane);
   lds_barrier();
@@ -688,7 +707,7 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_cross(FewIO io) {
 }
 
 template <class C, int NP>
-__global__ __launch_bounds__(C::TH, 1) void k_few_mlp(FewIO io) {
+__global__ __launch_bounds__(C::TH, C::MLP_WGS) void k_few_mlp(FewIO io) {
   typedef typename C::TT TT;
   typedef typename TT::elem elem;
   constexpr int H = C::H, NB = C::NB, KSTEP = TT::KSTEP;
@@ -708,16 +727,20 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_mlp(FewIO io) {
   FewRes<C> v;
   FewFilm<C> fm;
   fm.load(io, row, me.t, lane);
-  few_residual<C, NP>(io, row, wave, lane, v, [&]() { if constexpr (ST) gu.begin(io.w1, KD, slice * (CH / 16), 0, wave, lane); });
+  few_residual<C, NP>(io, row, wave, lane, v, [&]() {
+    if constexpr (ST) {
+      gu.with_bias(io.b1 + slice * CH, wave, lane);
+      gu.begin(io.w1, KD, slice * (CH / 16), 0, wave, lane);
+    }
+  });
   if (!me.live) return;
   few_norm<C>(io, fm, wave, lane, v, act, AS);
   if (slice == 0 && NP != 0) few_store_residual<C>(io, row, wave, lane, v);
   lds_barrier();
   auto epi_up = [&](int f, const f32x4 (&acc)[NB]) {
-    const f32x4 b = *reinterpret_cast<const f32x4*>(io.b1 + slice * CH + f * 16 + lg * 4);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      f32x4 r = acc[nb] + b;
+      f32x4 r = C::DYN ? acc[nb] + *reinterpret_cast<const f32x4*>(io.b1 + slice * CH + f * 16 + lg * 4) : acc[nb];
 #pragma unroll
       for (int i = 0; i < 4; ++i) r[i] = C::DYN ? gelu_tanh_f(r[i]) : gelu_fast(r[i]);
       if constexpr (C::WIDE) few_store_act<C>(io, row, nb * 16 + l16, M, slice * CH + f * 16 + lg * 4, TT::cvt(r));
@@ -725,7 +748,7 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_mlp(FewIO io) {
     }
   };
   if constexpr (ST) {
-    gu.run(act, AS, wave, lane, epi_up);
+    gu.template run<true>(act, AS, wave, lane, epi_up);
     if constexpr (C::WIDE) return;
     else gd.begin(io.w2, KM, 0, slice * KC, wave, lane);
   } else {
@@ -771,9 +794,10 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_out(FewIO io) {
   int slice, row;
   few_place(io, SL, slice, row);
   const FewRow me = few_row(io, row);
-  if (!me.live) return;
+  if (row >= io.safe_rows && !me.live) return;           // (below that: decided once the first loads are under way)
   const frag* wl = reinterpret_cast<const frag*>(io.w2) + ((size_t)slice * 4 * KS + wave * KW) * 64 + lane;
-  const typename TT::elem* al = reinterpret_cast<const typename TT::elem*>(io.part_in) + ((size_t)row * H + l16) * K +
+  const int row_in = min(row, io.R_cap - 1);
+  const typename TT::elem* al = reinterpret_cast<const typename TT::elem*>(io.part_in) + ((size_t)row_in * H + l16) * K +
                                 wave * KW * TT::KSTEP + lg * TT::VW;
   f32x4 acc[4][NB];
 #pragma unroll
@@ -781,6 +805,9 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_out(FewIO io) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0, 0, 0, 0};
   constexpr int U = KW < 8 ? KW : 8;                     // k-steps in flight
+  // the thread's share of the residual and of the bias, requested behind the first operands
+  constexpr int NJ = H * 64 / (C::TH * 4);
+  f32x4 res[NJ], bias[NJ];
 #pragma unroll
   for (int k0 = 0; k0 < KW; k0 += U) {
     frag a[U][4], b[U][NB];
@@ -791,7 +818,17 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_out(FewIO io) {
 #pragma unroll
       for (int mb = 0; mb < 4; ++mb) a[u][mb] = wl[((size_t)mb * KS + k0 + u) * 64];
     }
+    if (k0 == 0) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int i = threadIdx.x + j * C::TH;
+        res[j] = *reinterpret_cast<const f32x4*>(io.h_in + ((size_t)row_in * H + i / 16) * D + slice * 64 + i % 16 * 4);
+        bias[j] = *reinterpret_cast<const f32x4*>(io.bias_in + slice * 64 + i % 16 * 4);
+      }
+      asm volatile("" ::: "memory");
+    }
     __builtin_amdgcn_sched_barrier(0);
+    if (k0 == 0 && !me.live) return;
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -806,10 +843,10 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_out(FewIO io) {
       *reinterpret_cast<f32x4*>(at(wave, nb * 16 + l16, mb * 16 + lg * 4)) = acc[mb][nb];
   lds_barrier();
 #pragma unroll
-  for (int j = 0; j < H * 64 / (C::TH * 4); ++j) {
+  for (int j = 0; j < NJ; ++j) {
     const int i = threadIdx.x + j * C::TH, tok = i / 16, c = (i % 16) * 4;
     const size_t o = ((size_t)row * H + tok) * D + slice * 64 + c;
-    f32x4 v = *reinterpret_cast<const f32x4*>(io.h_in + o) + *reinterpret_cast<const f32x4*>(io.bias_in + slice * 64 + c);
+    f32x4 v = res[j] + bias[j];
 #pragma unroll
     for (int w = 0; w < C::NW; ++w) v += *reinterpret_cast<const f32x4*>(at(w, tok, c));
     *reinterpret_cast<f32x4*>(io.h_out + o) = v;
