@@ -65,6 +65,9 @@ inline bool flow_draft_pays(int environments, bool f32, size_t d, int layers, in
 // 4, 16, 32 rows 317 / 243, 634 / 579, 642 / 675 (328 / 363 with four drafts).  Two workgroups per unit at d = 256 meet at 32 rows
 // (256 / 251) and lose 5 % at 16.  tsdp_verify of one layer, d = 256, 8, 10, 12, 16 rows 24.3 / 22.6, 24.2 / 23.8, 23.9 / 24.1, 24.1 / 24.9
 // (two layers, 16 rows 37 / 34), d = 384, 16 rows 36 / 31.
+// With cross-attention (d = 512, 32 tokens), tsdp_verify of 1, 8, 9, 16 rows: one layer 46 / 42, 50 / 47, 51 / 62; two 81 / 65, 88 / 70,
+// 88 / 105; twelve 445 / 289, 462 / 307, 466 / 504, 472 / 524 (one group of tasks that take two rows in turn 466): beyond one row an XCD
+// every further one adds the 3 us of a task to each of the phases.
 inline bool flow_forward_pays(size_t tokens, bool f32, size_t d, int layers) {
   if (!f32) return tokens <= (layers * d >= 384 ? 256 : 160);
   return tokens <= 16 * (d >= 256 ? (layers >= 4 ? 56 : 40) : (layers >= 4 ? 16 : 8));

@@ -9,7 +9,8 @@
 //   head     LayerNorm -> output projection; in a rollout the sampler step, done by phase A of the next transition
 //
 // For the fewest rows (flow_forward_pays, flow_draft_pays): fp32 networks, whose products are worth sixteen units a row, rollouts
-// with cross-attention, and bf16 networks with a conditioning vector (one environment, d = 256, K = 8: round 250 -> 214 us).
+// with cross-attention, and bf16 networks (one environment, K = 8: d = 256 with a conditioning vector round 250 -> 214 us, d = 512
+// with cross-attention 773 -> 577).
 // What bounds a few rows is the chain of dependent steps, not their work.  With two launches per layer a step was 6 to
 // 12 us: 2.4 us between dependent launches, the weights requested only then, and partial sums of the whole row (up to 272 KB)
 // read by every workgroup.  Here a step is an exchange of 16 to 64 KB through the L2 (1 to 1.5 us), workgroups of the
@@ -78,7 +79,11 @@ struct FlowCfg {
   static constexpr int O_E = 0, O_H0 = HB, O_H1 = 2 * HB, O_H2 = SX ? 3 * HB : O_H1, O_Q = O_H2 + HB, O_U = O_Q + 3 * XB, O_XQ = O_U + 4 * XB,
                        SET_B = O_XQ + (SX ? XB : 0);
   static constexpr int STAT_B = 2 * NW * H * 4, RED_B = NW * 4 * FS * NB * 1024, STEP_B = 2 * 512 * 4;
-  static constexpr int lds(int A) { return STAT_B + RED_B + STEP_B + D * A * 4; }
+  // LDS: statistics, sums, a step's outputs and latents, token embedding.  Wide rows: the embedding (32 KB) lies over the last quarter
+  // of the sums, which phase A does not use: all of it would be 165 KB.
+  static constexpr bool WIDE = D * H >= FEW_WIDE;
+  static constexpr int O_ET = WIDE ? STAT_B : STAT_B + RED_B, O_RED = WIDE ? STAT_B + STEP_B : STAT_B, O_TOK = WIDE ? O_RED + RED_B / 4 * 3 : O_ET + STEP_B;
+  static constexpr int lds(int A) { return O_TOK + D * A * 4 > O_RED + RED_B ? O_TOK + D * A * 4 : O_RED + RED_B; }
   static_assert(DH % TT::KSTEP == 0 && H % 16 == 0 && D % (16 * FS) == 0, "shape");
 };
 
@@ -240,10 +245,10 @@ struct FlowTask {
   __device__ FlowTask(const FusedNet& n, const FlowIO& i, int s, int t, unsigned char* lds)
       : net(n), io(i), slice(s), tid(t), wave(__builtin_amdgcn_readfirstlane(t >> 6)), lane(t & 63), l16(t & 15), lg((t & 63) >> 4) {
     stat = reinterpret_cast<float*>(lds);
-    red = reinterpret_cast<f32x4*>(lds + C::STAT_B);
-    et = reinterpret_cast<float*>(lds + C::STAT_B + C::RED_B);
+    red = reinterpret_cast<f32x4*>(lds + C::O_RED);
+    et = reinterpret_cast<float*>(lds + C::O_ET);
     yt = et + 512;
-    tokw = yt + 512;
+    tokw = reinterpret_cast<float*>(lds + C::O_TOK);
   }
   __device__ int col(int ks, int q) const { return wave * DH + ks * KSTEP + lg * VW + q * 4; }
   __device__ __amdgpu_buffer_rsrc_t bufs(int row, int pass) const {

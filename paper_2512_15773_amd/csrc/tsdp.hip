@@ -485,7 +485,7 @@ void spread_kernels(FusedKernels& k) {
   if constexpr (layer_bytes(D, F32, SX > 0) >= FEW_LAYER_BYTES) {
     typedef FewCfg<TT, D, H, HEADS, SX> F;
     k.few_forward = few_forward<F>; k.few_draft = few_draft<F>; k.few_slices = std::max(F::NCH, F::HEADS);
-    constexpr bool FORWARD = F32 || (SX == 0 && D >= 256 && NARROW), DRAFT = F32 || (SX > 0 && NARROW);
+    constexpr bool FORWARD = F32 || (SX == 0 && D >= 256 && NARROW) || (SX > 0 && !NARROW), DRAFT = F32 || (SX > 0 && NARROW);
     if constexpr (FORWARD || DRAFT) {
       typedef FlowCfg<TT, D, H, HEADS, SX> X;
       if constexpr (FORWARD) { k.flow_forward = flow_forward<X>; k.flow_declare_forward = flow_declare<X, false>; }

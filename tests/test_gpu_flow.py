@@ -179,3 +179,19 @@ def test_launches_declare_the_lds_that_they_ask_for():
 def test_rollouts_with_cross_attention_and_the_most_lds(A):
     wl = ti.small_variant(ti.C4, B=3, K_max=3, A=A, base=ti.NetShape(1, 512, 8))
     _stage_parity(wl, 3, np.array([99, 40, 2]), np.array([3, 1, 3]), np.ones(3))
+
+
+@pytest.mark.parametrize("layers, B, K_max, A", [(1, 1, 1, 16), (2, 1, 8, 14), (3, 2, 4, 16), (2, 4, 2, 2), (1, 3, 3, 14)])
+def test_wide_bases_with_cross_attention(layers, B, K_max, A):
+    # up to eight rows of 32 x 512 in one launch (the last case: nine, in launches); A = 16 is the most embedding that shares the LDS of
+    # the hidden layer's sums.  Again after another call: the same bits
+    wl = ti.small_variant(ti.C4, B=B, K_max=K_max, A=A, base=ti.NetShape(layers, 512, 8))
+    t0 = np.linspace(wl.T - 1, 2, B).astype(int); K = np.full(B, K_max)
+    _stage_parity(wl, B, t0, K, np.ones(B), norm=layers % 2)
+    ctx = _context(wl)
+    x = to_dev(ti.make_latents(wl, B))
+    ref = _stages(ctx, x, t0, K, np.ones(B))
+    _stages(ctx, x[:1] * 2, t0[:1], K[:1], np.ones(1))
+    got = _stages(ctx, x, t0, K, np.ones(B))
+    assert all(bool((got[name] == ref[name]).all()) for name in ref) and ctx.tsdp_status() == 0
+    ctx.close()
