@@ -481,18 +481,11 @@ __global__ __launch_bounds__(C::TH) void k_flow(FusedNet net, FlowIO io, std::co
   if (__builtin_amdgcn_readfirstlane(drawn[1])) enter();
   for (;;) {
     lds_barrier();                                       // the task before has read its LDS
-    if (first_wave) {
-      int ticket = 0;
-      if (threadIdx.x == 0 && n_tasks) ticket = __hip_atomic_fetch_add(io.ticket + set * SYNC_LINE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned open = flow_free_sets(io, rows, threadIdx.x);     // (travels with the ticket)
-      if (threadIdx.x == 0) { drawn[0] = ticket; drawn[1] = open; }
-    }
+    if (threadIdx.x == 0) drawn[0] = n_tasks ? __hip_atomic_fetch_add(io.ticket + set * SYNC_LINE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     lds_barrier();
     const int ticket = __builtin_amdgcn_readfirstlane(drawn[0]);
     if (ticket >= n_tasks) {
-      if (__builtin_amdgcn_readfirstlane(drawn[1]) == 0) return;
-      lds_barrier();
-      if (first_wave) {
+      if (first_wave) {                                  // (only now: the owners' words are other XCDs', and far)
         const int late = flow_late_set(io, rows, xcc, threadIdx.x);
         if (threadIdx.x == 0) drawn[1] = late;
       }
