@@ -80,6 +80,15 @@ constexpr int FLOW_SPINS = 1 << 22, FLOW_LOOK = 64;
 enum FlowTurn { FLOW_POLL, FLOW_ASK, FLOW_GIVE_UP };   // behind poll n that found its data missing
 constexpr FlowTurn flow_turn(int n) { return n >= FLOW_SPINS ? FLOW_GIVE_UP : n % FLOW_LOOK == FLOW_LOOK - 1 ? FLOW_ASK : FLOW_POLL; }
 
+// Where a workgroup of a one-launch pass goes when the tickets it draws from have run out.  Sets as masks: `open` have rows and
+// no XCD yet, `ours` are its XCD's and it has not seen their tickets run out; `late`: it has looked long enough for the XCD of
+// an open set to have come.  A set of its own XCD comes first: one that changes hands is then worked by every workgroup of the
+// XCD that is waiting, not by the one that took it.
+constexpr int FLOW_LEAVE = -1, FLOW_STAY = -2;           // every set is in hand; look again
+constexpr int flow_next_set(unsigned open, unsigned ours, bool late) {
+  return ours ? __builtin_ctz(ours) : !open ? FLOW_LEAVE : late ? __builtin_ctz(open) : FLOW_STAY;
+}
+
 // Networks with run-time sizes: `tokens` a launch covers at most (the ragged batch's, the rollout's one row per environment).
 // A spread launch streams its weights once per row and adds max(heads, slices) partial sums of the whole row in every
 // workgroup; one launch per operator does neither but has six times the launches.  Rows at which both take the same time

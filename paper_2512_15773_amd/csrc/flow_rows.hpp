@@ -39,8 +39,10 @@
 // kind.  The rows of a set are its own, so the XCDs do not wait for each other.  Every wait is bounded all the same
 // (flow_turn): past the bound the status word reports it, the waits of the other tasks end too, and the launch drains.
 // A workgroup asks the hardware which XCD it is on and takes the set of that number for it (owner word); a set whose XCD has
-// no workgroup of this launch for FLOW_LATE looks (another partition mode, an XCD busy with other work) is taken by one that
-// has none left, so every set is worked off, each by one XCD.
+// no workgroup of this launch for FLOW_LATE looks (another partition mode, an XCD busy with other work) is taken by one whose
+// tickets have run out, and every workgroup of that XCD which waits or comes by joins it (flow_next_set).  So every set is
+// worked off, each by one XCD, at the rate of an XCD: pairs of C2 rounds (one environment, K = 7 / K = 8) of two contexts on two
+// streams 271 / 336 us, 346 / 417 where only the workgroup that took a set works on it (439 / 472 one after the other).
 // Visibility: what one workgroup writes for another in the same launch therefore meets in one L2.  Stores are plain (the L1
 // writes through), loads of device scope (sc1) pass the L1 by.  One way between two units of an XCD 0.26 us; with stores of
 // device scope, which go on to memory, 0.49 (0.65 to another XCD): one C2 environment 258 -> 230 us a round, four C4 914 -> 862.
@@ -173,20 +175,15 @@ __device__ __forceinline__ bool flow_take(const FlowIO& io, int set, int xcc) {
   __hip_atomic_compare_exchange_strong(io.owner + set * SYNC_LINE, &had, xcc + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return had == 0 || had == xcc + 1;
 }
-// (wavefront 0, all lanes) sets that have rows and no owner yet, as a mask
-__device__ __forceinline__ unsigned flow_free_sets(const FlowIO& io, int rows, int lane) {
+// (wavefront 0, all lanes) the set to draw from next, or FLOW_LEAVE: one of this XCD's that is not among `done`, or one that nobody
+// has taken although its own XCD had time to.  looks: so far in this launch (a workgroup that has waited once does not wait again)
+__device__ __forceinline__ int flow_other_set(const FlowIO& io, int rows, int xcc, unsigned done, int& looks, int lane) {
   const int n = min(rows, FLOW_SETS);
-  return (unsigned)__ballot(lane < n && flow_word_at(io.owner + min(lane, FLOW_SETS - 1) * SYNC_LINE) == 0);
-}
-// (wavefront 0) a set that nobody has taken although its own XCD had time to, or -1: all sets are in hand
-__device__ __forceinline__ int flow_late_set(const FlowIO& io, int rows, int xcc, int lane) {
-  for (int n = 0;; ++n) {
-    const unsigned open = flow_free_sets(io, rows, lane);
-    if (open == 0) return -1;
-    if (n >= FLOW_LATE) {
-      const int set = __ffs(open) - 1;
-      if (__builtin_amdgcn_readfirstlane(lane == 0 ? flow_take(io, set, xcc) : 0)) return set;
-    }
+  for (;; ++looks) {
+    const int32_t owner = flow_word_at(io.owner + min(lane, FLOW_SETS - 1) * SYNC_LINE);
+    const unsigned open = (unsigned)__ballot(lane < n && owner == 0), ours = (unsigned)__ballot(lane < n && owner == xcc + 1) & ~done;
+    const int set = flow_next_set(open, ours, looks >= FLOW_LATE);
+    if (set == FLOW_LEAVE || (set >= 0 && __builtin_amdgcn_readfirstlane(lane == 0 ? flow_take(io, set, xcc) : 0))) return set;
     __builtin_amdgcn_s_sleep(8);
   }
 }
@@ -469,6 +466,8 @@ __global__ __launch_bounds__(C::TH) void k_flow(FusedNet net, FlowIO io, std::co
   const int rows = ROLL ? io.R_cap : min(*io.word, io.R_cap), A = io.A;
   if (rows == 0) return;
   int phases = io.phases, n_tasks = 0;
+  unsigned done = 0;                                     // sets whose tickets this workgroup has seen run out
+  int looks = 0;
   auto enter = [&]() {                                   // the set's tasks; rollout: its longest one and the phase that ends it
     if (ROLL) {
       int k_max = 0;
@@ -485,9 +484,10 @@ __global__ __launch_bounds__(C::TH) void k_flow(FusedNet net, FlowIO io, std::co
     lds_barrier();
     const int ticket = __builtin_amdgcn_readfirstlane(drawn[0]);
     if (ticket >= n_tasks) {
+      done |= 1u << set;
       if (first_wave) {                                  // (only now: the owners' words are other XCDs', and far)
-        const int late = flow_late_set(io, rows, xcc, threadIdx.x);
-        if (threadIdx.x == 0) drawn[1] = late;
+        const int other = flow_other_set(io, rows, xcc, done, looks, threadIdx.x);
+        if (threadIdx.x == 0) drawn[1] = other;
       }
       lds_barrier();
       set = __builtin_amdgcn_readfirstlane(drawn[1]);

@@ -31,6 +31,7 @@ struct FewRun {                 // one forward pass of k_few_*
   float* eps_out;
   float* h[2]; float* part[2]; size_t pstride;
   unsigned char* buf; int32_t* sync; int32_t* status;   // k_flow: buffers of the rows, tickets and counters
+  int flow_wgs;                 // k_flow: workgroups of a launch at most, 0: as many as are of use
 };
 
 struct LayerOff {
@@ -113,6 +114,7 @@ struct tsdp_ctx {
   FewSize few_have;             // floats of few_h / few_part
   unsigned char* flow_buf = nullptr; size_t flow_have = 0;   // k_flow: buffers of the rows, empty between launches
   int32_t* sync = nullptr;      // k_flow: tickets and counters of the verify rows, then of the rollout's environments
+  int flow_wgs = 0;             // (FewRun::flow_wgs; tests)
   float *few_h[2] = {nullptr, nullptr}, *few_part[2] = {nullptr, nullptr}, *few_y[2] = {nullptr, nullptr}, *few_mod = nullptr;
   float* eps_tmp = nullptr;     // [B_max, D] drafter output of the current step
   int32_t *row_t_chk = nullptr, *row_env_chk = nullptr;   // [rows] range-checked copy of a caller's row table (tsdp_verify)
@@ -414,8 +416,9 @@ void flow_launch(const FusedNet& n, const FewRun& r, FlowIO& io, const std::cond
   io.x = r.x; io.row_t = r.row_t; io.row_env = r.row_env; io.T = r.T; io.A = r.A;
   io.mod = r.mod; io.mod_row = n.L * 4 * C::D; io.by_t = n.modtab != nullptr;
   io.buf = r.buf; io.eps_out = r.eps_out;
+  const int wgs = 8 * std::min(4 * io.groups * C::G, FLOW_WGS);
   if (r.R_cap > 0)
-    hipLaunchKernelGGL((k_flow<C, ROLL>), dim3(8 * std::min(4 * io.groups * C::G, FLOW_WGS)), dim3(C::TH), lds, s, n, io, dr);
+    hipLaunchKernelGGL((k_flow<C, ROLL>), dim3(r.flow_wgs > 0 ? std::min(r.flow_wgs, wgs) : wgs), dim3(C::TH), lds, s, n, io, dr);
 }
 // Declares the largest LDS request of any context (H A <= 512) on the device that is current: at every load, so that a launch has
 // nothing to set and contexts on several devices or with several A do not depend on each other.
@@ -817,7 +820,7 @@ FewRun few_run(tsdp_ctx* c, const Net& n, int R_cap, int safe_rows, const int32_
   for (int i = 0; i < 2; ++i) { r.h[i] = c->few_h[i]; r.part[i] = c->few_part[i]; }
   r.pstride = (size_t)R_cap * c->cfg.H * n.d;
   r.sync = c->sync + (&n == &c->net[1] ? (size_t)flow_lines(rows_max(c->cfg)) * SYNC_LINE : 0);
-  r.buf = c->flow_buf; r.status = c->status;
+  r.buf = c->flow_buf; r.status = c->status; r.flow_wgs = c->flow_wgs;
   return r;
 }
 
@@ -1603,5 +1606,13 @@ const char* tsdp_path_name(const tsdp_ctx* c, int which) {
 }
 
 const char* tsdp_last_error(const tsdp_ctx* c) { return c ? c->err.c_str() : "null context"; }
+
+// Not part of the interface, for tests: one-launch passes of this context with at most n workgroups (0: all), so that XCDs
+// without one leave their sets to others.  A launch makes progress with any number of workgroups, one included.
+int tsdp_internal_flow_workgroups(tsdp_ctx* c, int n) {
+  if (!c || n < 0) return TSDP_E_INVAL;
+  c->flow_wgs = n;
+  return TSDP_OK;
+}
 
 }  // extern "C"

@@ -17,6 +17,7 @@ int draft_pays(int environments, int f32, long d, int layers, int K_max, int lau
 int forward_pays(long tokens, int f32, long d, int layers) { return flow_forward_pays(tokens, f32 != 0, d, layers); }
 int dyn_pays(long tokens, long heads, long layer_bytes) { return few_dyn_pays(tokens, heads, layer_bytes); }
 int one_workgroup_pays(long tokens, long H, long layer_bytes) { return row_pays(tokens, H, layer_bytes); }
+int next_set(unsigned open, unsigned ours, int late) { return flow_next_set(open, ours, late != 0); }
 // polls of one workgroup's `waits` waits, one after the other, for data that never arrives
 long drain(int waits) {
   long polls = 0;
@@ -148,6 +149,58 @@ def test_a_launch_whose_data_cannot_arrive_drains_after_one_bound(plan):
     assert 1 << 20 <= bound <= (1 << 22) + 1
     for waits in (2, 97, 10000):
         assert plan.drain(waits) <= bound + 64 * (waits - 1), waits
+
+
+def _work_off(plan, first_at, wgs, tasks, late):
+    """A one-launch pass in steps: XCD i's workgroups start one by one from step first_at[i] on; a draw takes a step, a task eight.  Returns the
+    last step and, per set, the workgroups that worked on it."""
+    owner = [-1] * 8; drawn = [0] * 8; workers = [set() for _ in range(8)]
+    state = {(x, w): dict(at=first_at[x] + w, set=None, done=0, looks=0) for x in range(8) for w in range(wgs)}
+    step = 0
+    while state:
+        assert step < 100000, "the launch does not end"
+        seen = list(owner)                                # looks of one step see the words as they were
+        for (x, w), s in list(state.items()):
+            if s["at"] > step:
+                continue
+            if s["set"] is None:                          # the set of its own number
+                if owner[x] < 0:
+                    owner[x] = x
+                s["set"] = x
+            if s["set"] >= 0 and owner[s["set"]] == x and not s["done"] >> s["set"] & 1 and drawn[s["set"]] < tasks:
+                drawn[s["set"]] += 1
+                workers[s["set"]].add((x, w))
+                s["at"] = step + 8
+                continue
+            s["done"] |= 1 << s["set"]
+            open_ = sum(1 << i for i in range(8) if seen[i] < 0)
+            ours = sum(1 << i for i in range(8) if seen[i] == x) & ~s["done"]
+            n = plan.next_set(open_, ours, int(s["looks"] >= late))
+            s["looks"] += 1
+            if n == -1:
+                del state[(x, w)]
+            elif n >= 0:
+                if owner[n] < 0:
+                    owner[n] = x
+                if owner[n] == x:
+                    s["set"] = n
+        step += 1
+    assert all(d == tasks for d in drawn)
+    return step, workers
+
+
+def test_a_set_that_changes_hands_is_worked_by_the_whole_xcd(plan):
+    # XCDs 0 .. 6 are busy for a long time: XCD 7 works off all eight sets with all of its workgroups, and not one after the other
+    # with the workgroup that took the set; what the others find when they come is in hand
+    for wgs in (1, 2, 16):
+        steps, workers = _work_off(plan, [4000] * 7 + [0], wgs, tasks=256, late=64)
+        assert all(len({w for _, w in s}) >= wgs - 1 and len({x for x, _ in s}) == 1 for s in workers), wgs
+        assert steps <= max(4000, 8 * (256 // wgs + 2) * 8 + 64 * 2) + 8 * 2, (wgs, steps)
+    # an XCD that comes while its set is still open takes it, and nobody waits for long where every XCD comes
+    _, workers = _work_off(plan, [40] * 7 + [0], 16, tasks=256, late=64)
+    assert all({x for x, _ in workers[i]} == {i} for i in range(8))
+    steps, workers = _work_off(plan, [0] * 8, 16, tasks=256, late=64)
+    assert steps <= 8 * 17 + 16 + 4 and all({x for x, _ in workers[i]} == {i} for i in range(8))
 
 
 def test_no_kernel_is_compiled_that_no_network_reaches():

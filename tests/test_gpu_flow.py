@@ -124,6 +124,32 @@ def test_one_launch_passes_of_two_contexts_side_by_side():
         ctxs[i].close()
 
 
+@pytest.mark.parametrize("wl, B, K_max", [
+    (STATE, 9, 3), (ti.replace(ti.C3, base=ti.NetShape(2, 256, 4)), 3, 5), (ti.replace(ti.C4, base=ti.NetShape(1, 512, 8)), 11, 2),
+    (ti.replace(ti.C4, base=ti.NetShape(2, 512, 8)), 2, 4),
+])
+def test_sets_whose_xcd_does_not_come_are_worked_off_by_another(wl, B, K_max):
+    # fewer workgroups than XCDs: the sets of the others are taken over, with the bits of an ordinary launch; and ordinary launches
+    # in between, so that a set's owner changes from launch to launch
+    import torch
+    from paper_2512_15773_amd import load_library
+    wl = ti.small_variant(wl, B=B, K_max=K_max)
+    ctx = _context(wl)
+    limit = load_library().tsdp_internal_flow_workgroups
+    limit.argtypes = [ctypes.c_void_p, ctypes.c_int]
+    x = to_dev(ti.make_latents(wl, B))
+    K = 1 + np.arange(B) % K_max; K[0] = K_max
+    calls = (x, np.linspace(wl.T - 1, 2, B).astype(int), K, np.ones(B))
+    ref = _stages(ctx, *calls)
+    for wgs in (1, 3, 0, 2, 8, 9, 0):
+        assert limit(ctx.ctx, wgs) == 0
+        got = _stages(ctx, *calls)
+        for name in ref:
+            assert torch.equal(got[name], ref[name]), (wgs, name)
+        assert ctx.tsdp_status() == 0, wgs
+    ctx.close()
+
+
 @pytest.mark.parametrize("wl", [STATE, ti.replace(ti.C3, base=ti.NetShape(2, 256, 4)), ti.replace(ti.C4, base=ti.NetShape(1, 512, 8))])
 @pytest.mark.parametrize("payload", [0xFFFFFFFF, 0x7FC00000])
 def test_not_a_number_passes_through_and_leaves_nothing_behind(wl, payload):
