@@ -1,5 +1,6 @@
 // Run-time sizes, a row per workgroup: one launch carries a row through all layers (k_row), or an environment through all
-// transitions of its rollout (ROLL), with the residual and every activation in LDS and fp32 operands on the matrix cores.
+// transitions of its rollout (ROLL), with the residual and every activation in LDS and fp32 operands on the matrix cores; the
+// functions are those of the operator kernels.
 //
 // For networks whose layers are small (row_pays): one unit multiplies such a layer in less time than the two or more launches
 // and the partial sums cost that spreading it takes.  256 rows and 32 rollouts of eight transitions (d = 96, two layers, and
@@ -313,7 +314,7 @@ __device__ __forceinline__ void row_pass(const FusedNet& net, const RowIO& io, f
       for (int nb = 0; nb < NB; ++nb) {
         f32x4 r = acc[nb] + b;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) r[i] = gelu_fast(r[i]);
+        for (int i = 0; i < 4; ++i) r[i] = gelu_tanh_f(r[i]);   // (gelu_fast: 3.5 of 133 us less, error of the function 4.5e-8 for 3.9e-8)
         *reinterpret_cast<f32x4*>(u + (nb * 16 + l16) * US + c) = r;
       }
     });
