@@ -105,14 +105,19 @@ inline bool few_dyn_pays(size_t tokens, size_t heads, size_t layer_bytes) {
 // One workgroup per row or environment through all layers (k_row) instead of launches, for networks with run-time sizes.
 // A unit's time for a layer grows with its weights times the fragments of 16 tokens (fp32 matrix rate), and not with the rows
 // until every unit has one; a launch costs the same for any small layer, and grows with the rows.  Two layers, us, launches / one
-// workgroup a row; tsdp_verify of 8, 256, 512 rows of 16 tokens: d = 48 (0.1 MB a layer) 43 / 23, 68 / 23, 111 / 31; d = 96 (0.44 MB)
-// 51 / 40, 122 / 42, 222 / 62; d = 128 (0.79 MB) 56 / 50, 125 / 54, 230 / 83; d = 160 (1.2 MB) 65 / 77, 213 / 82, 381 / 126;
-// d = 256 (3.1 MB) 90 / 164, 304 / 165.  tsdp_draft of one layer, eight transitions of 1, 64 environments: 170 / 76, 167 / 79;
-// 214 / 134, 215 / 137; 234 / 178, 239 / 182; d = 160 272 / 285, 301 / 291.  32 tokens, verify of 8, 256 rows: d = 96 72 / 62,
-// 287 / 65, d = 128 82 / 86, 290 / 88.
-inline bool row_pays(size_t tokens, size_t H, size_t layer_bytes) {
+// workgroup a row; tsdp_verify of 8, 256, 512 rows of 16 tokens: d = 48, 3 heads (0.1 MB a layer) 42 / 24, 67 / 25, 111 / 32; d = 96, 3
+// heads (0.44 MB) 51 / 41, 122 / 43, 222 / 63; d = 128, 2 heads (0.79 MB) 55 / 51, 125 / 53, 230 / 82; d = 160, 5 heads (1.2 MB) 64 / 80,
+// 212 / 82, 381 / 126; d = 256, 8 heads (3.1 MB) 90 / 165, 302 / 164.  tsdp_draft of one layer, eight transitions of 1, 64 environments:
+// 169 / 82, 166 / 84; 213 / 140, 214 / 143; 233 / 185, 238 / 188; d = 160 272 / 294, 299 / 299.  32 tokens, verify of 8, 256 rows: d = 96, 3
+// heads 72 / 67, 289 / 69, d = 128, 4 heads 76 / 92, 324 / 93.
+// Layers of 0.9 to 1.6 MB, tsdp_verify of 64, 96, 128 rows of 16 tokens: d = 144, 3 heads 70 / 72, 81 / 73, 83 / 73; d = 160, 5 heads
+// 77 / 81, 106 / 81, 124 / 80, 10 heads 87 / 81, 131 / 81, 146 / 81; d = 176, 11 heads 96 / 91, 117 / 91, 126 / 91; d = 208, 13 heads, hidden
+// layer of twice the width 119 / 89, 131 / 90, 149 / 90; 32, 48, 64 rows of 32: d = 128, 4 heads 79 / 92, 102 / 92, 104 / 92, 8 heads 77 / 93,
+// 119 / 94, 123 / 93.  So from 1536 tokens on, or where the launches have 2.5 workgroups and more per unit (rows x heads).
+// What these lines give away: a context of which few rows live (4 of 128, d = 160: 64 / 80), which the capacity cannot tell.
+inline bool row_pays(size_t tokens, size_t H, size_t layer_bytes, size_t heads = 1) {
   const size_t work = layer_bytes * H / 16;
-  return work <= 900000 || (work <= 1600000 && tokens >= 1024);
+  return work <= 900000 || (work <= 1600000 && (tokens >= 1536 || (tokens >= 1024 && tokens / H * heads >= 640)));
 }
 
 // Floats of the two residual and of the two partial-sum buffers, shared by both networks.  Which networks take the spread

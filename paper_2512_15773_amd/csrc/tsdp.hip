@@ -585,7 +585,7 @@ hipError_t find_few_dyn(const tsdp_config& cf, int which, const Net& n, FusedKer
       !few_dyn_pays(dyn_tokens(cf, which), n.heads, bytes))
     return hipSuccess;
   // (twins: both of them or neither)
-  if (row_pays(dyn_tokens(cf, which), cf.H, bytes) && n.d <= ROW_MAX_D && 5 * n.d + n.m <= ROW_MAX_BIAS &&
+  if (row_pays(dyn_tokens(cf, which), cf.H, bytes, n.heads) && n.d <= ROW_MAX_D && 5 * n.d + n.m <= ROW_MAX_BIAS &&
       row_lds(n.d, cf.H, n.m, cf.A, true).total * 4 <= 160 * 1024)
     return cf.H == 16 ? row_kernels<1>(k) : row_kernels<2>(k);
   k.few_slices = std::max(n.heads, few_slices_dyn(n.m));

@@ -17,6 +17,7 @@ int draft_pays(int environments, int f32, long d, int layers, int K_max, int lau
 int forward_pays(long tokens, int f32, long d, int layers) { return flow_forward_pays(tokens, f32 != 0, d, layers); }
 int dyn_pays(long tokens, long heads, long layer_bytes) { return few_dyn_pays(tokens, heads, layer_bytes); }
 int one_workgroup_pays(long tokens, long H, long layer_bytes) { return row_pays(tokens, H, layer_bytes); }
+int one_workgroup_pays_heads(long tokens, long H, long layer_bytes, long heads) { return row_pays(tokens, H, layer_bytes, heads); }
 int next_set(unsigned open, unsigned ours, int late) { return flow_next_set(open, ours, late != 0); }
 // polls of one workgroup's `waits` waits, one after the other, for data that never arrives
 long drain(int waits) {
@@ -105,6 +106,15 @@ def test_a_row_per_workgroup_only_where_that_is_faster(plan):
     for d, H, rows, faster in ((48, 16, 8, 1), (96, 16, 512, 1), (128, 16, 8, 1), (160, 16, 8, 0), (160, 16, 256, 1), (256, 16, 8, 0),
                                (96, 32, 8, 1), (128, 32, 8, 0), (128, 32, 256, 1)):
         assert plan.one_workgroup_pays(C.c_long(H * rows), C.c_long(H), C.c_long(12 * d * d * 4)) == faster, (d, H, rows)
+
+
+def test_larger_layers_take_a_workgroup_per_row_only_from_enough_rows_on(plan):
+    # (d, heads, hidden layer, tokens of a row, rows, one workgroup per row was the faster one)
+    for d, heads, ratio, H, rows, faster in (
+            (144, 3, 4, 16, 64, 0), (144, 3, 4, 16, 96, 1), (160, 5, 4, 16, 64, 0), (160, 5, 4, 16, 96, 1), (160, 10, 4, 16, 64, 1), (176, 11, 4, 16, 64, 1),
+            (208, 13, 2, 16, 64, 1), (112, 7, 4, 32, 32, 0), (112, 7, 4, 32, 48, 1), (128, 4, 4, 32, 32, 0), (128, 4, 4, 32, 48, 1), (128, 8, 4, 32, 32, 0), (128, 8, 4, 32, 48, 1)):
+        layer = 4 * (4 + 2 * ratio) * d * d
+        assert plan.one_workgroup_pays_heads(C.c_long(H * rows), C.c_long(H), C.c_long(layer), C.c_long(heads)) == faster, (d, heads, H, rows)
 
 
 def test_compiled_kernels_are_spread_up_to_2048_and_2176_tokens(plan):
