@@ -4,7 +4,7 @@
 //
 // For networks whose layers are small (row_pays): one unit multiplies such a layer in less time than the two or more launches
 // and the partial sums cost that spreading it takes.  256 rows and 32 rollouts of eight transitions (d = 96, two layers, and
-// d = 48, one): round 307 -> 130 us.  What bounds it: seven barrier-separated phases a layer of 1000 to 3500 cycles each, of
+// d = 48, one): round 307 -> 132 us.  What bounds it: seven barrier-separated phases a layer of 1000 to 3500 cycles each, of
 // which the fp32 matrix rate is about half (a drafted transition of d = 48 8 us).  Eight wavefronts, two per SIMD; a wavefront's
 // fragments of a product are one stream whose next block of weights is requested before the current one is multiplied, and whose
 // first block is requested before the barrier ahead of the phase.
@@ -22,7 +22,7 @@ constexpr int ROW_NW = 8, ROW_TH = ROW_NW * 64;               // wavefronts
 template <int NB, bool ROLL> constexpr int row_block() { return (ROLL ? 8 : 4) / NB; }
 constexpr int ROW_JV = 2, ROW_MAX_D = ROW_JV * 128;           // 16-byte vectors of a token per lane (32 lanes a token)
 
-constexpr int ROW_BV = 2, ROW_MAX_BIAS = ROW_BV * 4 * ROW_TH;   // vectors of a layer's biases per thread: 5 D + M floats
+constexpr int ROW_MAX_BIAS = 4 * ROW_TH;          // a layer's biases, 5 D + M floats: a vector per thread (row_pays allows 1728)
 // LDS in floats: residual, normalised activations / attention output, q | k | v or the hidden layer, biases of a layer,
 // drafter output, latents and noise; token embedding and the embedding of an all-zero latent (rollout)
 struct RowLds { int h, act, scr, bias, hb, et, tok, total; };
@@ -191,19 +191,15 @@ __device__ __forceinline__ void row_pass(const FusedNet& net, const RowIO& io, f
 
   RowStream<row_block<NB, ROLL>()> st;
   RowFilm fm;
-  f32x4 bv[ROW_BV];                                      // the next layer's biases: q|k|v, output projection, down, up
+  f32x4 bv;                                              // the next layer's biases: q|k|v, output projection, down, up
   const int NBIAS = 5 * D + M;
   auto load_bias = [&](const FusedLayer& W) {            // (packed behind q | k | v)
     const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(W.qkv_b), 0, NBIAS * 4, 0x00020000);
-#pragma unroll
-    for (int j = 0; j < ROW_BV; ++j) bv[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)threadIdx.x * 16 + j * ROW_TH * 16, 0, 0));
+    bv = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)threadIdx.x * 16, 0, 0));
   };
   auto store_bias = [&](int l) {                         // (two regions: the layer before may still read its own)
-#pragma unroll
-    for (int j = 0; j < ROW_BV; ++j) {
-      const int i = threadIdx.x * 4 + j * ROW_TH * 4;
-      if (i < NBIAS) *reinterpret_cast<f32x4*>(biases + (l & 1) * NBIAS + i) = bv[j];
-    }
+    const int i = threadIdx.x * 4;
+    if (i < NBIAS) *reinterpret_cast<f32x4*>(biases + (l & 1) * NBIAS + i) = bv;
   };
   const int MROW = net.L * 4 * D * 4;
   const auto mrow = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(mod), 0, MROW, 0x00020000);
