@@ -551,7 +551,7 @@ def measure_workload(wl, point, steps, warmup, torch, Tsdp, dev, full):
     if fused:
         k_ms, k_med = time_kernel(ctx, lambda: ctx.tsdp_verify(wl.B, rows), 1, n_it)
         kd_ms, _ = time_kernel(ctx, lambda: ctx.tsdp_draft(x0d, t0d, Kd, sd, None, rows), 0, n_it)
-        kname = "verify forward (k_fused_forward, all layers in one launch; few rows: k_flow in one launch, or k_few_* in two per layer and more)"
+        kname = "verify forward (k_fused_forward, all layers in one launch; few rows: k_flow in one launch, or k_few_* in two per layer and more; run-time sizes, small layers: k_row)"
     else:
         k_ms, k_med, kd_ms, kname = t_verify[0], t_verify[1], None, "tsdp_verify (sequence of fp32 operator kernels)"
     lat["drafter_kernel"] = kd_ms

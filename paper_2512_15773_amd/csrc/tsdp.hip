@@ -1607,6 +1607,13 @@ const char* tsdp_path_name(const tsdp_ctx* c, int which) {
 
 const char* tsdp_last_error(const tsdp_ctx* c) { return c ? c->err.c_str() : "null context"; }
 
+// Not part of the interface, for tests: the kernels that a network's weights are loaded for.
+const char* tsdp_internal_kernels(const tsdp_ctx* c, int which) {
+  if (!c || which < 0 || which > 1) return "";
+  const Net& n = c->net[which];
+  return n.few ? (n.flow_row ? "k_flow" : n.few_slices ? "k_few" : "k_row") : n.fused ? "tiles" : "operators";
+}
+
 // Not part of the interface, for tests: one-launch passes of this context with at most n workgroups (0: all), so that XCDs
 // without one leave their sets to others.  A launch makes progress with any number of workgroups, one included.
 int tsdp_internal_flow_workgroups(tsdp_ctx* c, int n) {

@@ -26,6 +26,14 @@ def gpu_side(wl, wb, wd, cond, clip=None, B_max=None, K_max=None, seed=None, sam
     return ctx
 
 
+def kernels(ctx):
+    """The kernels that compute the base network and the drafter: k_flow, k_few, k_row, tiles or operators."""
+    import ctypes
+    name = ctx.lib.tsdp_internal_kernels
+    name.argtypes, name.restype = [ctypes.c_void_p, ctypes.c_int], ctypes.c_char_p
+    return tuple(name(ctx.ctx, which).decode() for which in (0, 1))
+
+
 def to_dev(a, dtype=None):
     import torch
     t = torch.from_numpy(np.ascontiguousarray(a))

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import tsdp_inputs as ti
-from tests.helpers import gpu_side, to_dev
+from tests.helpers import gpu_side, kernels, to_dev
 from tests.test_gpu_parity import _stage_parity
 
 pytestmark = pytest.mark.gpu
@@ -57,6 +57,7 @@ def _stages(ctx, x, t0, K, s):
     (ti.replace(ti.C2, base=ti.NetShape(3, 128, 4), draft=ti.NetShape(4, 256, 4)), 18, 7),
     (ti.replace(ti.C4, base=ti.NetShape(1, 512, 8)), 24, 2), (ti.replace(ti.C4, base=ti.NetShape(1, 512, 8), draft=ti.NetShape(3, 256, 8)), 11, 4),
     (ti.replace(ti.C3, base=ti.NetShape(3, 256, 4)), 4, 4), (ti.replace(ti.C5, base=ti.NetShape(1, 384, 6)), 16, 1),
+    (ti.replace(ti.C4, base=ti.NetShape(1, 512, 8)), 2, 4), (ti.replace(ti.C4, base=ti.NetShape(2, 512, 8)), 8, 1),   # wide bases
 ])
 def test_every_call_finds_the_buffers_empty(wl, B, K_max):
     # what a launch leaves behind shows in the next one: calls with fewer environments and rows, other inputs and finished
@@ -64,6 +65,7 @@ def test_every_call_finds_the_buffers_empty(wl, B, K_max):
     import torch
     wl = ti.small_variant(wl, B=B, K_max=K_max)
     ctx = _context(wl)
+    assert "k_flow" in kernels(ctx)
     rng = np.random.default_rng(B)
     x = to_dev(ti.make_latents(wl, B))
     first = (x, np.full(B, wl.T - 1), np.full(B, K_max), np.ones(B))
@@ -94,10 +96,11 @@ def test_equal_networks_in_fp32_give_equal_predictions(layers, d, B, K_max):
 
 
 def test_one_launch_passes_of_two_contexts_side_by_side():
-    # two contexts whose forward passes and rollouts are one launch each run rounds at the same time on two streams: the bits of
-    # running them one after the other
+    # contexts whose forward passes and rollouts are one launch each run rounds at the same time on streams of their own: the bits
+    # of running them one after the other
     import torch
-    wls = [ti.small_variant(ti.C2, B=7, K_max=8), ti.small_variant(ti.C4, B=9, K_max=4, base=ti.NetShape(2, 512, 8)), ti.small_variant(ti.C5, B=4, K_max=4)]
+    wls = [ti.small_variant(ti.C2, B=7, K_max=8), ti.small_variant(ti.C4, B=9, K_max=4, base=ti.NetShape(2, 512, 8)), ti.small_variant(ti.C5, B=4, K_max=4),
+           ti.small_variant(ti.C4, B=2, K_max=4, base=ti.NetShape(3, 512, 8))]
     ctxs = [_context(wl) for wl in wls]
     rng = np.random.default_rng(1)
     inputs = [(to_dev(ti.make_latents(wl, wl.B)), to_dev(rng.integers(30, wl.T, wl.B).astype(np.int32)), to_dev(rng.integers(1, wl.K_max + 1, wl.B).astype(np.int32)),
@@ -135,6 +138,7 @@ def test_sets_whose_xcd_does_not_come_are_worked_off_by_another(wl, B, K_max):
     from paper_2512_15773_amd import load_library
     wl = ti.small_variant(wl, B=B, K_max=K_max)
     ctx = _context(wl)
+    assert "k_flow" in kernels(ctx)
     limit = load_library().tsdp_internal_flow_workgroups
     limit.argtypes = [ctypes.c_void_p, ctypes.c_int]
     x = to_dev(ti.make_latents(wl, B))
@@ -150,21 +154,23 @@ def test_sets_whose_xcd_does_not_come_are_worked_off_by_another(wl, B, K_max):
     ctx.close()
 
 
-@pytest.mark.parametrize("wl", [STATE, ti.replace(ti.C3, base=ti.NetShape(2, 256, 4)), ti.replace(ti.C4, base=ti.NetShape(1, 512, 8))])
+@pytest.mark.parametrize("wl, B", [(STATE, 3), (ti.replace(ti.C3, base=ti.NetShape(2, 256, 4)), 3), (ti.replace(ti.C4, base=ti.NetShape(1, 512, 8)), 3),
+                                   (ti.replace(ti.C4, base=ti.NetShape(2, 512, 8)), 2)])
 @pytest.mark.parametrize("payload", [0xFFFFFFFF, 0x7FC00000])
-def test_not_a_number_passes_through_and_leaves_nothing_behind(wl, payload):
+def test_not_a_number_passes_through_and_leaves_nothing_behind(wl, B, payload):
     # the pattern of an empty buffer, as a latent: its environment's results are not numbers, the others' and those of the
-    # next calls have the same bits as without it (fp32, pairs of bf16, a rollout with cross-attention)
+    # next calls have the same bits as without it (fp32, pairs of bf16, a rollout with cross-attention, a wide base)
     import torch
-    wl = ti.small_variant(wl, B=3, K_max=4)
+    wl = ti.small_variant(wl, B=B, K_max=4)
     ctx = _context(wl)
-    x = to_dev(ti.make_latents(wl, 3)); bad = x.clone()
+    x = to_dev(ti.make_latents(wl, B)); bad = x.clone()
     bad[1].view(torch.int32).fill_(payload - (1 << 32) if payload >= 1 << 31 else payload)
-    calls = (np.array([99, 50, 3]), np.array([4, 3, 4]), np.ones(3))
+    calls = (np.array([99, 50, 3])[:B], np.array([4, 3, 4])[:B], np.ones(B))
+    assert "k_flow" in kernels(ctx)
     ref = _stages(ctx, x, *calls)
     for latents in (bad, x, bad, bad, x):
         got = _stages(ctx, latents, *calls)
-        keep = [0, 1, 2, 3, 7, 8, 9]                  # rows of environments 0 and 2
+        keep = [0, 1, 2, 3, 7, 8, 9][:4 if B == 2 else 7]   # rows of environments 0 and 2
         for name in ("states", "eps_p", "eps_q"):
             assert torch.equal(got[name][keep], ref[name][keep]), name
             if latents is bad:
@@ -215,6 +221,7 @@ def test_wide_bases_with_cross_attention(layers, B, K_max, A):
     t0 = np.linspace(wl.T - 1, 2, B).astype(int); K = np.full(B, K_max)
     _stage_parity(wl, B, t0, K, np.ones(B), norm=layers % 2)
     ctx = _context(wl)
+    assert kernels(ctx) == ("k_flow" if B * K_max <= 8 else "k_few", "k_flow")
     x = to_dev(ti.make_latents(wl, B))
     ref = _stages(ctx, x, t0, K, np.ones(B))
     _stages(ctx, x[:1] * 2, t0[:1], K[:1], np.ones(1))
