@@ -9,14 +9,14 @@ from tests.helpers import assert_latents_close, drafted_rows, gpu_side, list_nea
 
 pytestmark = pytest.mark.gpu
 
-# (dtype, cond_mode, base, drafter, H, A): fused bf16 / fp32 kernels and the general operator kernels
+# (dtype, cond_mode, base, drafter, H, A): fused bf16 / fp32 kernels, run-time sizes and the general operator kernels
 SHAPES = [
     ("bf16", 0, ti.NetShape(2, 256, 4), ti.NetShape(1, 128, 4), 16, 10),
     ("bf16", 0, ti.NetShape(1, 384, 6), ti.NetShape(1, 192, 6), 16, 7),
     ("bf16", 1, ti.NetShape(1, 512, 8), ti.NetShape(1, 256, 8), 32, 14),
     ("fp32", 0, ti.NetShape(2, 64, 2), ti.NetShape(1, 32, 2), 16, 2),
     ("fp32", 0, ti.NetShape(1, 256, 4), ti.NetShape(1, 128, 4), 16, 10),
-    ("fp32", 0, ti.NetShape(1, 96, 3), ti.NetShape(1, 48, 3), 16, 4),       # no fused kernel: operator path
+    ("fp32", 0, ti.NetShape(1, 96, 3), ti.NetShape(1, 48, 3), 16, 4),       # no fused kernel: a workgroup per row
     ("fp32", 1, ti.NetShape(1, 96, 3), ti.NetShape(1, 48, 3), 8, 3),
 ]
 

@@ -4,7 +4,7 @@ import pytest
 
 import tsdp_inputs as ti
 from oracle import philox, spec_round as sr
-from tests.helpers import assert_latents_close, drafted_rows, gpu_side, list_near_ties, oracle_side, scaled_err, to_dev
+from tests.helpers import assert_latents_close, drafted_rows, gpu_side, kernels, list_near_ties, oracle_side, scaled_err, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -191,11 +191,17 @@ def test_forward_of_few_rows_at_its_edges(base, B, K_max):
     ("fp32", 32, ti.NetShape(1, 144, 3, 3), ti.NetShape(1, 16, 1, 1), 3),   # nine k-steps, hidden width 27 fragments; one fragment in all
     ("fp32", 16, ti.NetShape(1, 272, 17), ti.NetShape(1, 96, 3), 2),     # 272 features: a second vector on some lanes
     ("bf16", 16, ti.NetShape(1, 320, 5), ti.NetShape(1, 64, 2), 9),      # bf16 weights, fp32 operands
+    ("fp32", 16, ti.NetShape(2, 192, 6), ti.NetShape(2, 208, 13), 5),    # layers too large for a workgroup per row, in both networks
+    ("fp32", 32, ti.NetShape(1, 160, 5), ti.NetShape(1, 176, 11), 3),    # the same with two token fragments
+    ("bf16", 32, ti.NetShape(1, 192, 3), ti.NetShape(2, 144, 9, 8), 2),
 ])
 def test_few_rows_of_run_time_sizes(dtype, H, base, draft, B):
     wl = ti.small_variant(ti.C2, dtype=dtype, H=H, A=6, cond_dim=32, K_max=3, base=base, draft=draft)
     t0 = np.full(B, 60); t0[-1] = 2
     K = np.full(B, 3); K[0] = 2
+    ctx = gpu_side(wl, ti.make_weights(wl, "base"), ti.make_weights(wl, "draft"), ti.make_cond(wl, B), B_max=B)
+    assert kernels(ctx) == ("k_row" if base.d == 112 else "k_few", "k_few" if draft.d > 128 else "k_row")
+    ctx.close()
     _stage_parity(wl, B, t0, K, np.full(B, 1.1), bonus=B == 2, paths=("f32-ops", "f32-ops"))
 
 
@@ -232,7 +238,7 @@ def test_run_time_sizes_on_both_sides_of_their_line(B, K_max, spread):
 ])
 @pytest.mark.parametrize("bonus, clip, norm", [(False, None, 0), (True, 1.5, 1)])
 def test_operator_kernels_with_vector_conditioning(dtype, H, base, draft, bonus, clip, norm):
-    # shapes that neither a compiled nor a spread kernel takes: one launch per operator, one pass per drafted transition
+    # shapes that neither a compiled kernel nor one with run-time sizes takes: one launch per operator, one pass per drafted transition
     wl = ti.small_variant(ti.C2, dtype=dtype, H=H, A=5, cond_dim=32, B=4, K_max=3, base=base, draft=draft)
     S = _setup(wl, 4, clip=clip, bonus=bonus, norm=norm)
     assert (S["ctx"].path_name(0), S["ctx"].path_name(1)) == ("f32-ops", "f32-ops")
@@ -1150,6 +1156,7 @@ def test_prepare_makes_a_fresh_context_capturable_and_short_chains_stop_where_as
     ti.small_variant(ti.C2, B=18, K_max=3, base=ti.NetShape(2, 256, 4)),
     ti.small_variant(ti.C4, B=2, K_max=3, base=ti.NetShape(1, 512, 8)),
     ti.small_variant(ti.C2, B=3, K_max=4, A=4, cond_dim=64, base=ti.NetShape(2, 96, 3), draft=ti.NetShape(1, 48, 3)),
+    ti.small_variant(ti.C2, B=3, K_max=4, A=4, cond_dim=64, base=ti.NetShape(2, 192, 6), draft=ti.NetShape(1, 208, 13)),
 ])
 def test_first_round_of_few_rows_can_be_captured(wl):
     # after tsdp_prepare the spread kernels need no allocation and no launch attribute: their first launch is recorded
