@@ -67,7 +67,9 @@ inline bool flow_draft_pays(int environments, bool f32, size_t d, int layers, in
 // (two layers, 16 rows 37 / 34), d = 384, 16 rows 36 / 31.
 // With cross-attention (d = 512, 32 tokens), tsdp_verify of 1, 8, 9, 16 rows: one layer 46 / 42, 50 / 47, 51 / 62; two 81 / 65, 88 / 70,
 // 88 / 105; twelve 445 / 289, 462 / 307, 466 / 504, 472 / 524 (one group of tasks that take two rows in turn 466): beyond one row an XCD
-// every further one adds the 3 us of a task to each of the phases.
+// every further one adds the 3 us of a task to each of the phases.  Whole rounds with launches / one launch, of 1 x 1, 1 x 8, 2 x 4, 8 x 1
+// environments and drafts: one layer 104 / 94, 373 / 324, 229 / 194, 113 / 102; two 139 / 110, 427 / 366, 271 / 227, 151 / 125; twelve 520 / 338,
+// 801 / 601, 654 / 444, 538 / 350; of eight environments one that runs 102 / 90, 139 / 114, 489 / 334.
 inline bool flow_forward_pays(size_t tokens, bool f32, size_t d, int layers) {
   if (!f32) return tokens <= (layers * d >= 384 ? 256 : 160);
   return tokens <= 16 * (d >= 256 ? (layers >= 4 ? 56 : 40) : (layers >= 4 ? 16 : 8));
@@ -97,6 +99,8 @@ constexpr int flow_next_set(unsigned open, unsigned ours, bool late) {
 // That is tokens x heads of 44 000 and more, near whose lower end the line is.  (64 rows, us, operators / spread: d = 96
 // 187 / 57, d = 512 with 16 heads 663 / 309; 2048 rows 671 / 800, 7164 / 8634.)  A layer of more than the 32 MB of all L2s
 // comes from beyond them for every row: d = 1024 meets at 90 rows (8 or 16 heads), 64 rows 1369 / 1182, 512 6434 / 9794.
+// (k_row stands behind this line too, which was measured for the launches alone: it has no partial sums, and where it meets the
+// operator kernels is not measured.)
 inline bool few_dyn_pays(size_t tokens, size_t heads, size_t layer_bytes) {
   return layer_bytes <= (32u << 20) ? tokens * std::max<size_t>(heads, 5) <= 47000
                                     : tokens * std::max<size_t>(heads, 16) <= 16384;

@@ -364,7 +364,8 @@ struct FewGemm {
   G g;
   f32x4 bias[MB];
   // requested ahead of the weights: in the epilogue nothing covers its way through the L2 (with k_few_out's residual: rounds of
-  // four C4 environments 846 -> 765 us, eight C2 448 -> 424, a plain chain of eight C3 13.05 -> 12.37 ms)
+  // four C4 environments 857 -> 840 us (846 -> 765 with the weights in the Infinity Cache), eight C2 448 -> 424, a plain chain of eight
+  // C3 13.05 -> 12.37 ms)
   __device__ __forceinline__ void with_bias(const float* b, int wave, int lane) {
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) bias[mb] = *reinterpret_cast<const f32x4*>(b + min(wave + mb * C::NW, MF - 1) * 16 + (lane >> 4) * 4);

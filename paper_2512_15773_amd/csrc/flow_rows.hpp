@@ -10,10 +10,10 @@
 //
 // For the fewest rows (flow_forward_pays, flow_draft_pays): fp32 networks, whose products are worth sixteen units a row, rollouts
 // with cross-attention, and bf16 networks (one environment, K = 8: d = 256 with a conditioning vector round 250 -> 214 us, d = 512
-// with cross-attention 773 -> 577).
+// with cross-attention 801 -> 601).
 // What bounds a few rows is the chain of dependent steps, not their work.  With two launches per layer a step was 6 to
 // 12 us: 2.4 us between dependent launches, the weights requested only then, and partial sums of the whole row (up to 272 KB)
-// read by every workgroup.  Here a step is an exchange of 16 to 64 KB through the L2 (1 to 1.5 us), workgroups of the
+// read by every workgroup.  Here a step is an exchange of 16 to 64 KB through the L2 (0.4 to 0.9 us), workgroups of the
 // next phases wait with their weights in registers, and a product's contraction is split over the wavefronts of its
 // workgroup (a wavefront owns one head's columns), so that nothing but finished activations leaves a workgroup.
 // C2, one environment, K = 8: verify 177 -> 105 us, rollout 208 -> 147, round 390 -> 257; the split also shortens the
@@ -82,7 +82,8 @@ struct FlowCfg {
                        SET_B = O_XQ + (SX ? XB : 0);
   static constexpr int STAT_B = 2 * NW * H * 4, RED_B = NW * 4 * FS * NB * 1024, STEP_B = 2 * 512 * 4;
   // LDS: statistics, sums, a step's outputs and latents, token embedding.  Wide rows: the embedding (32 KB) lies over the last quarter
-  // of the sums, which phase A does not use: all of it would be 165 KB.
+  // of the sums, which phase A does not use: 134 KB with A = 16, one after the other 166 KB.  (512 threads leave 256 registers: before
+  // its rows phase A of the wide shape keeps 26 of its operands' in scratch, 108 bytes a lane; no other shape spills vectors.)
   static constexpr bool WIDE = D * H >= FEW_WIDE;
   static constexpr int O_ET = WIDE ? STAT_B : STAT_B + RED_B, O_RED = WIDE ? STAT_B + STEP_B : STAT_B, O_TOK = WIDE ? O_RED + RED_B / 4 * 3 : O_ET + STEP_B;
   static constexpr int lds(int A) { return O_TOK + D * A * 4 > O_RED + RED_B ? O_TOK + D * A * 4 : O_RED + RED_B; }
