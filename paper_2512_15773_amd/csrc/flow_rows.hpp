@@ -459,16 +459,14 @@ __global__ __launch_bounds__(C::TH) void k_flow(FusedNet net, FlowIO io, std::co
   constexpr int D = C::D, H = C::H, DH = C::DH, NB = C::NB, KW = C::KW, KWM = C::KWM, CF = C::CF, VQ = C::VQ, VW = TT::VW, KSTEP = TT::KSTEP,
                 FS = C::FS, ES = sizeof(elem), KD = D / KSTEP, G = C::G;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  __shared__ int32_t drawn[2];
+  __shared__ int32_t drawn[4];                           // ticket; next set; sets whose tickets ran out, looks (registers across tasks: 0.5 % of a round)
   const int xcc = flow_xcc();
   const bool first_wave = threadIdx.x < 64;
   int set = xcc % FLOW_SETS;
-  if (threadIdx.x == 0) drawn[1] = flow_take(io, set, xcc);
+  if (threadIdx.x == 0) { drawn[1] = flow_take(io, set, xcc); drawn[2] = drawn[3] = 0; }
   const int rows = ROLL ? io.R_cap : min(*io.word, io.R_cap), A = io.A;
   if (rows == 0) return;
   int phases = io.phases, n_tasks = 0;
-  unsigned done = 0;                                     // sets whose tickets this workgroup has seen run out
-  int looks = 0;
   auto enter = [&]() {                                   // the set's tasks; rollout: its longest one and the phase that ends it
     if (ROLL) {
       int k_max = 0;
@@ -485,10 +483,11 @@ __global__ __launch_bounds__(C::TH) void k_flow(FusedNet net, FlowIO io, std::co
     lds_barrier();
     const int ticket = __builtin_amdgcn_readfirstlane(drawn[0]);
     if (ticket >= n_tasks) {
-      done |= 1u << set;
       if (first_wave) {                                  // (only now: the owners' words are other XCDs', and far)
+        const int done = drawn[2] | 1 << set;
+        int looks = drawn[3];
         const int other = flow_other_set(io, rows, xcc, done, looks, threadIdx.x);
-        if (threadIdx.x == 0) drawn[1] = other;
+        if (threadIdx.x == 0) { drawn[1] = other; drawn[2] = done; drawn[3] = looks; }
       }
       lds_barrier();
       set = __builtin_amdgcn_readfirstlane(drawn[1]);

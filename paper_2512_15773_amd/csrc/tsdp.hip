@@ -424,7 +424,7 @@ void flow_launch(const FusedNet& n, const FewRun& r, FlowIO& io, const std::cond
 // nothing to set and contexts on several devices or with several A do not depend on each other.
 template <class C, bool ROLL>
 hipError_t flow_declare() {
-  static_assert(C::lds(512 / C::H) + 16 <= 160 * 1024, "LDS");   // (16: the drawn ticket)
+  static_assert(C::lds(512 / C::H) + 16 <= 160 * 1024, "LDS");   // (16: the drawn ticket and set)
   return hipFuncSetAttribute((const void*)k_flow<C, ROLL>, hipFuncAttributeMaxDynamicSharedMemorySize, flow_lds<C, ROLL>(512 / C::H, 1));
 }
 
