@@ -1,12 +1,11 @@
 // Cross-attention keys / values of new observations, for the fused bf16 networks: every layer's K and V projection of
 // both networks in one launch, written straight in the fragment order the attention reads.
 //
-// The sums are k_linear's, bit for bit: fp32 fused multiply-adds over the features in ascending order, then the bias,
-// then one rounding to bf16.  mfma_f32_16x16x4_f32 adds its four products to the accumulator one after the other, each
-// with one rounding, in the order of the lane groups (checked on hardware, denormals included), so a chain of them over
-// ascending features is that sum.  Another order (three bf16 planes per observation: 0.92 ms instead of 2.83) rounds a few
-// keys to the other bf16 number, and at the first timesteps of a squared-cosine chain, where a noise prediction is
-// multiplied by 31, that is enough for a nearly tied draft to fall on the other side of its test.
+// The sums are k_linear's: fp32 fused multiply-adds over the features in ascending order, then the bias, then one rounding to
+// bf16.  Any other order rounds a few keys to the other bf16 number, and at the first timesteps of a squared-cosine chain,
+// where a noise prediction is multiplied by 31, that is enough for a nearly tied draft to fall on the other side of its test.
+// So the product runs on the bf16 matrix cores, where it is ordered otherwise, and the one number in a hundred that lies so close
+// to a rounding boundary that the order could matter is added up again, feature by feature.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -67,26 +66,34 @@ __global__ __launch_bounds__(256) void k_cond_vec(const float* __restrict__ cond
 
 struct CondNet {                 // one network's share of the launch
   const bf16x8* w;               // [L*2*d/16][KS][64] fragments: per layer the key rows, then the value rows
-  const float* bias;             // [L*2*d]
+  const float* bias;             // [L*2*d], behind them the 2-norms of the weight rows
   __bf16* kc; __bf16* vct;       // FusedNet::kc / vct
   int L, d, heads, tiles;        // tiles = L*2*d / 256
 };
 struct CondIO { CondNet net[2]; const float* cond; int M, C, KS, SF; };   // cond [M = B*S, C]
 
 // Tile: 256 features (16 fragments, all keys or all values of one layer because d is a multiple of 256) x 128 tokens
-// (8 fragments).  8 waves as 4 x 2, each 64 features x 64 tokens.  Per k-step the workgroup brings 16 KB of weights and
-// 16 KB of observations into LDS and does 1024 MFMAs, 8192 cycles of each matrix core: they bound it.  Two LDS buffers,
-// the next k-step travels through registers while the current one is multiplied; one barrier per k-step.  Two workgroups
-// per CU (128 registers, a few spilled before the loop and read back after it), one multiplies while the other waits at
-// its barrier: 2.83 ms instead of 3.04.
-// Lane group g supplies features 4m + g of a k-step to MFMA m: the weights are packed in that order (build_fused).
+// (8 fragments).  8 waves as 4 x 2, each 64 features x 64 tokens.  An observation is the sum of three bf16 numbers (its leading,
+// middle and last eight bits), the weights are bf16: three products on the bf16 matrix cores, each exact, summed in fp32.  Per
+// k-step of 32 features the workgroup brings 16 KB of weights and 24 KB of observation planes into LDS and does 384 MFMAs, 1536
+// cycles of each matrix core: they bound it.  Two LDS buffers, the next k-step travels through registers while the current one
+// is multiplied; one barrier per k-step; two workgroups per CU, one multiplies while the other waits or adds again.
 // Keys are computed features x tokens, values tokens x features, so that in both cases a lane's four accumulators are
 // the neighbouring entries of one 8-byte piece of the attention operand.
-// Measured, 256 environments x 64 tokens x 768, 12 layers of d = 512 and 2 of d = 256: 2.83 ms = 118 TFLOP/s (nominal fp32
-// matrix rate 157), against 4.9 ms of fp32 products on the vector units in 28 launches, each followed by two that rounded
-// and reordered its output.
-constexpr int COND_FF = 16, COND_TF = 8, COND_XS = 36;   // floats per token in LDS: 32 and the bank padding
-constexpr int COND_W_B = COND_FF * 64 * 16, COND_STAGE_B = COND_W_B + COND_TF * 16 * COND_XS * 4, COND_LDS = 2 * COND_STAGE_B;
+//
+// Which numbers are added again: those that round differently with COND_TIE times the product of the two 2-norms on either side
+// (an element of an empty token never).  A chain of fp32 additions ends about 0.3 of 2^-24 times that away from the exact sum
+// (standard deviation, terms of either sign), the matrix cores' sum comes on top: of the 2.2e8 numbers of 256 observations about 35 round the other way
+// with the line at 1.5, 10 at 2, none of three batches at 3 (1.25, 1.28, 1.30 ms; 4.5: 1.50).
+// The workgroup lists them in LDS, a thread takes one, and a second pass over the k-steps brings weights and observations
+// through the LDS as before.
+// Measured, 256 environments x 64 tokens x 768, 12 layers of d = 512 and 2 of d = 256: 1.30 ms (0.77 PFLOP/s in the three products),
+// 4 environments 71 us, against 2.50 ms and 109 us with fp32 operands on the fp32 matrix cores, whose chains are the sums themselves.
+constexpr int COND_FF = 16, COND_TF = 8, COND_XS = 36;   // floats per token in LDS (second pass): 32 and the bank padding
+constexpr int COND_W_B = COND_FF * 64 * 16, COND_STAGE_B = COND_W_B + 3 * COND_TF * 64 * 16, COND_LDS = 2 * COND_STAGE_B;
+constexpr int COND_AGAIN_B = COND_W_B + COND_TF * 16 * COND_XS * 4, COND_LIST = 512;
+constexpr float COND_TIE = 3.0f * 5.9604645e-8f;
+static_assert(2 * COND_AGAIN_B + 4 * (COND_LIST + 1) <= COND_LDS && COND_TF * 16 * 4 <= COND_LDS && 2 * COND_LDS <= 160 * 1024, "LDS");
 
 __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -117,14 +124,32 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
     }
     __builtin_amdgcn_sched_barrier(0);                  // (the scheduler would sink the loads to their use)
   };
+  auto observed = [&](int k, int j) { return k * 32 + xc < io.C ? rx[j] : f32x4{0, 0, 0, 0}; };   // (C is a multiple of 4; features beyond it are zero)
+  auto deposit_weights = [&](unsigned char* st) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) reinterpret_cast<bf16x8*>(st)[(wave * 2 + j) * 64 + lane] = rw[j];
+  };
+  // planes as fragments [plane][token fragment][64][8]
+  float xx[2] = {0.0f, 0.0f};                           // squares of the thread's observations
   auto deposit = [&](int k) {
     unsigned char* st = lds + (k & 1) * COND_STAGE_B;
-    const bool in = k * 32 + xc < io.C;                 // (C is a multiple of 4; features beyond it are zero)
+    deposit_weights(st);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      reinterpret_cast<bf16x8*>(st)[(wave * 2 + j) * 64 + lane] = rw[j];
-      *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(st + COND_W_B) + (xr + j * 64) * COND_XS + xc) =
-          in ? rx[j] : f32x4{0, 0, 0, 0};
+      f32x4 x = observed(k, j);
+      xx[j] += (x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]);
+      unsigned char* at = st + COND_W_B + ((j * 4 + xr / 16) * 64 + xr % 16 + 16 * (xc / 8)) * 16 + (xc % 8) * 2;
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        uint32_t b[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float v = x[i];
+          b[i] = __builtin_bit_cast(uint32_t, v) & 0xFFFF0000u;
+          x[i] = v - __builtin_bit_cast(float, b[i]);    // exact
+        }
+        *reinterpret_cast<uint2*>(at + p * (COND_TF * 64 * 16)) = make_uint2(b[0] >> 16 | b[1], b[2] >> 16 | b[3]);
+      }
     }
   };
   request(0);
@@ -142,49 +167,116 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
     for (int k = 0; k < KS; ++k) {
       __syncthreads();                                  // stage k is in LDS; stage k-1 has been read by every wave
       const unsigned char* st = lds + (k & 1) * COND_STAGE_B;
-      const float* xs = reinterpret_cast<const float*>(st + COND_W_B) + (wt * 64 + l16) * COND_XS + lg;
+      const bf16x8* xs = reinterpret_cast<const bf16x8*>(st + COND_W_B) + wt * 4 * 64 + lane;
       bf16x8 a[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) a[i] = reinterpret_cast<const bf16x8*>(st)[(wf * 4 + i) * 64 + lane];
       deposit(k + 1);
       request(k + 2);
 #pragma unroll
-      for (int m = 0; m < 8; ++m) {
-        float b[4];
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] = xs[j * 16 * COND_XS + 4 * m];
+        for (int p = 0; p < 3; ++p) {
+          const bf16x8 b = xs[(p * COND_TF + j) * 64];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc[i][j] = keys ? __builtin_amdgcn_mfma_f32_16x16x4f32((float)a[i][m], b[j], acc[i][j], 0, 0, 0)
-                             : __builtin_amdgcn_mfma_f32_16x16x4f32(b[j], (float)a[i][m], acc[i][j], 0, 0, 0);
-      }
+          for (int i = 0; i < 4; ++i)
+            acc[i][j] = keys ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b, acc[i][j], 0, 0, 0)
+                             : __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a[i], acc[i][j], 0, 0, 0);
+        }
     }
   };
   if (cls == 0) product(std::true_type{}); else product(std::false_type{});
   const int DH = n.d / n.heads, KH = DH / 32, CF = DH / 16, SF = io.SF;
+  // where the four numbers of lane `ln` in feature fragment fi of the tile and token fragment tj go
+  auto place = [&](int fi, int tj, int ln) {
+    const int fr = f_tile + fi * 16, fd = fr % n.d, head = fd / DH, fh = fd % DH, g = ln / 16;
+    const int tf = tf0 + tj, env = tf / SF, sf = tf % SF;
+    const size_t eh = ((size_t)env * n.L + layer) * n.heads + head;
+    return cls == 0 ? n.kc + (((eh * SF + sf) * KH + fh / 32) * 64 + ln % 16 + 16 * ((fh % 32) / 8 + g / 2)) * 8 + (g & 1) * 4   // a fragment is half of a 32-deep k-step
+                    : n.vct + (((eh * CF + fh / 16) * SF + sf) * 64 + ln) * 4;
+  };
+  // norms of the tokens: eight threads hold one
+  float* norm = reinterpret_cast<float*>(lds);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    float q = xx[j];
+#pragma unroll
+    for (int m = 1; m < 8; m *= 2) q += __shfl_xor(q, m);
+    if ((threadIdx.x & 7) == 0) norm[xr + j * 64] = COND_TIE * sqrtf(q);
+  }
+  __syncthreads();
+  uint64_t again = 0;                                   // bit (i * 4 + j) * 4 + e
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int fr = f_tile + (wf * 4 + i) * 16;          // first feature of the fragment, [layer][k|v][d]
-    const int fd = fr % n.d, head = fd / DH, fh = fd % DH;
+    const float *b = n.bias + f_tile + (wf * 4 + i) * 16, *wn = b + n.L * per_layer;
+    const f32x4 bias = cls == 0 ? *reinterpret_cast<const f32x4*>(b + lg * 4) : f32x4{b[l16], b[l16], b[l16], b[l16]};
+    const f32x4 wnorm = cls == 0 ? *reinterpret_cast<const f32x4*>(wn + lg * 4) : f32x4{wn[l16], wn[l16], wn[l16], wn[l16]};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int tf = tf0 + wt * 4 + j;
-      if (tf >= MF) continue;
-      const int env = tf / SF, sf = tf % SF;
-      const size_t eh = ((size_t)env * n.L + layer) * n.heads + head;
-      if (cls == 0) {
-        const f32x4 b = *reinterpret_cast<const f32x4*>(n.bias + fr + lg * 4);
-        const int ks = fh / 32, g = (fh % 32) / 8 + lg / 2;      // a fragment is half of a 32-deep k-step
-        __bf16* dst = n.kc + (((eh * SF + sf) * KH + ks) * 64 + l16 + 16 * g) * 8 + (lg & 1) * 4;
-        *reinterpret_cast<bf16x4*>(dst) = to_bf16x4(acc[i][j] + b);
-      } else {
-        const float b = n.bias[fr + l16];
-        __bf16* dst = n.vct + (((eh * CF + fh / 16) * SF + sf) * 64 + lane) * 4;
-        *reinterpret_cast<bf16x4*>(dst) = to_bf16x4(acc[i][j] + b);
+      if (tf0 + wt * 4 + j >= MF) continue;
+      const f32x4 v = acc[i][j] + bias;
+      *reinterpret_cast<bf16x4*>(place(wf * 4 + i, wt * 4 + j, lane)) = to_bf16x4(v);
+      const float* xn = norm + (wt * 4 + j) * 16;
+      const f32x4 tie = wnorm * (cls == 0 ? f32x4{xn[l16], xn[l16], xn[l16], xn[l16]} : *reinterpret_cast<const f32x4*>(xn + lg * 4));
+      unsigned m = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if ((float)(__bf16)(v[e] - tie[e]) != (float)(__bf16)(v[e] + tie[e]) || !(fabsf(v[e]) + tie[e] < 3.0e38f)) m |= 1u << e;   // (not finite: again)
+      again |= (uint64_t)m << ((i * 4 + j) * 4);
+    }
+  }
+  // second pass
+  int* list = reinterpret_cast<int*>(lds + 2 * COND_AGAIN_B);
+  int* listed = list + COND_LIST;
+  auto deposit_again = [&](int k) {
+    unsigned char* st = lds + (k & 1) * COND_AGAIN_B;
+    deposit_weights(st);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(st + COND_W_B) + (xr + j * 64) * COND_XS + xc) = observed(k, j);
+  };
+  for (;;) {
+    __syncthreads();                                    // the LDS is free, and what was stored above has left (the numbers added again are stored over it)
+    if (threadIdx.x == 0) *listed = 0;
+    __syncthreads();
+    while (again) {
+      const int slot = atomicAdd(listed, 1);
+      if (slot >= COND_LIST) break;
+      const int p = __builtin_ctzll(again);
+      again &= again - 1;
+      list[slot] = (int)threadIdx.x << 6 | p;
+    }
+    __syncthreads();
+    const int total = min(*listed, COND_LIST);
+    if (total == 0) break;
+    const bool mine = (int)threadIdx.x < total;
+    const int item = list[mine ? threadIdx.x : 0], ow = item >> 12, ol = item >> 6 & 63, p = item & 63;
+    const int fi = (ow & 3) * 4 + p / 16, tj = (ow >> 2) * 4 + p / 4 % 4, four = (ol >> 4) * 4 + p % 4;
+    const int fl = cls == 0 ? four : ol & 15, tk = tj * 16 + (cls == 0 ? ol & 15 : four);
+    request(0);
+    deposit_again(0);
+    request(1);
+    float sum = 0.0f;
+    for (int k = 0; k < KS; ++k) {
+      __syncthreads();
+      const unsigned char* st = lds + (k & 1) * COND_AGAIN_B;
+      deposit_again(k + 1);
+      request(k + 2);
+      if (mine) {
+        const bf16x8* w = reinterpret_cast<const bf16x8*>(st) + fi * 64 + fl;
+        const f32x4* x = reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(st + COND_W_B) + tk * COND_XS);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const bf16x8 wv = w[g * 16];
+          const f32x4 x0 = x[2 * g], x1 = x[2 * g + 1];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sum = fmaf(x0[i], (float)wv[i], sum);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sum = fmaf(x1[i], (float)wv[4 + i], sum);
+        }
       }
     }
+    if (mine) place(fi, tj, ol)[p % 4] = (__bf16)(sum + n.bias[f_tile + fi * 16 + fl]);
   }
 }
 

@@ -75,7 +75,7 @@ struct Net {
   uint16_t* kc_pk = nullptr;    // fragment-ordered bf16 keys / transposed values of every (env, layer, head)
   uint16_t* vct_pk = nullptr;
   uint8_t* kv_w = nullptr;      // key / value projections of all layers as MFMA fragments (fused bf16 cross-attention)
-  float* kv_b = nullptr;        // their biases, [L][k|v][d]
+  float* kv_b = nullptr;        // their biases, [L][k|v][d], and the 2-norms of their rows
 };
 
 }  // namespace
@@ -700,24 +700,23 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
     const size_t S = cf.cond_tokens, cnt = (size_t)cf.B_max * L * S * d;
     if (!n.kc_pk && (rc = dev_alloc(c, &n.kc_pk, cnt))) return rc;
     if (!n.vct_pk && (rc = dev_alloc(c, &n.vct_pk, cnt))) return rc;
-    // key / value projections, per layer the key rows then the value rows; inside a k-step entry i of lane group g is
-    // feature 4i + g (k_cond_kv)
+    // key / value projections, per layer the key rows then the value rows (k_cond_kv)
     std::vector<uint8_t> kv;
     std::vector<float> kvb;
-    const int C = cf.cond_dim, CP = (C + 31) / 32 * 32;
-    std::vector<float> ord((size_t)d * CP, 0.0f);
-    auto pack_kv = [&](const float* src) {
-      for (int r = 0; r < d; ++r)
-        for (int k = 0; k < C; ++k) ord[(size_t)r * CP + k / 32 * 32 + k % 4 * 8 + k % 32 / 4] = src[(size_t)r * C + k];
-      pack_frags(kv, false, ord.data(), CP, d, ident);
-    };
     for (int l = 0; l < L; ++l) {
       const LayerOff& o = n.lay[l];
-      pack_kv(&w[o.ck_w]);
-      pack_kv(&w[o.cv_w]);
+      pack_frags(kv, false, &w[o.ck_w], cf.cond_dim, d, ident);
+      pack_frags(kv, false, &w[o.cv_w], cf.cond_dim, d, ident);
       kvb.insert(kvb.end(), &w[o.ck_b], &w[o.ck_b] + d);
       kvb.insert(kvb.end(), &w[o.cv_b], &w[o.cv_b] + d);
     }
+    for (int l = 0; l < L; ++l)
+      for (const size_t at : {n.lay[l].ck_w, n.lay[l].cv_w})
+        for (int r = 0; r < d; ++r) {
+          double q = 0.0;
+          for (int k = 0; k < cf.cond_dim; ++k) { const double v = w[at + (size_t)r * cf.cond_dim + k]; q += v * v; }
+          kvb.push_back((float)std::sqrt(q));
+        }
     if (!n.kv_w && (rc = dev_alloc(c, &n.kv_w, kv.size()))) return rc;
     if (!n.kv_b && (rc = dev_alloc(c, &n.kv_b, kvb.size()))) return rc;
     HIPCHK(c, hipMemcpy(n.kv_w, kv.data(), kv.size(), hipMemcpyHostToDevice));

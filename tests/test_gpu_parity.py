@@ -170,6 +170,54 @@ def test_keys_and_values_add_the_observation_features_in_order(cond_dim, S):
     ctx.close()
 
 
+@pytest.mark.parametrize("cond_dim", [32, 36, 768])
+def test_keys_and_values_round_as_their_sums_in_order_do(cond_dim):
+    # with weights of one a key is an observation's features added up in ascending order.  The last feature puts that fp32 sum
+    # halfway between two bf16 numbers or one unit beside it, so that a sum in any other order rounds the other way in about every
+    # second token; the observation that holds the sum itself and zeros must give the same bits.  The last pair of environments: an
+    # empty token among the others, a not-a-number and an overflow
+    import torch
+    n, S = 5, 64
+    wl = ti.small_variant(ti.C4, B=2 * n, K_max=1, cond_dim=cond_dim, cond_tokens=S, base=ti.NetShape(1, 512, 8), draft=ti.NetShape(1, 256, 8))
+    nets = [ti.make_weights(wl, which) for which in ("base", "draft")]
+    for w in nets:
+        for name in w:
+            if name.endswith(("ck_w", "cv_w")):
+                w[name][:] = 1.0
+    rng = np.random.default_rng(cond_dim)
+    x = rng.standard_normal((n, S, cond_dim)).astype(np.float32)
+    part = np.zeros((n, S), np.float32)
+    for c in range(cond_dim - 1):
+        part += x[:, :, c]
+    b = (part.view(np.uint32) & np.uint32(0xFFFF0000)) + np.uint32(0x8000) + rng.integers(0, 2, (n, S)).astype(np.uint32)
+    x[:, :, -1] = b.view(np.float32) - part
+    x[-1, :8] = 0.0
+    total = np.zeros((n, S), np.float32)
+    for c in range(cond_dim):
+        total += x[:, :, c]
+    cond = np.zeros((2 * n, S, cond_dim), np.float32)
+    cond[0::2] = x
+    cond[1::2, :, 0] = total
+    ctx = gpu_side(wl, *nets, cond, B_max=2 * n)
+    rows = ctx.alloc_rows(2 * n)
+    one = np.ones(2 * n, np.int32)
+
+    def run():
+        ctx.tsdp_draft(to_dev(np.repeat(ti.make_latents(wl, 1), 2 * n, axis=0)), to_dev(50 * one), to_dev(one), to_dev(np.ones(2 * n, np.float32)),
+                       to_dev(7 * one), rows)
+        ctx.tsdp_verify(2 * n, rows)
+        return {name: rows[name].clone() for name in ("eps_p", "eps_q")}
+
+    finite = run()
+    for name, e in finite.items():
+        assert bool(torch.isfinite(e).all()) and torch.equal(e[0::2], e[1::2]), name
+    cond[-1, 3, 1] = np.nan; cond[-2, 3, :2] = 3e38
+    ctx.tsdp_set_cond(to_dev(cond))
+    for name, e in run().items():
+        assert torch.equal(e[:-2], finite[name][:-2]) and not bool(torch.isfinite(e[-1]).any()), name
+    ctx.close()
+
+
 @pytest.mark.parametrize("base, B, K_max", [
     (ti.replace(ti.C2, base=ti.NetShape(2, 256, 4)), 1, 1),       # one row
     (ti.replace(ti.C2, base=ti.NetShape(2, 256, 4)), 9, 1),       # rows not a multiple of the eight XCDs
