@@ -384,7 +384,7 @@ struct FewGemm {
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
       for (int nb = 0; nb < C::NB; ++nb) acc[mb][nb] = f32x4{0, 0, 0, 0};
-    g.run(act, stride, acc, lane, typename G::NoSide{}, std::integral_constant<int, G::PF>{});
+    g.run(act, stride, acc, lane, NoSide{}, std::integral_constant<int, G::PF>{});
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       const int f = wave + mb * C::NW;
@@ -896,7 +896,7 @@ __global__ __launch_bounds__(256, 1) void k_few_film(const void* __restrict__ mo
   lds_barrier();
   f32x4 acc[1][1] = {{f32x4{0, 0, 0, 0}}};
   if constexpr (DC > 0) {
-    g.run(sg, AS, acc, lane, typename G::NoSide{}, std::integral_constant<int, G::PF>{});
+    g.run(sg, AS, acc, lane, NoSide{}, std::integral_constant<int, G::PF>{});
   } else {
     few_gemm_dyn<1>(modw, KD, f, 1, 0, KD, reinterpret_cast<const float*>(sg), AS, 0, lane,
                     [&](int, const f32x4 (&a)[1]) { acc[0][0] = a[0]; });

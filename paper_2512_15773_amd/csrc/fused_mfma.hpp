@@ -37,6 +37,7 @@ struct FusedLayer {            // device pointers of one layer
 };
 
 constexpr int FUSED_MAX_LAYERS = 16;
+constexpr int MAX_DRAFTS = 64;   // K_max of a context (tsdp_create)
 
 struct FusedNet {
   FusedLayer layer[FUSED_MAX_LAYERS];
@@ -181,6 +182,8 @@ __device__ __forceinline__ void softmax_keys(f32x4 (&s)[NK], typename TT::vec4 (
 constexpr int INFLIGHT_CLK = 384;   // cycles of matrix work between the request of a weight fragment and its use
 constexpr int PF_MAX = 4;           // upper limit of the weight ring's depth in k-steps
 
+struct NoSide { __device__ __forceinline__ void operator()(int) const {} };
+
 // Weight-streaming GEMM on fragments:  acc[mb][nb] += W(frag rows mf0+mb, k-steps ks0..ks0+NKS) . act^T,
 // act = LDS bf16 [token][stride].  Fully unrolled with compile-time trip counts.  The weight fragments of
 // k-step k+PF are requested from L2 before the MFMAs of k-step k issue and the LDS operands of k-step k+1
@@ -198,7 +201,8 @@ struct FragGemm {
   static constexpr int PFW = (INFLIGHT_CLK + STEP_CLK - 1) / STEP_CLK;
   static constexpr int PF0 = PFX > 0 ? PFX : (PFW < 1 ? 1 : (PFW > PF_MAX ? PF_MAX : PFW));
   static constexpr int PF = PF0 > NKS ? NKS : PF0;
-  frag a[PF + 1][MB];
+  static constexpr int RING = PF < NKS ? PF + 1 : PF;
+  frag a[RING][MB];
   const frag* wl;
   int kst;                     // elements between the fragment rows of consecutive mb (in k-steps)
 
@@ -221,14 +225,19 @@ struct FragGemm {
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) a[p][mb] = wl[((size_t)mb * kst + p) * 64];
   }
+  // the first N k-steps at once
+  template <int N>
+  __device__ __forceinline__ void prime(const void* __restrict__ wp, int ks_total, int mf0, int ks0, int lane, int mfs = 1) {
+    prime_begin(wp, ks_total, mf0, ks0, lane, mfs);
+#pragma unroll
+    for (int p = 0; p < N; ++p) prime_stage(p);
+  }
   // to be called as side work of k-step k of a product of PREV k-steps: requests stage k - (PREV - PF)
   template <int PREV>
   __device__ __forceinline__ void prime_in_tail(int k) {
     static_assert(PREV >= PF, "the previous product is too short to hide the priming");
     if (k >= PREV - PF) prime_stage(k - (PREV - PF));
   }
-
-  struct NoSide { __device__ __forceinline__ void operator()(int) const {} };
 
   __device__ __forceinline__ void run(const elem* act, int stride, f32x4 (&acc)[MB][NB], int lane) {
     run(act, stride, acc, lane, NoSide{});
@@ -254,7 +263,7 @@ struct FragGemm {
       if (k + PF < NKS) {
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
-          a[(k + PF) % (PF + 1)][mb] = wl[((size_t)mb * kst + k + PF) * 64];
+          a[(k + PF) % RING][mb] = wl[((size_t)mb * kst + k + PF) * 64];
       }
       if (BD == 2 && k + 1 < NKS) {
 #pragma unroll
@@ -266,7 +275,7 @@ struct FragGemm {
       for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
-          TT::mma(a[k % (PF + 1)][mb], b[k % BD][nb], acc[mb][nb]);
+          TT::mma(a[k % RING][mb], b[k % BD][nb], acc[mb][nb]);
       side(k);
       if (BD == 1 && k + 1 < NKS) {
 #pragma unroll
@@ -309,7 +318,7 @@ struct FusedCfg {
   static constexpr int U_B = NT * US * ES;
   static constexpr int XT_B = NT * 64 * 4;              // fp32 latent staging of the verify kernel (A <= 64)
   // two hidden-chunk buffers (one barrier per chunk instead of two) when a single workgroup owns the CU's LDS
-  static constexpr bool UDB = (NW == 8) && (ACT_B + 2 * U_B + 2 * NW * NT * 4 + 7 * D * 4 <= 160 * 1024) && (2 * U_B >= QKV_B);
+  static constexpr bool UDB = (NW == 8) && CH < 4 * D && (ACT_B + 2 * U_B + 2 * NW * NT * 4 + 7 * D * 4 <= 160 * 1024) && (2 * U_B >= QKV_B);
   static constexpr int UU_B = UDB ? 2 * U_B : U_B;
   static constexpr int SCR0_B = QKV_B > UU_B ? QKV_B : UU_B;
   static constexpr int SCR_B = SCR0_B > XT_B ? SCR0_B : XT_B;
@@ -317,11 +326,19 @@ struct FusedCfg {
   static constexpr int UB_B = UDB ? 7 * D * 4 : 0;      // pipelined MLP: the layer's up-projection bias and the three residual biases (fp32)
   static constexpr int LDS_B = ACT_B + SCR_B + RED_B + UB_B;   // body; the drafter kernel appends its own regions
   static constexpr int WG_PER_CU = LDS_B <= 80 * 1024 && NW <= 4 ? 2 : 1;
+  static constexpr bool DRAFT = false, STAGED = false;
   static constexpr bool LN_STAGE = true;                // FiLM vectors come from global memory: fetch them cooperatively
   static constexpr int WAVES_PER_SIMD = (WG_PER_CU * NW + 3) / 4;
   static constexpr int BD = WAVES_PER_SIMD >= 2 ? 1 : 2; // LDS operand buffers: a second wave on the SIMD hides LDS latency
   static constexpr bool XPF = WAVES_PER_SIMD == 1;      // request the first weights of the MLP's products one phase early
                                                          // (those of the attention blocks always: C3 -1 %, C4, C5 no change beyond the noise)
+  // One row per workgroup, all heads and the whole hidden layer in one phase each, and a layer's weights fit three quarters of
+  // the registers: the rollout then keeps them in flight half a layer ahead (LayerStream).
+  static constexpr bool STREAM = NB == 1 && CM == 0 && CH == 4 * D && HP == HEADS &&
+                                 (MBQ + MBH + MBU) * (D / KSTEP) + MBH * (4 * D / KSTEP) <= (NW <= 4 ? 96 : 48);
+  static constexpr int TASKS = RPT * HP * NKF;          // of one phase of self-attention
+  static constexpr bool NOISE_ATT = STREAM && TASKS < NW;   // rollout: wavefronts without a task make the noise, else those without a part in the head
+  static constexpr int NOISE_W = NOISE_ATT ? TASKS : NB;
   static_assert(D % (16 * NW) == 0 && NT % 16 == 0 && H % 16 == 0 && NT % H == 0 && DH % KSTEP == 0, "shape");
   static_assert(D % KSTEP == 0 && CH % KSTEP == 0, "shape");
   static_assert((HEADS % HP) == 0 && (HP * 3 * DH) % (16 * NW) == 0 && (CM == 0 || (HPX * DH) % (16 * NW) == 0) &&
@@ -332,22 +349,89 @@ struct FusedCfg {
 
 // Configuration of the persistent drafter: a rollout has few workgroups in flight (one per environment tile), so no
 // second wave hides latency; it therefore always prefetches across phases and double-buffers the LDS operands.
-template <class Base>
+template <class Base, bool STAGED_>
 struct DraftCfg : Base {
-  static constexpr bool XPF = true;
-  static constexpr bool LN_STAGE = false;               // the drafter's FiLM vectors are already in LDS (or a small table)
+  static constexpr bool DRAFT = true, STAGED = STAGED_, XPF = true;   // STAGED: the token embedding is in LDS
+  static constexpr bool LN_STAGE = false;               // the drafter's FiLM vectors are already in LDS
   static constexpr int BD = 2;
 };
+
+// FiLM vectors of the tile's rows: load(r, i) = entries i .. i+3 of row r.  Pointers that come from memory are said to be global
+// and the rollout's vectors lie at computed LDS addresses: as generic pointers both were read by flat loads, which wait for
+// every weight that is on its way.
+struct FilmRows {
+  const float* const* row;
+  __device__ __forceinline__ f32x4 load(int r, int i) const {
+    return *reinterpret_cast<const __attribute__((address_space(1))) f32x4*>((const __attribute__((address_space(1))) float*)row[r] + i);
+  }
+};
+struct FilmLds {
+  const float* base; int stride;
+  __device__ __forceinline__ f32x4 load(int r, int i) const { return *reinterpret_cast<const f32x4*>(base + r * stride + i); }
+};
+
+// Weights of a layer in flight, half a layer ahead of the products.  A load is issued at the rate at which the unit takes its data
+// (1 KB: 16 cycles), and a wavefront does nothing else while it waits for its turn: the requests of a product one after the other
+// cost as much as the stream itself.  So they are spread over what the layer does besides, a few at every place: q | k | v and
+// the output projection of the next layer under the GELU and the down-projection, the up-projection in the first half of this layer, the
+// down-projection from the attention to the second normalisation.  (In the order of the products: loads return in order.)
+// 64 environments, 16 transitions of d = 128, two layers: 234 us before, 232 with each product's weights requested at once and
+// ahead of time, 192 spread, 187 with what follows below out of the way (a load or a store whose result is waited for in the loop drains
+// the stream).  Without any weights 167: the rest is the phases' latency (20 barriers, half of the time in waits, a quarter in vector
+// instructions).
+template <class C>
+struct LayerStream {
+  typedef typename C::TT TT;
+  static constexpr int KD = C::D / C::KSTEP, KM = 4 * C::D / C::KSTEP;
+  FragGemm<TT, C::MBQ, 1, KD, 2, KD> q;
+  FragGemm<TT, C::MBH, 1, KD, 2, KD> o;
+  FragGemm<TT, C::MBU, 1, KD, 2, KD> u;
+  FragGemm<TT, C::MBH, 1, KM, 2, KM> d;
+  FragGemm<TT, 1, 1, KD, 2, KD> head;                    // the first 16 components of the output head stay
+  typedef std::integral_constant<int, KD> FULL;
+  typedef std::integral_constant<int, KM> FULLM;
+  // sixteenths [FROM, TO) of a product's requests
+  template <int FROM, int TO, class G>
+  static __device__ __forceinline__ void feed(G& g, int ks) {
+#pragma unroll
+    for (int p = FROM * ks / 16; p < TO * ks / 16; ++p) g.prime_stage(p);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  template <int FROM, int TO> __device__ __forceinline__ void feed_q() { feed<FROM, TO>(q, KD); }
+  template <int FROM, int TO> __device__ __forceinline__ void feed_o() { feed<FROM, TO>(o, KD); }
+  template <int FROM, int TO> __device__ __forceinline__ void feed_u() { feed<FROM, TO>(u, KD); }
+  template <int FROM, int TO> __device__ __forceinline__ void feed_d() { feed<FROM, TO>(d, KM); }
+  __device__ __forceinline__ void first(const FusedLayer& W, const void* head_w, int wave, int lane) {
+    head.template prime<KD>(head_w, KD, 0, 0, lane);
+    next(W, wave, lane);
+    feed_q<0, 16>();
+    feed_o<0, 16>();
+  }
+  __device__ __forceinline__ void next(const FusedLayer& W, int wave, int lane) {
+    q.prime_begin(W.qkv, KD, wave, 0, lane, C::NW);
+    o.prime_begin(W.o, KD, wave * C::MBH, 0, lane);
+  }
+  __device__ __forceinline__ void here(const FusedLayer& W, int wave, int lane) {
+    u.prime_begin(W.up, KD, wave * C::MBU, 0, lane);
+    d.prime_begin(W.dn, KM, wave * C::MBH, 0, lane);
+  }
+};
+struct NoStream {};
+struct NoIdle { __device__ __forceinline__ void operator()(int, int) const {} };
 
 // One forward pass for the tile.  xt: LDS fp32 [NT][A] latent tokens (may alias the scratch region: it is
 // consumed before the first barrier-protected write).  mrow[r]: FiLM vectors of local row r, all layers (global
 // or LDS).  env_of_row: environment of local row r (cross-attention).
 // eps is written to eo[t*A + a] for local tokens t < ntok_live.
-template <class C>
+// Rollouts: lbias = biases in LDS, the head's 64 ahead of them, etok = the transposed token embedding and, behind it, tok_b + pos
+// [H][D] in LDS (C::STAGED),
+// idle(wave, lane) runs on the wavefronts from NOISE_W on, stream = the weights in flight (C::STREAM).
+template <class C, class Film, class Stream = NoStream, class Idle = NoIdle>
 __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* lds, const float* xt, int A,
-                                           const float* const* mrow,
+                                           const Film& film,
                                            const int32_t* env_of_row, float* eo, int ntok_live,
-                                           const float* lbias = nullptr) {
+                                           const float* lbias = nullptr, const float* etok = nullptr,
+                                           Stream&& stream = Stream{}, Idle&& idle = Idle{}) {
   constexpr int D = C::D, NT = C::NT, H = C::H, HEADS = C::HEADS, CM = C::CM, CH = C::CH, NW = C::NW;
   constexpr int DH = C::DH, HP = C::HP, NB = C::NB, MBH = C::MBH, MBQ = C::MBQ, MBU = C::MBU, MBC = C::MBC,
                 RPT = C::RPT, NKF = C::NKF, AS = C::AS, QS = C::QS, VS = C::VS, US = C::US, SF = C::SF;
@@ -388,33 +472,52 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
   typedef FragGemm<TT, (MBC > 0 ? MBC : 1), NB, KD, BD> GC;   // cross-attention query projection
 
   // ---- token embedding in fp32: h = tok_w x + tok_b + pos -------------------------------------------------
+  // (a product over the A components: mfma_f32_16x16x4_f32 adds its four products one after the other, each with one rounding)
   f32x4 h[MBH][NB];
 #pragma unroll
   for (int mb = 0; mb < MBH; ++mb) {
     const int f0 = (wave * MBH + mb) * 16 + lg * 4;
-    const f32x4 tb = *reinterpret_cast<const f32x4*>(net.tok_b + f0);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const int t = nb * 16 + l16;
-      h[mb][nb] = tb + *reinterpret_cast<const f32x4*>(net.pos + (t % H) * D + f0);
+      const int t = (nb * 16 + l16) % H;
+      if constexpr (C::STAGED) h[mb][nb] = *reinterpret_cast<const f32x4*>(etok + (A + t) * D + f0);
+      else h[mb][nb] = *reinterpret_cast<const f32x4*>(net.tok_b + f0) + *reinterpret_cast<const f32x4*>(net.pos + t * D + f0);
     }
-    for (int a = 0; a < A; ++a) {
-      f32x4 wv;
+  }
+  for (int a0 = 0; a0 < A; a0 += 16) {
+    float w[4][MBH], x[4][NB];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) wv[i] = net.tok_w[(f0 + i) * A + a];
+    for (int j = 0; j < 4; ++j) {
+      const int a = a0 + j * 4 + lg;
+      const bool in = a < A;
+#pragma unroll
+      for (int mb = 0; mb < MBH; ++mb) {
+        const int at = (in ? a : 0) * D + (wave * MBH + mb) * 16 + l16;
+        float v;
+        if constexpr (C::STAGED) v = etok[at];
+        else v = net.tok_wt[at];
+        w[j][mb] = in ? v : 0.0f;
+      }
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
-        const float xv = xt[(nb * 16 + l16) * A + a];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) h[mb][nb][i] = fmaf(xv, wv[i], h[mb][nb][i]);
+        const float v = xt[(nb * 16 + l16) * A + (in ? a : 0)];
+        x[j][nb] = in ? v : 0.0f;
       }
     }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (a0 + j * 4 < A)
+#pragma unroll
+        for (int mb = 0; mb < MBH; ++mb)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) h[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[j][mb], x[j][nb], h[mb][nb], 0, 0, 0);
   }
   lds_barrier();
 
   // writes LN(h) (1 + g) + b as bf16 into act; which = 0 (attention) / 2 (MLP) selects the FiLM pair, -1 = none.
   // Statistics: per-wave partial results (fp32) exchanged through LDS, one barrier.
-  auto write_ln = [&](int layer, int which) {
+  struct Nowhere { __device__ __forceinline__ void operator()() const {} };
+  auto write_ln_with = [&](int layer, int which, auto&& before, auto&& between) {   // work ahead of the statistics and behind their barrier
     FENCE_LANE_IDS();
     // FiLM vectors of the tile's rows: requested first, so they arrive while the statistics are reduced
     // (only where they fit in 64 registers; otherwise they are read fragment row by fragment row)
@@ -426,9 +529,9 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
       for (int mb = 0; mb < MBH; ++mb)
 #pragma unroll
         for (int r = 0; r < RPT; ++r) {
-          const float* mp = mrow[r] + layer * 4 * D + which * D + (wave * MBH + mb) * 16 + lg * 4;
-          fg[mb][r] = *reinterpret_cast<const f32x4*>(mp);
-          fb[mb][r] = *reinterpret_cast<const f32x4*>(mp + D);
+          const int at = (layer * 4 + which) * D + (wave * MBH + mb) * 16 + lg * 4;
+          fg[mb][r] = film.load(r, at);
+          fb[mb][r] = film.load(r, at + D);
         }
     }
     // Otherwise the wave fetches its block [row][g|b][its features] cooperatively, 16 distinct bytes per lane and
@@ -443,11 +546,11 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
         const int c = lane + 64 * i;
         if (c < CHK) {
           const int r = c / (2 * MBH * 4), rem = c % (2 * MBH * 4);
-          st[i] = *reinterpret_cast<const f32x4*>(mrow[r] + layer * 4 * D + which * D + (rem / (MBH * 4)) * D +
-                                                  (wave * MBH + (rem / 4) % MBH) * 16 + (rem % 4) * 4);
+          st[i] = film.load(r, (layer * 4 + which + rem / (MBH * 4)) * D + (wave * MBH + (rem / 4) % MBH) * 16 + (rem % 4) * 4);
         }
       }
     }
+    before();
     // Statistics.  fp32 networks (results are held to 1e-5): without cancellation -- every wave reduces the sum of
     // its D/NW features of a token and then their squared deviations from its own mean (registers only); the NW
     // (sum, M2) pairs are combined after one barrier, M2 = sum_w M2_w + n_w (mean_w - mean)^2; the roundings are
@@ -456,6 +559,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
     // RMSNorm takes the plain second moment either way.
     constexpr bool CENTRED = std::is_same<TT, TF32>::value;
     constexpr float NWF = (float)(D / NW);              // features per wave
+    constexpr bool PAIRS = C::DRAFT && NW % 2 == 0;      // (a rollout waits for every read: fewer of them)
     float mean[NB], rstd[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
@@ -479,15 +583,26 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
         s = add_half32(add_row16(s));
       }
       q = add_half32(add_row16(q));
-      if (lane < 16) { red1[wave * NT + nb * 16 + lane] = s; red2[wave * NT + nb * 16 + lane] = q; }
+      if (lane < 16) {
+        if (PAIRS) *reinterpret_cast<float2*>(red1 + (nb * 16 + lane) * 2 * NW + wave * 2) = make_float2(s, q);
+        else { red1[wave * NT + nb * 16 + lane] = s; red2[wave * NT + nb * 16 + lane] = q; }
+      }
     }
     lds_barrier();
+    between();
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       const int t = nb * 16 + l16;
       float sw[NW], s = 0.0f, q = 0.0f;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) { sw[w] = red1[w * NT + t]; s += sw[w]; q += red2[w * NT + t]; }
+      for (int w = 0; w < NW; ++w) {
+        if (PAIRS) {                                     // two wavefronts' sums in one read
+          const f32x4 v = *reinterpret_cast<const f32x4*>(red1 + t * 2 * NW + (w & ~1) * 2);
+          sw[w] = v[(w & 1) * 2]; s += sw[w]; q += v[(w & 1) * 2 + 1];
+        } else {
+          sw[w] = red1[w * NT + t]; s += sw[w]; q += red2[w * NT + t];
+        }
+      }
       mean[nb] = net.rms ? 0.0f : s * (1.0f / D);     // RMSNorm: no centring, the second moment as it is
       if (CENTRED) {
         if (!net.rms) {
@@ -528,9 +643,8 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
             const f32x4 b = *reinterpret_cast<const f32x4*>(fs + ((r * 2 + 1) * MBH + mb) * 16 + lg * 4);
             v = v * (1.0f + g) + b;
           } else {
-            const float* mp = mrow[(nb * 16) / H] + layer * 4 * D + which * D + f0;
-            const f32x4 g = *reinterpret_cast<const f32x4*>(mp);
-            const f32x4 b = *reinterpret_cast<const f32x4*>(mp + D);
+            const f32x4 g = film.load((nb * 16) / H, (layer * 4 + which) * D + f0);
+            const f32x4 b = film.load((nb * 16) / H, (layer * 4 + which + 1) * D + f0);
             v = v * (1.0f + g) + b;
           }
         }
@@ -540,6 +654,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
     }
     lds_barrier();
   };
+  auto write_ln = [&](int layer, int which) { write_ln_with(layer, which, Nowhere{}, Nowhere{}); };
 
   // softmax(q k^T) v for query fragment qf of (row, head) held in LDS; the result overwrites those q rows
   auto self_attention = [&](int r, int hh, int qf) {
@@ -645,12 +760,109 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
     }
   };
 
+  // q | k | v of a head group into LDS
+  auto put_qkv = [&](const f32x4 (&acc)[MBQ][NB], auto&& bias) {
+#pragma unroll
+    for (int mb = 0; mb < MBQ; ++mb) {
+      const int lr = (mb * NW + wave) * 16;             // first logical row of this fragment inside the group (rows are
+                                                        // dealt round-robin so every wave gets q, k and v rows)
+      const int hh = lr / (3 * DH), cls = (lr / DH) % 3, c0 = lr % DH + lg * 4;
+      const f32x4 b = bias(mb);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const f32x4 v = acc[mb][nb] + b;
+        const int t = nb * 16 + l16;
+        if (cls == 0) {
+          *reinterpret_cast<vec4*>(qbuf + t * QTS + hh * DH + c0) = TT::cvt(v);
+        } else if (cls == 1) {
+          *reinterpret_cast<vec4*>(kbuf + (hh * NT + t) * QS + c0) = TT::cvt(v);
+        } else {
+          elem* vp = vtb + ((size_t)(hh * RPT + t / H) * DH + c0) * VS + (t % H);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) vp[i * VS] = (elem)v[i];
+        }
+      }
+    }
+  };
+  auto attend = [&]() {
+    for (int task = wave; task < RPT * HP * NKF; task += NW)
+      self_attention((task / NKF) % RPT, task / (NKF * RPT), task % NKF);
+  };
+  // GELU(acc + bias) of a hidden chunk into LDS
+  auto put_hidden = [&](const f32x4 (&acc)[MBU][NB], auto&& bias, elem* ub) {
+#pragma unroll
+    for (int mb = 0; mb < MBU; ++mb) {
+      const int f0 = (wave * MBU + mb) * 16 + lg * 4;
+      const f32x4 b = bias(mb);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        f32x4 v = acc[mb][nb] + b;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = gelu_fast(v[i]);
+        *reinterpret_cast<vec4*>(ub + (nb * 16 + l16) * US + f0) = TT::cvt(v);
+      }
+    }
+  };
+
+  constexpr bool STREAMS = !std::is_same<std::remove_reference_t<Stream>, NoStream>::value;
+  if constexpr (STREAMS) {
+    typedef std::remove_reference_t<Stream> LS;
+    for (int layer = 0; layer < net.L; ++layer) {
+      const FusedLayer &W = net.layer[layer], &N = net.layer[layer + 1 < net.L ? layer + 1 : 0];
+      const float* lb = lbias + layer * 9 * D;           // output projection, MLP down, q | k | v, MLP up
+      stream.here(W, wave, lane);
+      write_ln_with(layer, 0, [&]() { stream.template feed_u<0, 4>(); }, [&]() { stream.template feed_u<4, 8>(); });
+      {
+        f32x4 acc[MBQ][NB];
+#pragma unroll
+        for (int mb = 0; mb < MBQ; ++mb) acc[mb][0] = f32x4{0, 0, 0, 0};
+        stream.q.run(act, AS, acc, lane, NoSide{}, typename LS::FULL{});
+        stream.template feed_u<8, 12>();
+        put_qkv(acc, [&](int mb) { return *reinterpret_cast<const f32x4*>(lb + 2 * D + (mb * NW + wave) * 16 + lg * 4); });
+      }
+      stream.template feed_u<12, 16>();
+      lds_barrier();
+      attend();
+      stream.template feed_d<0, 4>();
+      if (C::NOISE_ATT && layer == 0 && wave >= C::NOISE_W) idle(wave, lane);
+      lds_barrier();
+      stream.o.run(qbuf, QTS, h, lane, NoSide{}, typename LS::FULL{});
+#pragma unroll
+      for (int mb = 0; mb < MBH; ++mb) h[mb][0] += *reinterpret_cast<const f32x4*>(lb + (wave * MBH + mb) * 16 + lg * 4);
+      stream.next(N, wave, lane);
+      write_ln_with(layer, 2, [&]() { stream.template feed_d<4, 10>(); }, [&]() { stream.template feed_d<10, 16>(); });
+      {
+        f32x4 acc[MBU][NB];
+#pragma unroll
+        for (int mb = 0; mb < MBU; ++mb) acc[mb][0] = f32x4{0, 0, 0, 0};
+        stream.u.run(act, AS, acc, lane, NoSide{}, typename LS::FULL{});
+        put_hidden(acc, [&](int mb) {
+          if (mb == 1) stream.template feed_q<0, 4>();
+          if (mb == 3) stream.template feed_q<4, 8>();
+          return *reinterpret_cast<const f32x4*>(lb + 5 * D + (wave * MBU + mb) * 16 + lg * 4);
+        }, ubuf);
+      }
+      lds_barrier();
+      stream.d.run(ubuf, US, h, lane, [&](int k) {
+        if (k == 1) stream.template feed_q<8, 12>();
+        if (k == 4) stream.template feed_q<12, 16>();
+        if (k == 6) stream.template feed_o<0, 16>();
+      }, typename LS::FULLM{});
+#pragma unroll
+      for (int mb = 0; mb < MBH; ++mb) h[mb][0] += *reinterpret_cast<const f32x4*>(lb + D + (wave * MBH + mb) * 16 + lg * 4);
+    }
+  } else {
+  // first weights of a product ahead of the phase before it: the whole ring where a second wavefront does not hide their way
   GQ gq;
-  if (XPF) gq.issue(net.layer[0].qkv, KD, wave, 0, lane, NW);
+  typedef std::integral_constant<int, C::DRAFT ? GQ::PF : 1> PQ;
+  typedef std::integral_constant<int, C::DRAFT ? GO::PF : 1> PO;
+  typedef std::integral_constant<int, C::DRAFT ? GU::PF : 1> PU;
+  typedef std::integral_constant<int, C::DRAFT ? GD::PF : 1> PD;
+  if (XPF) gq.template prime<PQ::value>(net.layer[0].qkv, KD, wave, 0, lane, NW);
   for (int layer = 0; layer < net.L; ++layer) {
     const FusedLayer& W = net.layer[layer];
     // ================= self-attention block =================
-    if (!XPF) gq.issue(W.qkv, KD, wave, 0, lane, NW);
+    if (!XPF) gq.template prime<PQ::value>(W.qkv, KD, wave, 0, lane, NW);
     write_ln(layer, 0);
     if constexpr (BSTAGE) {
       // The layer's biases that are added outside a product's own latency shadow go to LDS: the MLP's GELU runs inside
@@ -678,36 +890,16 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0, 0, 0, 0};
         }
-        gq.run(act, AS, acc, lane);
-        go.issue(W.o, KD, wave * MBH, g * HP * KH, lane);      // needed only after the attention
+        gq.run(act, AS, acc, lane, NoSide{}, PQ{});
+        go.template prime<PO::value>(W.o, KD, wave * MBH, g * HP * KH, lane);      // needed only after the attention
         if (g > 0) lds_barrier();                     // previous group's O-projection has read qbuf
-#pragma unroll
-        for (int mb = 0; mb < MBQ; ++mb) {
-          const int lr = (mb * NW + wave) * 16;         // first logical row of this fragment inside the group (rows are
-                                                        // dealt round-robin so every wave gets q, k and v rows)
-          const int hh = lr / (3 * DH), cls = (lr / DH) % 3, c0 = lr % DH + lg * 4;
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) {
-            const f32x4 v = acc[mb][nb] + bias[mb];
-            const int t = nb * 16 + l16;
-            if (cls == 0) {
-              *reinterpret_cast<vec4*>(qbuf + t * QTS + hh * DH + c0) = TT::cvt(v);
-            } else if (cls == 1) {
-              *reinterpret_cast<vec4*>(kbuf + (hh * NT + t) * QS + c0) = TT::cvt(v);
-            } else {
-              elem* vp = vtb + ((size_t)(hh * RPT + t / H) * DH + c0) * VS + (t % H);
-#pragma unroll
-              for (int i = 0; i < 4; ++i) vp[i * VS] = (elem)v[i];
-            }
-          }
-        }
+        put_qkv(acc, [&](int mb) { return bias[mb]; });
       }
       lds_barrier();
-      for (int task = wave; task < RPT * HP * NKF; task += NW)
-          self_attention((task / NKF) % RPT, task / (NKF * RPT), task % NKF);
+      attend();
       lds_barrier();
-      if (g + 1 < NG) gq.issue(W.qkv, KD, (g + 1) * (HP * 3 * DH / 16) + wave, 0, lane, NW);
-      go.run(qbuf, QTS, h, lane);                        // one product over the heads of the group
+      if (g + 1 < NG) gq.template prime<PQ::value>(W.qkv, KD, (g + 1) * (HP * 3 * DH / 16) + wave, 0, lane, NW);
+      go.run(qbuf, QTS, h, lane, NoSide{}, PO{});       // one product over the heads of the group
     }
     add_bias_h(W.o_b, layer, 0);
     // ================= cross-attention block (observation tokens) =================
@@ -867,7 +1059,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
           if constexpr (PRIME) gd.run(ubuf + (c & 1) * NT * US, US, h, lane, side, DFULL{});
           else gd.run(ubuf + (c & 1) * NT * US, US, h, lane, side, ONE{});
         } else {
-          if constexpr (PRIME) gd.run(ubuf + (c & 1) * NT * US, US, h, lane, typename GD::NoSide{}, DFULL{});
+          if constexpr (PRIME) gd.run(ubuf + (c & 1) * NT * US, US, h, lane, NoSide{}, DFULL{});
           else gd.run(ubuf + (c & 1) * NT * US, US, h, lane);
         }
       };
@@ -891,7 +1083,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
       chunk(NC - 1, accA, accB, std::false_type{}, std::false_type{});
     } else {
     GU gu;
-    if (XPF) gu.issue(W.up, KD, wave * MBU, 0, lane);
+    if (XPF) gu.template prime<PU::value>(W.up, KD, wave * MBU, 0, lane);
     write_ln(layer, 2);                                  // its barriers also order the projection reads before ubuf writes
     for (int c = 0; c < NC; ++c) {
       FENCE_LANE_IDS();
@@ -905,52 +1097,52 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0, 0, 0, 0};
         }
-        if (!XPF) gu.issue(W.up, KD, c * (CH / 16) + wave * MBU, 0, lane);
-        gu.run(act, AS, acc, lane);
-        if (XPF) gd.issue(W.dn, KM, wave * MBH, c * (KC), lane);
+        if (!XPF) gu.template prime<PU::value>(W.up, KD, c * (CH / 16) + wave * MBU, 0, lane);
+        gu.run(act, AS, acc, lane, NoSide{}, PU{});
+        if (XPF) gd.template prime<PD::value>(W.dn, KM, wave * MBH, c * (KC), lane);
         // single buffer: the previous chunk's down-projection has read ubuf; double buffer: the buffer written
         // now was last read two chunks ago, and every wave has passed a barrier since
         if (c > 0 && !C::UDB) lds_barrier();
-        elem* ub = ubuf + (C::UDB ? (c & 1) * NT * US : 0);
-#pragma unroll
-        for (int mb = 0; mb < MBU; ++mb) {
-          const int f0 = (wave * MBU + mb) * 16 + lg * 4;
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) {
-            f32x4 v = acc[mb][nb] + bias[mb];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = gelu_fast(v[i]);
-            *reinterpret_cast<vec4*>(ub + (nb * 16 + l16) * US + f0) = TT::cvt(v);
-          }
-        }
+        put_hidden(acc, [&](int mb) { return bias[mb]; }, ubuf + (C::UDB ? (c & 1) * NT * US : 0));
       }
       lds_barrier();
       if (XPF) {
-        if (c + 1 < NC) gu.issue(W.up, KD, (c + 1) * (CH / 16) + wave * MBU, 0, lane);
-        else if (layer + 1 < net.L) gq.issue(net.layer[layer + 1].qkv, KD, wave, 0, lane, NW);
+        if (c + 1 < NC) gu.template prime<PU::value>(W.up, KD, (c + 1) * (CH / 16) + wave * MBU, 0, lane);
+        else if (layer + 1 < net.L) gq.template prime<PQ::value>(net.layer[layer + 1].qkv, KD, wave, 0, lane, NW);
       } else {
-        gd.issue(W.dn, KM, wave * MBH, c * (KC), lane);
+        gd.template prime<PD::value>(W.dn, KM, wave * MBH, c * (KC), lane);
       }
-      gd.run(ubuf + (C::UDB ? (c & 1) * NT * US : 0), US, h, lane);
+      gd.run(ubuf + (C::UDB ? (c & 1) * NT * US : 0), US, h, lane, NoSide{}, PD{});
     }
     }
     add_bias_h(W.dn_b, layer, 2);
   }
+  }
 
   // ---- output head: eps = head_w LN(h) + head_b ---------------------------------------------------------
+  constexpr int NBW = (NB + NW - 1) / NW;               // token fragments per wave
+  const int nb0 = wave * NBW;
+  FragGemm<TT, 1, NBW, KD, 2, C::DRAFT ? (KD < 8 ? KD : 8) : 0> gh;
+  typedef std::integral_constant<int, C::DRAFT ? decltype(gh)::PF : 1> PH;   // rollouts: ahead of the normalisation
+  if (C::DRAFT && !STREAMS && nb0 < NB) gh.template prime<PH::value>(net.head, KD, 0, 0, lane);
   write_ln(0, -1);
   {
-    constexpr int NBW = (NB + NW - 1) / NW;             // token fragments per wave
-    const int nb0 = wave * NBW;
-    if (nb0 < NB) {
+    if (nb0 >= NB) {
+      if (!C::NOISE_ATT) idle(wave, lane);
+    } else {
       // the head's A output rows are packed as ceil(A/16) fragment rows (zero rows pad the last one)
       for (int hf = 0; hf * 16 < A; ++hf) {
         f32x4 e[1][NBW];
 #pragma unroll
         for (int j = 0; j < NBW; ++j) e[0][j] = f32x4{0, 0, 0, 0};
-        FragGemm<TT, 1, NBW, KD> gh;
-        gh.issue(net.head, KD, hf, 0, lane);
-        gh.run(act + nb0 * 16 * AS, AS, e, lane);
+        bool done = false;
+        if constexpr (STREAMS) {
+          if (hf == 0) { stream.head.run(act, AS, e, lane, NoSide{}, std::integral_constant<int, KD>{}); done = true; }
+        }
+        if (!done) {
+          if (!C::DRAFT || STREAMS || hf) gh.template prime<PH::value>(net.head, KD, hf, 0, lane);
+          gh.run(act + nb0 * 16 * AS, AS, e, lane, NoSide{}, PH{});
+        }
 #pragma unroll
         for (int j = 0; j < NBW; ++j) {
           const int t = (nb0 + j) * 16 + l16;
@@ -958,7 +1150,10 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const int a = hf * 16 + lg * 4 + i;
-              if (a < A) eo[t * A + a] = e[0][j][i] + net.head_b[a];
+              float hb;
+              if constexpr (C::DRAFT) hb = lbias[a - 64];
+              else hb = a < A ? net.head_b[a] : 0.0f;
+              if (a < A) eo[t * A + a] = e[0][j][i] + hb;
             }
           }
         }
@@ -994,36 +1189,62 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void k_fused_forward(Fuse
     }
   }
   lds_barrier();
-  fused_body<C>(net, lds, xt, A, mrow, envs, io.eps_out + tok0 * A, ntok_live);
+  fused_body<C>(net, lds, xt, A, FilmRows{mrow}, envs, io.eps_out + tok0 * A, ntok_live);
 }
+
+// LDS of the rollout behind the body's: latents, drafter output (LayerStream: noise); FiLM vectors; biases of all layers (they are added right
+// after a product, where a global load has nothing to overlap it, K times per rollout, and behind the weights in flight it would
+// wait for them): output projections and MLP down, LayerStream also q | k | v and MLP up; transposed token embedding and tok_b + pos,
+// where there is room.
+constexpr int DRAFT_LDS = 157 * 1024;   // (the rest: the tile's environments and coefficients, at most 2.2 KB)
+template <class C>
+struct DraftLds {
+  static constexpr int NBIAS = C::STREAM ? 9 : 3;
+  static constexpr int tile(int A) { return C::NT * A; }
+  static constexpr int mod(int A) { return (C::STREAM ? 3 : 2) * tile(A); }
+  static constexpr int bias(int A, int L, int mod_cols) { return mod(A) + mod_cols * L * 4 * C::D; }
+  static constexpr int tok(int A, int L, int mod_cols) { return bias(A, L, mod_cols) + 64 + L * NBIAS * C::D; }   // (64: the head's)
+  static constexpr int bytes(int A, int L, int mod_cols, bool staged) {
+    return C::LDS_B + 4 * (tok(A, L, mod_cols) + (staged ? (A + C::H) * C::D : 0));
+  }
+  static constexpr bool ALWAYS = bytes(512 / C::H, FUSED_MAX_LAYERS, C::RPT, true) <= DRAFT_LDS;   // the embedding fits for every network
+};
 
 // Drafter rollout: the workgroup keeps the latents of RPT environments in LDS and runs their drafted
 // transitions k = 1 .. max K_eff back to back; every step is one forward pass plus the DDPM step
 //   y <- mu_p(y, eps, t_k) + s sigma_{t_k} xi_{env,t_k},   t_k = t0 - k + 1,
 // and stores the input state, the drafter output and the noise of the transition in its ragged row.
-template <class C>
+template <class C, bool STAGED>
 __global__ __launch_bounds__(C::THREADS) void k_fused_draft(FusedNet net, DraftIO io, int A) {
   typedef typename C::TT TT;
   typedef typename TT::elem elem;
-  constexpr int D = C::D, NT = C::NT, H = C::H, TH = C::THREADS, SGS = D + TT::PAD;
+  typedef DraftLds<C> Lds;
+  constexpr int D = C::D, NT = C::NT, H = C::H, TH = C::THREADS, SGS = D + TT::PAD, NW = C::NW;
   constexpr int RPT = C::RPT;
+  constexpr bool IDLE = C::NB < NW;                     // wavefronts without a part in the output head
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  __shared__ int32_t envs[RPT], s_t0[RPT], s_keff[RPT], s_rowp[RPT], s_kmax;
-  __shared__ const float* mrow[RPT];
+  __shared__ int32_t envs[RPT], s_t0[RPT], s_keff[RPT], s_rowp[RPT], s_id[RPT], s_kmax;
+  __shared__ float s_scale[RPT];
+  // coefficients of a transition, LayerStream of all of them: a load in the loop would wait for the weights on their way
+  constexpr int COEF = C::STREAM ? MAX_DRAFTS : 1;
+  __shared__ __attribute__((aligned(16))) float s_step[COEF][RPT][8];   //: sqrt_abar, sqrt_1m, c0, cx, ce, noise scale
   const int DE = H * A;                                 // elements of one latent
   const int mod_stride = net.L * 4 * D;
-  float* yt = reinterpret_cast<float*>(lds + C::LDS_B);              // [NT*A] latents
-  float* et = yt + NT * A;                                           // [NT*A] drafter output
-  // The FiLM product has 16 columns (one MFMA tile): column j = environment j / SPE, step offset j % SPE.  With
-  // mod_cols = 16 it yields the vectors of SPE = 16 / RPT consecutive steps at once, so the FiLM weights stream once
-  // per SPE steps; with mod_cols = RPT (when LDS is short) one step at a time.
   const int mod_cols = io.mod_cols, SPE = mod_cols / RPT;
-  float* modbuf = et + NT * A;                                       // [mod_cols][L*4D] FiLM vectors
-  elem* sgbuf = reinterpret_cast<elem*>(modbuf + mod_cols * mod_stride);   // [16][D+pad] SiLU(g), unused rows zero
-  // [L][3][D] residual biases (self-attention output, cross-attention output, MLP down) of all layers: they are added
-  // right after a product, where a global load has nothing to overlap it, K times per rollout
-  float* dbias = reinterpret_cast<float*>(sgbuf + 16 * SGS);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, lg = lane >> 4;
+  float* yt = reinterpret_cast<float*>(lds + C::LDS_B);              // [NT*A] latents
+  float* et = yt + Lds::tile(A);                                     // [NT*A] drafter output
+  // [NT*A] noise.  Made beside the output head it lies in the scratch region, which nothing else uses until the next attention.
+  float* zt = C::STREAM ? et + Lds::tile(A) : reinterpret_cast<float*>(lds + C::ACT_B);
+  static_assert(C::STREAM || RPT * 512 * 4 <= C::SCR_B, "noise");
+  // FiLM vectors.  The product has 16 columns (one MFMA tile): column j = environment j / SPE, step offset j % SPE.  With
+  // mod_cols = 16 it yields the vectors of SPE = 16 / RPT consecutive steps at once, so the FiLM weights stream once
+  // per SPE steps; with mod_cols = RPT (when LDS is short, and where they come from the table) one step at a time.
+  float* modbuf = yt + Lds::mod(A);                                  // [mod_cols][L*4D]
+  float* dbias = yt + Lds::bias(A, net.L, mod_cols) + 64;
+  float* tok = yt + Lds::tok(A, net.L, mod_cols);
+  elem* sgbuf = reinterpret_cast<elem*>(lds);                        // [16][D+pad] SiLU(g), over the activations: between two steps
+  static_assert(16 * SGS * C::ES <= C::ACT_B, "FiLM input");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, lg = lane >> 4;
   const int env0 = blockIdx.x * RPT;
   if (*io.gate == 0 && !io.bonus) return;
   if (threadIdx.x == 0) s_kmax = 0;
@@ -1038,14 +1259,25 @@ __global__ __launch_bounds__(C::THREADS) void k_fused_draft(FusedNet net, DraftI
     const int ke = live ? io.K_eff[b] : 0;
     s_keff[threadIdx.x] = ke;
     s_rowp[threadIdx.x] = live ? io.row_ptr[b] : 0;
+    s_id[threadIdx.x] = live && io.env_id ? io.env_id[b] : b;
+    s_scale[threadIdx.x] = live ? io.sigma_scale[b] : 0.0f;
     atomicMax(&s_kmax, ke);
   }
   const bool any = *io.gate != 0;
-  if (any) for (int i = threadIdx.x; i < 16 * SGS; i += TH) sgbuf[i] = (elem)0.0f;
-  if (any) for (int i = threadIdx.x; i < net.L * 3 * D; i += TH) {
-    const int l = i / (3 * D), which = (i / D) % 3, c = i % D;
-    const float* src = which == 0 ? net.layer[l].o_b : (which == 1 ? net.layer[l].co_b : net.layer[l].dn_b);
-    dbias[i] = src ? src[c] : 0.0f;
+  if (any) {
+    for (int i = threadIdx.x; i < net.L * Lds::NBIAS * D; i += TH) {
+      const int l = i / (Lds::NBIAS * D), at = i % (Lds::NBIAS * D), which = at / D, c = at % D;
+      const FusedLayer& W = net.layer[l];
+      float v;
+      if constexpr (C::STREAM) v = which == 0 ? W.o_b[c] : which == 1 ? W.dn_b[c] : which < 5 ? W.qkv_b[at - 2 * D] : W.up_b[at - 5 * D];
+      else v = which == 0 ? W.o_b[c] : which == 1 ? (W.co_b ? W.co_b[c] : 0.0f) : W.dn_b[c];
+      dbias[i] = v;
+    }
+    if (threadIdx.x < 64) dbias[(int)threadIdx.x - 64] = (int)threadIdx.x < A ? net.head_b[threadIdx.x] : 0.0f;
+    if constexpr (STAGED) {
+      for (int i = threadIdx.x; i < A * D; i += TH) tok[i] = net.tok_wt[i];
+      for (int i = threadIdx.x; i < H * D; i += TH) tok[A * D + i] = net.tok_b[i % D] + net.pos[i];
+    }
   }
   for (int i = threadIdx.x; i < NT * A; i += TH) {
     const int b = env0 + i / DE;
@@ -1053,35 +1285,30 @@ __global__ __launch_bounds__(C::THREADS) void k_fused_draft(FusedNet net, DraftI
   }
   lds_barrier();
   const int kmax = s_kmax;
-  for (int k = 1; k <= kmax; ++k) {
-    if (net.modtab) {                                   // FiLM vectors of timestep t_k straight from the table
-      if (threadIdx.x < RPT) {
-        int t = s_t0[threadIdx.x] - k + 1;
-        t = t < 0 ? 0 : t;
-        mrow[threadIdx.x] = net.modtab + (size_t)t * mod_stride;
+  // FiLM vectors of steps k .. k+SPE-1
+  auto film = [&](int k) {
+    if constexpr (C::CM == 1) {                         // the table's rows of timestep t_k
+      for (int i = threadIdx.x * 4; i < RPT * mod_stride; i += TH * 4) {
+        const int r = i / mod_stride;
+        const int t = max(s_t0[r] - k + 1, 0);
+        *reinterpret_cast<f32x4*>(modbuf + i) = *reinterpret_cast<const f32x4*>(net.modtab + (size_t)t * mod_stride + (i - r * mod_stride));
       }
     } else {
-    const int so = (k - 1) % SPE;                       // offset of this step in the current batch of SPE steps
-    if (threadIdx.x < RPT) mrow[threadIdx.x] = modbuf + (threadIdx.x * SPE + so) * mod_stride;
-    if (so == 0) {
-    // FiLM inputs of steps k .. k+SPE-1: SiLU(temb[t] + cemb[env]) as rows of the mod product's B operand
-    for (int i = threadIdx.x; i < mod_cols * D; i += TH) {
-      const int j = i / D, c = i % D, r = j / SPE;
-      int t = s_t0[r] - (k + j % SPE) + 1;
-      t = t < 0 ? 0 : t;
-      float g = net.temb[(size_t)t * D + c];
-      if (net.cemb) g += net.cemb[(size_t)envs[r] * D + c];
-      sgbuf[j * SGS + c] = (elem)silu_fast(g);
-    }
-    lds_barrier();
-    {
-      constexpr int MBM = 2;
-      const int fpw = net.L * 4 * D / (16 * C::NW);     // mod fragments per wave
+      // inputs: SiLU(temb[t] + cemb[env]) as rows of the product's B operand (rows from mod_cols on: columns that are not stored)
+      for (int i = threadIdx.x; i < mod_cols * D; i += TH) {
+        const int j = i / D, c = i % D, r = j / SPE;
+        const int t = max(s_t0[r] - (k + j % SPE) + 1, 0);
+        const float g = net.temb[(size_t)t * D + c] + net.cemb[(size_t)envs[r] * D + c];
+        sgbuf[j * SGS + c] = (elem)silu_fast(g);
+      }
+      lds_barrier();
+      constexpr int MBM = C::STREAM || C::ES == 4 ? 2 : 4;   // bf16 tiles: all weights of four fragment rows in flight
+      const int fpw = net.L * 4 * D / (16 * NW);        // mod fragments per wave
       for (int f = 0; f < fpw; f += MBM) {
         f32x4 acc[MBM][1];
 #pragma unroll
         for (int mb = 0; mb < MBM; ++mb) acc[mb][0] = f32x4{0, 0, 0, 0};
-        FragGemm<TT, MBM, 1, D / TT::KSTEP> gm;
+        FragGemm<TT, MBM, 1, D / TT::KSTEP, 2, C::ES == 4 ? 0 : D / TT::KSTEP> gm;
         gm.issue(net.modw, D / TT::KSTEP, wave * fpw + f, 0, lane);
         gm.run(sgbuf, SGS, acc, lane);
         if (l16 < mod_cols) {
@@ -1094,27 +1321,69 @@ __global__ __launch_bounds__(C::THREADS) void k_fused_draft(FusedNet net, DraftI
         }
       }
     }
-    }
-    }
     lds_barrier();
-    fused_body<DraftCfg<C>>(net, lds, yt, A, mrow, envs, et, NT, dbias);
+  };
+  // coefficients of environment r's transition k
+  auto coef_of = [&](int k, int r, f32x4& ca, f32x4& cb) {
+    const int t = max(s_t0[r] - k + 1, 0);
+    ca = f32x4{io.tb.sqrt_abar[t], io.tb.sqrt_1m[t], io.tb.c0[t], io.tb.cx[t]};
+    cb = f32x4{io.tb.ce[t], io.tb.sigma[t], 0.0f, 0.0f};
+  };
+  auto put_coef = [&](int at, int r, const f32x4& ca, f32x4 cb) {
+    cb[1] = s_scale[r] * cb[1];
+    *reinterpret_cast<f32x4*>(s_step[at][r]) = ca;
+    *reinterpret_cast<f32x4*>(s_step[at][r] + 4) = cb;
+  };
+  if constexpr (C::STREAM) {
+    for (int i = threadIdx.x; i < kmax * RPT; i += TH) {
+      f32x4 ca, cb;
+      coef_of(i / RPT + 1, i % RPT, ca, cb);
+      put_coef(i / RPT, i % RPT, ca, cb);
+    }
+  }
+  // noise blocks i, i + stride, .. of the tile, and by the last RPT lanes the transition's coefficients
+  auto noise = [&](int k, int i0, int stride) {
+    const int nblk = DE >> 2, rc = stride - 1 - i0;
+    f32x4 ca = {0, 0, 0, 0}, cb = {0, 0, 0, 0};
+    if (!C::STREAM && rc < RPT) coef_of(k, rc, ca, cb);
+    for (int i = i0; i < RPT * nblk * 2; i += stride) {  // half a block a lane
+      const int r = RPT == 1 ? 0 : i / (2 * nblk), blk = i / 2 - r * nblk;
+      if (k > s_keff[r]) continue;
+      const float2 z = xi_pair(io.seed, s_id[r], s_t0[r] - k + 1, blk, i & 1);
+      *reinterpret_cast<float2*>(zt + r * DE + 4 * blk + 2 * (i & 1)) = z;
+    }
+    if (!C::STREAM && rc < RPT) put_coef(0, rc, ca, cb);
+  };
+  std::conditional_t<C::STREAM, LayerStream<C>, NoStream> stream;
+  if (kmax > 0) film(1);
+  if constexpr (C::STREAM) {
+    if (kmax > 0) {
+      stream.first(net.layer[0], net.head, wave, lane);
+    }
+  }
+  for (int k = 1, so = 0; k <= kmax; ++k) {             // so: offset of the step in its batch of FiLM vectors
+    const FilmLds rows{modbuf + so * mod_stride, SPE * mod_stride};
+    if constexpr (IDLE) {                               // the wavefronts that the output head leaves idle make the noise
+      fused_body<DraftCfg<C, STAGED>>(net, lds, yt, A, rows, envs, et, NT, dbias, tok, stream,
+                              [&](int w, int ln) { noise(k, (w - C::NOISE_W) * 64 + ln, (NW - C::NOISE_W) * 64); });
+    } else {
+      fused_body<DraftCfg<C, STAGED>>(net, lds, yt, A, rows, envs, et, NT, dbias, tok, stream);
+      noise(k, threadIdx.x, TH);
+    }
     lds_barrier();
     // DDPM step of transition k for the environments that still draft
     const int nblk = DE >> 2;
     for (int i = threadIdx.x; i < RPT * nblk; i += TH) {
-      const int r = i / nblk, blk = i % nblk;
+      const int r = RPT == 1 ? 0 : i / nblk, blk = i - r * nblk;
       if (k > s_keff[r]) continue;
-      const int b = env0 + r;
-      const int t = s_t0[r] - k + 1;
       const size_t row = (size_t)s_rowp[r] + k - 1;
       float* yp = yt + r * DE + 4 * blk;
-      const float* ep = et + r * DE + 4 * blk;
       const f32x4 yv = *reinterpret_cast<const f32x4*>(yp);
-      const f32x4 ev = *reinterpret_cast<const f32x4*>(ep);
-      const float4 z4 = xi_block(io.seed, io.env_id ? io.env_id[b] : b, t, blk);
-      const f32x4 z = {z4.x, z4.y, z4.z, z4.w};
-      const float sa = io.tb.sqrt_abar[t], s1 = io.tb.sqrt_1m[t], c0 = io.tb.c0[t], cx = io.tb.cx[t], ce = io.tb.ce[t];
-      const float sig = io.sigma_scale[b] * io.tb.sigma[t];
+      const f32x4 ev = *reinterpret_cast<const f32x4*>(et + r * DE + 4 * blk);
+      const f32x4 z = *reinterpret_cast<const f32x4*>(zt + r * DE + 4 * blk);
+      const float* co = s_step[C::STREAM ? k - 1 : 0][r];
+      const f32x4 ca = *reinterpret_cast<const f32x4*>(co), cb = *reinterpret_cast<const f32x4*>(co + 4);
+      const float sa = ca[0], s1 = ca[1], c0 = ca[2], cx = ca[3], ce = cb[0], sig = cb[1];
       f32x4 o;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -1122,12 +1391,13 @@ __global__ __launch_bounds__(C::THREADS) void k_fused_draft(FusedNet net, DraftI
         if (io.clip) x0 = fminf(fmaxf(x0, -io.clip_val), io.clip_val);
         o[j] = c0 * x0 + cx * yv[j] + ce * ev[j] + sig * z[j];
       }
+      *reinterpret_cast<f32x4*>(yp) = o;
       *reinterpret_cast<f32x4*>(io.states + row * DE + 4 * blk) = yv;
       *reinterpret_cast<f32x4*>(io.eps_p + row * DE + 4 * blk) = ev;
       if (io.xi) *reinterpret_cast<f32x4*>(io.xi + row * DE + 4 * blk) = z;
-      *reinterpret_cast<f32x4*>(yp) = o;
     }
-    lds_barrier();
+    if (++so == SPE && k < kmax) { so = 0; film(k + 1); }   // (ends in a barrier)
+    else lds_barrier();
   }
   if (any) for (int i = threadIdx.x; i < NT * A; i += TH) {
     const int b = env0 + i / DE;
@@ -1136,12 +1406,12 @@ __global__ __launch_bounds__(C::THREADS) void k_fused_draft(FusedNet net, DraftI
   if (io.bonus) {                                       // the state reached by the last draft, with a base step's noise
     const int nblk = DE >> 2;
     for (int i = threadIdx.x; i < RPT * nblk; i += TH) {
-      const int r = i / nblk, blk = i % nblk, b = env0 + r;
+      const int r = i / nblk, blk = i % nblk;
       if (s_t0[r] < 0) continue;
       const int t = s_t0[r] - s_keff[r];
       const size_t row = (size_t)s_rowp[r] + s_keff[r];
       float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (t > 0) z = xi_block(io.seed, io.env_id ? io.env_id[b] : b, t, blk);
+      if (t > 0) z = xi_block(io.seed, s_id[r], t, blk);
       *reinterpret_cast<f32x4*>(io.states + row * DE + 4 * blk) = *reinterpret_cast<const f32x4*>(yt + r * DE + 4 * blk);
       *reinterpret_cast<f32x4*>(io.eps_p + row * DE + 4 * blk) = f32x4{0, 0, 0, 0};
       if (io.xi) *reinterpret_cast<f32x4*>(io.xi + row * DE + 4 * blk) = f32x4{z.x, z.y, z.z, z.w};

@@ -36,6 +36,15 @@ __device__ __forceinline__ float4 xi_block(uint64_t seed, int env, int t, int bl
   return make_float4(r0 * c0, r0 * s0, r1 * c1, r1 * s1);
 }
 
+// the first (half = 0) or second two of them
+__device__ __forceinline__ float2 xi_pair(uint64_t seed, int env, int t, int blk, int half) {
+  const u32x4 w = philox4x32_10((uint32_t)blk, (uint32_t)t, (uint32_t)env, 0u, (uint32_t)seed, (uint32_t)(seed >> 32));
+  const float r = sqrtf(-2.0f * logf(u01(half ? w.z : w.x)));
+  float s, c;
+  sincospif(2.0f * u01(half ? w.w : w.y), &s, &c);
+  return make_float2(r * c, r * s);
+}
+
 __device__ __forceinline__ float accept_uniform(uint64_t seed, int env, int t) {
   const u32x4 w = philox4x32_10(0u, (uint32_t)t, (uint32_t)env, 1u, (uint32_t)seed, (uint32_t)(seed >> 32));
   return u01(w.x);

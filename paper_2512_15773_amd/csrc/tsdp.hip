@@ -228,17 +228,10 @@ hipError_t launch_verify(const FusedNet& n, const FusedIO& io, int A, int R_cap,
   return hipSuccess;
 }
 
-template <class C>
-hipError_t launch_draft(const FusedNet& n, const DraftIO& io_in, int A, hipStream_t s) {
-  auto kern = k_fused_draft<C>;
-  DraftIO io = io_in;
-  // FiLM vectors of up to 16 / RPT steps per in-kernel product, as many as LDS has room for
-  const int fixed = C::LDS_B + 2 * C::NT * A * 4 + 16 * (C::D + C::TT::PAD) * C::ES + n.L * 3 * C::D * 4;
-  const int per_col = n.L * 4 * C::D * 4;
-  io.mod_cols = C::RPT;
-  for (int cols = 16; cols > C::RPT; cols /= 2)
-    if (cols % C::RPT == 0 && fixed + cols * per_col <= 160 * 1024) { io.mod_cols = cols; break; }
-  const int lds = fixed + io.mod_cols * per_col;
+template <class C, bool STAGED>
+hipError_t launch_draft_as(const FusedNet& n, const DraftIO& io, int A, hipStream_t s) {
+  auto kern = k_fused_draft<C, STAGED>;
+  const int lds = DraftLds<C>::bytes(A, n.L, io.mod_cols, STAGED);
   static int attr_lds = 0;
   if (lds > attr_lds) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -248,6 +241,19 @@ hipError_t launch_draft(const FusedNet& n, const DraftIO& io_in, int A, hipStrea
   const int tiles = (io.B + C::RPT - 1) / C::RPT;
   if (tiles > 0) hipLaunchKernelGGL(kern, dim3(tiles), dim3(C::THREADS), lds, s, n, io, A);
   return hipSuccess;
+}
+
+template <class C>
+hipError_t launch_draft(const FusedNet& n, const DraftIO& io_in, int A, hipStream_t s) {
+  typedef DraftLds<C> Lds;
+  DraftIO io = io_in;
+  // FiLM vectors of up to 16 / RPT steps per in-kernel product, as many as LDS has room for, then the token embedding
+  io.mod_cols = C::RPT;
+  for (int cols = 16; C::CM == 0 && cols > C::RPT; cols /= 2)
+    if (cols % C::RPT == 0 && Lds::bytes(A, n.L, cols, Lds::ALWAYS) <= DRAFT_LDS) { io.mod_cols = cols; break; }
+  if constexpr (!Lds::ALWAYS)
+    if (Lds::bytes(A, n.L, io.mod_cols, true) > DRAFT_LDS) return launch_draft_as<C, false>(n, io, A, s);
+  return launch_draft_as<C, true>(n, io, A, s);
 }
 
 template <int D>
@@ -975,7 +981,7 @@ int tsdp_create(const tsdp_config* cfg, tsdp_ctx** out) {
       f.cond_mode > 1 || f.cond_dim < 4 || f.cond_dim % 4 || (f.cond_mode == 1 && (f.cond_tokens < 1 || f.cond_tokens > 256)) ||
       bad(f.base_d, f.base_heads, f.base_layers, f.base_mlp_ratio) ||
       bad(f.draft_d, f.draft_heads, f.draft_layers, f.draft_mlp_ratio) || f.T < 1 || f.T > 4096 || f.schedule < 0 ||
-      f.schedule > 1 || f.B_max < 1 || f.K_max < 1 || f.K_max > 64 || (f.clip_x0 && !(f.clip_val > 0.0f)))
+      f.schedule > 1 || f.B_max < 1 || f.K_max < 1 || f.K_max > MAX_DRAFTS || (f.clip_x0 && !(f.clip_val > 0.0f)))
     return TSDP_E_INVAL;
   if (f.sampler < 0 || f.sampler > 1 || (f.sampler == 1 && !(f.eta > 0.0f && f.eta <= 1.0f))) return TSDP_E_INVAL;
   if (f.schedule == 0 && !(f.beta0 > 0.0f && f.beta1 >= f.beta0 && f.beta1 < 1.0f)) return TSDP_E_INVAL;

@@ -218,6 +218,22 @@ def test_keys_and_values_round_as_their_sums_in_order_do(cond_dim):
     ctx.close()
 
 
+@pytest.mark.parametrize("wl, B, K_max", [
+    (ti.small_variant(ti.C3, A=32, draft=ti.NetShape(16, 128, 4)), 2, 2),       # one row a workgroup, weights in flight: the most LDS
+    (ti.small_variant(ti.C3, A=4, draft=ti.NetShape(1, 128, 4)), 1, 64),        # one layer; the most transitions
+    (ti.small_variant(ti.C3, A=17, draft=ti.NetShape(3, 128, 4)), 3, 18),       # two fragments of components; more steps than a FiLM batch
+    (ti.small_variant(ti.C1, A=32, draft=ti.NetShape(16, 32, 2)), 2, 4),        # the same in fp32
+    (ti.small_variant(ti.C1, A=1, draft=ti.NetShape(3, 32, 2)), 2, 4),
+    (ti.small_variant(ti.C4, A=16, draft=ti.NetShape(6, 256, 8)), 25, 2),       # token embedding not in LDS
+    (ti.small_variant(ti.C5, A=32, ragged=False, draft=ti.NetShape(5, 192, 6)), 768, 1),   # four environments a workgroup, the same
+])
+@pytest.mark.parametrize("bonus, clip, norm", [(False, None, 0), (True, 1.5, 1)])
+def test_rollouts_of_a_workgroup_an_environment(wl, B, K_max, bonus, clip, norm):
+    wl = ti.replace(wl, B=B, K_max=K_max, base=ti.NetShape(1, wl.base.d, wl.base.heads))
+    t0 = np.full(B, -1); t0[-1] = wl.T // 2; t0[:2] = (wl.T - 1, min(K_max, wl.T - 1) // 2 + 1)[:B]
+    _stage_parity(wl, B, t0, np.full(B, K_max), np.full(B, 1.1), clip=clip, bonus=bonus, norm=norm)
+
+
 @pytest.mark.parametrize("base, B, K_max", [
     (ti.replace(ti.C2, base=ti.NetShape(2, 256, 4)), 1, 1),       # one row
     (ti.replace(ti.C2, base=ti.NetShape(2, 256, 4)), 9, 1),       # rows not a multiple of the eight XCDs
