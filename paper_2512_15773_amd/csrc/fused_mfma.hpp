@@ -149,6 +149,23 @@ __device__ __forceinline__ float add_half32(float x) { const float2 r = swap_hal
 __device__ __forceinline__ float max_row16(float x) { const float2 r = swap_row16(x); return fmaxf(r.x, r.y); }
 __device__ __forceinline__ float max_half32(float x) { const float2 r = swap_half32(x); return fmaxf(r.x, r.y); }
 
+// Four sums over the four rows of 16 lanes at once: row i of the result holds the sum of x[i], added as add_half32(add_row16(x[i]))
+// adds it (three swaps instead of eight)
+__device__ __forceinline__ float add_rows(const float (&x)[4]) {
+  auto swap16 = [](float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+    return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+  };
+  const float t = swap16(x[0], x[1]), u = swap16(x[2], x[3]);
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, t), __builtin_bit_cast(unsigned, u), false, false);
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+// x[i] = row i of v, in every row
+__device__ __forceinline__ void spread_rows(float v, float (&x)[4]) {
+  const float2 h = swap_half32(v), a = swap_row16(h.x), b = swap_row16(h.y);
+  x[0] = a.x; x[1] = a.y; x[2] = b.x; x[3] = b.y;
+}
+
 // Workgroup barrier that orders LDS accesses only.  __syncthreads also waits for every outstanding global load (loads
 // and stores share one counter), which would drain the weights that are requested ahead of a phase.
 __device__ __forceinline__ void lds_barrier() {
@@ -561,8 +578,28 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
     constexpr float NWF = (float)(D / NW);              // features per wave
     constexpr bool PAIRS = C::DRAFT && NW % 2 == 0;      // (a rollout waits for every read: fewer of them)
     float mean[NB], rstd[NB];
+    // Tiles of 64 tokens: a row of 16 lanes looks after one token fragment: fewer swaps, an eighth of the LDS reads and of the sums over
+    // wavefronts.  (With 1 + g made once and the q | k | v epilogue without a branch per token fragment, us before / after: verify of
+    // 64 x 16 rows of d = 256 260 / 248, 256 x 8 of d = 512 5230 / 5150; rollout of 1024 environments 866 / 808.)
+    constexpr bool ROWS = NB % 4 == 0 && !CENTRED;
+    float2* red = reinterpret_cast<float2*>(red1);
+    if constexpr (ROWS) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
+      for (int g = 0; g < NB / 4; ++g) {
+        float s[4], q[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          s[j] = q[j] = 0.0f;
+#pragma unroll
+          for (int mb = 0; mb < MBH; ++mb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { const float v = h[mb][g * 4 + j][i]; s[j] += v; q[j] = fmaf(v, v, q[j]); }
+        }
+        red[wave * NT + g * 64 + lane] = make_float2(add_rows(s), add_rows(q));
+      }
+    }
+#pragma unroll
+    for (int nb = 0; nb < (ROWS ? 0 : NB); ++nb) {
       float s = 0.0f, q = 0.0f;
       if (CENTRED && !net.rms) {
 #pragma unroll
@@ -590,8 +627,24 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
     }
     lds_barrier();
     between();
+    if constexpr (ROWS) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
+      for (int g = 0; g < NB / 4; ++g) {
+        float2 v[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v[w] = red[w * NT + g * 64 + lane];
+        float s = 0.0f, q = 0.0f, m[4], r[4];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) { s += v[w].x; q += v[w].y; }
+        const float mn = net.rms ? 0.0f : s * (1.0f / D);
+        spread_rows(mn, m);
+        spread_rows(rsqrtf(fmaxf(q * (1.0f / D) - mn * mn, 0.0f) + 1e-5f), r);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { mean[g * 4 + j] = m[j]; rstd[g * 4 + j] = r[j]; }
+      }
+    }
+#pragma unroll
+    for (int nb = 0; nb < (ROWS ? 0 : NB); ++nb) {
       const int t = nb * 16 + l16;
       float sw[NW], s = 0.0f, q = 0.0f;
 #pragma unroll
@@ -622,7 +675,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
 #pragma unroll
       for (int i = 0; i < CPL; ++i) {
         const int c = lane + 64 * i;
-        if (c < CHK) *reinterpret_cast<f32x4*>(fs + c * 4) = st[i];
+        if (c < CHK) *reinterpret_cast<f32x4*>(fs + c * 4) = c % (2 * MBH * 4) < MBH * 4 ? 1.0f + st[i] : st[i];   // 1 + g, b
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();                  // written and read by the same wave: LDS keeps its order
@@ -641,7 +694,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
             const int r = (nb * 16) / H;
             const f32x4 g = *reinterpret_cast<const f32x4*>(fs + ((r * 2 + 0) * MBH + mb) * 16 + lg * 4);
             const f32x4 b = *reinterpret_cast<const f32x4*>(fs + ((r * 2 + 1) * MBH + mb) * 16 + lg * 4);
-            v = v * (1.0f + g) + b;
+            v = v * g + b;
           } else {
             const f32x4 g = film.load((nb * 16) / H, (layer * 4 + which) * D + f0);
             const f32x4 b = film.load((nb * 16) / H, (layer * 4 + which + 1) * D + f0);
@@ -768,15 +821,16 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
                                                         // dealt round-robin so every wave gets q, k and v rows)
       const int hh = lr / (3 * DH), cls = (lr / DH) % 3, c0 = lr % DH + lg * 4;
       const f32x4 b = bias(mb);
+      if (cls < 2) {                                    // queries token-major over the heads of the group, keys per head
+        elem* p = cls == 0 ? qbuf + l16 * QTS + hh * DH + c0 : kbuf + (hh * NT + l16) * QS + c0;
+        const int stride = 16 * (cls == 0 ? QTS : QS);
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const f32x4 v = acc[mb][nb] + b;
-        const int t = nb * 16 + l16;
-        if (cls == 0) {
-          *reinterpret_cast<vec4*>(qbuf + t * QTS + hh * DH + c0) = TT::cvt(v);
-        } else if (cls == 1) {
-          *reinterpret_cast<vec4*>(kbuf + (hh * NT + t) * QS + c0) = TT::cvt(v);
-        } else {
+        for (int nb = 0; nb < NB; ++nb) *reinterpret_cast<vec4*>(p + nb * stride) = TT::cvt(acc[mb][nb] + b);
+      } else {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          const f32x4 v = acc[mb][nb] + b;
+          const int t = nb * 16 + l16;
           elem* vp = vtb + ((size_t)(hh * RPT + t / H) * DH + c0) * VS + (t % H);
 #pragma unroll
           for (int i = 0; i < 4; ++i) vp[i * VS] = (elem)v[i];
