@@ -854,6 +854,16 @@ __global__ __launch_bounds__(C::TH, 1) void k_few_out(FewIO io) {
   }
 }
 
+template <class TT>
+__device__ __forceinline__ f32x4 film_silu(f32x4 v) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if constexpr (std::is_same<TT, TF32>::value) v[j] = v[j] / (1.0f + expf(-v[j]));
+    else v[j] = silu_fast(v[j]);
+  }
+  return v;
+}
+
 // FiLM vectors of a few rows, all layers at once: mod[r, :] = W_mod SiLU(temb[t_r] + cemb[env_r]) + b_mod.  A workgroup
 // takes 16 rows and four fragment rows (64 outputs), so that one row tile already puts L*D/16 workgroups on the chip.
 // k_max > 0: the rows are the transitions of a rollout, r = env * k_max + (k - 1) at timestep t_arr[env] - (k - 1).
@@ -886,12 +896,7 @@ __global__ __launch_bounds__(256, 1) void k_few_film(const void* __restrict__ mo
     t = t < 0 ? 0 : (t >= T ? T - 1 : t);
     f32x4 v = *reinterpret_cast<const f32x4*>(temb + (size_t)t * D + c);
     if (cemb) v += *reinterpret_cast<const f32x4*>(cemb + (size_t)(k_max ? r / k_max : (env_arr ? env_arr[r] : r)) * D + c);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if constexpr (std::is_same<TT, TF32>::value) v[j] = v[j] / (1.0f + expf(-v[j]));
-      else v[j] = silu_fast(v[j]);
-    }
-    *reinterpret_cast<typename TT::vec4*>(sg + (i / (D / 4)) * AS + c) = TT::cvt(v);
+    *reinterpret_cast<typename TT::vec4*>(sg + (i / (D / 4)) * AS + c) = TT::cvt(film_silu<TT>(v));
   }
   lds_barrier();
   f32x4 acc[1][1] = {{f32x4{0, 0, 0, 0}}};

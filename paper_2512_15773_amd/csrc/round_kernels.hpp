@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
+#include "few_rows.hpp"
 #include "philox.hpp"
 
 namespace tsdp {
@@ -73,27 +74,29 @@ __global__ __launch_bounds__(1024) void k_plan(const int32_t* __restrict__ t0, c
 // the L2) to find its own first row.  Up to PLAN_ROWS_B environments that costs less than the launch it saves (a chain of
 // one environment: 4.5 us of a 330 us round); beyond it the counting grows with B^2.
 constexpr int PLAN_ROWS_B = 1024;
-__global__ __launch_bounds__(128) void k_plan_rows(const float* __restrict__ x, const int32_t* __restrict__ t0,
-                                                   const int32_t* __restrict__ K, const float* __restrict__ sigma_scale, int B,
-                                                   int K_max, int T, int D, int bonus, int gated, int32_t* __restrict__ K_eff,
-                                                   int32_t* __restrict__ row_ptr, int32_t* __restrict__ status,
-                                                   int32_t* __restrict__ n_draft, int32_t* __restrict__ live,
-                                                   int32_t* __restrict__ rounds_run, int32_t* __restrict__ row_t, int32_t* __restrict__ row_env,
-                                                   float* __restrict__ y, float* __restrict__ states, float* __restrict__ eps_p,
-                                                   float* __restrict__ xi, int32_t* __restrict__ sync, int lines) {
-  __shared__ int32_t part[3][2];
-  const int b = blockIdx.x, k_min = bonus ? 0 : 1;
-  clear_sync(sync, lines, b * 128 + threadIdx.x, B * 128);
-  auto plan = [&](int kk, int tt, int& ke) {            // rows of an environment
-    const int k = min(max(kk, k_min), K_max), t = min(tt, T - 1);
+struct PlanIO {
+  const float* x; const int32_t* t0; const int32_t* K; const float* sigma_scale;
+  int B, K_max, T, D, bonus, gated;
+  int32_t *K_eff, *row_ptr, *status, *n_draft, *live, *rounds_run, *row_t, *row_env;
+  float *y, *states, *eps_p, *xi;
+  int32_t* sync; int lines;
+  // rows of an environment, ke of them drafted
+  __device__ __forceinline__ int rows(int k, int t, int& ke) const {
+    k = min(max(k, bonus ? 0 : 1), K_max); t = min(t, T - 1);
     ke = t < 0 ? 0 : min(k, t);
     return t < 0 ? 0 : (bonus ? ke + 1 : max(ke, 1));
-  };
-  const int my_k = K[b], my_t = t0[b];
+  }
+};
+template <int TH>
+__device__ __forceinline__ void plan_rows(const PlanIO& io, int b) {
+  __shared__ int32_t part[3][TH / 64];
+  const int k_min = io.bonus ? 0 : 1, B = io.B;
+  clear_sync(io.sync, io.lines, b * TH + threadIdx.x, B * TH);
+  const int my_k = io.K[b], my_t = io.t0[b];
   int before = 0, total = 0, drafts = 0;
-  for (int e = threadIdx.x; e < B; e += 128) {
+  for (int e = threadIdx.x; e < B; e += TH) {
     int ke;
-    const int n = plan(K[e], t0[e], ke);
+    const int n = io.rows(io.K[e], io.t0[e], ke);
     total += n; drafts |= ke;
     if (e < b) before += n;
   }
@@ -104,33 +107,124 @@ __global__ __launch_bounds__(128) void k_plan_rows(const float* __restrict__ x, 
     part[0][w] = before; part[1][w] = total; part[2][w] = drafts;
   }
   __syncthreads();
-  const int r0 = part[0][0] + part[0][1], R = part[1][0] + part[1][1];
+  int r0 = 0, R = 0, any = 0;
+#pragma unroll
+  for (int w = 0; w < TH / 64; ++w) { r0 += part[0][w]; R += part[1][w]; any |= part[2][w]; }
   int ke;
-  const int n = plan(my_k, my_t, ke);
+  const int n = io.rows(my_k, my_t, ke);
   if (threadIdx.x == 0) {
-    if (my_k < k_min || my_k > K_max) atomicOr(status, 1);
-    if (my_t >= T) atomicOr(status, 2);
-    if (my_t >= 0 && !(sigma_scale[b] > 0.0f)) atomicOr(status, 4);
-    K_eff[b] = ke; row_ptr[b] = r0;
-    if (b == B - 1) row_ptr[B] = R;
+    if (my_k < k_min || my_k > io.K_max) atomicOr(io.status, 1);
+    if (my_t >= io.T) atomicOr(io.status, 2);
+    if (my_t >= 0 && !(io.sigma_scale[b] > 0.0f)) atomicOr(io.status, 4);
+    io.K_eff[b] = ke; io.row_ptr[b] = r0;
+    if (b == B - 1) io.row_ptr[B] = R;
     if (b == 0) {
-      n_draft[0] = R > 0 ? B : 0; n_draft[1] = part[2][0] | part[2][1] ? B : 0;
-      if (live) *live = 0;
-      if (rounds_run && R > 0) *rounds_run += 1;
+      io.n_draft[0] = R > 0 ? B : 0; io.n_draft[1] = any ? B : 0;
+      if (io.live) *io.live = 0;
+      if (io.rounds_run && R > 0) *io.rounds_run += 1;
     }
   }
-  if (gated && R == 0) return;                          // chain driver: no environment is running any more
-  const int t = min(my_t, T - 1);
-  for (int j = threadIdx.x; j < n; j += 128) { row_t[r0 + j] = t - j; row_env[r0 + j] = b; }
-  for (int e = threadIdx.x; e < D; e += 128) {
-    const float v = x[(long long)b * D + e];
-    y[(long long)b * D + e] = v;
+  if (io.gated && R == 0) return;                       // chain driver: no environment is running any more
+  const int t = min(my_t, io.T - 1), D = io.D;
+  for (int j = threadIdx.x; j < n; j += TH) { io.row_t[r0 + j] = t - j; io.row_env[r0 + j] = b; }
+  for (int e = threadIdx.x; e < D; e += TH) {
+    const float v = io.x[(long long)b * D + e];
+    io.y[(long long)b * D + e] = v;
     if (t == 0) {
-      states[(long long)r0 * D + e] = v;
-      eps_p[(long long)r0 * D + e] = 0.0f;
-      if (xi) xi[(long long)r0 * D + e] = 0.0f;
+      io.states[(long long)r0 * D + e] = v;
+      io.eps_p[(long long)r0 * D + e] = 0.0f;
+      if (io.xi) io.xi[(long long)r0 * D + e] = 0.0f;
     }
   }
+}
+__global__ __launch_bounds__(128) void k_plan_rows(PlanIO io) { plan_rows<128>(io, blockIdx.x); }
+
+// The row table and the FiLM vectors of the round in one launch, where those are a small product (k_few_film): the base network's
+// rows, the transitions of a rollout that is spread or in one launch.  Both follow from K and t0 alone, so a workgroup that multiplies
+// finds its 16 rows by the scan that the row table makes, and nothing has to be waited for.  Sums in the order of k_few_film.
+// Up to PLAN_FILM_B environments (one a thread).  One launch instead of two or three, us before / after: rounds of one environment
+// with d = 64 / 32 57.0 / 55.8, of d = 256 / 128 in fp32 224.4 / 217.8, 32 of d = 96 / 48 129.2 / 123.4, a plain chain of 100 rounds 12 350 / 12 210.
+constexpr int PLAN_FILM_B = 256;
+struct FilmJob {
+  const void* modw; const float *modb, *temb, *cemb; float* mod;
+  int D, Nm, nx, tiles;          // nx workgroups over the outputs, `tiles` tiles of 16 rows (0: no such job)
+  int k_max;                     // > 0: transitions of a rollout, [env][k_max]; 0: rows of the round's table
+};
+template <class TT>
+__device__ __forceinline__ void film_tile(const PlanIO& io, const FilmJob& job, int fx, int row0) {
+  typedef typename TT::elem elem;
+  typedef typename TT::frag frag;
+  extern __shared__ __attribute__((aligned(16))) unsigned char film_mem[];
+  __shared__ int32_t part[2][4], row_t[16], row_env[16];
+  elem* sg = reinterpret_cast<elem*>(film_mem);
+  const int D = job.D, AS = D + TT::PAD, KD = D / TT::KSTEP;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, lg = lane >> 4;
+  const int f = min(fx * 4 + wave, job.Nm / 16 - 1);    // (a wave past the last fragment row repeats it)
+  constexpr int P = 16;                                  // k-steps of weights in flight
+  const frag* w = reinterpret_cast<const frag*>(job.modw) + (size_t)f * KD * 64 + lane;
+  frag a[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    if (p < KD) a[p] = w[(size_t)p * 64];
+  // rows of every environment, one a thread
+  const int e = threadIdx.x;
+  const int te = e < io.B ? io.t0[e] : -1;
+  int ke = 0;
+  const int n = e < io.B ? io.rows(io.K[e], te, ke) : 0;
+  int upto = n;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(upto, o); if (lane >= o) upto += v; }
+  const bool drafts = __ballot(ke > 0) != 0;
+  if (lane == 63) { part[0][wave] = upto; part[1][wave] = drafts; }
+  __syncthreads();
+  int at = upto - n, R = 0, any = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { if (i < wave) at += part[0][i]; R += part[0][i]; any |= part[1][i]; }
+  if (job.k_max) {
+    if (!any) return;                                    // no environment drafts
+    R = io.B * job.k_max;
+    if (threadIdx.x < 16) {
+      const int r = min(row0 + (int)threadIdx.x, R - 1);
+      row_env[threadIdx.x] = r / job.k_max;
+      row_t[threadIdx.x] = min(io.t0[r / job.k_max], io.T - 1) - r % job.k_max;
+    }
+  } else {
+    for (int j = max(row0 - at, 0); j < n && at + j < row0 + 16; ++j) { row_t[at + j - row0] = min(te, io.T - 1) - j; row_env[at + j - row0] = e; }
+  }
+  if (row0 >= R) return;
+  __syncthreads();
+  for (int i = threadIdx.x; i < 16 * (D / 4); i += 256) {
+    const int rl = min(i / (D / 4), R - 1 - row0), c = (i % (D / 4)) * 4;
+    const int t = min(max(row_t[rl], 0), io.T - 1);
+    f32x4 v = *reinterpret_cast<const f32x4*>(job.temb + (size_t)t * D + c);
+    if (job.cemb) v += *reinterpret_cast<const f32x4*>(job.cemb + (size_t)row_env[rl] * D + c);
+    *reinterpret_cast<typename TT::vec4*>(sg + (i / (D / 4)) * AS + c) = TT::cvt(film_silu<TT>(v));
+  }
+  __syncthreads();
+  f32x4 acc = {0, 0, 0, 0};
+  const elem* al = sg + l16 * AS + lg * TT::VW;
+  for (int k0 = 0; k0 < KD; k0 += P) {
+    if (k0) {
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+        if (k0 + p < KD) a[p] = w[(size_t)(k0 + p) * 64];
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+      if (k0 + p < KD) TT::mma(a[p], *reinterpret_cast<const frag*>(al + (k0 + p) * TT::KSTEP), acc);
+  }
+  if (row0 + l16 < R)
+    *reinterpret_cast<f32x4*>(job.mod + (size_t)(row0 + l16) * job.Nm + f * 16 + lg * 4) =
+        acc + *reinterpret_cast<const f32x4*>(job.modb + f * 16 + lg * 4);
+}
+template <class TT>
+__global__ __launch_bounds__(256) void k_plan_film(PlanIO io, FilmJob base, FilmJob roll) {
+  int i = (int)blockIdx.x - io.B;
+  if (i < 0) return plan_rows<256>(io, blockIdx.x);
+  const bool first = i < base.nx * base.tiles;
+  if (!first) i -= base.nx * base.tiles;
+  const FilmJob& job = first ? base : roll;
+  film_tile<TT>(io, job, i % job.nx, i / job.nx * 16);
 }
 
 // Range check of a caller-supplied row table (tsdp_verify): copies with the timestep clamped to 0..T-1 and the

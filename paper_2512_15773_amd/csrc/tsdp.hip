@@ -1195,16 +1195,18 @@ int tsdp_set_cond(tsdp_ctx* c, const float* d_cond, int B, void* stream) {
   return TSDP_OK;
 }
 
+enum BaseMod { MOD_NONE, MOD_DONE, MOD_BESIDE };   // the base network's FiLM vectors: not yet, on the caller's stream, on the auxiliary one
+
 // gated: chain driver -- the row-table kernel also returns at once when no environment has rows (the drafter kernels
 // always do: without rows there is nothing to draft)
 static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0, const int32_t* d_K,
                       const float* d_sigma_scale, const int32_t* d_env_id, int32_t* d_row_ptr, int32_t* d_row_t,
                       int32_t* d_row_env, float* d_states, float* d_eps_p, float* d_xi, float* d_y_last, bool gated,
-                      void* stream, int base_mod_rows = 0, bool* base_mod_started = nullptr, int32_t* live = nullptr,
+                      void* stream, int base_mod_rows = 0, BaseMod* base_mod = nullptr, int32_t* live = nullptr,
                       int32_t* rounds_run = nullptr) {
   // live: word that the round's k_accept counts the running environments in (cleared here), rounds_run: rounds that had rows, or null
-  // base_mod_rows > 0 (whole rounds): once the row table exists, the base network's per-row FiLM vectors of up to that
-  // many rows are computed on the auxiliary stream, beside the rollout; *base_mod_started tells the caller to join
+  // base_mod_rows > 0 (whole rounds): the base network's per-row FiLM vectors of up to that many rows are computed with the row
+  // table where the product is small, else, once the table exists, on the auxiliary stream beside the rollout; *base_mod says which
   int rc = check_ready(c, B, true);
   if (rc) return rc;
   if (B == 0) return TSDP_OK;                        // an empty batch is valid and touches nothing
@@ -1215,10 +1217,41 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
   hipStream_t s = (hipStream_t)stream;
   const tsdp_config& cf = c->cfg;
   const int D = c->D;
+  Net &dn = c->net[1], &bn = c->net[0];
+  // persistent drafter kernel (or the spread launches): pick the tile (environments per workgroup) that fills the chip best
+  const bool big = dn.fused && (B + dn.draft_rpt_big - 1) / dn.draft_rpt_big >= 192;
+  const bool kernel = dn.few_roll || (dn.fused && fused_draft_lds(dn, cf, big ? dn.draft_rpt_big : dn.draft_rpt_small) <= 160 * 1024);
+  bool roll_film = false;                               // the rollout's FiLM vectors are part of the first launch
   if (B <= PLAN_ROWS_B) {
-    hipLaunchKernelGGL(k_plan_rows, dim3(B), dim3(128), 0, s, d_x, d_t0, d_K, d_sigma_scale, B, cf.K_max, cf.T, D, cf.bonus_row,
-                       gated ? 1 : 0, c->K_eff, d_row_ptr, c->status, c->n_draft, live, rounds_run, d_row_t, d_row_env, d_y_last, d_states,
-                       d_eps_p, d_xi, c->sync, sync_lines(c));
+    const PlanIO plan{d_x, d_t0, d_K, d_sigma_scale, B, cf.K_max, cf.T, D, cf.bonus_row, gated ? 1 : 0, c->K_eff, d_row_ptr, c->status,
+                      c->n_draft, live, rounds_run, d_row_t, d_row_env, d_y_last, d_states, d_eps_p, d_xi, c->sync, sync_lines(c)};
+    // (bf16 networks and those with run-time sizes, which have fp32 operands, do not share a launch)
+    auto f32 = [&](const Net& n) { return cf.dtype == 0 || !n.fused; };
+    auto lds = [&](const Net& n) { return 16 * (n.d + (f32(n) ? TF32::PAD : TBF16::PAD)) * (f32(n) ? 4 : 2); };
+    auto small = [&](const Net& n) { return n.few_film && !n.fnet.modtab && lds(n) <= 60 * 1024; };
+    auto job = [&](const Net& n, int rows, int k_max, float* mod) {
+      const int Nm = n.L * 4 * n.d;
+      return FilmJob{n.fnet.modw, n.modb, n.temb, n.fnet.cemb, mod, n.d, Nm, (Nm / 16 + 3) / 4, (rows + 15) / 16, k_max};
+    };
+    const bool timed = c->timing && ((c->timing_mask >> 3) & 1);   // (the product on its own)
+    FilmJob jb{}, jr{};
+    jb.nx = jr.nx = 1;
+    if (B <= PLAN_FILM_B) {
+      if (dn.few_roll && small(dn)) { jr = job(dn, B * cf.K_max, cf.K_max, c->few_mod); roll_film = true; }
+      // (a rollout keeps its FiLM vectors in LDS or in few_mod; the operator kernels would use the buffer that the base network's go to)
+      if (base_mod_rows > 0 && kernel && !timed && (bn.few || (bn.fused && !bn.fused_mod)) && small(bn) && (!roll_film || f32(bn) == f32(dn))) {
+        jb = job(bn, base_mod_rows, 0, c->mod);
+        if (base_mod) *base_mod = MOD_DONE;
+      }
+    }
+    const int wgs = jb.nx * jb.tiles + jr.nx * jr.tiles;
+    if (wgs == 0) {
+      hipLaunchKernelGGL(k_plan_rows, dim3(B), dim3(128), 0, s, plan);
+    } else {
+      const int bytes = std::max(jb.tiles ? lds(bn) : 0, jr.tiles ? lds(dn) : 0);
+      const auto kern = f32(jr.tiles ? dn : bn) ? k_plan_film<TF32> : k_plan_film<TBF16>;
+      hipLaunchKernelGGL(kern, dim3(B + wgs), dim3(256), bytes, s, plan, jb, jr);
+    }
   } else {
     hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, d_t0, d_K, d_sigma_scale, B, cf.K_max, cf.T, cf.bonus_row, c->K_eff,
                        d_row_ptr, c->status, c->n_draft, live, rounds_run);
@@ -1230,44 +1263,36 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
       hipLaunchKernelGGL(k_bonus_rows, dim3(B), dim3(128), 0, s, d_t0, (const int32_t*)c->K_eff, (const int32_t*)d_row_ptr,
                          d_env_id, cf.T, D, cf.seed, (const float*)d_y_last, d_states, d_eps_p, d_xi);
   };
-  Net& dn = c->net[1];
-  if (dn.fused || dn.few_roll) {
-    // persistent drafter kernel (or the spread launches): pick the tile (environments per workgroup) that fills the chip best
-    const bool big = dn.fused && (B + dn.draft_rpt_big - 1) / dn.draft_rpt_big >= 192;
-    const int rpt = big ? dn.draft_rpt_big : dn.draft_rpt_small;
-    const size_t lds = fused_draft_lds(dn, cf, rpt);
-    if (dn.few_roll || lds <= 160 * 1024) {
-      Net& bn = c->net[0];
-      if (base_mod_rows > 0 && bn.fused && bn.fused_mod && !bn.few && !bn.fnet.modtab) {
-        // fork: a rollout keeps its FiLM vectors in LDS or in few_mod, so the shared buffer is free for the base network's.
-        // (Not for few rows: their product takes 6 us, the fork and join about 30 us of every round of an enqueued chain.)
-        HIPCHK(c, hipEventRecord(c->ev_fork, s));
-        HIPCHK(c, hipStreamWaitEvent(c->aux, c->ev_fork, 0));
-        bn.fused_mod(bn.fnet, d_row_t, 0, d_row_env, cf.T, d_row_ptr + B, base_mod_rows, c->mod, c->aux);
-        HIPCHK(c, hipEventRecord(c->ev_join, c->aux));
-        if (base_mod_started) *base_mod_started = true;
-      }
-      DraftIO io;
-      io.B = B; io.t0 = d_t0; io.K_eff = c->K_eff; io.row_ptr = d_row_ptr; io.sigma_scale = d_sigma_scale;
-      io.env_id = d_env_id;
-      io.tb = {c->tb.sqrt_abar, c->tb.sqrt_1m, c->tb.c0, c->tb.cx, c->tb.sigma, c->tb.ce, c->tb.T};
-      io.clip = cf.clip_x0; io.clip_val = cf.clip_val; io.seed = cf.seed;
-      io.y = d_y_last; io.states = d_states; io.eps_p = d_eps_p; io.xi = d_xi;
-      io.gate = c->n_draft + 1;
-      io.bonus = cf.bonus_row;
-      tick(c, 0, 0, s);
-      if (dn.few_roll) {
-        if (!dn.fnet.modtab) dn.few_film(dn.fnet, d_t0, 0, nullptr, cf.K_max, cf.T, nullptr, c->n_draft + 1, B * cf.K_max, c->few_mod, s);
-        const FewRun r = few_run(c, dn, B, few_safe_rows(!gated, B, B), d_t0, nullptr, c->few_mod);   // (d_y_last has B rows)
-        dn.few_draft(dn.fnet, r, io, cf.K_max, c->few_y, s);
-      } else {
-        HIPCHK(c, (big ? dn.fused_draft_big : dn.fused_draft_small)(dn.fnet, io, cf.A, s));
-      }
-      tick(c, 0, 1, s);
-      if (dn.few_roll) bonus_rows();
-      HIPCHK(c, hipGetLastError());
-      return TSDP_OK;
+  if (kernel) {
+    if (base_mod_rows > 0 && bn.fused && bn.fused_mod && !bn.few && !bn.fnet.modtab) {
+      // fork: a rollout keeps its FiLM vectors in LDS or in few_mod, so the shared buffer is free for the base network's.
+      // (Not for few rows: their product takes 6 us, the fork and join about 30 us of every round of an enqueued chain.)
+      HIPCHK(c, hipEventRecord(c->ev_fork, s));
+      HIPCHK(c, hipStreamWaitEvent(c->aux, c->ev_fork, 0));
+      bn.fused_mod(bn.fnet, d_row_t, 0, d_row_env, cf.T, d_row_ptr + B, base_mod_rows, c->mod, c->aux);
+      HIPCHK(c, hipEventRecord(c->ev_join, c->aux));
+      if (base_mod) *base_mod = MOD_BESIDE;
     }
+    DraftIO io;
+    io.B = B; io.t0 = d_t0; io.K_eff = c->K_eff; io.row_ptr = d_row_ptr; io.sigma_scale = d_sigma_scale;
+    io.env_id = d_env_id;
+    io.tb = {c->tb.sqrt_abar, c->tb.sqrt_1m, c->tb.c0, c->tb.cx, c->tb.sigma, c->tb.ce, c->tb.T};
+    io.clip = cf.clip_x0; io.clip_val = cf.clip_val; io.seed = cf.seed;
+    io.y = d_y_last; io.states = d_states; io.eps_p = d_eps_p; io.xi = d_xi;
+    io.gate = c->n_draft + 1;
+    io.bonus = cf.bonus_row;
+    tick(c, 0, 0, s);
+    if (dn.few_roll) {
+      if (!dn.fnet.modtab && !roll_film) dn.few_film(dn.fnet, d_t0, 0, nullptr, cf.K_max, cf.T, nullptr, c->n_draft + 1, B * cf.K_max, c->few_mod, s);
+      const FewRun r = few_run(c, dn, B, few_safe_rows(!gated, B, B), d_t0, nullptr, c->few_mod);   // (d_y_last has B rows)
+      dn.few_draft(dn.fnet, r, io, cf.K_max, c->few_y, s);
+    } else {
+      HIPCHK(c, (big ? dn.fused_draft_big : dn.fused_draft_small)(dn.fnet, io, cf.A, s));
+    }
+    tick(c, 0, 1, s);
+    if (dn.few_roll) bonus_rows();
+    HIPCHK(c, hipGetLastError());
+    return TSDP_OK;
   }
   for (int k = 1; k <= cf.K_max; ++k) {
     // every environment runs the drafter at step k; the DDPM step masks those with K_eff < k
@@ -1290,7 +1315,7 @@ int tsdp_draft(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0, const 
 
 static int verify_impl(tsdp_ctx* c, int B, int R_cap, const int32_t* d_row_ptr, const int32_t* d_row_t,
                        const int32_t* d_row_env, const float* d_states, float* d_eps_q, bool own_table, void* stream,
-                       bool mod_ready = false, bool gated = false) {
+                       BaseMod mod = MOD_NONE, bool gated = false) {
   int rc = check_ready(c, B, true);
   if (rc) return rc;
   if (B == 0 || R_cap == 0) return TSDP_OK;
@@ -1308,8 +1333,8 @@ static int verify_impl(tsdp_ctx* c, int B, int R_cap, const int32_t* d_row_ptr, 
     d_row_t = c->row_t_chk;
     d_row_env = c->row_env_chk;
   }
-  if (mod_ready) HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));   // join: the FiLM vectors computed beside the rollout
-  if ((rc = forward(c, c->net[0], d_states, R_cap, d_row_ptr + B, d_row_t, 0, d_row_env, d_eps_q, s, mod_ready,
+  if (mod == MOD_BESIDE) HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));   // join: the FiLM vectors computed beside the rollout
+  if ((rc = forward(c, c->net[0], d_states, R_cap, d_row_ptr + B, d_row_t, 0, d_row_env, d_eps_q, s, mod != MOD_NONE,
                     few_safe_rows(own_table && !gated, B, R_cap))))
     return rc;
   HIPCHK(c, hipGetLastError());
@@ -1397,11 +1422,11 @@ static int round_impl(tsdp_ctx* c, int B, float* d_x, int32_t* d_t, const int32_
   if (!d_x || !d_t || !d_K || !d_sigma_scale) return fail(c, TSDP_E_INVAL, "null pointer passed to tsdp_round");
   if ((rc = ensure_round_buffers(c))) return rc;
   const int R_cap = B * (c->cfg.K_max + (c->cfg.bonus_row ? 1 : 0));
-  bool mod_started = false;
+  BaseMod mod = MOD_NONE;
   if ((rc = draft_impl(c, B, d_x, d_t, d_K, d_sigma_scale, d_env_id, c->row_ptr, c->row_t, c->row_env, c->states,
-                       c->eps_p, c->xi, c->y_last, gated, stream, R_cap, &mod_started, chain.live, rounds_run)))
+                       c->eps_p, c->xi, c->y_last, gated, stream, R_cap, &mod, chain.live, rounds_run)))
     return rc;
-  if ((rc = verify_impl(c, B, R_cap, c->row_ptr, c->row_t, c->row_env, c->states, c->eps_q, true, stream, mod_started, gated)))
+  if ((rc = verify_impl(c, B, R_cap, c->row_ptr, c->row_t, c->row_env, c->states, c->eps_q, true, stream, mod, gated)))
     return rc;
   // x and t are overwritten in place: the acceptance kernel reads only the round's own buffers
   return accept_impl(c, B, c->row_ptr, c->row_t, d_env_id, d_sigma_scale, d_lambda, c->states, c->eps_p, c->eps_q, c->xi,

@@ -1246,3 +1246,32 @@ def test_first_round_of_few_rows_can_be_captured(wl):
         assert torch.equal(x, xe) and torch.equal(t, te), i
     del graph
     eager.close(); ctx.close()
+
+
+@pytest.mark.parametrize("wl, B, K_max", [
+    (ti.small_variant(ti.C1, draft=ti.NetShape(1, 32, 2)), 1, 1),                                     # one row
+    (ti.small_variant(ti.C2, base=ti.NetShape(1, 256, 4), draft=ti.NetShape(1, 128, 4)), 5, 7),      # both networks' vectors, rows not a multiple of 16
+    (ti.small_variant(ti.C3, base=ti.NetShape(1, 256, 4), draft=ti.NetShape(1, 128, 4)), 9, 9),      # bf16, the base network's alone
+    (ti.small_variant(ti.C1, base=ti.NetShape(1, 64, 2), draft=ti.NetShape(1, 32, 2)), 256, 2),      # one environment a thread
+    (ti.small_variant(ti.C1, base=ti.NetShape(1, 64, 2), draft=ti.NetShape(1, 32, 2)), 257, 2),      # one more: in launches of their own
+    (ti.small_variant(ti.C2, A=4, base=ti.NetShape(1, 96, 3), draft=ti.NetShape(1, 48, 3)), 20, 5),  # run-time sizes
+    (ti.small_variant(ti.C1, A=4, base=ti.NetShape(1, 64, 2), draft=ti.NetShape(1, 36, 3)), 3, 3),   # a drafter in operator kernels
+])
+@pytest.mark.parametrize("bonus", [False, True])
+def test_a_round_finds_the_vectors_of_its_stages(wl, B, K_max, bonus):
+    # a whole round makes the FiLM vectors with its row table, the three stages make them from the table: the same bits
+    import torch
+    S = _setup(wl, B, K_max=K_max, bonus=bonus)
+    ctx, rng = S["ctx"], np.random.default_rng(B)
+    t0 = rng.integers(-1, wl.T, B).astype(np.int32); t0[0] = wl.T - 1
+    K = rng.integers(0 if bonus else 1, K_max + 1, B).astype(np.int32); s = rng.uniform(1, 1.5, B).astype(np.float32)
+    x, t = to_dev(S["x"]), to_dev(t0)
+    n_acc = torch.zeros(B, dtype=torch.int32, device="cuda"); n_adv = torch.zeros_like(n_acc)
+    rows = ctx.alloc_rows(B)
+    ctx.tsdp_draft(x, t, to_dev(K), to_dev(s), None, rows)
+    ctx.tsdp_verify(B, rows)
+    out = dict(x_out=torch.empty_like(x), **{k: torch.empty(B, dtype=torch.int32, device="cuda") for k in ("t_next", "n_accept", "n_adv")})
+    ctx.tsdp_accept_into(B, to_dev(s), None, rows, out)
+    ctx.tsdp_round(x, t, to_dev(K), to_dev(s), None, n_acc, n_adv)
+    assert torch.equal(x, out["x_out"]) and torch.equal(t, out["t_next"]) and torch.equal(n_acc, out["n_accept"])
+    ctx.close()
