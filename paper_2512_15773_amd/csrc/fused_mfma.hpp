@@ -347,7 +347,7 @@ struct FusedCfg {
   static constexpr bool LN_STAGE = true;                // FiLM vectors come from global memory: fetch them cooperatively
   static constexpr int WAVES_PER_SIMD = (WG_PER_CU * NW + 3) / 4;
   static constexpr int BD = WAVES_PER_SIMD >= 2 ? 1 : 2; // LDS operand buffers: a second wave on the SIMD hides LDS latency
-  static constexpr bool XPF = WAVES_PER_SIMD == 1;      // request the first weights of the MLP's products one phase early
+  static constexpr bool XPF = WAVES_PER_SIMD == 1 || NB == 1;      // request the first weights of the MLP's products one phase early
                                                          // (those of the attention blocks always: C3 -1 %, C4, C5 no change beyond the noise)
   // One row per workgroup, all heads and the whole hidden layer in one phase each, and a layer's weights fit three quarters of
   // the registers: the rollout then keeps them in flight half a layer ahead (LayerStream).
@@ -907,11 +907,12 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
     }
   } else {
   // first weights of a product ahead of the phase before it: the whole ring where a second wavefront does not hide their way
+  constexpr bool AHEAD = C::DRAFT || (NB == 1 && XPF);
   GQ gq;
-  typedef std::integral_constant<int, C::DRAFT ? GQ::PF : 1> PQ;
-  typedef std::integral_constant<int, C::DRAFT ? GO::PF : 1> PO;
-  typedef std::integral_constant<int, C::DRAFT ? GU::PF : 1> PU;
-  typedef std::integral_constant<int, C::DRAFT ? GD::PF : 1> PD;
+  typedef std::integral_constant<int, AHEAD ? GQ::PF : 1> PQ;
+  typedef std::integral_constant<int, AHEAD ? GO::PF : 1> PO;
+  typedef std::integral_constant<int, AHEAD ? GU::PF : 1> PU;
+  typedef std::integral_constant<int, AHEAD ? GD::PF : 1> PD;
   if (XPF) gq.template prime<PQ::value>(net.layer[0].qkv, KD, wave, 0, lane, NW);
   for (int layer = 0; layer < net.L; ++layer) {
     const FusedLayer& W = net.layer[layer];
