@@ -352,14 +352,19 @@ __device__ __forceinline__ void few_store_residual(const FewIO& io, int row, int
 }
 
 // One product of a workgroup: MF fragment rows dealt to the waves round-robin, contraction over NKS k-steps of a matrix
-// with ks_total.  begin() requests weights (compile-time sizes: up to 40 fragments per wave, 20 of eight waves), run() multiplies and
+// with ks_total.  begin() requests weights (compile-time sizes), run() multiplies and
 // hands every finished fragment row to epi(index, accumulators).
 template <class C, int MF, int NKS>
 struct FewGemm {
   typedef typename C::TT TT;
   static constexpr int MB = (MF + C::NW - 1) / C::NW;
   static_assert(MF % C::NW == 0 || MB <= 2, "at most the last fragment of a wave may be missing");
-  static constexpr int DEEP0 = (C::NW == 4 ? 40 : 20) / MB, DEEP = DEEP0 < 1 ? 1 : DEEP0;
+  // Fragments of weights that a wavefront requests ahead.  A unit takes 16 cycles for each, and a wavefront does nothing else until
+  // its requests are issued: with 40 the four held up the normalisation for 2500 cycles; too few, and the product waits.  us with 40,
+  // 20, 12, 9, 6, 4: fp32 verify of 128 rows of d = 256 503, 495, 471, 455, 450, 452; bf16 128 rows 179, 173, 171, 173, 171, 169, 64 rows
+  // 124, 124, 120, 121, 127, 130, a plain chain of eight (few workgroups a unit) 12 230, 12 240, 11 885, 12 050, 12 620, 12 920.
+  static constexpr int AHEAD = C::NW == 8 ? 20 : std::is_same<TT, TF32>::value ? 8 : 12;
+  static constexpr int DEEP0 = AHEAD / MB, DEEP = DEEP0 < 1 ? 1 : DEEP0;
   typedef FragGemm<TT, MB, C::NB, NKS, 2, DEEP> G;
   G g;
   f32x4 bias[MB];
