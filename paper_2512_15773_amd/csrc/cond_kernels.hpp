@@ -84,7 +84,7 @@ struct CondIO { CondNet net[2]; const float* cond; int M, C, KS, SF; };   // con
 // Which numbers are added again: those that round differently with COND_TIE times the product of the two 2-norms on either side
 // (an element of an empty token never).  A chain of fp32 additions ends about 0.3 of 2^-24 times that away from the exact sum
 // (standard deviation, terms of either sign), the matrix cores' sum comes on top: of the 2.2e8 numbers of 256 observations about 35 round the other way
-// with the line at 1.5, 10 at 2, none of three batches at 3 (1.25, 1.28, 1.30 ms; 4.5: 1.50).
+// with the line at 1.5, 10 at 2, at 3 none of three batches and very few in others (1.25, 1.28, 1.30 ms; 4.5: 1.50).
 // The workgroup lists them in LDS, a thread takes one, and a second pass over the k-steps brings weights and observations
 // through the LDS as before.
 // Measured, 256 environments x 64 tokens x 768, 12 layers of d = 512 and 2 of d = 256: 1.30 ms (0.77 PFLOP/s in the three products),
