@@ -4,8 +4,9 @@
 // The sums are k_linear's: fp32 fused multiply-adds over the features in ascending order, then the bias, then one rounding to
 // bf16.  Any other order rounds a few keys to the other bf16 number, and at the first timesteps of a squared-cosine chain,
 // where a noise prediction is multiplied by 31, that is enough for a nearly tied draft to fall on the other side of its test.
-// So the product runs on the bf16 matrix cores, where it is ordered otherwise, and the one number in a hundred that lies so close
-// to a rounding boundary that the order could matter is added up again, feature by feature.
+// So the product runs on the bf16 matrix cores, where it is ordered otherwise, and the numbers that lie so close to a rounding
+// boundary that the order may matter (of Gaussian observations one in a hundred) are added up again, feature by feature.  How close
+// that is follows from how far apart the two sums were measured to end up: it is no bound for every input (that would list one number in seven).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -70,7 +71,22 @@ struct CondNet {                 // one network's share of the launch
   __bf16* kc; __bf16* vct;       // FusedNet::kc / vct
   int L, d, heads, tiles;        // tiles = L*2*d / 256
 };
-struct CondIO { CondNet net[2]; const float* cond; int M, C, KS, SF; };   // cond [M = B*S, C]
+struct CondIO { CondNet net[2]; const float* cond; float* size; int M, C, KS, SF; };   // cond [M = B*S, C], size [M]
+
+// size[m] = 2-norm of token m.  A wavefront a token.
+__global__ __launch_bounds__(256) void k_cond_size(CondIO io) {
+  const int m = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (m >= io.M) return;
+  float q = 0.0f;
+#pragma unroll 4
+  for (int i = lane * 4; i < io.C; i += 256) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(io.cond + (size_t)m * io.C + i);
+    q += (x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]);
+  }
+#pragma unroll
+  for (int o = 1; o < 64; o *= 2) q += __shfl_xor(q, o);
+  if (lane == 0) io.size[m] = sqrtf(q);
+}
 
 // Tile: 256 features (16 fragments, all keys or all values of one layer because d is a multiple of 256) x 128 tokens
 // (8 fragments).  8 waves as 4 x 2, each 64 features x 64 tokens.  An observation is the sum of three bf16 numbers (its leading,
@@ -81,19 +97,25 @@ struct CondIO { CondNet net[2]; const float* cond; int M, C, KS, SF; };   // con
 // Keys are computed features x tokens, values tokens x features, so that in both cases a lane's four accumulators are
 // the neighbouring entries of one 8-byte piece of the attention operand.
 //
-// Which numbers are added again: those that round differently with COND_TIE times the product of the two 2-norms on either side
-// (an element of an empty token never).  A chain of fp32 additions ends about 0.3 of 2^-24 times that away from the exact sum
-// (standard deviation, terms of either sign), the matrix cores' sum comes on top: of the 2.2e8 numbers of 256 observations about 35 round the other way
-// with the line at 1.5, 10 at 2, at 3 none of three batches and very few in others (1.25, 1.28, 1.30 ms; 4.5: 1.50).
-// The workgroup lists them in LDS, a thread takes one, and a second pass over the k-steps brings weights and observations
+// Which numbers are added again: those v that round differently with the largest of three terms on either side, u = 2^-24.
+//   3 u |x| |w|       terms of either sign: a chain of fp32 additions ends 0.30 u |x| |w| away from the exact sum (standard deviation), the
+//                     matrix cores' sum 0.18.  With 1.5 35 numbers of the 2.2e8 of 256 observations round the other way, with 2 ten, with 3 none.
+//   2.2 r u |v|       r = sqrt(C) + C / 128.  Sums that grow steadily, as of one sign: standard deviation of the difference 8.5 u |v| at C = 768, 16.5
+//                     (mean 38) at 3072, 2.4 at 64, so seven and more of them (at 3072 five beyond the mean).
+//   3.5 r u |x| |w| s sums that were far larger on the way and cancel: s is the largest of the thread's 64 partial sums after a quarter, half
+//                     and three quarters of the features in units of their |x| |w|.  Only where r s > 4.8, four standard deviations of a sum
+//                     of either sign: most threads only compare their largest partial sum with the least that could be that.
+// The deviations are those of 2.6e5 sums each against fp64 (Gaussian; of one sign; half of each sign in turn; large in the first eighth).
+// The workgroup lists the numbers in LDS, a thread takes one, and a second pass over the k-steps brings weights and observations
 // through the LDS as before.
-// Measured, 256 environments x 64 tokens x 768, 12 layers of d = 512 and 2 of d = 256: 1.30 ms (0.77 PFLOP/s in the three products),
-// 4 environments 71 us, against 2.50 ms and 109 us with fp32 operands on the fp32 matrix cores, whose chains are the sums themselves.
+// Measured, 256 environments x 64 tokens x 768, 12 layers of d = 512 and 2 of d = 256, with k_cond_size: 1.45 ms, 4 environments 83 us
+// (1.35 ms and 74 us with the first term alone), against 2.50 ms and 112 us with fp32 operands on the fp32 matrix cores, whose chains are
+// the sums themselves.  128 registers: 39 spilled before and after the loop over the k-steps, three read in it.
 constexpr int COND_FF = 16, COND_TF = 8, COND_XS = 36;   // floats per token in LDS (second pass): 32 and the bank padding
 constexpr int COND_W_B = COND_FF * 64 * 16, COND_STAGE_B = COND_W_B + 3 * COND_TF * 64 * 16, COND_LDS = 2 * COND_STAGE_B;
 constexpr int COND_AGAIN_B = COND_W_B + COND_TF * 16 * COND_XS * 4, COND_LIST = 512;
-constexpr float COND_TIE = 3.0f * 5.9604645e-8f;
-static_assert(2 * COND_AGAIN_B + 4 * (COND_LIST + 1) <= COND_LDS && COND_TF * 16 * 4 <= COND_LDS && 2 * COND_LDS <= 160 * 1024, "LDS");
+constexpr float COND_ULP = 5.9604645e-8f, COND_TIE = 3.0f * COND_ULP, COND_OWN = 2.2f, COND_GROWN = 3.5f, COND_UNUSUAL = 4.8f;
+static_assert(2 * COND_AGAIN_B + 4 * (COND_LIST + 1) <= COND_LDS && 2 * COND_LDS <= 160 * 1024, "LDS");
 
 __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -110,9 +132,10 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
   // a thread fetches two pieces of weights (fragments 2 wave, 2 wave + 1) and of observations (tokens xr, xr + 64)
   const bf16x8* wsrc = n.w + ((size_t)ft * COND_FF + wave * 2) * KS * 64 + lane;
   const int xr = threadIdx.x >> 3, xc = (threadIdx.x & 7) * 4;
-  const float* xsrc[2];
+  const float* xsrc = io.cond + (size_t)tf0 * 16 * io.C;
+  unsigned xat[2];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) xsrc[j] = io.cond + (size_t)min(tf0 * 16 + xr + j * 64, io.M - 1) * io.C;
+  for (int j = 0; j < 2; ++j) xat[j] = (unsigned)min(xr + j * 64, io.M - 1 - tf0 * 16) * io.C;
   bf16x8 rw[2];
   f32x4 rx[2];
   auto request = [&](int k) {
@@ -120,7 +143,7 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       rw[j] = wsrc[((size_t)j * KS + k) * 64];
-      rx[j] = *reinterpret_cast<const f32x4*>(xsrc[j] + min(k * 32 + xc, io.C - 4));
+      rx[j] = *reinterpret_cast<const f32x4*>(xsrc + (xat[j] + min(k * 32 + xc, io.C - 4)));
     }
     __builtin_amdgcn_sched_barrier(0);                  // (the scheduler would sink the loads to their use)
   };
@@ -130,14 +153,12 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
     for (int j = 0; j < 2; ++j) reinterpret_cast<bf16x8*>(st)[(wave * 2 + j) * 64 + lane] = rw[j];
   };
   // planes as fragments [plane][token fragment][64][8]
-  float xx[2] = {0.0f, 0.0f};                           // squares of the thread's observations
   auto deposit = [&](int k) {
     unsigned char* st = lds + (k & 1) * COND_STAGE_B;
     deposit_weights(st);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       f32x4 x = observed(k, j);
-      xx[j] += (x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]);
       unsigned char* at = st + COND_W_B + ((j * 4 + xr / 16) * 64 + xr % 16 + 16 * (xc / 8)) * 16 + (xc % 8) * 2;
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
@@ -152,6 +173,34 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
       }
     }
   };
+  const int per_layer = 2 * n.d, f_tile = ft * COND_FF * 16;       // first feature of the tile in [layer][k|v][d]
+  const int layer = f_tile / per_layer, cls = (f_tile % per_layer) / n.d;   // 0 keys, 1 values
+  const float *bias0 = n.bias + f_tile + wf * 64, *norm0 = bias0 + n.L * per_layer, *size0 = io.size + tf0 * 16;
+  // of the wave's feature fragment i the lane's four features, of its token fragment j the lane's four tokens (one of them four times)
+  auto features = [&](bool keys, const float* v, int i) {
+    return keys ? *reinterpret_cast<const f32x4*>(v + i * 16 + lg * 4) : f32x4{1, 1, 1, 1} * v[i * 16 + l16];
+  };
+  auto tokens = [&](bool keys, int j) {
+    const float* v = size0 + min(wt * 4 + j, MF - 1 - tf0) * 16;
+    return keys ? f32x4{1, 1, 1, 1} * v[l16] : *reinterpret_cast<const f32x4*>(v + lg * 4);
+  };
+  // Largest of the thread's partial sums on the way, in units of |x| |w|, where one is more than `unusual` of them; looked at three
+  // times.  The least product of the thread's norms tells first whether there can be one.
+  const float root = sqrtf((float)io.C) + io.C * (1.0f / 128), unusual = COND_UNUSUAL / root;
+  float seen = 0.0f;
+  auto limit = [&](auto KEYS) {
+    constexpr bool keys = decltype(KEYS)::value;
+    float lw = INFINITY, lx = INFINITY;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const f32x4 w = features(keys, norm0, i), x = tokens(keys, i);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { lw = fminf(lw, w[e] > 0.0f ? w[e] : INFINITY); lx = fminf(lx, x[e] > 0.0f ? x[e] : INFINITY); }
+    }
+    return lw * lx * unusual;
+  };
+  const float least = cls == 0 ? limit(std::true_type{}) : limit(std::false_type{});
+  const int quarter = (KS + 3) / 4;
   request(0);
   deposit(0);
   request(1);
@@ -160,10 +209,31 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
-  const int per_layer = 2 * n.d, f_tile = ft * COND_FF * 16;       // first feature of the tile in [layer][k|v][d]
-  const int layer = f_tile / per_layer, cls = (f_tile % per_layer) / n.d;   // 0 keys, 1 values
   auto product = [&](auto KEYS) {
     constexpr bool keys = decltype(KEYS)::value;
+    auto look = [&]() {
+      float most = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) most = fmaxf(most, fabsf(acc[i][j][e]));
+      if (!__any(most > least)) return;
+      for (int j = 0; j < 4; ++j) {                      // (not unrolled: registers)
+        const f32x4 x = tokens(keys, j);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const f32x4 w = features(keys, norm0, i);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float s = j == 0 ? acc[i][0][e] : j == 1 ? acc[i][1][e] : j == 2 ? acc[i][2][e] : acc[i][3][e];
+            seen = fmaxf(seen, fabsf(s) * __builtin_amdgcn_rcpf(w[e] * x[e]));   // (0 / 0 of an empty token or row: left out)
+          }
+        }
+      }
+    };
+    int next = quarter - 1;
     for (int k = 0; k < KS; ++k) {
       __syncthreads();                                  // stage k is in LDS; stage k-1 has been read by every wave
       const unsigned char* st = lds + (k & 1) * COND_STAGE_B;
@@ -183,6 +253,7 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
             acc[i][j] = keys ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b, acc[i][j], 0, 0, 0)
                              : __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a[i], acc[i][j], 0, 0, 0);
         }
+      if (k == next) { look(); next += quarter; }
     }
   };
   if (cls == 0) product(std::true_type{}); else product(std::false_type{});
@@ -195,34 +266,26 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
     return cls == 0 ? n.kc + (((eh * SF + sf) * KH + fh / 32) * 64 + ln % 16 + 16 * ((fh % 32) / 8 + g / 2)) * 8 + (g & 1) * 4   // a fragment is half of a 32-deep k-step
                     : n.vct + (((eh * CF + fh / 16) * SF + sf) * 64 + ln) * 4;
   };
-  // norms of the tokens: eight threads hold one
-  float* norm = reinterpret_cast<float*>(lds);
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    float q = xx[j];
-#pragma unroll
-    for (int m = 1; m < 8; m *= 2) q += __shfl_xor(q, m);
-    if ((threadIdx.x & 7) == 0) norm[xr + j * 64] = COND_TIE * sqrtf(q);
-  }
-  __syncthreads();
+  const float line = seen > unusual ? fmaxf(COND_TIE, COND_GROWN * COND_ULP * root * seen) : COND_TIE, own = (COND_OWN * root + 2.0f) * COND_ULP;
   uint64_t again = 0;                                   // bit (i * 4 + j) * 4 + e
+  f32x4 x[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) x[j] = tokens(cls == 0, j) * line;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const float *b = n.bias + f_tile + (wf * 4 + i) * 16, *wn = b + n.L * per_layer;
-    const f32x4 bias = cls == 0 ? *reinterpret_cast<const f32x4*>(b + lg * 4) : f32x4{b[l16], b[l16], b[l16], b[l16]};
-    const f32x4 wnorm = cls == 0 ? *reinterpret_cast<const f32x4*>(wn + lg * 4) : f32x4{wn[l16], wn[l16], wn[l16], wn[l16]};
+    const f32x4 bias = features(cls == 0, bias0, i), wnorm = features(cls == 0, norm0, i);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if (tf0 + wt * 4 + j >= MF) continue;
       const f32x4 v = acc[i][j] + bias;
       *reinterpret_cast<bf16x4*>(place(wf * 4 + i, wt * 4 + j, lane)) = to_bf16x4(v);
-      const float* xn = norm + (wt * 4 + j) * 16;
-      const f32x4 tie = wnorm * (cls == 0 ? f32x4{xn[l16], xn[l16], xn[l16], xn[l16]} : *reinterpret_cast<const f32x4*>(xn + lg * 4));
+      const f32x4 drawn = wnorm * x[j];
       unsigned m = 0;
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if ((float)(__bf16)(v[e] - tie[e]) != (float)(__bf16)(v[e] + tie[e]) || !(fabsf(v[e]) + tie[e] < 3.0e38f)) m |= 1u << e;   // (not finite: again)
+      for (int e = 0; e < 4; ++e) {
+        const float tie = fmaxf(drawn[e], own * fabsf(v[e]));
+        if ((float)(__bf16)(v[e] - tie) != (float)(__bf16)(v[e] + tie) || !(fabsf(v[e]) + tie < 3.0e38f)) m |= 1u << e;   // (not finite: again)
+      }
       again |= (uint64_t)m << ((i * 4 + j) * 4);
     }
   }

@@ -99,6 +99,7 @@ struct tsdp_ctx {
   Net net[2];
   bool cond_set = false;
   int cond_B = 0;
+  float* cond_size = nullptr;   // [B_max * tokens] their 2-norms (k_cond_kv)
   int32_t* status = nullptr;
   int32_t* live = nullptr;      // environments still running (chain driver)
   int32_t* K_sel = nullptr;     // [B_max] per-round picks from the stage tables (staged chain driver)
@@ -706,6 +707,7 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   if (cf.cond_mode == 1) {
     const size_t S = cf.cond_tokens, cnt = (size_t)cf.B_max * L * S * d;
     if (!n.kc_pk && (rc = dev_alloc(c, &n.kc_pk, cnt))) return rc;
+    if (!c->cond_size && (rc = dev_alloc(c, &c->cond_size, (size_t)cf.B_max * S))) return rc;
     if (!n.vct_pk && (rc = dev_alloc(c, &n.vct_pk, cnt))) return rc;
     // key / value projections, per layer the key rows then the value rows (k_cond_kv)
     std::vector<uint8_t> kv;
@@ -1186,8 +1188,9 @@ int tsdp_set_cond(tsdp_ctx* c, const float* d_cond, int B, void* stream) {
     }
   }
   if (const int tiles = io.net[0].tiles + io.net[1].tiles) {
-    io.cond = d_cond;
+    io.cond = d_cond; io.size = c->cond_size;
     io.M = B * cf.cond_tokens; io.C = cf.cond_dim; io.KS = (cf.cond_dim + 31) / 32; io.SF = cf.cond_tokens / 16;
+    hipLaunchKernelGGL(k_cond_size, dim3((io.M + 3) / 4), dim3(256), 0, s, io);
     hipLaunchKernelGGL(k_cond_kv, dim3(tiles * ((io.M / 16 + COND_TF - 1) / COND_TF)), dim3(512), COND_LDS, s, io);
   }
   HIPCHK(c, hipGetLastError());

@@ -218,6 +218,56 @@ def test_keys_and_values_round_as_their_sums_in_order_do(cond_dim):
     ctx.close()
 
 
+def _summed_observations(kind, n, S, cond_dim, rng):
+    """Observations [n, S, cond_dim] whose features, added up in ascending order in fp32, end halfway between two bf16 numbers or one
+    unit beside, and these sums."""
+    x = rng.standard_normal((n, S, cond_dim)).astype(np.float32)
+    if kind != "either":
+        x = np.abs(x)
+    if kind == "cancelling":
+        x[:, :, cond_dim // 2:] *= -1
+    if kind == "early":                                     # large at once, then small terms of either sign
+        x[:, :, cond_dim // 8:] = 0.02 * rng.standard_normal((n, S, cond_dim - cond_dim // 8)).astype(np.float32)
+    part = np.zeros((n, S), np.float32)
+    for c in range(cond_dim - 1):
+        part += x[:, :, c]
+    b = (part.view(np.uint32) & np.uint32(0xFFFF0000)) + np.uint32(0x8000) + rng.integers(0, 2, (n, S)).astype(np.uint32)
+    x[:, :, -1] = b.view(np.float32) - part
+    total = np.zeros((n, S), np.float32)
+    for c in range(cond_dim):
+        total += x[:, :, c]
+    return x, total
+
+
+@pytest.mark.parametrize("cond_dim", [32, 768, 3072])
+@pytest.mark.parametrize("kind", ["either", "one sign", "cancelling", "early"])
+def test_keys_and_values_round_as_their_sums_in_order_do_whatever_the_signs(kind, cond_dim):
+    # as above (weights of one, an observation against one that holds its sum and zeros), but the sums of the matrix cores and those in order
+    # lie up to 20 units of 2^-24 |x| |w| apart (45 with 3072 features); 256 tokens, so that a sum beyond the line is among them
+    import torch
+    n, S = 4, 64
+    wl = ti.small_variant(ti.C4, B=2 * n, K_max=1, cond_dim=cond_dim, cond_tokens=S, base=ti.NetShape(1, 512, 8), draft=ti.NetShape(1, 256, 8))
+    nets = [ti.make_weights(wl, which) for which in ("base", "draft")]
+    for w in nets:
+        for name in w:
+            if name.endswith(("ck_w", "cv_w")):
+                w[name][:] = 1.0
+    x, total = _summed_observations(kind, n, S, cond_dim, np.random.default_rng(cond_dim))
+    cond = np.zeros((2 * n, S, cond_dim), np.float32)
+    cond[0::2] = x
+    cond[1::2, :, 0] = total
+    ctx = gpu_side(wl, *nets, cond, B_max=2 * n)
+    rows = ctx.alloc_rows(2 * n)
+    one = np.ones(2 * n, np.int32)
+    ctx.tsdp_draft(to_dev(np.repeat(ti.make_latents(wl, 1), 2 * n, axis=0)), to_dev(50 * one), to_dev(one), to_dev(np.ones(2 * n, np.float32)),
+                   to_dev(7 * one), rows)
+    ctx.tsdp_verify(2 * n, rows)
+    for name in ("eps_p", "eps_q"):
+        e = rows[name]
+        assert bool(torch.isfinite(e).all()) and torch.equal(e[0::2], e[1::2]), name
+    ctx.close()
+
+
 @pytest.mark.parametrize("wl, B, K_max", [
     (ti.small_variant(ti.C3, A=32, draft=ti.NetShape(16, 128, 4)), 2, 2),       # one row a workgroup, weights in flight: the most LDS
     (ti.small_variant(ti.C3, A=4, draft=ti.NetShape(1, 128, 4)), 1, 64),        # one layer; the most transitions
