@@ -65,27 +65,36 @@ __global__ __launch_bounds__(256) void k_cond_vec(const float* __restrict__ cond
   if (e < B && f < n.d) n.out[(size_t)e * n.d + f] = acc + n.b[f];
 }
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
 struct CondNet {                 // one network's share of the launch
   const bf16x8* w;               // [L*2*d/16][KS][64] fragments: per layer the key rows, then the value rows
   const float* bias;             // [L*2*d], behind them the 2-norms of the weight rows
   __bf16* kc; __bf16* vct;       // FusedNet::kc / vct
   int L, d, heads, tiles;        // tiles = L*2*d / 256
 };
+constexpr int COND_FEW = 10;
 struct CondIO { CondNet net[2]; const float* cond; float* size; int M, C, KS, SF; };   // cond [M = B*S, C], size [M]
 
-// size[m] = 2-norm of token m.  A wavefront a token.
+// size[m] = 2-norm of token m, negative where the kernel below would add most of its numbers again: an infinity among its features,
+// or a few features of two leading bits each (a mask, an index), whose sums end on rounding boundaries.  A wavefront a token.
 __global__ __launch_bounds__(256) void k_cond_size(CondIO io) {
   const int m = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (m >= io.M) return;
   float q = 0.0f;
+  unsigned bits = 0;
+  int count = 0;
 #pragma unroll 4
   for (int i = lane * 4; i < io.C; i += 256) {
     const f32x4 x = *reinterpret_cast<const f32x4*>(io.cond + (size_t)m * io.C + i);
     q += (x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { bits |= __builtin_bit_cast(unsigned, x[e]); count += x[e] != 0.0f; }
   }
 #pragma unroll
-  for (int o = 1; o < 64; o *= 2) q += __shfl_xor(q, o);
-  if (lane == 0) io.size[m] = sqrtf(q);
+  for (int o = 1; o < 64; o *= 2) { q += __shfl_xor(q, o); bits |= __shfl_xor(bits, o); count += __shfl_xor(count, o); }
+  const bool again = q == INFINITY || (count > 1 && count <= COND_FEW && (bits & 0x1FFFFF) == 0);
+  if (lane == 0) io.size[m] = again ? -sqrtf(q) : sqrtf(q);
 }
 
 // Tile: 256 features (16 fragments, all keys or all values of one layer because d is a multiple of 256) x 128 tokens
@@ -107,13 +116,17 @@ __global__ __launch_bounds__(256) void k_cond_size(CondIO io) {
 //                     of either sign: most threads only compare their largest partial sum with the least that could be that.
 // The deviations are those of 2.6e5 sums each against fp64 (Gaussian; of one sign; half of each sign in turn; large in the first eighth).
 // The workgroup lists the numbers in LDS, a thread takes one, and a second pass over the k-steps brings weights and observations
-// through the LDS as before.
-// Measured, 256 environments x 64 tokens x 768, 12 layers of d = 512 and 2 of d = 256, with k_cond_size: 1.45 ms, 4 environments 83 us
-// (1.35 ms and 74 us with the first term alone), against 2.50 ms and 112 us with fp32 operands on the fp32 matrix cores, whose chains are
-// the sums themselves.  128 registers: 39 spilled before and after the loop over the k-steps, three read in it.
+// through the LDS as before, 512 numbers at a time: 0.35 ms each where all tiles take one.
+// Observations of a few features of two leading bits (masks, indices) list 8 to 22 % of their numbers, since their sums end on boundaries,
+// and infinities all of them.  Beyond 3072 numbers a tile is multiplied once more with fp32 operands on the fp32 matrix cores, whose
+// chains are the sums in order themselves (2.5 ms where all tiles do), and a tile with 16 marked tokens (k_cond_size) at once.
+// Measured, 256 environments x 64 tokens x 768, 12 layers of d = 512 and 2 of d = 256, with k_cond_size: Gaussian 1.43 ms, of one sign 1.35,
+// a mask of 5 % 1.66, of 1 %, four or two features set, infinities 2.55, sums that cancel 3.57; 4 environments 83 us, at most 176.  With every
+// tile in order 2.50 ms and 112 us; without the last step 3.6, 4.5, 5.9, 19.8 (infinities, not-a-numbers), 4.0 and up to 1.1 ms.
+// 128 registers: 41 spilled before and after the loop over the k-steps, none in it.
 constexpr int COND_FF = 16, COND_TF = 8, COND_XS = 36;   // floats per token in LDS (second pass): 32 and the bank padding
 constexpr int COND_W_B = COND_FF * 64 * 16, COND_STAGE_B = COND_W_B + 3 * COND_TF * 64 * 16, COND_LDS = 2 * COND_STAGE_B;
-constexpr int COND_AGAIN_B = COND_W_B + COND_TF * 16 * COND_XS * 4, COND_LIST = 512;
+constexpr int COND_AGAIN_B = COND_W_B + COND_TF * 16 * COND_XS * 4, COND_LIST = 512, COND_AGAIN = 6 * COND_LIST, COND_MARKED = 16;
 constexpr float COND_ULP = 5.9604645e-8f, COND_TIE = 3.0f * COND_ULP, COND_OWN = 2.2f, COND_GROWN = 3.5f, COND_UNUSUAL = 4.8f;
 static_assert(2 * COND_AGAIN_B + 4 * (COND_LIST + 1) <= COND_LDS && 2 * COND_LDS <= 160 * 1024, "LDS");
 
@@ -182,7 +195,8 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
   };
   auto tokens = [&](bool keys, int j) {
     const float* v = size0 + min(wt * 4 + j, MF - 1 - tf0) * 16;
-    return keys ? f32x4{1, 1, 1, 1} * v[l16] : *reinterpret_cast<const f32x4*>(v + lg * 4);
+    const f32x4 x = keys ? f32x4{1, 1, 1, 1} * v[l16] : *reinterpret_cast<const f32x4*>(v + lg * 4);
+    return f32x4{fabsf(x[0]), fabsf(x[1]), fabsf(x[2]), fabsf(x[3])};
   };
   // Largest of the thread's partial sums on the way, in units of |x| |w|, where one is more than `unusual` of them; looked at three
   // times.  The least product of the thread's norms tells first whether there can be one.
@@ -201,14 +215,13 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
   };
   const float least = cls == 0 ? limit(std::true_type{}) : limit(std::false_type{});
   const int quarter = (KS + 3) / 4;
-  request(0);
-  deposit(0);
-  request(1);
   f32x4 acc[4][4];
+  auto zero = [&]() {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
+      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
+  };
   auto product = [&](auto KEYS) {
     constexpr bool keys = decltype(KEYS)::value;
     auto look = [&]() {
@@ -234,6 +247,10 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
       }
     };
     int next = quarter - 1;
+    request(0);
+    deposit(0);
+    request(1);
+    zero();
     for (int k = 0; k < KS; ++k) {
       __syncthreads();                                  // stage k is in LDS; stage k-1 has been read by every wave
       const unsigned char* st = lds + (k & 1) * COND_STAGE_B;
@@ -256,7 +273,6 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
       if (k == next) { look(); next += quarter; }
     }
   };
-  if (cls == 0) product(std::true_type{}); else product(std::false_type{});
   const int DH = n.d / n.heads, KH = DH / 32, CF = DH / 16, SF = io.SF;
   // where the four numbers of lane `ln` in feature fragment fi of the tile and token fragment tj go
   auto place = [&](int fi, int tj, int ln) {
@@ -266,81 +282,145 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
     return cls == 0 ? n.kc + (((eh * SF + sf) * KH + fh / 32) * 64 + ln % 16 + 16 * ((fh % 32) / 8 + g / 2)) * 8 + (g & 1) * 4   // a fragment is half of a 32-deep k-step
                     : n.vct + (((eh * CF + fh / 16) * SF + sf) * 64 + ln) * 4;
   };
-  const float line = seen > unusual ? fmaxf(COND_TIE, COND_GROWN * COND_ULP * root * seen) : COND_TIE, own = (COND_OWN * root + 2.0f) * COND_ULP;
-  uint64_t again = 0;                                   // bit (i * 4 + j) * 4 + e
-  f32x4 x[4];
+  auto each = [&](auto&& f) {                           // f(i, j, sums with their biases) of the thread's pieces, stored as well
 #pragma unroll
-  for (int j = 0; j < 4; ++j) x[j] = tokens(cls == 0, j) * line;
+    for (int i = 0; i < 4; ++i) {
+      const f32x4 bias = features(cls == 0, bias0, i);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const f32x4 bias = features(cls == 0, bias0, i), wnorm = features(cls == 0, norm0, i);
+      for (int j = 0; j < 4; ++j) {
+        if (tf0 + wt * 4 + j >= MF) continue;
+        const f32x4 v = acc[i][j] + bias;
+        *reinterpret_cast<bf16x4*>(place(wf * 4 + i, wt * 4 + j, lane)) = to_bf16x4(v);
+        f(i, j, v);
+      }
+    }
+  };
+  // observations as they are, [token][COND_XS]
+  auto deposit_x = [&](unsigned char* st, int k) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (tf0 + wt * 4 + j >= MF) continue;
-      const f32x4 v = acc[i][j] + bias;
-      *reinterpret_cast<bf16x4*>(place(wf * 4 + i, wt * 4 + j, lane)) = to_bf16x4(v);
+    for (int j = 0; j < 2; ++j) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(st + COND_W_B) + (xr + j * 64) * COND_XS + xc) = observed(k, j);
+  };
+  // how many of the tile's tokens had better be added in order right away
+  int marked = 0;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) marked += __builtin_popcountll(__ballot(lane + j * 64 < io.M - tf0 * 16 && size0[min(lane + j * 64, io.M - 1 - tf0 * 16)] < 0.0f));
+  if (marked < COND_MARKED) {
+    if (cls == 0) product(std::true_type{}); else product(std::false_type{});
+    const float line = seen > unusual ? fmaxf(COND_TIE, COND_GROWN * COND_ULP * root * seen) : COND_TIE, own = (COND_OWN * root + 2.0f) * COND_ULP;
+    uint64_t again = 0;                                 // bit (i * 4 + j) * 4 + e
+    f32x4 x[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = tokens(cls == 0, j) * line;
+    f32x4 wnorm;
+    each([&](int i, int j, const f32x4& v) {
+      if (j == 0) wnorm = features(cls == 0, norm0, i);
       const f32x4 drawn = wnorm * x[j];
       unsigned m = 0;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float tie = fmaxf(drawn[e], own * fabsf(v[e]));
-        if ((float)(__bf16)(v[e] - tie) != (float)(__bf16)(v[e] + tie) || !(fabsf(v[e]) + tie < 3.0e38f)) m |= 1u << e;   // (not finite: again)
+        // (drawn is a not-a-number where an observation or a weight is one, and the sum is one in any order)
+        if (drawn[e] == drawn[e] && ((float)(__bf16)(v[e] - tie) != (float)(__bf16)(v[e] + tie) || !(fabsf(v[e]) + tie < 3.0e38f))) m |= 1u << e;
       }
       again |= (uint64_t)m << ((i * 4 + j) * 4);
-    }
-  }
-  // second pass
-  int* list = reinterpret_cast<int*>(lds + 2 * COND_AGAIN_B);
-  int* listed = list + COND_LIST;
-  auto deposit_again = [&](int k) {
-    unsigned char* st = lds + (k & 1) * COND_AGAIN_B;
-    deposit_weights(st);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(st + COND_W_B) + (xr + j * 64) * COND_XS + xc) = observed(k, j);
-  };
-  for (;;) {
+    });
+    int* list = reinterpret_cast<int*>(lds + 2 * COND_AGAIN_B);
+    int* listed = list + COND_LIST;
     __syncthreads();                                    // the LDS is free, and what was stored above has left (the numbers added again are stored over it)
     if (threadIdx.x == 0) *listed = 0;
     __syncthreads();
-    while (again) {
-      const int slot = atomicAdd(listed, 1);
-      if (slot >= COND_LIST) break;
-      const int p = __builtin_ctzll(again);
-      again &= again - 1;
-      list[slot] = (int)threadIdx.x << 6 | p;
-    }
+    int slot = again ? atomicAdd(listed, __builtin_popcountll(again)) : 0;
     __syncthreads();
-    const int total = min(*listed, COND_LIST);
-    if (total == 0) break;
-    const bool mine = (int)threadIdx.x < total;
-    const int item = list[mine ? threadIdx.x : 0], ow = item >> 12, ol = item >> 6 & 63, p = item & 63;
-    const int fi = (ow & 3) * 4 + p / 16, tj = (ow >> 2) * 4 + p / 4 % 4, four = (ol >> 4) * 4 + p % 4;
-    const int fl = cls == 0 ? four : ol & 15, tk = tj * 16 + (cls == 0 ? ol & 15 : four);
+    const int total = *listed;
+    if (total <= COND_AGAIN) {
+      for (int from = 0; from < total; from += COND_LIST) {
+        __syncthreads();                                // the list and both stages have been read
+        for (; again && slot < from + COND_LIST; ++slot) {
+          list[slot - from] = (int)threadIdx.x << 6 | __builtin_ctzll(again);
+          again &= again - 1;
+        }
+        __syncthreads();
+        const bool mine = (int)threadIdx.x < total - from;
+        const int item = list[mine ? threadIdx.x : 0], ow = item >> 12, ol = item >> 6 & 63, p = item & 63;
+        const int fi = (ow & 3) * 4 + p / 16, tj = (ow >> 2) * 4 + p / 4 % 4, four = (ol >> 4) * 4 + p % 4;
+        const int fl = cls == 0 ? four : ol & 15, tk = tj * 16 + (cls == 0 ? ol & 15 : four);
+        auto deposit_again = [&](int k) {
+          unsigned char* st = lds + (k & 1) * COND_AGAIN_B;
+          deposit_weights(st);
+          deposit_x(st, k);
+        };
+        request(0);
+        deposit_again(0);
+        request(1);
+        float sum = 0.0f;
+        for (int k = 0; k < KS; ++k) {
+          __syncthreads();
+          const unsigned char* st = lds + (k & 1) * COND_AGAIN_B;
+          deposit_again(k + 1);
+          request(k + 2);
+          if (mine) {
+            const bf16x8* w = reinterpret_cast<const bf16x8*>(st) + fi * 64 + fl;
+            const f32x4* x = reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(st + COND_W_B) + tk * COND_XS);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              const bf16x8 wv = w[g * 16];
+              const f32x4 x0 = x[2 * g], x1 = x[2 * g + 1];
+#pragma unroll
+              for (int i = 0; i < 4; ++i) sum = fmaf(x0[i], (float)wv[i], sum);
+#pragma unroll
+              for (int i = 0; i < 4; ++i) sum = fmaf(x1[i], (float)wv[4 + i], sum);
+            }
+          }
+        }
+        if (mine) place(fi, tj, ol)[p % 4] = (__bf16)(sum + n.bias[f_tile + fi * 16 + fl]);
+      }
+      return;
+    }
+  }
+  // The whole tile in order.  mfma_f32_16x16x4_f32 adds its four products to the accumulator one after the other, each with one
+  // rounding, in the order of the lane groups (checked on hardware, denormals included): lane group g supplies features 4m + g of a
+  // k-step to MFMA m, so its weights lie as entries m of lane 16 g + row.
+  auto deposit_ordered = [&](int k) {
+    unsigned char* st = lds + (k & 1) * COND_AGAIN_B;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<bf16x2*>(st + (((wave * 2 + j) * 64 + 16 * g + l16) * 8 + 2 * lg) * 2) = bf16x2{rw[j][g], rw[j][4 + g]};
+    deposit_x(st, k);
+  };
+  auto ordered = [&](auto KEYS) {
+    constexpr bool keys = decltype(KEYS)::value;
+    __syncthreads();
     request(0);
-    deposit_again(0);
+    deposit_ordered(0);
     request(1);
-    float sum = 0.0f;
+    zero();
     for (int k = 0; k < KS; ++k) {
       __syncthreads();
       const unsigned char* st = lds + (k & 1) * COND_AGAIN_B;
-      deposit_again(k + 1);
+      const float* xs = reinterpret_cast<const float*>(st + COND_W_B) + (wt * 64 + l16) * COND_XS + lg;
+      bf16x8 a[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = reinterpret_cast<const bf16x8*>(st)[(wf * 4 + i) * 64 + lane];
+      deposit_ordered(k + 1);
       request(k + 2);
-      if (mine) {
-        const bf16x8* w = reinterpret_cast<const bf16x8*>(st) + fi * 64 + fl;
-        const f32x4* x = reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(st + COND_W_B) + tk * COND_XS);
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const bf16x8 wv = w[g * 16];
-          const f32x4 x0 = x[2 * g], x1 = x[2 * g + 1];
+      for (int m = 0; m < 8; ++m) {
+        float b[4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) sum = fmaf(x0[i], (float)wv[i], sum);
+        for (int j = 0; j < 4; ++j) b[j] = xs[j * 16 * COND_XS + 4 * m];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) sum = fmaf(x1[i], (float)wv[4 + i], sum);
-        }
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[i][j] = keys ? __builtin_amdgcn_mfma_f32_16x16x4f32((float)a[i][m], b[j], acc[i][j], 0, 0, 0)
+                             : __builtin_amdgcn_mfma_f32_16x16x4f32(b[j], (float)a[i][m], acc[i][j], 0, 0, 0);
       }
     }
-    if (mine) place(fi, tj, ol)[p % 4] = (__bf16)(sum + n.bias[f_tile + fi * 16 + fl]);
-  }
+  };
+  if (cls == 0) ordered(std::true_type{}); else ordered(std::false_type{});
+  each([](int, int, const f32x4&) {});
 }
 
 }  // namespace tsdp
