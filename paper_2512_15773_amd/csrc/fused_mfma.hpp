@@ -1251,7 +1251,6 @@ __global__ __launch_bounds__(C::THREADS, C::WG_PER_CU) void k_fused_forward(Fuse
 // after a product, where a global load has nothing to overlap it, K times per rollout, and behind the weights in flight it would
 // wait for them): output projections and MLP down, LayerStream also q | k | v and MLP up; transposed token embedding and tok_b + pos,
 // where there is room.
-constexpr int DRAFT_LDS = 157 * 1024;   // (the rest: the tile's environments and coefficients, at most 2.2 KB)
 template <class C>
 struct DraftLds {
   static constexpr int NBIAS = C::STREAM ? 9 : 3;
@@ -1262,7 +1261,8 @@ struct DraftLds {
   static constexpr int bytes(int A, int L, int mod_cols, bool staged) {
     return C::LDS_B + 4 * (tok(A, L, mod_cols) + (staged ? (A + C::H) * C::D : 0));
   }
-  static constexpr bool ALWAYS = bytes(512 / C::H, FUSED_MAX_LAYERS, C::RPT, true) <= DRAFT_LDS;   // the embedding fits for every network
+  static constexpr int MOST = 160 * 1024 - ((C::STREAM ? MAX_DRAFTS : 1) * 32 + 24) * C::RPT - 64;   // beside the tile's coefficients and environments
+  static constexpr bool ALWAYS = bytes(512 / C::H, FUSED_MAX_LAYERS, C::RPT, true) <= MOST;   // the embedding fits for every network
 };
 
 // Drafter rollout: the workgroup keeps the latents of RPT environments in LDS and runs their drafted

@@ -38,6 +38,14 @@ struct LayerOff {
   size_t mod_w, mod_b, qkv_w, qkv_b, o_w, o_b, cq_w, cq_b, ck_w, ck_b, cv_w, cv_b, co_w, co_b, up_w, up_b, dn_w, dn_b;
 };
 
+// a tile of the persistent rollout: `rpt` environments a workgroup; fits: its LDS suffices for this network
+struct DraftTile {
+  hipError_t (*launch)(const FusedNet&, const DraftIO&, int A, hipStream_t) = nullptr;
+  bool (*fits_of)(int A, int L) = nullptr;
+  int rpt = 0;
+  bool fits = false;
+};
+
 struct Net {
   int L = 0, d = 0, heads = 0, m = 0;
   size_t n_floats = 0;
@@ -61,9 +69,7 @@ struct Net {
   hipError_t (*fused_verify_few)(const FusedNet&, const FusedIO&, int A, int R_cap, hipStream_t) = nullptr;
   int verify_rpt = 1;
   void (*fused_mod)(const FusedNet&, const int32_t*, int, const int32_t*, int, const int32_t*, int, float*, hipStream_t) = nullptr;
-  hipError_t (*fused_draft_small)(const FusedNet&, const DraftIO&, int A, hipStream_t) = nullptr;   // few environments per workgroup
-  hipError_t (*fused_draft_big)(const FusedNet&, const DraftIO&, int A, hipStream_t) = nullptr;     // many environments per workgroup
-  int draft_rpt_small = 0, draft_rpt_big = 0;
+  DraftTile draft_small, draft_big;   // few, many environments per workgroup
   bool few = false;             // the forward pass of this context's rows is spread over the chip (k_few_*)
   bool few_roll = false;        // so is the drafter's rollout
   void (*few_forward)(const FusedNet&, const FewRun&, hipStream_t) = nullptr;
@@ -251,10 +257,17 @@ hipError_t launch_draft(const FusedNet& n, const DraftIO& io_in, int A, hipStrea
   // FiLM vectors of up to 16 / RPT steps per in-kernel product, as many as LDS has room for, then the token embedding
   io.mod_cols = C::RPT;
   for (int cols = 16; C::CM == 0 && cols > C::RPT; cols /= 2)
-    if (cols % C::RPT == 0 && Lds::bytes(A, n.L, cols, Lds::ALWAYS) <= DRAFT_LDS) { io.mod_cols = cols; break; }
+    if (cols % C::RPT == 0 && Lds::bytes(A, n.L, cols, Lds::ALWAYS) <= Lds::MOST) { io.mod_cols = cols; break; }
   if constexpr (!Lds::ALWAYS)
-    if (Lds::bytes(A, n.L, io.mod_cols, true) > DRAFT_LDS) return launch_draft_as<C, false>(n, io, A, s);
+    if (Lds::bytes(A, n.L, io.mod_cols, true) > Lds::MOST) return launch_draft_as<C, false>(n, io, A, s);
   return launch_draft_as<C, true>(n, io, A, s);
+}
+template <class C>
+bool draft_fits(int A, int L) { return DraftLds<C>::bytes(A, L, C::RPT, DraftLds<C>::ALWAYS) <= DraftLds<C>::MOST; }
+template <class C, bool USED>
+DraftTile draft_tile_of() {
+  if constexpr (USED) return {launch_draft<C>, draft_fits<C>, C::RPT};
+  else return {nullptr, nullptr, C::RPT};
 }
 
 template <int D>
@@ -483,9 +496,7 @@ struct FusedKernels {
   int rpt_verify = 0;
   void (*mod)(const FusedNet&, const int32_t*, int, const int32_t*, int, const int32_t*, int, float*, hipStream_t) = nullptr;
   hipError_t (*verify)(const FusedNet&, const FusedIO&, int, int, hipStream_t) = nullptr;
-  hipError_t (*draft_small)(const FusedNet&, const DraftIO&, int, hipStream_t) = nullptr;
-  hipError_t (*draft_big)(const FusedNet&, const DraftIO&, int, hipStream_t) = nullptr;
-  int rpt_small = 0, rpt_big = 0;
+  DraftTile draft_small, draft_big;
 };
 
 // The spread kernels of a compiled shape, where few_pays can choose them.
@@ -525,14 +536,17 @@ bool find_fused(int dtype, int D, int H, int heads, int cm, int S, int mlp_ratio
     spread_kernels<TT_, D_, H_, HD_, SX_>(k);                                                                  \
     k.few_film = launch_few_film<TT_, D_>;                                                                       \
     k.mod = DT_ == 1 ? launch_mod<D_> : nullptr;                                                               \
-    k.draft_small = launch_draft<FusedCfg<TT_, D_, NTS, H_, HD_, CM_, CHS, SX_, HPS, NWS>>; k.rpt_small = NTS / H_; \
-    k.draft_big = launch_draft<FusedCfg<TT_, D_, NTB, H_, HD_, CM_, CHB, SX_, HPB, NWD>>;   k.rpt_big = NTB / H_;   \
+    k.draft_small = draft_tile_of<FusedCfg<TT_, D_, NTS, H_, HD_, CM_, CHS, SX_, HPS, NWS>, (D_ < 512)>();    \
+    k.draft_big = draft_tile_of<FusedCfg<TT_, D_, NTB, H_, HD_, CM_, CHB, SX_, HPB, NWD>, DT_ == 0 || (D_ <= 192)>(); \
     return true;                                                                                               \
   }
   // The drafter's small tile (one environment per workgroup) is latency-bound: it takes all heads in one attention
   // phase and the whole MLP hidden layer in one chunk (d = 256 with cross-attention: half of it, 512; 1024 does not
   // fit the LDS), which minimises the number of barrier-separated phases; its four-environment tile at d = 192 takes
   // the hidden layer in two chunks of 384 (measured against 128 / 256: -15 % at d = 256, -3.5 % at d = 192).
+  // Rollout tiles that lose to a forward pass per transition are not compiled: of many environments from d = 256 on (tsdp_draft, us, eight
+  // transitions, two layers, tile / forward passes: 1024 environments of d = 256 671 / 656, four layers 1493 / 1171, d = 384 1341 / 1113; 512 of
+  // d = 256 with cross-attention 880 / 870), of one at d = 512 (64 environments 1709 / 1513).
   //         type dtype  D   H heads cm  S | verify: NT  CH  HP NW HPX | draft small: NT CH HP NW | big: NT CH HP | NW
   if (dtype == 1 && D == 256 && H == 16 && heads == 4 && cm == 0)
     k.verify_few = launch_verify<FusedCfg<TBF16, 256, 64, 16, 4, 0, 256, 0, 2, 8>>;
@@ -739,8 +753,8 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   n.fused_verify_few = fk.verify_few;
   n.verify_rpt = fk.rpt_verify;
   n.fused_mod = fk.mod;
-  n.fused_draft_small = fk.draft_small; n.fused_draft_big = fk.draft_big;
-  n.draft_rpt_small = fk.rpt_small; n.draft_rpt_big = fk.rpt_big;
+  n.draft_small = fk.draft_small; n.draft_big = fk.draft_big;
+  for (DraftTile* t : {&n.draft_small, &n.draft_big}) t->fits = t->fits_of && t->fits_of(cf.A, L);
   n.few_forward = fk.few_forward; n.few_draft = fk.few_draft; n.few_film = fk.few_film; n.few_slices = fk.few_slices; n.flow_row = 0;
   // Few rows: the spread kernels.  The capacity of the context decides, not the call: an environment's result must not
   // depend on the batch it is computed in.
@@ -869,14 +883,15 @@ int forward(tsdp_ctx* c, Net& n, const float* x_rows, int R_cap, const int32_t* 
   return TSDP_OK;
 }
 
-// dynamic LDS of the persistent drafter kernel for `rpt` environments per workgroup (mirrors launch_draft)
-size_t fused_draft_lds(const Net& n, const tsdp_config& cf, int rpt) {
-  const size_t ES = cf.dtype == 0 ? 4 : 2, PAD = cf.dtype == 0 ? 4 : 8;
-  const size_t D = n.d, NT = (size_t)rpt * cf.H, DH = D / n.heads, HP = n.heads;      // upper bounds over the
-  const size_t CH = 4 * D;                                                             // compiled tile variants
-  const size_t act = NT * (D + PAD) * ES, q = HP * NT * (DH + PAD) * ES, vt = HP * rpt * DH * (cf.H + 4) * ES;
-  const size_t scr = std::max(std::max(2 * q + vt, NT * (CH + PAD) * ES), NT * 64 * 4);
-  return act + scr + 2 * 8 * NT * 4 + 2 * NT * cf.A * 4 + (size_t)rpt * n.L * 4 * D * 4 + 16 * (D + PAD) * ES;  // upper bound
+// Tile of the persistent rollout for B environments; null: a forward pass per transition, in the verify kernel's tiles.  From 192 of
+// the tiles of many environments on these fill the chip; where a network is too large for one or has none, the verify kernel's tiles of 64 or 128
+// tokens stream the weights less often than tiles of one environment.  tsdp_draft, us, eight transitions of 1024 environments, one / four
+// environments a workgroup / forward passes: d = 128, 2 and 9 layers 443 / 283 / 569, 1577 / 1251 / 2017; d = 192, 2, 4 and 5 layers 877 / 449 / 883,
+// 1600 / 958 / 1595, 2384 / - / 2048.
+const DraftTile* draft_tile(const Net& n, int B) {
+  if (!n.fused) return nullptr;
+  const DraftTile& t = (B + n.draft_big.rpt - 1) / n.draft_big.rpt >= 192 ? n.draft_big : n.draft_small;
+  return t.fits ? &t : nullptr;
 }
 
 int sync_lines(const tsdp_ctx* c) { return flow_lines(rows_max(c->cfg)) + flow_lines(c->cfg.B_max); }
@@ -1222,9 +1237,9 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
   const tsdp_config& cf = c->cfg;
   const int D = c->D;
   Net &dn = c->net[1], &bn = c->net[0];
-  // persistent drafter kernel (or the spread launches): pick the tile (environments per workgroup) that fills the chip best
-  const bool big = dn.fused && (B + dn.draft_rpt_big - 1) / dn.draft_rpt_big >= 192;
-  const bool kernel = dn.few_roll || (dn.fused && fused_draft_lds(dn, cf, big ? dn.draft_rpt_big : dn.draft_rpt_small) <= 160 * 1024);
+  // persistent drafter kernel (or the spread launches), else a forward pass per transition
+  const DraftTile* tile = draft_tile(dn, B);
+  const bool kernel = dn.few_roll || tile;
   bool roll_film = false;                               // the rollout's FiLM vectors are part of the first launch
   if (B <= PLAN_ROWS_B) {
     const PlanIO plan{d_x, d_t0, d_K, d_sigma_scale, B, cf.K_max, cf.T, D, cf.bonus_row, gated ? 1 : 0, c->K_eff, d_row_ptr, c->status,
@@ -1291,7 +1306,7 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
       const FewRun r = few_run(c, dn, B, few_safe_rows(!gated, B, B), d_t0, nullptr, c->few_mod);   // (d_y_last has B rows)
       dn.few_draft(dn.fnet, r, io, cf.K_max, c->few_y, s);
     } else {
-      HIPCHK(c, (big ? dn.fused_draft_big : dn.fused_draft_small)(dn.fnet, io, cf.A, s));
+      HIPCHK(c, tile->launch(dn.fnet, io, cf.A, s));
     }
     tick(c, 0, 1, s);
     if (dn.few_roll) bonus_rows();
@@ -1548,12 +1563,9 @@ int tsdp_prepare(tsdp_ctx* c) {
     if (bn.fused_verify_few) HIPCHK(c, bn.fused_verify_few(bn.fnet, io, c->cfg.A, 0, nullptr));
   }
   Net& dn = c->net[1];
-  if (dn.fused) {                                     // the tile variants tsdp_draft may pick (those that fit the LDS)
-    if (fused_draft_lds(dn, c->cfg, dn.draft_rpt_small) <= 160 * 1024)
-      HIPCHK(c, dn.fused_draft_small(dn.fnet, dio, c->cfg.A, nullptr));
-    if (fused_draft_lds(dn, c->cfg, dn.draft_rpt_big) <= 160 * 1024)
-      HIPCHK(c, dn.fused_draft_big(dn.fnet, dio, c->cfg.A, nullptr));
-  }
+  if (dn.fused)                                       // the tiles tsdp_draft may pick
+    for (const DraftTile* t : {&dn.draft_small, &dn.draft_big})
+      if (t->fits) HIPCHK(c, t->launch(dn.fnet, dio, c->cfg.A, nullptr));
   return TSDP_OK;
 }
 
@@ -1646,6 +1658,12 @@ const char* tsdp_internal_kernels(const tsdp_ctx* c, int which) {
   if (!c || which < 0 || which > 1) return "";
   const Net& n = c->net[which];
   return n.few ? (n.flow_row ? "k_flow" : n.few_slices ? "k_few" : "k_row") : n.fused ? "tiles" : "operators";
+}
+
+// Not part of the interface, for tests: environments per workgroup of the persistent rollout of B environments, 0: another kernel's.
+int tsdp_internal_rollout_tile(const tsdp_ctx* c, int B) {
+  const DraftTile* t = c && !c->net[1].few_roll ? draft_tile(c->net[1], B) : nullptr;
+  return t ? t->rpt : 0;
 }
 
 // Not part of the interface, for tests: one-launch passes of this context with at most n workgroups (0: all), so that XCDs

@@ -349,13 +349,39 @@ def test_tiles_in_order_give_the_bits_of_tiles_that_are_not(marked, dense, cond_
     (ti.small_variant(ti.C1, A=32, draft=ti.NetShape(16, 32, 2)), 2, 4),        # the same in fp32
     (ti.small_variant(ti.C1, A=1, draft=ti.NetShape(3, 32, 2)), 2, 4),
     (ti.small_variant(ti.C4, A=16, draft=ti.NetShape(6, 256, 8)), 25, 2),       # token embedding not in LDS
-    (ti.small_variant(ti.C5, A=32, ragged=False, draft=ti.NetShape(5, 192, 6)), 768, 1),   # four environments a workgroup, the same
+    (ti.small_variant(ti.C5, A=32, ragged=False, draft=ti.NetShape(4, 192, 6)), 768, 1),   # four environments a workgroup, the same
 ])
 @pytest.mark.parametrize("bonus, clip, norm", [(False, None, 0), (True, 1.5, 1)])
 def test_rollouts_of_a_workgroup_an_environment(wl, B, K_max, bonus, clip, norm):
     wl = ti.replace(wl, B=B, K_max=K_max, base=ti.NetShape(1, wl.base.d, wl.base.heads))
     t0 = np.full(B, -1); t0[-1] = wl.T // 2; t0[:2] = (wl.T - 1, min(K_max, wl.T - 1) // 2 + 1)[:B]
     _stage_parity(wl, B, t0, np.full(B, K_max), np.full(B, 1.1), clip=clip, bonus=bonus, norm=norm)
+
+
+@pytest.mark.parametrize("wl, B, rpt", [
+    (ti.small_variant(ti.C5, A=8, draft=ti.NetShape(2, 192, 6)), 768, 4),       # four environments a workgroup with more components
+    (ti.small_variant(ti.C5, A=7, draft=ti.NetShape(5, 192, 6)), 765, 4),       # and layers: the most that fit; the last workgroup of one environment
+    (ti.small_variant(ti.C5, A=32, draft=ti.NetShape(4, 192, 6)), 768, 4),
+    (ti.small_variant(ti.C5, A=32, draft=ti.NetShape(5, 192, 6)), 768, 0),      # one too many
+    (ti.small_variant(ti.C5, A=32, draft=ti.NetShape(5, 192, 6)), 764, 1),
+    (ti.small_variant(ti.C3, A=8, draft=ti.NetShape(11, 128, 4)), 768, 4),
+    (ti.small_variant(ti.C3, A=8, draft=ti.NetShape(12, 128, 4)), 768, 0),
+    (ti.small_variant(ti.C4, A=16, draft=ti.NetShape(9, 256, 8)), 25, 1),       # cross-attention
+    (ti.small_variant(ti.C4, A=1, draft=ti.NetShape(10, 256, 8)), 25, 0),       # more layers than the LDS holds biases and vectors of
+    (ti.small_variant(ti.C4, A=16, draft=ti.NetShape(16, 256, 8)), 25, 0),
+    (ti.small_variant(ti.C5, A=16, draft=ti.NetShape(13, 384, 6)), 2, 1),
+    (ti.small_variant(ti.C5, A=16, draft=ti.NetShape(14, 384, 6)), 2, 0),
+    (ti.small_variant(ti.C2, A=32, draft=ti.NetShape(16, 256, 4)), 33, 1),      # fp32
+])
+def test_rollout_tile_is_the_one_whose_lds_suffices(wl, B, rpt):
+    K = 2 if wl.dtype == "fp32" else 1                      # (fp32 rollouts of one transition are spread)
+    wl = ti.replace(wl, B=B, K_max=K, ragged=False, base=ti.NetShape(1, wl.base.d, wl.base.heads))
+    S = _setup(wl, B, K_max=K)
+    lib = S["ctx"].lib
+    assert lib.tsdp_internal_rollout_tile(S["ctx"].ctx, B) == rpt
+    S["ctx"].close()
+    t0 = np.full(B, -1); t0[-1] = wl.T // 2; t0[0] = wl.T - 1
+    _stage_parity(wl, B, t0, np.full(B, K), np.full(B, 1.1))
 
 
 @pytest.mark.parametrize("base, B, K_max", [
