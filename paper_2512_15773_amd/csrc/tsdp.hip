@@ -1252,13 +1252,13 @@ static int draft_impl(tsdp_ctx* c, int B, const float* d_x, const int32_t* d_t0,
       const int Nm = n.L * 4 * n.d;
       return FilmJob{n.fnet.modw, n.modb, n.temb, n.fnet.cemb, mod, n.d, Nm, (Nm / 16 + 3) / 4, (rows + 15) / 16, k_max};
     };
-    const bool timed = c->timing && ((c->timing_mask >> 3) & 1);   // (the product on its own)
+    auto timed = [&](int stage) { return c->timing && ((c->timing_mask >> stage) & 1); };   // (a product that a timed stage contains stays in it)
     FilmJob jb{}, jr{};
     jb.nx = jr.nx = 1;
     if (B <= PLAN_FILM_B) {
-      if (dn.few_roll && small(dn)) { jr = job(dn, B * cf.K_max, cf.K_max, c->few_mod); roll_film = true; }
+      if (dn.few_roll && small(dn) && !timed(0)) { jr = job(dn, B * cf.K_max, cf.K_max, c->few_mod); roll_film = true; }
       // (a rollout keeps its FiLM vectors in LDS or in few_mod; the operator kernels would use the buffer that the base network's go to)
-      if (base_mod_rows > 0 && kernel && !timed && (bn.few || (bn.fused && !bn.fused_mod)) && small(bn) && (!roll_film || f32(bn) == f32(dn))) {
+      if (base_mod_rows > 0 && kernel && !timed(3) && (bn.few || (bn.fused && !bn.fused_mod)) && small(bn) && (!roll_film || f32(bn) == f32(dn))) {
         jb = job(bn, base_mod_rows, 0, c->mod);
         if (base_mod) *base_mod = MOD_DONE;
       }

@@ -958,6 +958,25 @@ def test_two_contexts_on_two_streams_do_not_share_state():
         S[i]["ctx"].close()
 
 
+def test_timed_rollouts_contain_their_film_product():
+    # 128 environments draft once; with K_max = 64 their FiLM product has 64 times the rows (100 MB of vectors), the rollout is the same
+    import torch
+    took = []
+    for K_max in (1, 64):
+        wl = ti.small_variant(ti.C2, A=4, B=128, K_max=K_max, cond_dim=64, base=ti.NetShape(1, 96, 3), draft=ti.NetShape(16, 48, 3))
+        S = _setup(wl, 128, K_max=K_max)
+        ctx = S["ctx"]
+        assert kernels(ctx)[1] == "k_row"
+        ctx.tsdp_kernel_timing(2)
+        ms = []
+        for _ in range(5):
+            _gpu_draft(S, np.full(128, 50), np.ones(128), np.ones(128), None)
+            ms.append(ctx.tsdp_kernel_ms(0))
+        took.append(min(ms))
+        ctx.close()
+    assert took[1] > 1.15 * took[0], took
+
+
 def test_kernel_timing_brackets_the_chosen_stages():
     # measurement aid: event pairs around the stage kernels; a stage without a timed launch is an error, not a number
     from paper_2512_15773_amd import TsdpError
