@@ -861,6 +861,7 @@ __device__ __forceinline__ void fused_body(const FusedNet& net, unsigned char* l
   constexpr bool STREAMS = !std::is_same<std::remove_reference_t<Stream>, NoStream>::value;
   if constexpr (STREAMS) {
     typedef std::remove_reference_t<Stream> LS;
+    static_assert(MBU >= 4 && LS::KM >= 7, "a fragment row or k-step behind which weights are requested is missing: they would be multiplied unread");
     for (int layer = 0; layer < net.L; ++layer) {
       const FusedLayer &W = net.layer[layer], &N = net.layer[layer + 1 < net.L ? layer + 1 : 0];
       const float* lb = lbias + layer * 9 * D;           // output projection, MLP down, q | k | v, MLP up
