@@ -42,8 +42,7 @@ constexpr int MAX_DRAFTS = 64;   // K_max of a context (tsdp_create)
 struct FusedNet {
   FusedLayer layer[FUSED_MAX_LAYERS];
   int L, D, heads, M;
-  const float* tok_w; const float* tok_b; const float* pos;   // fp32 [D,A], [D], [H,D]
-  const float* tok_wt;         // [A,D] (k_few_*)
+  const float* tok_wt; const float* tok_b; const float* pos;   // fp32 [A,D], [D], [H,D]
   const void* head;            // [ceil(A/16)][D/32][64] fragments of head_w, rows padded to a multiple of 16
   const float* head_b;         // [A]
   const void* modw;            // [L*4D/16][D/32][64] FiLM projections of all layers (drafter kernel)

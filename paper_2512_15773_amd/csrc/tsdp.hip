@@ -713,7 +713,7 @@ int build_fused(tsdp_ctx* c, Net& n, const std::vector<float>& w, const std::vec
   if (!n.tok_wt && (rc = dev_alloc(c, &n.tok_wt, tokt.size()))) return rc;
   HIPCHK(c, hipMemcpy(n.tok_wt, tokt.data(), tokt.size() * sizeof(float), hipMemcpyHostToDevice));
   f.tok_wt = n.tok_wt;
-  f.tok_w = n.blob + n.tok_w; f.tok_b = n.blob + n.tok_b; f.pos = n.blob + n.pos;
+  f.tok_b = n.blob + n.tok_b; f.pos = n.blob + n.pos;
   f.head = P(head_off); f.head_b = n.blob + n.head_b;
   f.modtab = nullptr;
   f.rms = cf.norm;
