@@ -15,10 +15,11 @@ namespace tsdp {
 inline int few_safe_rows(bool ahead, int B, int R_cap) { return ahead ? std::min(B, R_cap) : 0; }
 
 // Networks with compiled kernels.  One workgroup per tile takes the same time from 1 to 256 tiles, the spread launches grow
-// with the rows; they meet at about 2100 tokens.  Rounds, us, tile / spread at 64, 128, 144 rows of 16 tokens: bf16 d = 256
-// 498 / 409, 498 / 443, 497 / 511; bf16 d = 384 880 / 729, 881 / 869, -; fp32 d = 256 799 / 504, 800 / 724, and at 136 rows
-// 797 / 835; at 64, 128 rows of 32 tokens, d = 512: 1577 / 1252, 1591 / 1856.  A layer of less than 700 KB passes through one
-// compute unit faster than through two launches (fp32 d = 64, 393 KB in all: 21 us against 25); one launch was not measured there.
+// with the rows; they meet at about 2100 tokens.  tsdp_verify of four layers, us, tile / spread: fp32 d = 256, 112, 128 rows of 16 tokens
+// 241 / 214, 242 / 233; bf16 d = 256, 128, 136 rows 122 / 94, 122 / 117; bf16 d = 384, 112, 128 rows 205 / 189, 204 / 194, but 136 rows 204 / 244
+// (the line is one for both); 48, 64, 68 rows of 32 tokens, d = 512: 364 / 263, 362 / 270, 362 / 356.  A layer of less than 700 KB passes through
+// one compute unit faster than through two launches (fp32 d = 64, 393 KB in all: 21 us against 25, before either became faster); one
+// launch was not measured there.
 constexpr size_t FEW_LAYER_BYTES = 700000;
 constexpr size_t layer_bytes(size_t d, bool f32, bool cross) { return (cross ? 14 : 12) * d * d * (f32 ? 4 : 2); }
 inline bool few_pays(size_t tokens, bool f32, size_t layer_bytes) {
@@ -28,11 +29,11 @@ inline bool few_pays(size_t tokens, bool f32, size_t layer_bytes) {
 // Launches of a spread rollout (two bf16 networks of one shape; fp32 drafters beyond flow_draft_pays): every transition up to
 // K_max has its own, whether drafted or not (the draft counts are on the device).  With half of K_max or more the spread rollout
 // is the faster one, and what fewer drafts lose grows with K_max.  Rounds of one environment, two bf16 networks of d = 256, us,
-// persistent rollout and tile kernels / all spread: two layers, K = 1, 4, 8 of 8 170 / 164, 296 / 220, 464 / 293; 1, 4, 9 of 9 169 / 178,
-// 296 / 232, 507 / 321; 1, 8, 16 of 16 170 / 279, 464 / 390, 802 / 532; four layers 1, 2, 4 of 4 283 / 213, 384 / 244, 589 / 307, 1, 8
-// of 8 282 / 310, 1031 / 531.  With the fp32 drafter of d = 128, two layers (spread 23 us a drafted and 6 to 15 an undrafted transition,
-// persistent 39), K = 1, 4, 8 of 8 226 / 277, 344 / 331, 495 / 396; 4, 64 of 64 344 / 1085, 2673 / 1888.  So up to 40 launches (two layers:
-// K_max = 9) the rollout is spread -- the loss stays below a quarter of a round -- and beyond it is one launch.
+// persistent rollout and tile kernels / all spread: two layers, K = 1, 4, 8 of 8 148 / 143, 264 / 197, 419 / 263; 1, 4, 9 of 9 149 / 154,
+// 267 / 208, 457 / 291; 1, 8, 16 of 16 150 / 250, 419 / 346, 724 / 480; four layers 1, 2, 4 of 4 251 / 189, 338 / 218, 508 / 275, 1, 8
+// of 8 251 / 272, 849 / 475.  With the fp32 drafter of d = 128, two layers, K = 1, 4, 8 of 8, persistent (and the forward pass in one
+// launch) / all spread 155 / 246, 263 / 297, 402 / 361; 4, 64 of 64 (both spread) 319 / 826, 2030 / 1595.  So up to 40 launches (two layers:
+// K_max = 9) the rollout is spread -- the two networks' loss stays below a quarter of a round -- and beyond it is one launch.
 constexpr int FEW_ROLL_LAUNCHES = 40;
 inline bool few_rollout_pays(int layers, bool wide, bool cross, int K_max) {
   return layers * (wide ? 2 : 1) * (cross ? 3 : 2) * K_max + 1 <= FEW_ROLL_LAUNCHES;
@@ -41,14 +42,14 @@ inline bool few_rollout_pays(int layers, bool wide, bool cross, int K_max) {
 // Rollout in one launch (k_flow) instead of in launches (where that pays, `launches`) or in the persistent kernel.
 // fp32: the XCDs work side by side, and from the third environment of an XCD on a transition grows by about a quarter with
 // every other one, where the launches fill the chip at the same time.  tsdp_draft, us, launches / one launch, four transitions of
-// 8, 12, 16, 18, 24, 32 environments, two layers: d = 128 105 / 87, 107 / 95, 107 / 96, 108 / 113, 108 / 113, 109 / 137 (one
-// transition of 64, 128: 40 / 69, 57 / 115); d = 256 197 / 124, 202 / 182, 202 / 183, 231 / 257, 232 / 256, 239 / 336.  One layer of
-// d = 128 is too short for the exchanges unless there are several transitions: 16 environments, K_max = 1, 2, 4, 7 23 / 27, 37 /
-// 39, 64 / 63, 105 / 98.  Against the persistent kernel (four layers, K_max = 7, 8 / 18 environments) d = 128 515 / 249, 515 / 335,
-// d = 256 1992 / 357, 1972 / 797; it does not grow with the environments, and at 32 one launch takes 0.83 (0.55) of its time.
-// bf16 with cross-attention, d = 256, 32 tokens: eight transitions of 1, 4, 8, 16, 32 environments 317, 346, 350, 373, 518, the
-// persistent kernel (one workgroup an environment) 425 to 463; tsdp_draft, persistent / one launch, 24 environments, K_max = 1, 2, 8, one
-// layer 38 / 42, 66 / 71, 236 / 236, two 67 / 66, 122 / 117, 459 / 420; one layer, 16 environments 36.8 / 38.5, 65 / 63, 235 / 208.
+// 8, 12, 16, 18, 24, 32 environments, two layers: d = 128 103 / 76, 104 / 88, 104 / 88, 104 / 103, 110 / 109, 110 / 136 (one
+// transition of 64, 128: 41 / 68, 56 / 115); d = 256 181 / 121, 184 / 183, 185 / 186, 210 / 258, 212 / 260, 219 / 344.  One layer of
+// d = 128 is too short for the exchanges unless there are several transitions: 16 environments, K_max = 1, 2, 4, 7 27 / 28, 38 /
+// 39, 64 / 60, 103 / 92 (eight environments 26 / 25, 37 / 33, 63 / 49, 102 / 72: there the line gives up to an eighth away).  Against the
+// persistent kernel (four layers, K_max = 7, 8 / 18 environments) d = 128 506 / 205, 507 / 299, d = 256 1962 / 344, 1958 / 801.
+// bf16 with cross-attention, d = 256, 32 tokens, two layers, eight transitions of 1, 4, 8, 16, 32 environments 277, 281, 304, 320, 523, the
+// persistent kernel (one workgroup an environment) 399 to 434; tsdp_draft, persistent / one launch, 24 environments, K_max = 1, 2, 8, one
+// layer 40 / 44, 66 / 70, 220 / 222, two 72 / 68, 123 / 116, 428 / 403; one layer, 16 environments 40 / 38, 66 / 59, 219 / 179.
 inline bool flow_draft_pays(int environments, bool f32, size_t d, int layers, int K_max, bool launches) {
   if (!f32) return environments <= (layers >= 2 ? 24 : K_max >= 2 ? 16 : 8);
   return launches ? environments <= 16 && (layers * d >= 256 || K_max >= 4) : environments <= 32;
@@ -56,20 +57,20 @@ inline bool flow_draft_pays(int environments, bool f32, size_t d, int layers, in
 
 // Forward pass in one launch (k_flow): its dependent steps are shorter than two launches per layer, but a row costs it more of
 // the chip (registers for one workgroup per unit, tasks that take their rows in turn).
-// fp32, tsdp_verify, us, launches / one launch: d = 256, one layer, 32, 40, 48, 64 rows of 16 tokens 41 / 39, 45 / 43, 45 / 49, 49 / 56;
-// two 66 / 64, 73 / 69, 76 / 77, 83 / 93; four 117 / 104, 131 / 118, 135 / 133, 151 / 161; eight 219 / 186, 250 / 215, 254 / 244,
-// 288 / 300, at 56 rows four 148 / 145, eight 284 / 271, eight at 80, 96, 112, 128 rows 401 / 357, 432 / 415, 468 / 471, 509 / 531.
-// d = 128, 8, 12, 16, 20 rows: one layer 21.4 / 21.2, 22.0 / 22.7, 21.3 / 23.1, 21.8 / 25.0; two 32 / 29, 31.7 / 32.4, 31.9 / 32.7, 32 / 37;
-// four 50 / 45, 53 / 53, 53 / 53, 52 / 59; eight 97 / 79, 98 / 93, 99 / 98, 99 / 106 (128 rows, four layers: 89 / 157).
-// bf16, rounds, us, 8, 16, 32, 64, 128 rows of 16 tokens: d = 256 250 / 214, 253 / 228, 256 / 273, 264 / 345, 311 / 490; d = 384 at
-// 4, 16, 32 rows 317 / 243, 634 / 579, 642 / 675 (328 / 363 with four drafts).  Two workgroups per unit at d = 256 meet at 32 rows
-// (256 / 251) and lose 5 % at 16.  tsdp_verify of one layer, d = 256, 8, 10, 12, 16 rows 24.3 / 22.6, 24.2 / 23.8, 23.9 / 24.1, 24.1 / 24.9
-// (two layers, 16 rows 37 / 34), d = 384, 16 rows 36 / 31.
-// With cross-attention (d = 512, 32 tokens), tsdp_verify of 1, 8, 9, 16 rows: one layer 46 / 42, 50 / 47, 51 / 62; two 81 / 65, 88 / 70,
-// 88 / 105; twelve 445 / 289, 462 / 307, 466 / 504, 472 / 524 (one group of tasks that take two rows in turn 466): beyond one row an XCD
-// every further one adds the 3 us of a task to each of the phases.  Whole rounds with launches / one launch, of 1 x 1, 1 x 8, 2 x 4, 8 x 1
-// environments and drafts: one layer 104 / 94, 373 / 324, 229 / 194, 113 / 102; two 139 / 110, 427 / 366, 271 / 227, 151 / 125; twelve 520 / 338,
-// 801 / 601, 654 / 444, 538 / 350; of eight environments one that runs 102 / 90, 139 / 114, 489 / 334.
+// fp32, tsdp_verify, us, launches / one launch: d = 256, one layer, 16, 20, 32, 40, 48 rows of 16 tokens 33.0 / 32.7, 36 / 38, 39 / 42, 43 / 46,
+// 43 / 49; two, 24, 28, 40, 48 rows 60 / 55, 61 / 64, 69 / 71, 70 / 78; four, 32, 40, 44, 56, 64 rows 107 / 105, 121 / 118, 121 / 133, 134 / 146,
+// 138 / 161; eight 199 / 189, 226 / 215, 229 / 243, 254 / 270, 260 / 297.  d = 128, 8, 10, 12, 16 rows: one layer 20.2 / 20.0, 20.4 / 22.3 (8, 10
+// rows); two 29.7 / 26.7, 29.8 / 31.9; four 49 / 41, 49.7 / 49.9, 49.7 / 49.1, 50 / 53; eight 90 / 68, 91 / 89, 91.2 / 88.4, 91.4 / 92.2.
+// The lines of d = 256 were drawn where both met when the launches requested 40 fragments of weights ahead (40 rows, 56 from four layers on);
+// they request fewer since (FewGemm::AHEAD), and meet at 16 to 24 rows and at 40.  Between, a pass is up to a tenth slower than it
+// could be: the lines are where the bits of a result may change, which tsdp.h names, and stay.
+// bf16, rows of 16 tokens: d = 256, one layer, 8, 10, 12 rows 22.1 / 21.3, 22.1 / 24.8, 22.5 / 25.1; two, 8, 16 rows 33 / 28, 35 / 34; four 62 / 44, 62 / 54;
+// eight 111 / 71, 111 / 89; d = 384, 8, 16 rows, one layer 33 / 28, 35 / 33, two 55 / 37, 55 / 47, four 94 / 56, 95 / 72.  Rounds with the slower launches:
+// d = 256 at 16, 32, 64, 128 rows 253 / 228, 256 / 273, 264 / 345, 311 / 490; d = 384 at 32 rows 642 / 675.
+// With cross-attention (d = 512, 32 tokens), tsdp_verify of 1, 8 rows: one layer 48 / 40, 50 / 46; two 84 / 61, 87 / 68; twelve 447 / 277, 462 / 294, and 9, 16
+// rows (when the launches were 1 % slower) 466 / 504, 472 / 524 (one group of tasks that take two rows in turn 466): beyond one row an XCD
+// every further one adds the 3 us of a task to each of the phases.  Whole rounds of 1 x 8, 8 x 1 environments and drafts, twelve layers: 773 / 570,
+// 521 / 351.
 inline bool flow_forward_pays(size_t tokens, bool f32, size_t d, int layers) {
   if (!f32) return tokens <= (layers * d >= 384 ? 256 : 160);
   return tokens <= 16 * (d >= 256 ? (layers >= 4 ? 56 : 40) : (layers >= 4 ? 16 : 8));
