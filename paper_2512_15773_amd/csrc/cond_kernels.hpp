@@ -112,22 +112,22 @@ __global__ __launch_bounds__(256) void k_cond_size(CondIO io) {
 //   2.2 r u |v|       r = sqrt(C) + C / 128.  Sums that grow steadily, as of one sign: standard deviation of the difference 8.5 u |v| at C = 768, 16.5
 //                     (mean 38) at 3072, 2.4 at 64, so seven and more of them (at 3072 five beyond the mean).
 //   3.5 r u |x| |w| s sums that were far larger on the way and cancel: s is the largest of the thread's 64 partial sums after a quarter, half
-//                     and three quarters of the features in units of their |x| |w|.  Only where r s > 4.8, four standard deviations of a sum
-//                     of either sign: most threads only compare their largest partial sum with the least that could be that.
+//                     and three quarters of the features in units of their |x| |w|.  Only where r s > 5.4, 4.5 standard deviations of a sum
+//                     of either sign: most wavefronts only compare their largest partial sum with the least that could be that.
 // The deviations are those of 2.6e5 sums each against fp64 (Gaussian; of one sign; half of each sign in turn; large in the first eighth).
 // The workgroup lists the numbers in LDS, a thread takes one, and a second pass over the k-steps brings weights and observations
 // through the LDS as before, 512 numbers at a time: 0.35 ms each where all tiles take one.
 // Observations of a few features of two leading bits (masks, indices) list 8 to 22 % of their numbers, since their sums end on boundaries,
 // and infinities all of them.  Beyond 3072 numbers a tile is multiplied once more with fp32 operands on the fp32 matrix cores, whose
 // chains are the sums in order themselves (2.5 ms where all tiles do), and a tile with 16 marked tokens (k_cond_size) at once.
-// Measured, 256 environments x 64 tokens x 768, 12 layers of d = 512 and 2 of d = 256, with k_cond_size: Gaussian 1.43 ms, of one sign 1.35,
-// a mask of 5 % 1.66, of 1 %, four or two features set, infinities 2.55, sums that cancel 3.57; 4 environments 83 us, at most 176.  With every
-// tile in order 2.50 ms and 112 us; without the last step 3.6, 4.5, 5.9, 19.8 (infinities, not-a-numbers), 4.0 and up to 1.1 ms.
-// 128 registers: 41 spilled before and after the loop over the k-steps, none in it.
+// Measured, 256 environments x 64 tokens x 768, 12 layers of d = 512 and 2 of d = 256, with k_cond_size, Gaussian observations: 1.31 ms
+// (1.28 ms and 71 us with the first term alone); of one sign 1.3, a mask of 5 % 1.62, of 1 %, four or two features set, infinities 2.54, sums
+// that cancel 3.55; 4 environments 77 us, at most 173 us.  With every tile in order 2.50 ms and 112 us; without the fp32 tiles 3.6, 4.5, 5.9, 19.8
+// (infinities, not-a-numbers), 4.0 and up to 1.1 ms.  Of the 128 registers 42 are spilled before and after the loop over the k-steps, none in it.
 constexpr int COND_FF = 16, COND_TF = 8, COND_XS = 36;   // floats per token in LDS (second pass): 32 and the bank padding
 constexpr int COND_W_B = COND_FF * 64 * 16, COND_STAGE_B = COND_W_B + 3 * COND_TF * 64 * 16, COND_LDS = 2 * COND_STAGE_B;
 constexpr int COND_AGAIN_B = COND_W_B + COND_TF * 16 * COND_XS * 4, COND_LIST = 512, COND_AGAIN = 6 * COND_LIST, COND_MARKED = 16;
-constexpr float COND_ULP = 5.9604645e-8f, COND_TIE = 3.0f * COND_ULP, COND_OWN = 2.2f, COND_GROWN = 3.5f, COND_UNUSUAL = 4.8f;
+constexpr float COND_ULP = 5.9604645e-8f, COND_TIE = 3.0f * COND_ULP, COND_OWN = 2.2f, COND_GROWN = 3.5f, COND_UNUSUAL = 5.4f;
 static_assert(2 * COND_AGAIN_B + 4 * (COND_LIST + 1) <= COND_LDS && 2 * COND_LDS <= 160 * 1024, "LDS");
 
 __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
@@ -197,6 +197,13 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
     const float* v = size0 + min(wt * 4 + j, MF - 1 - tf0) * 16;
     const f32x4 x = keys ? f32x4{1, 1, 1, 1} * v[l16] : *reinterpret_cast<const f32x4*>(v + lg * 4);
     return f32x4{fabsf(x[0]), fabsf(x[1]), fabsf(x[2]), fabsf(x[3])};
+  };
+  // (the same without a branch, by addresses)
+  const int fb = cls == 0 ? lg * 4 : l16, fs = cls == 0 ? 1 : 0, tb = cls == 0 ? l16 : lg * 4, ts = 1 - fs;
+  auto features_of = [&](const float* v, int i) { v += i * 16 + fb; return f32x4{v[0], v[fs], v[2 * fs], v[3 * fs]}; };
+  auto tokens_of = [&](int j) {
+    const float* v = size0 + min(wt * 4 + j, MF - 1 - tf0) * 16 + tb;
+    return f32x4{fabsf(v[0]), fabsf(v[ts]), fabsf(v[2 * ts]), fabsf(v[3 * ts])};
   };
   // Largest of the thread's partial sums on the way, in units of |x| |w|, where one is more than `unusual` of them; looked at three
   // times.  The least product of the thread's norms tells first whether there can be one.
@@ -270,7 +277,7 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
             acc[i][j] = keys ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b, acc[i][j], 0, 0, 0)
                              : __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a[i], acc[i][j], 0, 0, 0);
         }
-      if (k == next) { look(); next += quarter; }
+      if (k == next && k < KS - 1) { look(); next += quarter; }
     }
   };
   const int DH = n.d / n.heads, KH = DH / 32, CF = DH / 16, SF = io.SF;
@@ -285,7 +292,7 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
   auto each = [&](auto&& f) {                           // f(i, j, sums with their biases) of the thread's pieces, stored as well
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const f32x4 bias = features(cls == 0, bias0, i);
+      const f32x4 bias = features_of(bias0, i);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if (tf0 + wt * 4 + j >= MF) continue;
@@ -310,10 +317,10 @@ __global__ __launch_bounds__(512, 4) void k_cond_kv(CondIO io) {
     uint64_t again = 0;                                 // bit (i * 4 + j) * 4 + e
     f32x4 x[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) x[j] = tokens(cls == 0, j) * line;
+    for (int j = 0; j < 4; ++j) x[j] = tokens_of(j) * line;
     f32x4 wnorm;
     each([&](int i, int j, const f32x4& v) {
-      if (j == 0) wnorm = features(cls == 0, norm0, i);
+      if (j == 0) wnorm = features_of(norm0, i);
       const f32x4 drawn = wnorm * x[j];
       unsigned m = 0;
 #pragma unroll
