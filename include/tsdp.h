@@ -195,10 +195,10 @@ int tsdp_chain_staged(tsdp_ctx* ctx, int B, float* d_x, int32_t* d_t, const int3
 /* The same chain with no host round trip (Section 1 and Section 3.2, the inference loop; Section 3.3 for the stage
  * tables): exactly n_rounds rounds are enqueued on `stream` and the call returns; nothing is read back and nothing
  * synchronises.  Every kernel of a round reads the round's live row count on the device and returns at once when no
- * environment is running any more, so rounds past the end of the chain cost their launches without work -- about 1.5 us
- * each: 6 launches a round (one environment, fp32, d = 256 x 8 and 128 x 2 layers, K_max = 8: 10 us), and 2 to 6 more per
- * layer where few rows are spread over several launches (two environments, d = 512 x 12 and 256 x 2 layers: 76 launches,
- * 117 us) -- and leave latents, timesteps and totals untouched.
+ * environment is running any more, so rounds past the end of the chain cost their launches without work -- about 1.5 to
+ * 2.3 us each: 4 launches a round (one environment, fp32, d = 256 x 8 and 128 x 2 layers, K_max = 8: 9 us), and 2 to 6 more
+ * per layer where few rows are spread over several launches (two environments, d = 512 x 12 and 256 x 2 layers: 76 launches,
+ * 119 us) -- and leave latents, timesteps and totals untouched.
  * A round advances every running environment by at least one step, so n_rounds = (largest t) + 1 <= T always completes
  * the chain.  Finished environments own no rows: the ragged verify batch of a round holds the running environments only,
  * and tiles beyond its live row count exit.
