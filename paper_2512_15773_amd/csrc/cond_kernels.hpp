@@ -108,13 +108,15 @@ __global__ __launch_bounds__(256) void k_cond_size(CondIO io) {
 //
 // Which numbers are added again: those v that round differently with the largest of three terms on either side, u = 2^-24.
 //   3 u |x| |w|       terms of either sign: a chain of fp32 additions ends 0.30 u |x| |w| away from the exact sum (standard deviation), the
-//                     matrix cores' sum 0.18.  With 1.5 35 numbers of the 2.2e8 of 256 observations round the other way, with 2 ten, with 3 none.
+//                     matrix cores' sum 0.18.  With 1.5 35 numbers of the 2.2e8 of 256 observations round the other way, with 2 ten, with 3 none to two.
 //   2.2 r u |v|       r = sqrt(C) + C / 128.  Sums that grow steadily, as of one sign: standard deviation of the difference 8.5 u |v| at C = 768, 16.5
 //                     (mean 38) at 3072, 2.4 at 64, so seven and more of them (at 3072 five beyond the mean).
 //   3.5 r u |x| |w| s sums that were far larger on the way and cancel: s is the largest of the thread's 64 partial sums after a quarter, half
 //                     and three quarters of the features in units of their |x| |w|.  Only where r s > 5.4, 4.5 standard deviations of a sum
 //                     of either sign: most wavefronts only compare their largest partial sum with the least that could be that.
-// The deviations are those of 2.6e5 sums each against fp64 (Gaussian; of one sign; half of each sign in turn; large in the first eighth).
+// The deviations are those of 2.6e5 sums each against fp64 (Gaussian; of one sign; half of each sign in turn; large in the first eighth).  With all
+// three the noise predictions of 60 batches of 256 environments (six of each of ten kinds, weights of either and of one sign) had no bit other than
+// with every number added in order; with the first alone those of one or two environments of every second Gaussian batch had.
 // The workgroup lists the numbers in LDS, a thread takes one, and a second pass over the k-steps brings weights and observations
 // through the LDS as before, 512 numbers at a time: 0.35 ms each where all tiles take one.
 // Observations of a few features of two leading bits (masks, indices) list 8 to 22 % of their numbers, since their sums end on boundaries,
